@@ -263,71 +263,97 @@ __global__ __launch_bounds__(1024) void setup_kernel(ParseChunk chunk, ListDesc*
 // from the stream (neighbouring lanes, neighbouring words), all of them in flight
 // together, and compares each with the one before it.  Wavefronts never wait for
 // each other.  The pass also checks that positions ascend and stay below d.
+// A position is one load of four bytes from the byte it starts in (two aligned words a record before: half of the
+// kernel's loads): 24.5 -> 20.2 us for 32 streams of 11.2 M coordinates and, with the search below, 203 -> 142 us
+// for 100 of 25.6 M.
 constexpr uint32_t kTabTurns = kTabChunk / kWave;  // records of an item a lane looks at
 
+// Fields at any bit: one load from the byte the field starts in (global loads need no alignment).
+struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
+struct __attribute__((packed, aligned(1))) Bytes8 { uint64_t v; };
+typedef const unsigned char __attribute__((address_space(1))) * GlobalBytePtr;
+__device__ __forceinline__ uint32_t load4(GlobalBytePtr p) { return ((const Bytes4 __attribute__((address_space(1)))*)p)->v; }
+__device__ __forceinline__ uint64_t load8(GlobalBytePtr p) { return ((const Bytes8 __attribute__((address_space(1)))*)p)->v; }
+
+// The list that owns item q (last list with item_start <= q), whole wavefront, 64 probes a round: two rounds for up
+// to 4096 lists.  (A binary search by every lane costs log2 rounds, in LDS a copy of item_start per workgroup first:
+// beyond 2048 lists, where the copy did not fit, it was twelve dependent loads per item and two thirds of the kernel.)
+__device__ __forceinline__ uint32_t owner_of(const uint32_t* __restrict__ item_start, uint32_t n_active, uint32_t q) {
+  const uint32_t lane = lane_id();
+  uint32_t a = 0, len = n_active;  // the owner is one of a .. a + len - 1
+  while (len > 1) {
+    const uint32_t step = (len + kWave - 1u) / kWave;
+    const uint32_t at = a + lane * step;
+    const bool hit = lane * step < len && item_start[min(at, n_active)] <= q;
+    const uint32_t last = (uint32_t)__popcll(__ballot(hit)) - 1u;  // item_start ascends and its first entry is 0: the hits are a prefix
+    a += last * step;
+    len = min(step, len - last * step);
+  }
+  return __builtin_amdgcn_readfirstlane(a);
+}
+
+// WIDE: positions of more than 25 bits, which need not lie in the four bytes from the one they start in.
+template <bool WIDE>
 __global__ __launch_bounds__(kBlock, 8) void tile_table_kernel(const CompactDesc* __restrict__ cdesc,
                                                          const uint32_t* __restrict__ item_start,
                                                          const DecodeCtl* __restrict__ ctl, uint32_t* table,
                                                          uint32_t d, uint32_t n_tiles, uint32_t* status) {
-  constexpr uint32_t kStartCache = 2048;
-  __shared__ uint32_t s_start[kStartCache];
   const uint32_t tid = threadIdx.x, lane = lane_id();
   const uint32_t n_active = ctl->n_active, n_items = ctl->n_items;
-  const bool cached = n_active <= kStartCache;
-  if (cached)
-    for (uint32_t i = tid; i < n_active; i += kBlock) s_start[i] = item_start[i];
-  __syncthreads();
-  const uint32_t n_waves = gridDim.x * kWavesPerBlock;
+  // A wavefront takes neighbouring items, so that it looks for the owner of the first one only and then walks on.
+  const uint64_t n_waves = gridDim.x * kWavesPerBlock, me = blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(tid / kWave);
+  const uint32_t q_begin = (uint32_t)(me * n_items / n_waves), q_end = (uint32_t)((me + 1u) * n_items / n_waves);
+  if (q_begin >= q_end) return;  // uniform
+  uint32_t a = owner_of(item_start, n_active, q_begin);
+  uint32_t first_item = item_start[a], next_list = item_start[a + 1u];  // uniform
   bool bad = false;
-  for (uint32_t q = blockIdx.x * kWavesPerBlock + tid / kWave; q < n_items; q += n_waves) {  // uniform per wavefront
-    uint32_t a = 0, b = n_active;  // the list that owns item q: last list with item_start <= q
-    while (b - a > 1) {
-      const uint32_t mid = (a + b) >> 1;
-      const uint32_t v = cached ? s_start[mid] : item_start[mid];
-      if (v <= q) a = mid; else b = mid;
+  for (uint32_t q = q_begin; q < q_end; ++q) {  // uniform per wavefront
+    while (q >= next_list) {  // every list has an item: one step at most
+      ++a;
+      first_item = next_list;
+      next_list = item_start[a + 1u];
     }
-    a = __builtin_amdgcn_readfirstlane(a);
-    const uint32_t first_item = __builtin_amdgcn_readfirstlane(cached ? s_start[a] : item_start[a]);
     // the list's descriptor is the same for all lanes: keeping it in scalar registers keeps the address
     // arithmetic of the loads below off the vector unit
     const uint4* dsrc = reinterpret_cast<const uint4*>(cdesc + a);
     const uint4 d0 = dsrc[0], d1 = dsrc[1];
-    GlobalConstWordPtr pay = (GlobalConstWordPtr)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(d0.y) << 32) |
-                                                  (uint32_t)__builtin_amdgcn_readfirstlane(d0.x));
+    const uint64_t pay = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(d0.y) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane(d0.x);
     const uint32_t P = __builtin_amdgcn_readfirstlane(d1.x), wsy = __builtin_amdgcn_readfirstlane(d1.y);
     const uint32_t W = wsy & 0xFFu, s = (wsy >> 8) & 0xFFu;
-    const uint32_t pid_mask = s >= 32 ? 0xFFFFFFFFu : (1u << s) - 1u;
+    const uint32_t pid_mask = (1u << s) - 1u;  // s <= 31
     const uint32_t e0 = (q - first_item) * kTabChunk, cnt = min(P - e0, kTabChunk);
     uint32_t* row = table + (size_t)a * (n_tiles + 1);
     // The window of the item starts at the record before the run (the run's first record for the first
     // item of a list); records are addressed by their number in the window, bits by their offset from the
-    // window's first word: both stay far below 2^24.
+    // byte `src`, eight before the window's first word (a stream's headers lie in front of its first payload, so
+    // the bytes are there): everything stays far below 2^24.
     const uint32_t lead = e0 ? 1u : 0u;
     const uint64_t bit0 = (uint64_t)(e0 - lead) * W;
-    GlobalConstWordPtr src = pay + (bit0 >> 5);
-    const uint32_t sh0 = (uint32_t)bit0 & 31u;
-    const uint64_t words_left = ((((uint64_t)P * W + 31u) >> 5) - 1u) - (bit0 >> 5);  // the list's last word, from src
-    const uint32_t rel_last = words_left < (1u << 24) ? (uint32_t)words_left : 1u << 24;
-    // position field of record r of the window: its s <= 31 low bits lie in at most two words
-    auto request = [&](uint32_t r, uint32_t& w0, uint32_t& w1) {
-      const uint32_t bit = sh0 + __umul24(r, W), w = bit >> 5;
-      w0 = src[w];
-      w1 = src[min(w + 1u, rel_last)];
-      return bit & 31u;
+    GlobalBytePtr src = (GlobalBytePtr)(pay + (bit0 >> 5) * 4u - 8u);
+    const uint32_t sh0 = ((uint32_t)bit0 & 31u) + 64u;
+    // the last place a whole load may start at: the list's payload ends there
+    const uint64_t left = (((uint64_t)P * W + 31u) >> 5) * 4u - (bit0 >> 5) * 4u + 8u - (WIDE ? 8u : 4u);
+    const uint32_t rel_last = left < (1u << 24) ? (uint32_t)left : 1u << 24;
+    // position field of record r of the window
+    auto request = [&](uint32_t r, uint32_t& sh) {
+      const uint32_t bit = sh0 + __umul24(r, W), at = min(bit >> 3, rel_last);
+      sh = bit - at * 8u;
+      if constexpr (WIDE) return load8(src + at); else return load4(src + at);
     };
-    uint32_t lo[kTabTurns], hi[kTabTurns], sh[kTabTurns], c_lo, c_hi, c_sh;
-    c_sh = request(0u, c_lo, c_hi);  // the record before the run (uniform)
+    decltype(request(0u, a)) w[kTabTurns], c_w;
+    uint32_t sh[kTabTurns], c_sh;
+    c_w = request(0u, c_sh);  // the record before the run (uniform)
 #pragma unroll
     for (uint32_t i = 0; i < kTabTurns; ++i)  // no branch: a lane past the end reads the last record again
-      sh[i] = request(lead + min(i * kWave + lane, cnt - 1u), lo[i], hi[i]);
-    uint32_t carry = __builtin_amdgcn_alignbit(c_hi, c_lo, c_sh) & pid_mask;
+      w[i] = request(lead + min(i * kWave + lane, cnt - 1u), sh[i]);
+    uint32_t carry = (uint32_t)(c_w >> c_sh) & pid_mask;
 #pragma unroll
     for (uint32_t i = 0; i < kTabTurns; ++i) {
       if (i * kWave >= cnt) break;  // uniform
       const uint32_t j = i * kWave + lane;
       const bool live = j < cnt;
       const uint32_t e = e0 + j;
-      const uint32_t pid = __builtin_amdgcn_alignbit(hi[i], lo[i], sh[i]) & pid_mask;
+      const uint32_t pid = (uint32_t)(w[i] >> sh[i]) & pid_mask;
       // the record before mine sits in the lane below; lane 0 takes the last one of the turn before
       const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)carry, (int)pid, 0x138 /* wave_shr:1 */, 0xF, 0xF, false);
       carry = __builtin_amdgcn_readlane(pid, kWave - 1);
@@ -751,8 +777,8 @@ int cvlc_decode_aggregate(uint32_t n, const void* const* d_streams, const size_t
   if (n > 0) {
     StageScope scope(CVLC_STAGE_DEC_TABLE, stream);
     // the number of work items is only known on the device: 2048 workgroups (eight per CU) walk them
-    hipLaunchKernelGGL(tile_table_kernel, dim3(2048), dim3(kBlock), 0, stream, cdesc, item_start, ctl, table, d,
-                       L.n_tiles, status);
+    auto kernel = position_bits(d) > 25u ? tile_table_kernel<true> : tile_table_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(2048), dim3(kBlock), 0, stream, cdesc, item_start, ctl, table, d, L.n_tiles, status);
   }
   {
     StageScope scope(CVLC_STAGE_DEC_TILES, stream);
