@@ -22,8 +22,10 @@ constexpr uint32_t kBlock = 256;           // threads per workgroup (4 wavefront
 constexpr uint32_t kWave = 64;
 constexpr uint32_t kWavesPerBlock = kBlock / kWave;
 constexpr uint32_t kSubTile = 1024;        // coordinates one wavefront holds in registers (16 per lane)
-constexpr uint32_t kRegion = 8192;         // coordinates one wavefront filters as a unit (8 sub-tiles)
-constexpr uint32_t kSpan = 512;            // candidates one wavefront classifies as a unit (8 rows of 64)
+constexpr uint32_t kRegionShiftMin = 10;   // a region, the coordinates one wavefront filters as a unit, has 1 ...
+constexpr uint32_t kRegionShiftMax = 13;   // ... to 8 sub-tiles, by the size of the batch
+constexpr uint32_t kSpanShift = 9;
+constexpr uint32_t kSpan = 1u << kSpanShift;  // candidates one wavefront classifies as a unit (8 rows of 64)
 constexpr uint32_t kChunkSpans = 8;        // spans per emit chunk (4096 candidates, one workgroup)
 constexpr uint32_t kSampleBins = 8192;     // sample histogram on key >> 18 (8 exponent + 5 mantissa bits)
 constexpr uint32_t kSampleShift = 18;

@@ -14,7 +14,7 @@
 //   sample_hist   strided sample of |U| -> histogram of the top 13 key bits
 //   sample_walk   conservative candidate threshold tau_lo from that histogram
 //   filter        the one full pass over U.  Every wavefront owns regions of
-//                 8192 consecutive coordinates and writes the coordinates with
+//                 1024 to 8192 consecutive coordinates and writes the coordinates with
 //                 key >= tau_lo to the front of the region's slot, in position
 //                 order; it also counts the level-1 digit (top 11 key bits) of
 //                 what it keeps and sums the squares of what it drops
@@ -51,6 +51,9 @@
 namespace cvlc {
 namespace {
 
+constexpr uint32_t kWideBlock = 1024;
+constexpr uint32_t kWideWaves = kWideBlock / kWave;
+
 // ------------------------------------------------------------------ workspace layout
 // Per-client, per-group constants of the last stages, written by the layout kernel.
 struct GroupInfo {
@@ -64,7 +67,7 @@ struct EncodeLayout {
   size_t status, ctl, params, region_cnt, region_sumsq, cand_idx, cand_val, dense_idx, dense_val, nz_off, nz_run, span_first, span_cnt, group_info,
       tie_list, sel_part, l3_hist, norm_limbs, total;
   size_t zero_bytes;        // [status, params) is cleared at the start of a call
-  uint32_t n_regions, max_spans;
+  uint32_t region_shift, n_regions, max_spans;
   uint32_t dense_cap;       // candidates the dense list of a client has room for
   uint32_t sel_blocks;      // workgroups per client in a level-2/3 selection pass
 };
@@ -82,11 +85,30 @@ uint32_t filter_blocks_per_client(uint32_t n_regions, uint32_t n, uint32_t resid
   return (waves + kWavesPerBlock - 1) / kWavesPerBlock;
 }
 
+// Regions of 1 << region_shift coordinates.  A batch of several regions per resident wavefront takes the longest
+// ones (long runs for the gather, few entries for the region scan).  A smaller batch leaves wavefronts without
+// work, and the few that have some go through the eight sub-tiles of a long region one after the other, 2.5 us
+// each: it takes the shortest regions, down to one sub-tile, that still give no wavefront a second one (seven
+// workgroups of four wavefronts fit a CU; six are counted on) and the region scan no third round.
+// filter: 20.6 -> 5.8 us for one client of 65 536 coordinates, 20.6 -> 14.4 us for 8 of 1.2 M.  One client of
+// 11.2 M with regions of 2048: filter 24.3 -> 19.4 us, but scan_l1 6.7 -> 13.1 and the gather 12.0 -> 14.1 us.
+uint32_t region_shift_for(uint32_t d, uint32_t n) {
+  constexpr uint64_t kWavesCounted = 256u * 6u * kWavesPerBlock, kScanRounds = 2u * kWideBlock;
+  uint32_t shift = kRegionShiftMax;
+  while (shift > kRegionShiftMin) {
+    const uint64_t regions = ((uint64_t)d + (1u << (shift - 1u)) - 1u) >> (shift - 1u);
+    if (regions > kScanRounds || regions * n > kWavesCounted) break;
+    --shift;
+  }
+  return shift;
+}
+
 // `cap`: candidates (coordinates at or above the sampled threshold) a client may have; the filter's own
 // output is laid out by region and stays d long, everything behind it is as long as the candidates.
 EncodeLayout encode_layout(uint32_t d, uint32_t n, uint32_t cap) {
   EncodeLayout L;
-  L.n_regions = (uint32_t)(((uint64_t)d + kRegion - 1) / kRegion);
+  L.region_shift = region_shift_for(d, n);
+  L.n_regions = (uint32_t)(((uint64_t)d + (1u << L.region_shift) - 1) >> L.region_shift);
   L.dense_cap = cap < d ? cap : d;
   L.max_spans = (uint32_t)(((uint64_t)L.dense_cap + kSpan - 1) / kSpan);
   {
@@ -136,7 +158,7 @@ struct Workspace {  // device pointers into the caller's workspace
   uint32_t* sel_part;
   uint32_t* l3_hist;   // level-3 digit counts per (client, slot), zero between uses
   unsigned long long* norm_limbs;  // QSGD: per (client, group) the exact sum of squares in 32-bit limbs
-  uint32_t d, n_regions, max_spans, dense_cap, filter_blocks, sel_blocks;
+  uint32_t d, region_shift, n_regions, max_spans, dense_cap, filter_blocks, sel_blocks;
 };
 
 // ------------------------------------------------------------------ parameter upload
@@ -192,9 +214,6 @@ __device__ __forceinline__ uint32_t lanes_below4(uint64_t m0, uint64_t m1, uint6
 typedef const float __attribute__((address_space(1))) * GlobalFloatPtr;
 typedef float __attribute__((ext_vector_type(4))) Float4V;
 typedef const Float4V __attribute__((address_space(1))) * GlobalFloat4Ptr;
-
-constexpr uint32_t kWideBlock = 1024;
-constexpr uint32_t kWideWaves = kWideBlock / kWave;
 
 // ------------------------------------------------------------------ 1. sample histogram
 // Reads n_s 256-byte pieces spread evenly over the vector and histograms the
@@ -315,13 +334,14 @@ __device__ __forceinline__ void load_subtile(SubTile& t, GlobalFloatPtr U, uint3
 constexpr uint32_t kStageCap = 448;
 constexpr uint32_t kStageFlushAt = kStageCap - 256;  // more staged than this: flush
 
-static_assert(kRegion <= 65536 && (kRegion & (kRegion - 1)) == 0, "positions inside a region are kept in 16 bits");
+static_assert(kRegionShiftMax <= 16 && (1u << kRegionShiftMin) == kSubTile, "positions inside a region are kept in 16 bits; a sub-tile lies in one region");
 
 struct FilterWave {
   uint2* stage;            // this wavefront's staging rows in LDS
   uint16_t* __restrict__ out_idx;  // the region's slot in global memory: positions inside the region (13 bits)
   uint32_t* __restrict__ out_val;  // ... and value bits
   uint32_t* hist;          // the workgroup's level-1 histogram in LDS
+  uint32_t pos_mask;       // coordinates per region - 1
   uint32_t fill;           // staged entries (uniform)
   uint32_t run;            // entries already written to `out` (uniform)
   uint32_t nonfinite;      // a kept key was Inf or NaN (per lane)
@@ -336,7 +356,7 @@ __device__ __forceinline__ void flush_rows(FilterWave& w, uint32_t lane, bool al
   uint32_t g = 0;
   for (; g + kWave <= w.fill; g += kWave) {
     const uint2 e = w.stage[g + lane];
-    w.out_idx[w.run + g + lane] = (uint16_t)(e.x & (kRegion - 1u));
+    w.out_idx[w.run + g + lane] = (uint16_t)(e.x & w.pos_mask);
     w.out_val[w.run + g + lane] = e.y;
     atomicAdd(&w.hist[(e.y & 0x7FFFFFFFu) >> 20], 1u);
     w.nonfinite |= (e.y & 0x7FFFFFFFu) >= 0x7F800000u ? 1u : 0u;
@@ -347,7 +367,7 @@ __device__ __forceinline__ void flush_rows(FilterWave& w, uint32_t lane, bool al
     if (lane < left) e = w.stage[g + lane];
     if (all) {
       if (lane < left) {
-        w.out_idx[w.run + g + lane] = (uint16_t)(e.x & (kRegion - 1u));
+        w.out_idx[w.run + g + lane] = (uint16_t)(e.x & w.pos_mask);
         w.out_val[w.run + g + lane] = e.y;
         atomicAdd(&w.hist[(e.y & 0x7FFFFFFFu) >> 20], 1u);
         w.nonfinite |= (e.y & 0x7FFFFFFFu) >= 0x7F800000u ? 1u : 0u;
@@ -409,7 +429,7 @@ __global__ __launch_bounds__(kBlock) void filter_kernel(const ClientParams* __re
   const ClientParams& p = params[client];
   ClientCtl* ctl = ctls + client;
   const uint32_t tau_lo = ctl->tau_lo;
-  const uint32_t d = ws.d, n_regions = ws.n_regions;
+  const uint32_t d = ws.d, n_regions = ws.n_regions, region_len = 1u << ws.region_shift;
   GlobalFloatPtr U = (GlobalFloatPtr)p.update;
   const uint32_t lane = lane_id();
   for (uint32_t i = threadIdx.x; i < kL1Bins; i += kBlock) s_hist[i] = 0;
@@ -420,6 +440,7 @@ __global__ __launch_bounds__(kBlock) void filter_kernel(const ClientParams* __re
   FilterWave w;
   w.stage = s_stage[wave_id()];
   w.hist = s_hist;
+  w.pos_mask = region_len - 1u;
   w.nonfinite = 0;
   // Software pipeline over all sub-tiles of all of this wavefront's regions: the
   // loads of the next sub-tile (of the next region, at a region's end) are issued
@@ -444,11 +465,11 @@ __global__ __launch_bounds__(kBlock) void filter_kernel(const ClientParams* __re
     SubTile cur, nxt;
     bool upcoming_static = false;
     uint32_t claimed = 0;
-    uint32_t sbase = region * kRegion;
+    uint32_t sbase = region << ws.region_shift;
     load_subtile(cur, U, sbase, lane, d);
     while (true) {
-      const uint32_t rbase = region * kRegion;
-      const uint32_t rend = (d - rbase < kRegion) ? d : rbase + kRegion;
+      const uint32_t rbase = region << ws.region_shift;
+      const uint32_t rend = (d - rbase < region_len) ? d : rbase + region_len;
       if (sbase == rbase) {
         w.out_idx = ws.cand_idx + (size_t)client * d + rbase;
         w.out_val = ws.cand_val + (size_t)client * d + rbase;
@@ -464,7 +485,7 @@ __global__ __launch_bounds__(kBlock) void filter_kernel(const ClientParams* __re
       if (last_of_region)
         next_region = upcoming_static ? region + n_waves
                                       : (n_static < n_regions ? n_static + (uint32_t)__builtin_amdgcn_readfirstlane(claimed) : n_regions);
-      const uint32_t next_sbase = last_of_region ? next_region * kRegion : sbase + kSubTile;
+      const uint32_t next_sbase = last_of_region ? next_region << ws.region_shift : sbase + kSubTile;
       const bool more = next_region < n_regions;
       if (more) load_subtile(nxt, U, next_sbase, lane, d);
       if (sbase + kSubTile <= d) {
@@ -571,11 +592,11 @@ __global__ __launch_bounds__(kWideBlock) void scan_l1_kernel(const ClientParams*
     __syncthreads();  // the runs written above are overwritten
     double* rsq = ws.region_sumsq + (size_t)client * n_regions;
     for (uint32_t j = tid; j < n_regions; j += kWideBlock) {
-      nz_off[j] = j * kRegion;
+      nz_off[j] = j << ws.region_shift;
       nz_run[j] = j;
       rsq[j] = 0.0;  // nothing is dropped before the selection
     }
-    for (uint32_t sp = tid; (uint64_t)sp * kSpan < d; sp += kWideBlock) span_first[sp] = sp / (kRegion / kSpan);
+    for (uint32_t sp = tid; (uint64_t)sp * kSpan < d; sp += kWideBlock) span_first[sp] = sp >> (ws.region_shift - kSpanShift);
     if (tid == 0) {
       nz_off[n_regions] = d;
       ctl->n_cand = d;
@@ -799,7 +820,7 @@ struct CandView {
   const uint32_t* __restrict__ nz_off;      // n_nz + 1 entries, the last = n
   const uint32_t* __restrict__ nz_run;
   const uint32_t* __restrict__ span_first;  // q of candidate 512 s
-  uint32_t n_nz, n;
+  uint32_t n_nz, n, region_shift;
 };
 
 __device__ __forceinline__ CandView cand_view(const Workspace& ws, const ClientCtl* ctl, uint32_t client) {
@@ -811,6 +832,7 @@ __device__ __forceinline__ CandView cand_view(const Workspace& ws, const ClientC
   view.span_first = ws.span_first + (size_t)client * (ws.max_spans + 1);
   view.n_nz = ctl->n_nz;
   view.n = ctl->n_cand;
+  view.region_shift = ws.region_shift;
   return view;
 }
 
@@ -843,8 +865,8 @@ __device__ __forceinline__ void span_slots(const CandView& cv, uint32_t span, co
   const uint32_t begin = span * kSpan;
   const uint32_t end = min(begin + kSpan, cv.n);
   uint32_t base = win.base, wo = win.wo, wr = win.wr;
-  // slot of candidate i in run (region r, first candidate o): r * kRegion + (i - o); kept as i + shift
-  const uint32_t shift0 = __builtin_amdgcn_readlane(wr, 0) * kRegion - __builtin_amdgcn_readlane(wo, 0);
+  // slot of candidate i in run (region r, first candidate o): (r << region_shift) + (i - o); kept as i + shift
+  const uint32_t shift0 = (__builtin_amdgcn_readlane(wr, 0) << cv.region_shift) - __builtin_amdgcn_readlane(wo, 0);
 #pragma unroll
   for (uint32_t j = 0; j < kPerLane; ++j) slot[j] = shift0;
   while (true) {
@@ -859,7 +881,7 @@ __device__ __forceinline__ void span_slots(const CandView& cv, uint32_t span, co
     if (m <= kSerialRuns) {
       for (uint32_t t = 1; t <= m; ++t) {
         const uint32_t ot = __builtin_amdgcn_readlane(wo, t);
-        const uint32_t shift = __builtin_amdgcn_readlane(wr, t) * kRegion - ot;
+        const uint32_t shift = (__builtin_amdgcn_readlane(wr, t) << cv.region_shift) - ot;
 #pragma unroll
         for (uint32_t j = 0; j < kPerLane; ++j) {
           const uint32_t i = begin + j * kWave + lane;
@@ -878,7 +900,7 @@ __device__ __forceinline__ void span_slots(const CandView& cv, uint32_t span, co
           if (pos + step <= m && probe <= i) pos += step;
         }
         const uint32_t ro = (uint32_t)__shfl((int)wo, (int)pos, kWave), rr = (uint32_t)__shfl((int)wr, (int)pos, kWave);
-        if (i >= first_here) slot[j] = rr * kRegion - ro;
+        if (i >= first_here) slot[j] = (rr << cv.region_shift) - ro;
       }
     }
     if (!more) break;
@@ -972,7 +994,7 @@ __global__ __launch_bounds__(kWideBlock) void gather_l2_kernel(const ClientParam
         // sixteen loads of a span go out together
         const uint32_t sl = min(slot[j], ws.d - 1u);
         v[j] = src_val[sl];
-        x[j] = keep_all.value ? sl : (sl & ~(kRegion - 1u)) + cv.idx[sl];  // a slot starts where its region starts
+        x[j] = keep_all.value ? sl : ((sl >> cv.region_shift) << cv.region_shift) + cv.idx[sl];  // a slot starts where its region starts
       }
 #pragma unroll
       for (uint32_t j = 0; j < kPerLane; ++j) {
@@ -2149,6 +2171,7 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
   ws.l3_hist = reinterpret_cast<uint32_t*>(base + L.l3_hist);
   ws.norm_limbs = reinterpret_cast<unsigned long long*>(base + L.norm_limbs);
   ws.d = d;
+  ws.region_shift = L.region_shift;
   ws.n_regions = L.n_regions;
   ws.max_spans = L.max_spans;
   ws.dense_cap = L.dense_cap;
