@@ -29,15 +29,20 @@ constexpr uint32_t kSpan = 1u << kSpanShift;  // candidates one wavefront classi
 constexpr uint32_t kChunkSpans = 8;        // spans per emit chunk (4096 candidates, one workgroup)
 constexpr uint32_t kSampleBins = 8192;     // sample histogram on key >> 18 (8 exponent + 5 mantissa bits)
 constexpr uint32_t kSampleShift = 18;
-constexpr uint32_t kL1Bins = 2048;         // level-1 digit: key >> 20 (8 exponent + 3 mantissa bits)
-constexpr uint32_t kDigitBins = 1024;      // level-2 and level-3 digits: 10 bits each
-constexpr uint32_t kSlotGroup = 15;        // boundaries refined per level-2/3 launch (60 KB of LDS) for plans of up to 15 groups
-constexpr uint32_t kSlotGroupWide = 31;    // ... for plans of more groups: all boundaries at once (124 KB of LDS)
+// Selection bins: a window of kMapBins sample bins, each cut into 1 .. 1024 fine bins by its share of the sample,
+// so that no fine bin holds much more than 2 / (number aimed at) of the candidates; outside the window one bin per octave.
+constexpr uint32_t kMapBins = 512;         // 16 octaves
+constexpr uint32_t kFineMin = 128, kFineMax = 1024;  // fine bins aimed at ...
+constexpr uint32_t kFineShare = 256;       // ... so that one holds about this many of the k kept coordinates
+constexpr uint32_t kOctaves = 256;         // values of the exponent field
+constexpr uint32_t kFineBins = kFineMax + kMapBins;  // at most: the shares add up to the number aimed at, every sample bin has one fine bin at least
+constexpr uint32_t kSelBins = kOctaves + kFineBins + kOctaves;  // below the window, the window, above it: ascending with the key
+constexpr uint32_t kMemberSlots = CVLC_MAX_CODED;  // member lists per client: one per boundary
+constexpr uint32_t kMemberPoolMin = 2048, kMemberPoolMax = 8192;  // entries of a member list, by the number of candidates
 constexpr uint32_t kSamplePieceQuads = 16;    // a piece of the sample: 16 float4 = 64 coordinates = 256 bytes (random 64-byte
                                               // reads run at a fifth of what HBM gives 256-byte ones: 21 against 14 us for the pass)
 constexpr uint32_t kSamplePiece = 4u * kSamplePieceQuads;  // coordinates per piece
 constexpr uint32_t kSampleChunksMax = 4096;   // pieces in the sample (256 Ki coordinates)
-constexpr uint32_t kTieCap = 2048;         // boundary-class members kept per histogram slot for tie resolution
 constexpr uint32_t kSampleBlocks = 16;     // workgroups per client in the sample pass
 constexpr uint32_t kStatsStride = CVLC_STATS_STRIDE;
 constexpr uint32_t kNormLimbs = 20;        // 32-bit limbs of an exact sum of up to 2^31 squares of fp32 values
@@ -69,15 +74,17 @@ struct ClientCtl {
   uint32_t claim;            // regions of the filter's claimed part taken so far
   uint32_t emit_claim;       // chunks of the packing pass taken beyond every workgroup's first
   double seg_sumsq[32];      // energy of every coded group; entry R: candidates below the last boundary (atomic)
-  uint32_t tie_cnt[32];      // kept-aside class members per histogram slot
-  uint32_t sel_prefix[2][32];  // key prefix of boundary r after level 1 (11 bits) and level 2 (21 bits); 0xFFFFFFFF: Z_r = 0
-  uint32_t sel_rem[2][32];     // rank of the boundary element inside that prefix class, 1-based from the top
+  uint32_t over_cnt[32];     // members of a boundary's bin that found no room in the share of their workgroup
+  uint32_t sel_bin[32];      // selection bin that holds boundary r's key; kNoBin: Z_r = 0
+  uint32_t sel_rem[32];      // rank of the boundary element inside that bin, 1-based from the largest key
+  uint32_t anchor;           // first sample bin of the window that has fine selection bins
   uint32_t tau[32];          // Z_r-th largest key (0xFFFFFFFF: Z_r = 0)
   uint32_t iota[32];         // last of the key == tau_r candidates inside the top Z_r, by its number in the position-ordered list
   uint32_t seg_max_enc[32];  // max over the group of ordered(x); 0 = empty
   uint32_t seg_negmin_enc[32];  // max over the group of ~ordered(x); 0 = empty
   uint32_t hist_sample[kSampleBins];  // sample histogram, accumulated with device-wide atomics
-  uint32_t hist_l1[kL1Bins];    // level-1 digit counts of the candidates (device-wide atomics from the filter)
+  uint32_t bin_map[kMapBins];         // per sample bin of the window: its first selection bin, and above 16 bits the shift that finds the others
+  alignas(8) uint32_t hist_bin[kSelBins];  // candidates per selection bin (device-wide atomics from the filter, two counters each)
 };
 
 // ---- decoder -------------------------------------------------------------------

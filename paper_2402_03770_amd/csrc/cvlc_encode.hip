@@ -12,24 +12,23 @@
 //   upload        per-client parameters as kernel arguments; clears the
 //                 call's control blocks
 //   sample_hist   strided sample of |U| -> histogram of the top 13 key bits
-//   sample_walk   conservative candidate threshold tau_lo from that histogram
+//   sample_walk   conservative candidate threshold tau_lo from that histogram,
+//                 and the selection bins: the range of keys above tau_lo cut
+//                 into pieces of about a thousandth of the candidates each
 //   filter        the one full pass over U.  Every wavefront owns regions of
 //                 1024 to 8192 consecutive coordinates and writes the coordinates with
 //                 key >= tau_lo to the front of the region's slot, in position
-//                 order; it also counts the level-1 digit (top 11 key bits) of
-//                 what it keeps and sums the squares of what it drops
+//                 order; it also counts the selection bins of what it keeps
+//                 and sums the squares of what it drops
 //   scan_l1       prefix over the region counts, list of the non-empty runs;
-//                 level-1 bins of the boundaries (for a client whose sample
+//                 selection bins of the boundaries (for a client whose sample
 //                 misjudged, every coordinate becomes a candidate here)
-//   gather_l2     copies the runs into one dense, position-ordered candidate
-//                 list, spans of 512 candidates per wavefront, and histograms
-//                 level 2 (the next 10 key bits) of the boundaries
-//   select_pass3  level 3: LDS histograms of the last 10 key bits of the
-//                 candidates that match a boundary's 21-bit prefix
-//   select_walk   adds up the histograms, fixes the next digit of every
-//                 boundary; after level 3 the exact boundary keys and, where a
-//                 boundary cuts a class of equal magnitudes, the position of
-//                 its last member inside the boundary
+//   gather        copies the runs into one dense, position-ordered candidate
+//                 list, spans of 512 candidates per wavefront, and sets the
+//                 members of the boundaries' bins aside
+//   select        finds every boundary's element among the members of its bin:
+//                 its key, and its number in the dense list, which cuts a class
+//                 of equal magnitudes
 //   count         per span: group of every candidate and its number among the
 //                 span's members of that group (left for emit, 16 bits per
 //                 candidate), per-group count, min/max/sum of squares; for the
@@ -42,6 +41,7 @@
 //                 on request the error energy of every group
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <type_traits>
@@ -53,6 +53,10 @@ namespace {
 
 constexpr uint32_t kWideBlock = 1024;
 constexpr uint32_t kWideWaves = kWideBlock / kWave;
+constexpr uint32_t kGatherBlock = 1024;  // threads of a gather workgroup
+constexpr uint32_t kGatherWaves = kGatherBlock / kWave;
+constexpr uint32_t kGatherResident = 512;   // gather workgroups the device holds
+constexpr uint32_t kGatherBlocksMax = 64;   // ... and of one client's
 
 // ------------------------------------------------------------------ workspace layout
 // Per-client, per-group constants of the last stages, written by the layout kernel.
@@ -65,11 +69,12 @@ struct GroupInfo {
 
 struct EncodeLayout {
   size_t status, ctl, params, region_cnt, region_sumsq, cand_idx, cand_val, dense_idx, dense_val, nz_off, nz_run, span_first, span_cnt, group_info,
-      tie_list, sel_part, l3_hist, norm_limbs, total;
+      members, seg_cnt, norm_limbs, total;
   size_t zero_bytes;        // [status, params) is cleared at the start of a call
   uint32_t region_shift, n_regions, max_spans;
   uint32_t dense_cap;       // candidates the dense list of a client has room for
-  uint32_t sel_blocks;      // workgroups per client in a level-2/3 selection pass
+  uint32_t gather_blocks;   // workgroups per client in the gather
+  uint32_t member_pool;     // entries of a member list
 };
 
 size_t align256(size_t v) { return (v + 255u) & ~(size_t)255u; }
@@ -88,12 +93,12 @@ uint32_t filter_blocks_per_client(uint32_t n_regions, uint32_t n, uint32_t resid
 // Regions of 1 << region_shift coordinates.  A batch of several regions per resident wavefront takes the longest
 // ones (long runs for the gather, few entries for the region scan).  A smaller batch leaves wavefronts without
 // work, and the few that have some go through the eight sub-tiles of a long region one after the other, 2.5 us
-// each: it takes the shortest regions, down to one sub-tile, that still give no wavefront a second one (seven
-// workgroups of four wavefronts fit a CU; six are counted on) and the region scan no third round.
+// each: it takes the shortest regions, down to one sub-tile, that still give no wavefront a second one (32
+// wavefronts fit a CU; 24 are counted on) and the region scan no third round.
 // filter: 20.6 -> 5.8 us for one client of 65 536 coordinates, 20.6 -> 14.4 us for 8 of 1.2 M.  One client of
 // 11.2 M with regions of 2048: filter 24.3 -> 19.4 us, but scan_l1 6.7 -> 13.1 and the gather 12.0 -> 14.1 us.
 uint32_t region_shift_for(uint32_t d, uint32_t n) {
-  constexpr uint64_t kWavesCounted = 256u * 6u * kWavesPerBlock, kScanRounds = 2u * kWideBlock;
+  constexpr uint64_t kWavesCounted = 256u * 24u, kScanRounds = 2u * kWideBlock;
   uint32_t shift = kRegionShiftMax;
   while (shift > kRegionShiftMin) {
     const uint64_t regions = ((uint64_t)d + (1u << (shift - 1u)) - 1u) >> (shift - 1u);
@@ -112,13 +117,12 @@ EncodeLayout encode_layout(uint32_t d, uint32_t n, uint32_t cap) {
   L.dense_cap = cap < d ? cap : d;
   L.max_spans = (uint32_t)(((uint64_t)L.dense_cap + kSpan - 1) / kSpan);
   {
-    uint32_t b = (512u + n - 1) / n;
-    L.sel_blocks = b < 2 ? 2u : (b > 32 ? 32u : b);
+    uint32_t b = (kGatherResident + n - 1) / n;
+    L.gather_blocks = b < 2 ? 2u : (b > kGatherBlocksMax ? kGatherBlocksMax : b);
   }
   size_t off = 0;
   L.status = off; off = align256(off + 256);
   L.ctl = off; off = align256(off + (size_t)n * sizeof(ClientCtl));
-  L.l3_hist = off; off = align256(off + (size_t)n * kSlotGroupWide * kDigitBins * sizeof(uint32_t));
   L.norm_limbs = off; off = align256(off + (size_t)n * 32 * kNormLimbs * sizeof(uint64_t));
   L.zero_bytes = off;
   L.params = off; off = align256(off + (size_t)n * sizeof(ClientParams));
@@ -133,8 +137,10 @@ EncodeLayout encode_layout(uint32_t d, uint32_t n, uint32_t cap) {
   L.span_first = off; off = align256(off + (size_t)n * (L.max_spans + 1) * sizeof(uint32_t));
   L.span_cnt = off; off = align256(off + (size_t)n * (L.max_spans + 1) * 32 * sizeof(uint32_t));
   L.group_info = off; off = align256(off + (size_t)n * sizeof(GroupInfo));
-  L.tie_list = off; off = align256(off + (size_t)n * kSlotGroupWide * kTieCap * sizeof(uint2));
-  L.sel_part = off; off = align256(off + (size_t)n * L.sel_blocks * kSlotGroupWide * kDigitBins * sizeof(uint32_t));
+  // twice what a list is expected to hold at most; three quarters shared out between the gather's workgroups
+  L.member_pool = std::min(kMemberPoolMin + L.dense_cap / 256u, kMemberPoolMax);
+  L.members = off; off = align256(off + (size_t)n * kMemberSlots * L.member_pool * sizeof(uint2));
+  L.seg_cnt = off; off = align256(off + (size_t)n * kMemberSlots * kGatherBlocksMax * sizeof(uint32_t));
   L.total = off;
   return L;
 }
@@ -154,11 +160,10 @@ struct Workspace {  // device pointers into the caller's workspace
   uint32_t* span_first;  // index (into the non-empty runs) of the run that holds candidate 512 s, per span s
   uint32_t* span_cnt;  // per span of 512 candidates: members of every group, then their exclusive prefix
   GroupInfo* group_info;
-  uint2* tie_list;
-  uint32_t* sel_part;
-  uint32_t* l3_hist;   // level-3 digit counts per (client, slot), zero between uses
+  uint2* members;      // per (client, boundary): the candidates in the boundary's selection bin, {number in the dense list, key}
+  uint32_t* seg_cnt;   // ... and how many of them each of the gather's workgroups has seen
   unsigned long long* norm_limbs;  // QSGD: per (client, group) the exact sum of squares in 32-bit limbs
-  uint32_t d, region_shift, n_regions, max_spans, dense_cap, filter_blocks, sel_blocks;
+  uint32_t d, region_shift, n_regions, max_spans, dense_cap, filter_blocks, gather_blocks, member_pool;
 };
 
 // ------------------------------------------------------------------ parameter upload
@@ -227,7 +232,6 @@ __global__ __launch_bounds__(kBlock) void sample_hist_kernel(const ClientParams*
   const uint32_t client = blockIdx.y;
   const ClientParams& p = params[client];
   ClientCtl* ctl = ctls + client;
-  if (p.sample_rank == 0) return;  // keep-all plan: the threshold stays 0
   for (uint32_t i = threadIdx.x; i < kSampleBins; i += kBlock) hist[i] = 0;
   __syncthreads();
   GlobalFloat4Ptr src = (GlobalFloat4Ptr)p.update;
@@ -264,38 +268,93 @@ __global__ __launch_bounds__(kBlock) void sample_hist_kernel(const ClientParams*
   }
 }
 
+// ---- selection bins
+constexpr uint32_t kNoBin = 0xFFFFFFFFu;
+
+// Selection bin of a key; bins ascend with the keys.
+__device__ __forceinline__ uint32_t selection_bin(const uint32_t* map, uint32_t anchor, uint32_t key) {
+  const uint32_t top = key >> kSampleShift, t = top - anchor;  // keys below the window wrap to large values
+  const uint32_t m = map[min(t, kMapBins - 1u)];
+  const uint32_t fine = (m & 0xFFFFu) + ((key & ((1u << kSampleShift) - 1u)) >> (m >> 16));
+  const uint32_t coarse = (key >> 23) + (top < anchor ? 0u : kOctaves + kFineBins);
+  return t < kMapBins ? fine : coarse;
+}
+
+// The bin map for the window that begins at sample bin `anchor`: hist(b) of the `mass` keys at hand lie in sample
+// bin b.  Whole workgroup of kWideBlock threads; thread w returns entry w (threads past the window: nothing of use).
+template <class Hist>
+__device__ __forceinline__ uint32_t build_bin_map(ClientCtl* ctl, uint32_t k, uint32_t anchor, uint32_t mass, uint32_t* scan_tmp, Hist hist) {
+  const uint32_t aim = max(kFineMin, min(kFineMax, k / kFineShare));
+  const uint32_t w = threadIdx.x;
+  const bool mine = w < kMapBins;
+  uint32_t bits = 0;
+  if (mine && anchor + w < kSampleBins) {
+    const uint32_t share = (uint32_t)((uint64_t)hist(anchor + w) * aim / (mass ? mass : 1u));
+    if (share > 1u) bits = min(31u - (uint32_t)__builtin_clz(share), 10u);
+  }
+  uint32_t total;
+  const uint32_t first = kOctaves + block_excl_scan<kWideWaves>(mine ? 1u << bits : 0u, scan_tmp, &total);
+  const uint32_t entry = first | ((kSampleShift - bits) << 16);
+  if (mine) ctl->bin_map[w] = entry;
+  if (w == 0) ctl->anchor = anchor;
+  return entry;
+}
+static_assert(kSelBins == 2u * kWideBlock, "two bins per thread in the scan");
+static_assert(kMapBins <= kWideBlock && kOctaves + kFineBins < (1u << 16), "one thread per entry of the bin map, bins in 16 bits");
+
+// Sample bins of a thread, largest keys first: thread t owns `kWalkBins` of them, ending at kSampleBins - 1 - kWalkBins * t.
+constexpr uint32_t kWalkBins = kSampleBins / kWideBlock;
+
+// The sample bin that holds the `target`-th largest of the keys counted in h (the caller's bins, `above` keys in
+// larger ones), and how many keys lie in it or above it: written by the one thread that has it.
+__device__ __forceinline__ void find_sample_bin(const uint32_t (&h)[kWalkBins], uint32_t above, uint32_t target,
+                                                uint32_t* bin_out, uint32_t* reached_out) {
+  const uint32_t top = kSampleBins - 1 - kWalkBins * threadIdx.x;
+  uint32_t acc = above;
+#pragma unroll
+  for (uint32_t i = 0; i < kWalkBins; ++i) {
+    if (acc < target && target <= acc + h[i]) {
+      *bin_out = top - i;
+      *reached_out = acc + h[i];
+    }
+    acc += h[i];
+  }
+}
+
 // One workgroup per client walks the sample histogram from the large keys down
 // to the sample rank the host derived from k/d plus a 6-sigma margin.  The
-// lower edge of that bin becomes the candidate threshold.
+// lower edge of that bin becomes the candidate threshold and the window of fine
+// selection bins begins there.  Without a threshold (every coordinate is a
+// candidate) the window ends where the 4096th part of the sample with the
+// largest keys begins: it reaches 16 octaves down from there.
 __global__ __launch_bounds__(kWideBlock) void sample_walk_kernel(const ClientParams* __restrict__ params,
                                                                  ClientCtl* __restrict__ ctls) {
   __shared__ uint32_t scan_tmp[kWideWaves];
+  __shared__ uint32_t s_bin[2], s_reached[2];
   const uint32_t client = blockIdx.x;
   const ClientParams& p = params[client];
   ClientCtl* ctl = ctls + client;
-  if (p.sample_rank == 0) return;
-  // thread t owns `per` bins ending at top = kSampleBins - 1 - per * t, largest keys first
-  constexpr uint32_t per = kSampleBins / kWideBlock;
-  const uint32_t top = kSampleBins - 1 - per * threadIdx.x;
-  uint32_t h[per], mine = 0;
+  const uint32_t target = p.sample_rank;
+  const uint32_t top = kSampleBins - 1 - kWalkBins * threadIdx.x;
+  uint32_t h[kWalkBins], mine = 0;
 #pragma unroll
-  for (uint32_t i = 0; i < per; ++i) {
+  for (uint32_t i = 0; i < kWalkBins; ++i) {
     h[i] = ctl->hist_sample[top - i];
     mine += h[i];
   }
+  if (threadIdx.x < 2u) {
+    s_bin[threadIdx.x] = 0;
+    s_reached[threadIdx.x] = 0;
+  }
   uint32_t total;
   const uint32_t above = block_excl_scan<kWideWaves>(mine, scan_tmp, &total);
-  const uint32_t target = p.sample_rank;
-  if (above < target && target <= above + mine) {
-    uint32_t acc = above, bin = top;
-#pragma unroll
-    for (uint32_t i = 0; i < per; ++i) {
-      acc += h[i];
-      if (acc >= target) { bin = top - i; break; }
-    }
-    ctl->tau_lo = bin << kSampleShift;
-  }
-  // target beyond the sample: tau_lo keeps its cleared value 0 (everything is a candidate)
+  const bool sampled = target != 0u && target <= total;  // else tau_lo keeps its cleared value 0 (everything is a candidate)
+  if (sampled) find_sample_bin(h, above, target, &s_bin[0], &s_reached[0]);
+  else find_sample_bin(h, above, total / 4096u + 1u, &s_bin[1], &s_reached[1]);
+  __syncthreads();
+  if (sampled && threadIdx.x == 0) ctl->tau_lo = s_bin[0] << kSampleShift;
+  const uint32_t anchor = sampled ? s_bin[0] : (s_bin[1] >= kMapBins ? s_bin[1] - (kMapBins - 1u) : 0u);
+  build_bin_map(ctl, p.k, anchor, sampled ? s_reached[0] : total, scan_tmp, [&](uint32_t b) { return ctl->hist_sample[b]; });
 }
 
 // ------------------------------------------------------------------ 2. filter (the full pass)
@@ -326,7 +385,7 @@ __device__ __forceinline__ void load_subtile(SubTile& t, GlobalFloatPtr U, uint3
 }
 
 // Kept coordinates are staged per wavefront in LDS and leave in rows of 64 (one
-// coalesced 512-byte store each); a row also feeds the level-1 histogram.  Loads
+// coalesced 512-byte store each); a row also feeds the histogram over the selection bins.  Loads
 // and stores share one outstanding-operation counter on this hardware, so a
 // wavefront that has just stored must wait for the store's acknowledgement
 // before it can consume its next loads: rows are therefore held back until the
@@ -340,7 +399,9 @@ struct FilterWave {
   uint2* stage;            // this wavefront's staging rows in LDS
   uint16_t* __restrict__ out_idx;  // the region's slot in global memory: positions inside the region (13 bits)
   uint32_t* __restrict__ out_val;  // ... and value bits
-  uint32_t* hist;          // the workgroup's level-1 histogram in LDS
+  uint32_t* hist;          // the workgroup's counts per selection bin, in LDS
+  const uint32_t* map;     // the client's bin map, in LDS
+  uint32_t anchor;
   uint32_t pos_mask;       // coordinates per region - 1
   uint32_t fill;           // staged entries (uniform)
   uint32_t run;            // entries already written to `out` (uniform)
@@ -358,7 +419,7 @@ __device__ __forceinline__ void flush_rows(FilterWave& w, uint32_t lane, bool al
     const uint2 e = w.stage[g + lane];
     w.out_idx[w.run + g + lane] = (uint16_t)(e.x & w.pos_mask);
     w.out_val[w.run + g + lane] = e.y;
-    atomicAdd(&w.hist[(e.y & 0x7FFFFFFFu) >> 20], 1u);
+    atomicAdd(&w.hist[selection_bin(w.map, w.anchor, e.y & 0x7FFFFFFFu)], 1u);
     w.nonfinite |= (e.y & 0x7FFFFFFFu) >= 0x7F800000u ? 1u : 0u;
   }
   const uint32_t left = w.fill - g;  // < 64
@@ -369,7 +430,7 @@ __device__ __forceinline__ void flush_rows(FilterWave& w, uint32_t lane, bool al
       if (lane < left) {
         w.out_idx[w.run + g + lane] = (uint16_t)(e.x & w.pos_mask);
         w.out_val[w.run + g + lane] = e.y;
-        atomicAdd(&w.hist[(e.y & 0x7FFFFFFFu) >> 20], 1u);
+        atomicAdd(&w.hist[selection_bin(w.map, w.anchor, e.y & 0x7FFFFFFFu)], 1u);
         w.nonfinite |= (e.y & 0x7FFFFFFFu) >= 0x7F800000u ? 1u : 0u;
       }
       g += left;
@@ -421,7 +482,8 @@ __device__ __forceinline__ void filter_subtile(const SubTile& t, uint32_t sbase,
 
 __global__ __launch_bounds__(kBlock) void filter_kernel(const ClientParams* __restrict__ params,
                                                         ClientCtl* __restrict__ ctls, Workspace ws) {
-  __shared__ uint32_t s_hist[kL1Bins];
+  __shared__ alignas(8) uint32_t s_hist[kSelBins];
+  __shared__ uint32_t s_map[kMapBins];
   __shared__ uint2 s_stage[kWavesPerBlock][kStageCap];
   // workgroups start in the order of their number, and the older ones get ahead: every client gets its share of both
   const uint32_t lin = blockIdx.y * gridDim.x + blockIdx.x;
@@ -432,7 +494,8 @@ __global__ __launch_bounds__(kBlock) void filter_kernel(const ClientParams* __re
   const uint32_t d = ws.d, n_regions = ws.n_regions, region_len = 1u << ws.region_shift;
   GlobalFloatPtr U = (GlobalFloatPtr)p.update;
   const uint32_t lane = lane_id();
-  for (uint32_t i = threadIdx.x; i < kL1Bins; i += kBlock) s_hist[i] = 0;
+  for (uint32_t i = threadIdx.x; i < kSelBins; i += kBlock) s_hist[i] = 0;
+  for (uint32_t i = threadIdx.x; i < kMapBins; i += kBlock) s_map[i] = ctl->bin_map[i];
   __syncthreads();
 
   double sq = 0.0;
@@ -440,6 +503,8 @@ __global__ __launch_bounds__(kBlock) void filter_kernel(const ClientParams* __re
   FilterWave w;
   w.stage = s_stage[wave_id()];
   w.hist = s_hist;
+  w.map = s_map;
+  w.anchor = ctl->anchor;
   w.pos_mask = region_len - 1u;
   w.nonfinite = 0;
   // Software pipeline over all sub-tiles of all of this wavefront's regions: the
@@ -511,28 +576,31 @@ __global__ __launch_bounds__(kBlock) void filter_kernel(const ClientParams* __re
   // a threshold in the Inf/NaN range can only come from a sample that held such values
   if (w.nonfinite || tau_lo > 0x7F800000u) atomicOr(ws.status, CVLC_DEV_NONFINITE);
   __syncthreads();
-  for (uint32_t i = threadIdx.x; i < kL1Bins; i += kBlock) {
-    const uint32_t h = s_hist[i];
-    if (h) atomicAdd(&ctl->hist_l1[i], h);
+  // two counters an atomic; no carry between them: a client has fewer than 2^32 candidates
+  for (uint32_t i = threadIdx.x; i < kSelBins / 2u; i += kBlock) {
+    const unsigned long long h = reinterpret_cast<const unsigned long long*>(s_hist)[i];
+    if (h) atomicAdd(reinterpret_cast<unsigned long long*>(ctl->hist_bin) + i, h);
   }
 }
 
-// ------------------------------------------------------------------ 3. region prefix + selection level 1
+// ------------------------------------------------------------------ 3. region prefix + the boundaries' selection bins
 // One workgroup per client.  Turns the region counts into exclusive offsets
 // and lists the non-empty runs with the number of their first candidate (the
 // candidates' position-ordered numbering; the gather works in spans of 512
-// candidates, and the run holding every span's first candidate is noted), then reads the level-1
-// histogram the filter's workgroups accumulated and locates, for every boundary
+// candidates, and the run holding every span's first candidate is noted), then reads the counts per
+// selection bin that the filter's workgroups accumulated and locates, for every boundary
 // Z_r, the bin holding the Z_r-th largest key and the rank left inside it.
 // Should the sampled threshold have kept fewer than k coordinates (the sample
 // misjudged: six standard deviations, or a vector built against the sampling
 // pattern), every coordinate becomes a candidate: the runs are then the regions
-// themselves, read from the vector, and this workgroup counts the level-1
-// digits of the whole vector on its own: slow, and next to never needed.
+// themselves, read from the vector, and this workgroup draws up the bin map again, from
+// the whole vector, and counts its selection bins on its own: slow, and next to never needed.
 __global__ __launch_bounds__(kWideBlock) void scan_l1_kernel(const ClientParams* __restrict__ params,
                                                              ClientCtl* __restrict__ ctls, Workspace ws) {
-  __shared__ uint32_t hist[kL1Bins];
-  __shared__ uint32_t incl[kL1Bins];  // keys in bins >= b
+  __shared__ uint32_t hist[kSelBins];
+  __shared__ uint32_t incl[kSelBins];  // keys in bins >= b
+  __shared__ uint32_t top_hist[kSampleBins];  // a misjudged sample: counts of key >> 18 of the whole vector
+  __shared__ uint32_t s_bin, s_reached;
   __shared__ uint32_t scan_tmp[kWideWaves];
   const uint32_t client = blockIdx.x, tid = threadIdx.x;
   const ClientParams& p = params[client];
@@ -542,11 +610,11 @@ __global__ __launch_bounds__(kWideBlock) void scan_l1_kernel(const ClientParams*
   uint32_t* nz_off = ws.nz_off + (size_t)client * (n_regions + 1);
   uint32_t* nz_run = ws.nz_run + (size_t)client * (n_regions + 1);
   uint32_t* span_first = ws.span_first + (size_t)client * (ws.max_spans + 1);
-  // one workgroup per client, all latency: the first two rounds' counts and the level-1 histogram are
+  // one workgroup per client, all latency: the first two rounds' counts and the histogram are
   // requested before anything is waited for
   const uint32_t ahead0 = tid < n_regions ? cnt[tid] : 0u;
   const uint32_t ahead1 = tid + kWideBlock < n_regions ? cnt[tid + kWideBlock] : 0u;
-  const uint32_t l1_even = ctl->hist_l1[2u * tid], l1_odd = ctl->hist_l1[2u * tid + 1];
+  const uint32_t bins_even = ctl->hist_bin[2u * tid], bins_odd = ctl->hist_bin[2u * tid + 1];
   uint32_t run = 0, n_nz = 0;
   for (uint32_t base = 0; base < n_regions; base += kWideBlock) {
     const uint32_t j = base + tid;
@@ -585,8 +653,8 @@ __global__ __launch_bounds__(kWideBlock) void scan_l1_kernel(const ClientParams*
       ctl->n_cand = run;
       ctl->n_nz = n_nz;
     }
-    hist[2u * tid] = l1_even;
-    hist[2u * tid + 1] = l1_odd;
+    hist[2u * tid] = bins_even;
+    hist[2u * tid + 1] = bins_odd;
   } else {
     const uint32_t d = ws.d;
     __syncthreads();  // the runs written above are overwritten
@@ -605,26 +673,45 @@ __global__ __launch_bounds__(kWideBlock) void scan_l1_kernel(const ClientParams*
     }
     hist[2u * tid] = 0;
     hist[2u * tid + 1] = 0;
+    for (uint32_t i = tid; i < kSampleBins; i += kWideBlock) top_hist[i] = 0;
     __syncthreads();
     const uint32_t* __restrict__ bits = reinterpret_cast<const uint32_t*>(p.update);
-    bool nonfinite = false;
-    for (uint32_t base = 0; base < d; base += kWideBlock * 8u) {
-      uint32_t v[8];
+    auto each_key = [&](auto visit) {
+      for (uint32_t base = 0; base < d; base += kWideBlock * 8u) {
+        uint32_t v[8];
 #pragma unroll
-      for (uint32_t u = 0; u < 8; ++u) v[u] = bits[min(base + u * kWideBlock + tid, d - 1u)];
+        for (uint32_t u = 0; u < 8; ++u) v[u] = bits[min(base + u * kWideBlock + tid, d - 1u)];
 #pragma unroll
-      for (uint32_t u = 0; u < 8; ++u) {
-        if (base + u * kWideBlock + tid < d) {
-          const uint32_t key = v[u] & 0x7FFFFFFFu;
-          nonfinite |= key >= 0x7F800000u;
-          atomicAdd(&hist[key >> 20], 1u);
-        }
+        for (uint32_t u = 0; u < 8; ++u)
+          if (base + u * kWideBlock + tid < d) visit(v[u] & 0x7FFFFFFFu);
       }
-    }
+    };
+    bool nonfinite = false;
+    each_key([&](uint32_t key) {
+      nonfinite |= key >= 0x7F800000u;
+      atomicAdd(&top_hist[key >> kSampleShift], 1u);
+    });
     if (nonfinite) atomicOr(ws.status, CVLC_DEV_NONFINITE);
+    __syncthreads();
+    uint32_t h[kWalkBins], mine = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kWalkBins; ++i) {
+      h[i] = top_hist[kSampleBins - 1 - kWalkBins * tid - i];
+      mine += h[i];
+    }
+    uint32_t all;
+    const uint32_t above = block_excl_scan<kWideWaves>(mine, scan_tmp, &all);
+    find_sample_bin(h, above, p.k, &s_bin, &s_reached);  // 1 <= k <= d here: fewer than k were kept
+    __syncthreads();
+    const uint32_t anchor = s_bin;
+    const uint32_t entry = build_bin_map(ctl, p.k, anchor, s_reached, scan_tmp, [&](uint32_t b) { return top_hist[b]; });
+    uint32_t* map = incl;  // not yet in use
+    if (tid < kMapBins) map[tid] = entry;
+    __syncthreads();
+    each_key([&](uint32_t key) { atomicAdd(&hist[selection_bin(map, anchor, key)], 1u); });
   }
   __syncthreads();
-  const uint32_t top = kL1Bins - 1 - 2u * tid;
+  const uint32_t top = kSelBins - 1 - 2u * tid;
   const uint32_t h0 = hist[top], h1 = hist[top - 1];
   uint32_t total;
   const uint32_t above = block_excl_scan<kWideWaves>(h0 + h1, scan_tmp, &total);
@@ -632,178 +719,36 @@ __global__ __launch_bounds__(kWideBlock) void scan_l1_kernel(const ClientParams*
   incl[top - 1] = above + h0 + h1;
   __syncthreads();
   if (tid < 32) {
-    uint32_t pre = 0xFFFFFFFFu, rem = 0;
+    uint32_t bin = kNoBin, rem = 0;
     if (tid < p.R) {
       const uint32_t Z = p.Z[tid];
       if (Z > total) atomicOr(ws.status, CVLC_DEV_INTERNAL);  // cannot happen once the filter kept >= k
       if (Z != 0 && Z <= total) {
-        uint32_t lo = 0, hi = kL1Bins - 1;  // largest bin b with incl[b] >= Z
+        uint32_t lo = 0, hi = kSelBins - 1;  // largest bin b with incl[b] >= Z
         while (lo < hi) {
           const uint32_t mid = (lo + hi + 1) >> 1;
           if (incl[mid] >= Z) lo = mid; else hi = mid - 1;
         }
-        pre = lo;
+        bin = lo;
         rem = Z - (incl[lo] - hist[lo]);
       }
     }
-    ctl->sel_prefix[0][tid] = pre;
-    ctl->sel_rem[0][tid] = rem;
+    ctl->sel_bin[tid] = bin;
+    ctl->sel_rem[tid] = rem;
     ctl->tau[tid] = 0xFFFFFFFFu;  // boundaries with Z_r = 0 keep "nothing inside"
     ctl->iota[tid] = 0u;
   }
 }
 
-// ------------------------------------------------------------------ 4. selection, levels 2 and 3
-// LEVEL 2 refines bits 19..10, LEVEL 3 bits 9..0 of the boundary keys.  The
-// kernels come in two sizes SG: room for 15 boundaries (plans of up to 15
-// groups: 60 KB of counters, two workgroups to a CU) or for all 31 (124 KB, one
-// workgroup to a CU).  Boundaries that share a prefix share a histogram
-// ("slot").  The pass (level 2: the gather) histograms, in LDS, the next digit
-// of every candidate whose key starts with a slot's prefix; level 2 stores one
-// partial histogram per workgroup, level 3 adds its few counts to one table per
-// client; the walk kernel (one workgroup per slot and client) adds them up and
-// reads off every boundary's digit.
-// During level 3 the few candidates matching a boundary's 21-bit prefix are
-// also kept aside, so that a boundary cutting through a class of equal keys
-// can find the position of the last member inside it (ties rank by position).
-constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
-
-template <uint32_t SG>
-struct SlotTable {
-  uint32_t prefix[SG];  // slot -> key prefix (11 bits at level 2, 21 bits at level 3)
-  uint32_t leader[SG];  // boundary inside the group -> its slot, kNoSlot for Z_r = 0
-  uint32_t n;
-};
-
-// Lane of the first of the lanes 0..SG-1 that are `valid` and hold the
-// caller's value (the caller's own lane if none is earlier).  Whole wavefront;
-// the result means something for valid lanes below SG only.
-template <uint32_t SG>
-__device__ __forceinline__ uint32_t first_equal_lane(uint32_t value, bool valid) {
-  const uint64_t vmask = __ballot(valid);
-  const uint32_t lane = lane_id();
-  uint32_t first = lane;
-#pragma unroll
-  for (int j = (int)SG - 1; j >= 0; --j) {
-    const uint32_t vj = __builtin_amdgcn_readlane(value, j);
-    if (((vmask >> j) & 1u) && (uint32_t)j < lane && vj == value) first = (uint32_t)j;
-  }
-  return first;
-}
-
-// Slots in order of first appearance among the group's boundaries.  Run by one
-// whole wavefront whose lane b < nb holds boundary b's prefix.  Returns the
-// caller's slot (kNoSlot: Z_r = 0 or no boundary) and whether it opens it.
-template <uint32_t SG>
-__device__ __forceinline__ uint32_t build_slots(SlotTable<SG>& st, uint32_t pre, uint32_t nb, bool* opens) {
-  const uint32_t lane = lane_id();
-  const bool valid = lane < nb && pre != 0xFFFFFFFFu;
-  const uint32_t first = first_equal_lane<SG>(pre, valid);
-  const bool leader = valid && first == lane;
-  const uint64_t leaders = __ballot(leader);
-  const uint32_t slot = valid ? (uint32_t)__popcll(leaders & ((1ull << first) - 1ull)) : kNoSlot;
-  if (leader) st.prefix[slot] = pre;
-  if (lane < SG) st.leader[lane] = slot;
-  if (lane == 0) st.n = (uint32_t)__popcll(leaders);
-  *opens = leader;
-  return slot;
-}
-
-constexpr uint32_t kNoDigit = 0xFFFFFFFFu;
-constexpr uint32_t kTieStage = 64;  // kept-aside candidates a workgroup stages per slot
-static_assert(kTieStage <= kWave, "one wavefront moves a slot's staged candidates in one step");
-
-// LEVEL 2 counts every candidate of a boundary's level-1 bin: a full histogram per slot.  LEVEL 3 counts the
-// handful of candidates that share a boundary's 21-bit prefix (more only when many keys are equal, and
-// equal keys share the digit): per slot one digit with its count, met first by the workgroup; candidates
-// with another digit are added straight to the client's table.
-template <uint32_t SG, int LEVEL>
-struct SelectShared {
-  uint32_t hist[LEVEL == 2 ? SG * kDigitBins : 1];
-  uint32_t l3_digit[SG], l3_count[SG];
-  // level 3: the candidates kept aside wait here and join the client's lists when the workgroup is done (one
-  // device-wide atomic per slot and workgroup instead of one per wavefront row that holds such a candidate:
-  // a client's counters share a cache line, and atomics to one line queue up); what does not fit goes directly
-  uint2 tie_stage[LEVEL == 3 ? SG : 1][kTieStage];
-  uint32_t tie_n[SG];
-  SlotTable<SG> slots;
-  // top 11 key bits -> 1 + (level 2: slot, level 3: bin id); 4 bits each for up to 15 slots, 8 bits beyond
-  static constexpr uint32_t kTagBits = SG <= 15 ? 4u : 8u, kTagsPerWord = 32u / kTagBits;
-  uint32_t bin_slot[kL1Bins / kTagsPerWord];
-  uint32_t digit_map[SG][kDigitBins / 32];  // level 3: second digits present per bin id
-  uint32_t tie_full[SG];                 // this workgroup has seen the slot's kept-aside list overflow
-
-  __device__ __forceinline__ uint32_t bin_tag(uint32_t top11) const {
-    return (bin_slot[top11 / kTagsPerWord] >> ((top11 % kTagsPerWord) * kTagBits)) & ((1u << kTagBits) - 1u);
-  }
-  __device__ __forceinline__ void set_bin_tag(uint32_t top11, uint32_t tag) {  // once per top11, tag <= SG
-    atomicOr(&bin_slot[top11 / kTagsPerWord], tag << ((top11 % kTagsPerWord) * kTagBits));
-  }
-};
-// Level 2 for up to 15 boundaries: two workgroups to a CU.  All 31 at once: one workgroup.
-static_assert(sizeof(SelectShared<kSlotGroup, 2>) <= 65536 && sizeof(SelectShared<kSlotGroupWide, 2>) <= 160 * 1024 - 2048,
-              "SelectShared must fit the CU's LDS");
-
-// Counts one candidate per lane (`live` lanes only); dense_i is its number in the
-// position-ordered candidate list (which ranks equal keys just as positions do).
-// Must be reached by all lanes of the wavefront.
-template <int LEVEL, uint32_t SG>
-__device__ __forceinline__ void select_count(SelectShared<SG, LEVEL>& S, uint32_t key, uint32_t dense_i, bool live,
-                                             uint32_t* tie_cnt, uint2* __restrict__ ties, uint32_t* table) {
-  uint32_t q = kNoSlot;
-  if (live) {
-    const uint32_t tag = S.bin_tag(key >> 20);
-    if (tag) {
-      if (LEVEL == 2) {
-        atomicAdd(&S.hist[(tag - 1) * kDigitBins + ((key >> 10) & (kDigitBins - 1))], 1u);
-      } else {
-        const uint32_t second = (key >> 10) & (kDigitBins - 1);
-        if ((S.digit_map[tag - 1][second >> 5] >> (second & 31u)) & 1u) {
-          const uint32_t pre = key >> 10, ns = S.slots.n;
-          for (uint32_t qq = 0; qq < ns; ++qq)
-            if (S.slots.prefix[qq] == pre) q = qq;
-        }
-      }
-    }
-  }
-  if (LEVEL == 3) {
-    const uint32_t digit = key & (kDigitBins - 1);
-    uint64_t todo = __ballot(q != kNoSlot);
-    while (todo) {  // one round per distinct (slot, last digit) present in the wavefront
-      const uint32_t leader = (uint32_t)__builtin_ctzll(todo);
-      const uint32_t qs = __builtin_amdgcn_readlane(q, leader), ds = __builtin_amdgcn_readlane(digit, leader);
-      const bool mine = q == qs && digit == ds;
-      const uint64_t peers = __ballot(mine);
-      const uint32_t n_peers = (uint32_t)__popcll(peers);
-      uint32_t staged = 0;
-      if (lane_id() == leader) {
-        const uint32_t seen = atomicCAS(&S.l3_digit[qs], kNoDigit, ds);
-        if (seen == kNoDigit || seen == ds) atomicAdd(&S.l3_count[qs], n_peers);
-        else atomicAdd(&table[qs * kDigitBins + ds], n_peers);
-        staged = atomicAdd(&S.tie_n[qs], n_peers);  // grows past kTieStage once the stage is full
-      }
-      staged = __builtin_amdgcn_readlane(staged, leader);
-      const uint32_t place = staged + lanes_below(peers);
-      if (mine && place < kTieStage) S.tie_stage[qs][place] = make_uint2(dense_i, digit);
-      const uint64_t over = __ballot(mine && place >= kTieStage);
-      if (over) {  // uniform
-        const uint32_t first_over = (uint32_t)__builtin_ctzll(over);
-        uint32_t base = kTieCap;
-        if (lane_id() == first_over && !S.tie_full[qs]) {
-          base = atomicAdd(&tie_cnt[qs], (uint32_t)__popcll(over));
-          if (base >= kTieCap) S.tie_full[qs] = 1u;  // the count is past the cap for good: stop adding to it
-        }
-        base = __builtin_amdgcn_readlane(base, first_over);
-        if (mine && place >= kTieStage) {
-          const uint32_t pos = base + lanes_below(over);
-          if (pos < kTieCap) ties[qs * kTieCap + pos] = make_uint2(dense_i, digit);
-        }
-      }
-      todo &= ~peers;
-    }
-  }
-}
-
+// ------------------------------------------------------------------ 4. selection inside the boundaries' bins
+// scan_l1 has left, for every boundary, the selection bin its key lies in and
+// the boundary's rank inside that bin.  A bin holds about a thousandth of the
+// candidates, so the gather, which reads every candidate anyway, sets the
+// members of the boundaries' bins aside ({number in the dense list, key}), and
+// the select kernel finds each boundary's element among them.  Its number in the
+// dense list cuts a class of equal keys (ties rank by position, and that
+// numbering preserves positions): keys above tau are inside, and so are those
+// equal to it up to number iota.
 // ---- walking the filter's output in position order
 constexpr uint32_t kNoGroup = 0xFFFFFFFFu;
 constexpr uint32_t kEmitBlock = kSpan * kChunkSpans / 8u;  // threads of a count/emit workgroup: 8 candidates each
@@ -912,80 +857,98 @@ __device__ __forceinline__ void span_slots(const CandView& cv, uint32_t span, co
   for (uint32_t j = 0; j < kPerLane; ++j) slot[j] += begin + j * kWave + lane;  // meaningless for i >= n, never used there
 }
 
-// A workgroup's partial level-2 histogram is stored in 16-bit counters when no workgroup can
-// see more than 65535 candidates (the gather: whole spans dealt round the wavefronts; the
-// later passes: an equal share each): half the bytes written and read back.
-__device__ __forceinline__ bool narrow_partials(uint32_t n_cand, uint32_t blocks) { return n_cand <= 32768u * blocks; }
-
-__device__ __forceinline__ void store_partials(const uint32_t* hist, uint32_t used, uint32_t* part, bool narrow) {
-  if (narrow) {
-    for (uint32_t i = threadIdx.x; i < used / 2u; i += kWideBlock) part[i] = hist[2u * i] | (hist[2u * i + 1u] << 16);
-  } else {
-    for (uint32_t i = threadIdx.x; i < used; i += kWideBlock) part[i] = hist[i];
-  }
+// How a client's member lists are laid out: a piece for every gather workgroup that has spans to go through, three
+// quarters of the list in all, and behind them the room for what found its piece full.
+struct MemberPieces {
+  uint32_t blocks, cap, over_first, over_room;
+};
+__device__ __forceinline__ MemberPieces member_pieces(const Workspace& ws, uint32_t n_cand) {
+  MemberPieces mp;
+  mp.blocks = max(1u, min(ws.gather_blocks, (n_cand + kSpan * kGatherWaves - 1u) / (kSpan * kGatherWaves)));
+  mp.cap = ws.member_pool / 4u * 3u / mp.blocks;
+  mp.over_first = mp.blocks * mp.cap;
+  mp.over_room = ws.member_pool - mp.over_first;
+  return mp;
 }
 
-// Fills the workgroup's slot tables for the plan's boundaries.
-template <int LEVEL, uint32_t SG>
-__device__ __forceinline__ void select_setup(SelectShared<SG, LEVEL>& S, const ClientCtl* ctl, uint32_t nb) {
-  const uint32_t tid = threadIdx.x;
-  if (LEVEL == 2)
-    for (uint32_t i = tid; i < SG * kDigitBins; i += kWideBlock) S.hist[i] = 0;
-  if (tid < SG) {
-    S.l3_digit[tid] = kNoDigit;
-    S.l3_count[tid] = 0;
-    S.tie_n[tid] = 0;
-  }
-  for (uint32_t i = tid; i < kL1Bins / SelectShared<SG, LEVEL>::kTagsPerWord; i += kWideBlock) S.bin_slot[i] = 0;
-  for (uint32_t i = tid; i < SG * (kDigitBins / 32); i += kWideBlock) (&S.digit_map[0][0])[i] = 0;
-  if (tid < SG) S.tie_full[tid] = 0;
-  uint32_t pre = 0xFFFFFFFFu;
-  if (tid < nb) pre = ctl->sel_prefix[LEVEL - 2][tid];
-  __syncthreads();
-  if (tid < kWave) {  // the first wavefront, lane b = boundary b
-    bool opens;
-    const uint32_t slot = build_slots<SG>(S.slots, pre, nb, &opens);
-    if (LEVEL == 2) {
-      if (opens) S.set_bin_tag(pre, slot + 1);
-    } else {
-      // the slots' top 11 bits are numbered in order of first appearance as well
-      const uint32_t top11 = pre >> 10, second = pre & (kDigitBins - 1);
-      const uint32_t first = first_equal_lane<SG>(top11, opens);
-      const uint64_t bin_openers = __ballot(opens && first == tid);
-      if (opens) {
-        const uint32_t bin = (uint32_t)__popcll(bin_openers & ((1ull << first) - 1ull));
-        if (first == tid) S.set_bin_tag(top11, bin + 1);
-        atomicOr(&S.digit_map[bin][second >> 5], 1u << (second & 31u));
-      }
-    }
-  }
-  __syncthreads();
-}
+// What the wavefronts of a gather workgroup share.
+struct GatherShared {
+  uint32_t map[kMapBins];
+  uint8_t tag[kSelBins];       // per selection bin: 1 + the first boundary whose key lies in it, 0: none
+  uint32_t seen[kMemberSlots + 1];  // members of every boundary's bin met by this workgroup
+  uint32_t full[kMemberSlots + 1];  // the bin's list has no room left
+  uint32_t bin[32];
+};
 
-// Level 2, fused with the gather: every
-// wavefront takes spans of 512 candidates (gw, gw + wavefronts, ...), collects
+// Every wavefront takes spans of 512 candidates (gw, gw + wavefronts, ...), collects
 // them from the region runs they lie in, stores them at their place in the
-// dense position-ordered candidate list and counts the level-2 digits on the
-// way.  Every span is the same amount of work wherever its candidates lie.
-// The wavefronts do not wait for each other until the histogram is stored.
-template <uint32_t SG>
-__global__ __launch_bounds__(kWideBlock) void gather_l2_kernel(const ClientParams* __restrict__ params,
-                                                               ClientCtl* __restrict__ ctls, Workspace ws) {
-  __shared__ SelectShared<SG, 2> S;
+// dense position-ordered candidate list and sets the members of the boundaries'
+// bins aside.  Every span is the same amount of work wherever its candidates lie,
+// and the wavefronts do not wait for each other.
+// Bound by its mixed traffic (6 bytes read and 8 written per candidate).  A member list is shared out: every
+// workgroup has a piece of its own, so that a member takes its place with an LDS atomic; only what a piece has no
+// room for takes one with a device-wide atomic, behind the pieces, and what finds that full too is not stored
+// (the select kernel then walks the dense list).
+__global__ __launch_bounds__(kGatherBlock) void gather_kernel(const ClientParams* __restrict__ params,
+                                                              ClientCtl* __restrict__ ctls, Workspace ws) {
+  __shared__ GatherShared S;
   const uint32_t client = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
   const ClientParams& p = params[client];
   ClientCtl* ctl = ctls + client;
   if (ctl->dead) return;  // the workspace was too short for this client (whole workgroup)
-  const uint32_t nb = min(p.R, SG);
-  select_setup<2, SG>(S, ctl, nb);
+  const uint32_t R = p.R, anchor = ctl->anchor;
+  for (uint32_t i = tid; i < kMapBins; i += kGatherBlock) S.map[i] = ctl->bin_map[i];
+  for (uint32_t i = tid; i < kSelBins / 4u; i += kGatherBlock) reinterpret_cast<uint32_t*>(S.tag)[i] = 0;
+  if (tid < 32) {
+    S.bin[tid] = tid < R ? ctl->sel_bin[tid] : kNoBin;
+    S.seen[tid] = 0;
+    S.full[tid] = 0;
+  }
+  __syncthreads();
+  if (tid < R) {
+    const uint32_t bin = S.bin[tid];
+    bool first = bin != kNoBin;
+    for (uint32_t b = 0; b < tid; ++b) first = first && S.bin[b] != bin;
+    if (first) S.tag[bin] = (uint8_t)(tid + 1u);
+  }
+  __syncthreads();
   const CandView cv = cand_view(ws, ctl, client);
   uint32_t* __restrict__ dst_idx = ws.dense_idx + (size_t)client * ws.dense_cap;
   uint32_t* __restrict__ dst_val = ws.dense_val + (size_t)client * ws.dense_cap;
+  uint2* __restrict__ members = ws.members + (size_t)client * kMemberSlots * ws.member_pool;
+  const MemberPieces mp = member_pieces(ws, cv.n);
+  if (blockIdx.x >= mp.blocks) return;  // no span is left for this workgroup
+  const uint32_t piece = blockIdx.x * mp.cap;
+  // slot: 1 + boundary, 0: in no boundary's bin
+  auto set_aside = [&](uint32_t slot, uint32_t dense_i, uint32_t key) {
+    bool over = false;
+    if (slot) {
+      const uint32_t place = atomicAdd(&S.seen[slot - 1u], 1u);
+      if (place < mp.cap) members[(slot - 1u) * ws.member_pool + piece + place] = make_uint2(dense_i, key);
+      else over = S.full[slot - 1u] == 0;
+    }
+    uint64_t todo = __ballot(over);
+    while (todo) {  // one device-wide atomic per boundary and row
+      const uint32_t leader = (uint32_t)__builtin_ctzll(todo), q = __builtin_amdgcn_readlane(slot, leader) - 1u;
+      const uint64_t peers = __ballot(over && slot == q + 1u);
+      uint32_t base = 0;
+      if (lane == leader) {
+        base = atomicAdd(&ctl->over_cnt[q], (uint32_t)__popcll(peers));
+        if (base >= mp.over_room) S.full[q] = 1u;  // the count is past the room for good: stop adding to it
+      }
+      base = __builtin_amdgcn_readlane(base, leader);
+      if (over && slot == q + 1u) {
+        const uint32_t place = base + lanes_below(peers);
+        if (place < mp.over_room) members[q * ws.member_pool + mp.over_first + place] = make_uint2(dense_i, key);
+      }
+      todo &= ~peers;
+    }
+  };
   const uint32_t n_spans = (cv.n + kSpan - 1) / kSpan;
   // keep_all: a slot is a region of the vector itself and a candidate's place in it its position
   auto copy_spans = [&](auto keep_all) {
     const uint32_t* __restrict__ src_val = keep_all.value ? reinterpret_cast<const uint32_t*>(p.update) : cv.val;
-    for (uint32_t span = blockIdx.x * kWideWaves + wave; span < n_spans; span += gridDim.x * kWideWaves) {
+    for (uint32_t span = blockIdx.x * kGatherWaves + wave; span < n_spans; span += mp.blocks * kGatherWaves) {
       uint32_t slot[kPerLane], v[kPerLane], x[kPerLane];
       span_slots(cv, span, span_window(cv, span), slot);
 #pragma unroll
@@ -996,225 +959,192 @@ __global__ __launch_bounds__(kWideBlock) void gather_l2_kernel(const ClientParam
         v[j] = src_val[sl];
         x[j] = keep_all.value ? sl : ((sl >> cv.region_shift) << cv.region_shift) + cv.idx[sl];  // a slot starts where its region starts
       }
+      uint32_t tag[kPerLane];
 #pragma unroll
       for (uint32_t j = 0; j < kPerLane; ++j) {
         const uint32_t i = span * kSpan + j * kWave + lane;
-        if (i - lane >= cv.n) break;  // uniform
         if (i < cv.n) {
           dst_val[i] = v[j];
           dst_idx[i] = x[j];
         }
-        if (nb) select_count<2, SG>(S, v[j] & 0x7FFFFFFFu, 0u, i < cv.n, nullptr, nullptr, nullptr);
+        tag[j] = i < cv.n ? S.tag[selection_bin(S.map, anchor, v[j] & 0x7FFFFFFFu)] : 0u;
       }
+#pragma unroll
+      for (uint32_t j = 0; j < kPerLane; ++j)
+        if (__ballot(tag[j] != 0u)) set_aside(tag[j], span * kSpan + j * kWave + lane, v[j] & 0x7FFFFFFFu);
     }
   };
   if (ctl->keep_all) copy_spans(std::true_type{}); else copy_spans(std::false_type{});
   __syncthreads();
-  if (nb == 0) return;
-  uint32_t* part = ws.sel_part + ((size_t)client * gridDim.x + blockIdx.x) * SG * kDigitBins;
-  store_partials(S.hist, S.slots.n * kDigitBins, part, narrow_partials(cv.n, gridDim.x));
+  if (tid < R) ws.seg_cnt[((size_t)client * kMemberSlots + tid) * kGatherBlocksMax + blockIdx.x] = S.seen[tid];
 }
 
-// Level 3 reads the dense list.  (With 31 slots the compiler would keep 90 scalar registers, and past 80 or so a
-// CU takes one workgroup of 1024 threads instead of two: capped.)
-template <uint32_t SG>
-__global__ __launch_bounds__(kWideBlock) __attribute__((amdgpu_num_sgpr(64))) void select_pass3_kernel(const ClientParams* __restrict__ params,
-                                                                  ClientCtl* __restrict__ ctls, Workspace ws) {
-  __shared__ SelectShared<SG, 3> S;
-  const uint32_t client = blockIdx.y, tid = threadIdx.x, wave = tid / kWave;
+// One workgroup per (boundary, client); boundaries whose keys lie in one bin are
+// all served by the first of them.  A member is one 64-bit number, the key above
+// the complement of its number in the dense list, so that members rank as the
+// coordinates do (larger keys first, earlier positions first) and no two are
+// alike.  Ten bits at a time below the highest bit in which the members differ
+// are counted, until a wavefront's worth of them is left.
+// All latency: one or two rounds of a handful of barriers each.
+constexpr uint32_t kSelectBlock = 512;
+constexpr uint32_t kSelectList = 2048;  // members kept in LDS; more are read again for every round
+constexpr uint32_t kSelectWaves = kSelectBlock / kWave;
+constexpr uint32_t kSelectDigits = 2u * kSelectBlock;  // two per thread
+static_assert(kSelectDigits == 1024u, "ten bits a round");
+
+__global__ __launch_bounds__(kSelectBlock) void select_kernel(const ClientParams* __restrict__ params,
+                                                              ClientCtl* __restrict__ ctls, Workspace ws) {
+  __shared__ unsigned long long list[kSelectList];
+  __shared__ uint32_t map[kMapBins];
+  __shared__ uint32_t hist[kSelectDigits];
+  __shared__ uint32_t s_bin[32], s_rem[32], seg_first[kGatherBlocksMax + 1], scan_tmp[kSelectWaves];
+  __shared__ unsigned long long s_min, s_max, s_answer, few[kWave];
+  __shared__ uint32_t s_digit, s_left, s_in_digit, n_few;
+  const uint32_t r = blockIdx.x, client = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wave = wave_id();
   const ClientParams& p = params[client];
   ClientCtl* ctl = ctls + client;
-  if (ctl->dead) return;  // the workspace was too short for this client (whole workgroup)
-  if (p.R == 0) return;  // nothing is coded
-  const uint32_t nb = min(p.R, SG);
-  const uint32_t* __restrict__ val = ws.dense_val + (size_t)client * ws.dense_cap;
-  uint2* ties = ws.tie_list + (size_t)client * SG * kTieCap;
-  uint32_t* tie_cnt = ctl->tie_cnt;
-  uint32_t* table = ws.l3_hist + (size_t)client * SG * kDigitBins;
-  select_setup<3, SG>(S, ctl, nb);
-
-  const uint32_t n = ctl->n_cand;
-  const uint32_t span = (uint32_t)(((uint64_t)n + gridDim.x - 1) / gridDim.x);
-  const uint64_t begin64 = (uint64_t)blockIdx.x * span;
-  const uint32_t begin = (uint32_t)(begin64 < n ? begin64 : n);
-  const uint32_t end = (uint32_t)(begin64 + span < n ? begin64 + span : n);
-  for (uint32_t base = begin; base < end; base += kWideBlock * 8u) {
-    uint32_t v[8];
-#pragma unroll
-    for (uint32_t u = 0; u < 8; ++u) {
-      const uint32_t i = base + u * kWideBlock + tid;
-      v[u] = 0;
-      if (i < end) v[u] = val[i];
-    }
-#pragma unroll
-    for (uint32_t u = 0; u < 8; ++u) {
-      const uint32_t i = base + u * kWideBlock + tid;
-      if (base + u * kWideBlock + wave * kWave >= end) break;  // uniform per wavefront
-      select_count<3, SG>(S, v[u] & 0x7FFFFFFFu, i, i < end, tie_cnt, ties, table);
-    }
-  }
-  __syncthreads();
-  // the slots' own digits go to the client's table now, the staged candidates to the kept-aside lists
-  if (tid < S.slots.n && S.l3_count[tid]) atomicAdd(&table[tid * kDigitBins + S.l3_digit[tid]], S.l3_count[tid]);
-  const uint32_t lane = lane_id();
-  for (uint32_t q = wave; q < S.slots.n; q += kWideWaves) {  // a wavefront per slot
-    const uint32_t n_staged = min(S.tie_n[q], kTieStage);
-    if (n_staged == 0) continue;
-    uint32_t base = kTieCap;
-    if (lane == 0) base = atomicAdd(&tie_cnt[q], n_staged);  // a count past the cap only says "too many"
-    base = __builtin_amdgcn_readlane(base, 0);
-    if (lane < n_staged && base + lane < kTieCap) ties[q * kTieCap + base + lane] = S.tie_stage[q][lane];
-  }
-}
-
-// One workgroup per (histogram slot, client): thread t owns digit t.  The
-// partial histograms are added up, a suffix sum from the largest digit gives
-// "keys with digit >= t", and every boundary that shares the slot reads off its
-// digit and the rank left inside it.
-template <int LEVEL, uint32_t SG>
-__global__ __launch_bounds__(kWideBlock) void select_walk_kernel(const ClientParams* __restrict__ params,
-                                                                 ClientCtl* __restrict__ ctls, Workspace ws) {
-  __shared__ SlotTable<SG> slots;
-  __shared__ uint32_t s_digit[SG], s_quota[SG], s_need[SG], s_rem[SG];
-  __shared__ uint32_t s_found;
-  __shared__ uint32_t scan_tmp[kWideWaves];
-  __shared__ uint2 s_list[LEVEL == 3 ? kTieCap : 1];
-  const uint32_t slot = blockIdx.x, client = blockIdx.y, tid = threadIdx.x;
-  const ClientParams& p = params[client];
-  ClientCtl* ctl = ctls + client;
-  if (ctl->dead) return;  // the workspace was too short for this client (whole workgroup)
-  const uint32_t n_cand = ctl->n_cand;  // asked for together with R
-  if (p.R == 0) return;
-  const uint32_t nb = min(p.R, SG);
-  const uint32_t n_parts = ws.sel_blocks;
-  const uint32_t* parts = ws.sel_part + (size_t)client * n_parts * SG * kDigitBins;
-  // Everything the walk reads from global memory is requested here, before the
-  // first wait.  Thread t takes digit 1023 - t, so that the scan runs from the top
-  // digit down; a slot past the last one in use adds up stale partials for nothing.
-  uint32_t pre = 0xFFFFFFFFu, rem_in = 0;
-  if (tid < nb) {
-    pre = ctl->sel_prefix[LEVEL - 2][tid];
-    rem_in = ctl->sel_rem[LEVEL - 2][tid];
-    // the level's results go to arrays of their own: other workgroups of this launch may still have to read its inputs
-    if (LEVEL == 2 && slot == 0 && pre == 0xFFFFFFFFu) ctl->sel_prefix[1][tid] = pre;
-  }
-  const uint32_t kept = LEVEL == 3 ? ctl->tie_cnt[slot] : 0u;
-  const uint32_t digit = kDigitBins - 1 - tid;
-  uint32_t h = 0;
-  if (LEVEL == 3) {  // one table per client; left cleared for the next call
-    uint32_t* mine = ws.l3_hist + ((size_t)client * SG + slot) * kDigitBins + digit;
-    h = *mine;
-    *mine = 0;
-  } else {
-    if (narrow_partials(n_cand, n_parts)) {
-      const uint16_t* narrow = reinterpret_cast<const uint16_t*>(parts);
-#pragma unroll 8
-      for (uint32_t b = 0; b < n_parts; ++b)
-        h += narrow[((size_t)b * SG * kDigitBins) * 2u + (size_t)slot * kDigitBins + digit];
-    } else {
-#pragma unroll 8
-      for (uint32_t b = 0; b < n_parts; ++b) h += parts[((size_t)b * SG + slot) * kDigitBins + digit];
-    }
-  }
-  if (tid < SG) {
-    s_need[tid] = 0;
-    s_rem[tid] = rem_in;
+  // everything that is read from the control block is asked for together
+  const uint32_t dead = ctl->dead, R = p.R, n_cand = ctl->n_cand, over_cnt = ctl->over_cnt[r];
+  const uint32_t my_bin = tid < 32 ? ctl->sel_bin[tid] : kNoBin, my_rem = tid < 32 ? ctl->sel_rem[tid] : 0u;
+  uint32_t seen = 0;
+  if (tid < ws.gather_blocks) seen = ws.seg_cnt[((size_t)client * kMemberSlots + r) * kGatherBlocksMax + tid];
+  const MemberPieces mp = member_pieces(ws, n_cand);
+  if (dead || r >= R) return;  // uniform (dead: the workspace was too short for this client)
+  if (tid < 32) {
+    s_bin[tid] = my_bin;
+    s_rem[tid] = my_rem;
   }
   if (tid < kWave) {
-    bool opens;
-    build_slots<SG>(slots, pre, nb, &opens);
+    static_assert(kGatherBlocksMax <= kWave, "one lane per piece of a member list");
+    const uint32_t here = tid < mp.blocks ? min(seen, mp.cap) : 0u, incl = wave_incl_scan_u32(here);
+    seg_first[tid] = incl - here;
+    if (tid == kWave - 1u) seg_first[kWave] = incl;
   }
   __syncthreads();
-  if (slot >= slots.n) return;
-  uint32_t total;
-  const uint32_t above = block_excl_scan<kWideWaves>(h, scan_tmp, &total);  // keys with a larger digit
-  const uint32_t prefix = slots.prefix[slot];
-  for (uint32_t b = 0; b < nb; ++b) {
-    if (slots.leader[b] != slot) continue;
-    const uint32_t r = b;
-    const uint32_t rem = s_rem[b];
-    if (rem > total && tid == 0) atomicOr(ws.status, CVLC_DEV_INTERNAL);  // histogram short of the rank
-    if (above < rem && rem <= above + h) {  // exactly one thread
-      const uint32_t quota = rem - above;   // rank inside the digit class, 1-based
-      const uint32_t full = (prefix << 10) | digit;
-      if (LEVEL == 2) {
-        ctl->sel_prefix[1][r] = full;
-        ctl->sel_rem[1][r] = quota;
-      } else {
-        ctl->tau[r] = full;
-        ctl->iota[r] = 0xFFFFFFFFu;  // every member of the class is inside unless it straddles Z_r
-        s_digit[b] = digit;
-        s_quota[b] = quota;
-        s_need[b] = quota < h ? 1u : 0u;
+  const uint32_t bin = s_bin[r];
+  if (bin == kNoBin) return;
+  for (uint32_t b = 0; b < r; ++b)
+    if (s_bin[b] == bin) return;  // uniform: served by the workgroup of boundary b
+  const bool walk_all = over_cnt > mp.over_room;  // some members were not stored
+  const uint32_t in_segs = seg_first[kWave], m = in_segs + min(over_cnt, mp.over_room);
+  auto member_of = [](uint32_t dense_i, uint32_t key) { return ((unsigned long long)key << 32) | (uint32_t)~dense_i; };
+  const uint2* __restrict__ src = ws.members + ((size_t)client * kMemberSlots + r) * ws.member_pool;
+  auto stored_member = [&](uint32_t e) {
+    uint32_t at = mp.over_first + e - in_segs;
+    if (e < in_segs) {  // a thread finds its member's piece by the pieces' first places: six probes
+      uint32_t s = 0;
+#pragma unroll
+      for (uint32_t step = kWave / 2u; step; step >>= 1)
+        if (seg_first[s + step] <= e) s += step;
+      at = s * mp.cap + e - seg_first[s];
+    }
+    const uint2 x = src[at];
+    return member_of(x.x, x.y);
+  };
+  const bool in_lds = m <= kSelectList;
+  if (walk_all) {
+    for (uint32_t i = tid; i < kMapBins; i += kSelectBlock) map[i] = ctl->bin_map[i];
+  } else if (in_lds) {
+    for (uint32_t e = tid; e < m; e += kSelectBlock) list[e] = stored_member(e);
+  }
+  const uint32_t anchor = ctl->anchor;
+  const uint32_t* __restrict__ val = ws.dense_val + (size_t)client * ws.dense_cap;
+  auto each_member = [&](auto visit) {
+    if (!walk_all) {  // entries of `list` that this thread has written itself
+      for (uint32_t e = tid; e < m; e += kSelectBlock) visit(in_lds ? list[e] : stored_member(e));
+    } else {  // next to never: a bin with thousands of equal keys
+      for (uint32_t base = 0; base < n_cand; base += kSelectBlock * 8u) {
+        uint32_t v[8];
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) v[u] = val[min(base + u * kSelectBlock + tid, n_cand - 1u)];
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) {
+          const uint32_t i = base + u * kSelectBlock + tid, key = v[u] & 0x7FFFFFFFu;
+          if (i < n_cand && selection_bin(map, anchor, key) == bin) visit(member_of(i, key));
+        }
       }
     }
-  }
-  if (LEVEL == 3) {
-    __syncthreads();
-    // a class of equal keys straddles the boundary: find its quota-th member in position order
-    const uint2* list = ws.tie_list + ((size_t)client * SG + slot) * kTieCap;
-    const uint32_t* __restrict__ val = ws.dense_val + (size_t)client * ws.dense_cap;
-    const uint32_t n = ctl->n_cand;
-    for (uint32_t b = 0; b < nb; ++b) {
-      if (!s_need[b]) continue;  // uniform
-      const uint32_t r = b, w_digit = s_digit[b], w_quota = s_quota[b];
-      if (kept <= kTieCap) {
-        // position-order rank of every kept-aside member of the class, all threads, list in LDS
+  };
+  for (uint32_t b = r; b < R; ++b) {
+    if (s_bin[b] != bin) continue;  // uniform
+    uint32_t rem = s_rem[b];
+    unsigned long long prefix = 0;  // members at hand: those whose bits from `known` up are `prefix`
+    uint32_t known = 63;            // keys have 31 bits
+    bool found = false;
+    while (!found) {
+      __syncthreads();  // the map is in place; the round before is done with what is written below
+      if (tid == 0) {
+        s_min = ~0ull;
+        s_max = 0;
+        s_in_digit = 0;
+        n_few = 0;
+        s_answer = ~0ull;
+      }
+      hist[tid] = 0;
+      hist[tid + kSelectBlock] = 0;
+      __syncthreads();
+      unsigned long long lo = ~0ull, hi = 0;
+      each_member([&](unsigned long long c) {
+        if ((c >> known) != prefix) return;
+        lo = c < lo ? c : lo;
+        hi = c > hi ? c : hi;
+      });
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const unsigned long long lo2 = __shfl_xor(lo, o, 64), hi2 = __shfl_xor(hi, o, 64);
+        lo = lo2 < lo ? lo2 : lo;
+        hi = hi2 > hi ? hi2 : hi;
+      }
+      if (lane == 0 && lo <= hi) {
+        atomicMin(&s_min, lo);
+        atomicMax(&s_max, hi);
+      }
+      __syncthreads();
+      lo = s_min;
+      hi = s_max;
+      if (lo > hi) break;  // uniform: no member at hand (cannot happen; reported below)
+      const uint32_t top_bit = lo == hi ? 0u : 63u - (uint32_t)__builtin_clzll(lo ^ hi);
+      const uint32_t shift = top_bit > 9u ? top_bit - 9u : 0u;
+      each_member([&](unsigned long long c) {
+        if ((c >> known) == prefix) atomicAdd(&hist[(uint32_t)(c >> shift) & (kSelectDigits - 1u)], 1u);
+      });
+      __syncthreads();
+      const uint32_t digit = kSelectDigits - 1u - 2u * tid;  // and the one below; larger digits first
+      const uint32_t h0 = hist[digit], h1 = hist[digit - 1u];
+      uint32_t total;
+      const uint32_t above = block_excl_scan<kSelectWaves>(h0 + h1, scan_tmp, &total);
+      if (above < rem && rem <= above + h0 + h1) {  // exactly one thread
+        const bool second = rem > above + h0;
+        s_digit = second ? digit - 1u : digit;
+        s_left = rem - above - (second ? h0 : 0u);
+        s_in_digit = second ? h1 : h0;
+      }
+      __syncthreads();
+      if (s_in_digit == 0) break;  // uniform: fewer members than the rank (cannot happen; reported below)
+      prefix = ((lo >> shift) & ~(unsigned long long)(kSelectDigits - 1u)) | s_digit;  // the bits above the digit are common to all
+      known = shift;
+      rem = s_left;
+      if (s_in_digit <= kWave) {
+        each_member([&](unsigned long long c) {
+          if ((c >> known) == prefix) few[atomicAdd(&n_few, 1u)] = c;
+        });
         __syncthreads();
-        for (uint32_t e = tid; e < kept; e += kWideBlock) s_list[e] = list[e];
-        __syncthreads();
-        for (uint32_t e = tid; e < kept; e += kWideBlock) {
-          const uint2 me = s_list[e];
-          if (me.y != w_digit) continue;
+        if (wave == 0) {
+          const unsigned long long mine = lane < s_in_digit ? few[lane] : 0ull;
           uint32_t before = 0;
-          for (uint32_t o = 0; o < kept; ++o) {
-            const uint2 other = s_list[o];
-            before += (other.y == w_digit && other.x < me.x) ? 1u : 0u;
-          }
-          if (before + 1 == w_quota) ctl->iota[r] = me.x;
+          for (uint32_t o = 0; o < s_in_digit; ++o) before += few[o] > mine ? 1u : 0u;
+          if (lane < s_in_digit && before + 1u == rem) s_answer = mine;
         }
+        __syncthreads();
+        found = true;
+      }
+    }
+    if (tid == 0) {
+      if (!found || s_answer == ~0ull) {
+        atomicOr(ws.status, CVLC_DEV_INTERNAL);
       } else {
-        // too many to keep aside: walk the whole candidate list.  Every wavefront counts the members
-        // of the class in a contiguous sixteenth of the list; the one whose share holds the
-        // quota-th member then walks it again, row by row.  No workgroup barrier inside the walks.
-        const uint32_t tau = (prefix << 10) | w_digit;
-        const uint32_t lane = lane_id(), wave = tid / kWave;
-        const uint32_t share = ((n + kWideBlock - 1) / kWideBlock) * kWave;  // a multiple of 64
-        const uint32_t w_begin = min(wave * share, n), w_end = min(w_begin + share, n);
-        __syncthreads();
-        if (tid == 0) s_found = 0;
-        uint32_t mine = 0;
-        for (uint32_t base = w_begin; base < w_end; base += kWave * 8u) {
-          uint32_t v[8];
-#pragma unroll
-          for (uint32_t u = 0; u < 8; ++u) v[u] = val[min(base + u * kWave + lane, n - 1u)];
-#pragma unroll
-          for (uint32_t u = 0; u < 8; ++u)
-            mine += (uint32_t)__popcll(__ballot(base + u * kWave + lane < w_end && (v[u] & 0x7FFFFFFFu) == tau));
-        }
-        if (lane == 0) scan_tmp[wave] = mine;
-        __syncthreads();
-        uint32_t before = 0;
-        for (uint32_t w = 0; w < wave; ++w) before += scan_tmp[w];
-        if (before < w_quota && w_quota <= before + mine) {  // uniform per wavefront: exactly one takes this
-          uint32_t left = w_quota - before;
-          for (uint32_t base = w_begin; base < w_end; base += kWave) {
-            const uint32_t i = base + lane;
-            const bool hit = i < w_end && (val[min(i, n - 1u)] & 0x7FFFFFFFu) == tau;
-            const uint64_t m = __ballot(hit);
-            const uint32_t c = (uint32_t)__popcll(m);
-            if (left <= c) {
-              if (hit && lanes_below(m) + 1u == left) {
-                ctl->iota[r] = i;
-                s_found = 1;
-              }
-              break;
-            }
-            left -= c;
-          }
-        }
-        __syncthreads();
-        if (tid == 0 && !s_found) atomicOr(ws.status, CVLC_DEV_INTERNAL);
+        ctl->tau[b] = (uint32_t)(s_answer >> 32);
+        ctl->iota[b] = ~(uint32_t)s_answer;
       }
     }
   }
@@ -2166,9 +2096,8 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
   ws.span_first = reinterpret_cast<uint32_t*>(base + L.span_first);
   ws.span_cnt = reinterpret_cast<uint32_t*>(base + L.span_cnt);
   ws.group_info = reinterpret_cast<GroupInfo*>(base + L.group_info);
-  ws.tie_list = reinterpret_cast<uint2*>(base + L.tie_list);
-  ws.sel_part = reinterpret_cast<uint32_t*>(base + L.sel_part);
-  ws.l3_hist = reinterpret_cast<uint32_t*>(base + L.l3_hist);
+  ws.members = reinterpret_cast<uint2*>(base + L.members);
+  ws.seg_cnt = reinterpret_cast<uint32_t*>(base + L.seg_cnt);
   ws.norm_limbs = reinterpret_cast<unsigned long long*>(base + L.norm_limbs);
   ws.d = d;
   ws.region_shift = L.region_shift;
@@ -2176,19 +2105,19 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
   ws.max_spans = L.max_spans;
   ws.dense_cap = L.dense_cap;
   ws.filter_blocks = filter_blocks_per_client(L.n_regions, n, filter_resident_blocks());
-  ws.sel_blocks = L.sel_blocks;
+  ws.gather_blocks = L.gather_blocks;
+  ws.member_pool = L.member_pool;
 
   // sample geometry: 256-byte pieces spread evenly; all of them when the vector is short
   const uint32_t n_src = d / kSamplePiece;
   const uint32_t n_s = n_src < kSampleChunksMax ? n_src : kSampleChunksMax;
 
   profile_mark(CVLC_STAGE_ENC_SETUP, true, stream);
-  // the status word, the control blocks and the level-3 table start every call at zero
+  // the status word and the control blocks start every call at zero
   uint32_t zero_n16 = (uint32_t)(L.zero_bytes / 16u);  // n <= 65535 clients: below 2^32 pieces
 
   // per-client parameters, shipped as kernel arguments
   uint32_t max_R = 0;
-  bool any_sampled = false;
   {
     UploadChunk chunk;
     chunk.n_clients = 0;
@@ -2222,7 +2151,6 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
       }
       cp.k = z;
       cp.sample_rank = sample_rank(d, z, n_s * kSamplePiece);
-      any_sampled |= cp.sample_rank != 0;
       if (pl.n_coded > max_R) max_R = pl.n_coded;
       for (int attempt = 0; attempt < 2; ++attempt) {
         uint32_t t = 0;
@@ -2252,11 +2180,12 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
   }
   profile_mark(CVLC_STAGE_ENC_SETUP, false, stream);
 
-  if (any_sampled) {
+  {
     StageScope scope(CVLC_STAGE_ENC_SAMPLE, stream);
-    // n_src < 2^26 and n_s <= 2^12: the step is below 2^58 / n_s and j * step below 2^58
-    hipLaunchKernelGGL(sample_hist_kernel, dim3(kSampleBlocks, n), dim3(kBlock), 0, stream, ws.params, ws.ctl, n_s,
-                       n_s ? ((uint64_t)n_src << 32) / n_s : 0u);
+    // also for plans that keep everything: the selection bins are laid out by the sample.  n_src < 2^26 and n_s <= 2^12: the step is below 2^58 / n_s and j * step below 2^58
+    if (n_s)
+      hipLaunchKernelGGL(sample_hist_kernel, dim3(kSampleBlocks, n), dim3(kBlock), 0, stream, ws.params, ws.ctl, n_s,
+                         ((uint64_t)n_src << 32) / n_s);
     hipLaunchKernelGGL(sample_walk_kernel, dim3(n), dim3(kWideBlock), 0, stream, ws.params, ws.ctl);
   }
   {
@@ -2269,23 +2198,10 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
   }
   {
     StageScope scope(CVLC_STAGE_ENC_SELECT, stream);
-    const dim3 grid(L.sel_blocks, n);
-    // The gather also builds the dense candidate list (also when nothing is coded).  Up to 15 boundaries:
-    // 60 KB of LDS counters, two workgroups to a CU.  More: all of them in one round of launches with
-    // 124 KB of counters, one workgroup to a CU, instead of three rounds over the candidates.
-    if (max_R <= kSlotGroup) {
-      constexpr uint32_t SG = kSlotGroup;
-      hipLaunchKernelGGL(gather_l2_kernel<SG>, grid, dim3(kWideBlock), 0, stream, ws.params, ws.ctl, ws);
-      hipLaunchKernelGGL((select_walk_kernel<2, SG>), dim3(SG, n), dim3(kWideBlock), 0, stream, ws.params, ws.ctl, ws);
-      hipLaunchKernelGGL(select_pass3_kernel<SG>, grid, dim3(kWideBlock), 0, stream, ws.params, ws.ctl, ws);
-      hipLaunchKernelGGL((select_walk_kernel<3, SG>), dim3(SG, n), dim3(kWideBlock), 0, stream, ws.params, ws.ctl, ws);
-    } else {
-      constexpr uint32_t SG = kSlotGroupWide;
-      hipLaunchKernelGGL(gather_l2_kernel<SG>, grid, dim3(kWideBlock), 0, stream, ws.params, ws.ctl, ws);
-      hipLaunchKernelGGL((select_walk_kernel<2, SG>), dim3(SG, n), dim3(kWideBlock), 0, stream, ws.params, ws.ctl, ws);
-      hipLaunchKernelGGL(select_pass3_kernel<SG>, grid, dim3(kWideBlock), 0, stream, ws.params, ws.ctl, ws);
-      hipLaunchKernelGGL((select_walk_kernel<3, SG>), dim3(SG, n), dim3(kWideBlock), 0, stream, ws.params, ws.ctl, ws);
-    }
+    // the gather also builds the dense candidate list (also when nothing is coded)
+    hipLaunchKernelGGL(gather_kernel, dim3(L.gather_blocks, n), dim3(kGatherBlock), 0, stream, ws.params, ws.ctl, ws);
+    if (max_R)
+      hipLaunchKernelGGL(select_kernel, dim3(max_R, n), dim3(kSelectBlock), 0, stream, ws.params, ws.ctl, ws);
   }
   // count: wavefronts walk the spans; about what the device holds at once (four workgroups per CU)
   uint32_t g_count = (1024u + n - 1) / n;

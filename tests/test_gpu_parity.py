@@ -245,6 +245,36 @@ def test_region_lengths(n, d):
     check_encode(host, plans, 14, list(range(n)))
 
 
+def _selection_vectors(kind, d, rng):
+    """Magnitudes that the selection bins (a thousandth of the sampled candidates each, 16 octaves of them) fit badly."""
+    sign = np.where(rng.random(d) < 0.5, -1.0, 1.0)
+    if kind == "octaves":          # far more octaves than the fine bins reach
+        return (sign * 10.0 ** rng.uniform(-36.0, 36.0, d)).astype(np.float32)
+    if kind == "few values":       # thousands of equal keys in every boundary's bin
+        return (sign * 2.0 ** rng.integers(-3, 4, d)).astype(np.float32)
+    if kind == "bfloat16":         # seven mantissa bits: every bin one key, some of them full
+        return (torch.from_numpy((rng.standard_normal(d) * 1e-2).astype(np.float32)).to(torch.bfloat16).float().numpy().copy())
+    if kind == "zeros":            # nothing above zero below the first tenth
+        return np.where(rng.random(d) < 0.1, sign * rng.random(d), 0.0).astype(np.float32)
+    U = (rng.standard_normal(d) * 1e-3).astype(np.float32)
+    if kind == "one outlier":
+        U[rng.integers(d)] = 1e30
+    return U
+
+
+@pytest.mark.parametrize("share", [0.02, 0.45, 1.0])
+@pytest.mark.parametrize("kind", ["octaves", "few values", "bfloat16", "zeros", "one outlier", "plain"])
+@pytest.mark.parametrize("d", [50, 5000, 600_000])
+def test_selection_bins(d, kind, share):
+    """Boundaries in bins that hold next to nothing, everything, or more than their list has room for; with `share` 1
+    every coordinate is coded and no threshold is sampled."""
+    U = _selection_vectors(kind, d, np.random.default_rng(d))
+    counts = [max(1, int(d * share * f)) for f in (0.001, 0.009, 0.09, 0.2, 0.3, 0.2)]
+    counts.append(max(int(d * share) - sum(counts), 0))
+    p = orc.plan_manual(d, [12, 10, 8, 6, 4, 2, 1], counts)
+    check_encode([U], [p], 17, [4])
+
+
 # --------------------------------------------------------------------------- batches of clients with different plans
 def test_batch_with_mixed_plans():
     d = 150_000
