@@ -84,7 +84,6 @@ struct ClientCtl {
   uint32_t seg_negmin_enc[32];  // max over the group of ~ordered(x); 0 = empty
   uint32_t hist_sample[kSampleBins];  // sample histogram, accumulated with device-wide atomics
   uint32_t bin_map[kMapBins];         // per sample bin of the window: its first selection bin, and above 16 bits the shift that finds the others
-  alignas(8) uint32_t hist_bin[kSelBins];  // candidates per selection bin (device-wide atomics from the filter, two counters each)
 };
 
 // ---- decoder -------------------------------------------------------------------

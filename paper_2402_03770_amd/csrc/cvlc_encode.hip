@@ -69,12 +69,13 @@ struct GroupInfo {
 
 struct EncodeLayout {
   size_t status, ctl, params, region_cnt, region_sumsq, cand_idx, cand_val, dense_idx, dense_val, nz_off, nz_run, span_first, span_cnt, group_info,
-      members, seg_cnt, norm_limbs, total;
+      hist_bins, members, seg_cnt, norm_limbs, total;
   size_t zero_bytes;        // [status, params) is cleared at the start of a call
   uint32_t region_shift, n_regions, max_spans;
   uint32_t dense_cap;       // candidates the dense list of a client has room for
   uint32_t gather_blocks;   // workgroups per client in the gather
   uint32_t member_pool;     // entries of a member list
+  uint32_t hist_copies;     // of a client's counts per selection bin
 };
 
 size_t align256(size_t v) { return (v + 255u) & ~(size_t)255u; }
@@ -94,11 +95,12 @@ uint32_t filter_blocks_per_client(uint32_t n_regions, uint32_t n, uint32_t resid
 // ones (long runs for the gather, few entries for the region scan).  A smaller batch leaves wavefronts without
 // work, and the few that have some go through the eight sub-tiles of a long region one after the other, 2.5 us
 // each: it takes the shortest regions, down to one sub-tile, that still give no wavefront a second one (32
-// wavefronts fit a CU; 24 are counted on) and the region scan no third round.
+// wavefronts fit a CU; 24 are counted on) and the region scan no fourth round.
 // filter: 20.6 -> 5.8 us for one client of 65 536 coordinates, 20.6 -> 14.4 us for 8 of 1.2 M.  One client of
-// 11.2 M with regions of 2048: filter 24.3 -> 19.4 us, but scan_l1 6.7 -> 13.1 and the gather 12.0 -> 14.1 us.
+// 11.2 M: filter 27.8 -> 20.6 us with regions of 4096 (scan_l1 and the gather 1.5 and 1.2 us more); with regions of
+// 2048 scan_l1 takes 13.1 us and more is lost than won.
 uint32_t region_shift_for(uint32_t d, uint32_t n) {
-  constexpr uint64_t kWavesCounted = 256u * 24u, kScanRounds = 2u * kWideBlock;
+  constexpr uint64_t kWavesCounted = 256u * 24u, kScanRounds = 3u * kWideBlock;
   uint32_t shift = kRegionShiftMax;
   while (shift > kRegionShiftMin) {
     const uint64_t regions = ((uint64_t)d + (1u << (shift - 1u)) - 1u) >> (shift - 1u);
@@ -124,6 +126,10 @@ EncodeLayout encode_layout(uint32_t d, uint32_t n, uint32_t cap) {
   L.status = off; off = align256(off + 256);
   L.ctl = off; off = align256(off + (size_t)n * sizeof(ClientCtl));
   L.norm_limbs = off; off = align256(off + (size_t)n * 32 * kNormLimbs * sizeof(uint64_t));
+  // The filter's workgroups add their counts to the client's by atomics, which queue up at each cache line: with few
+  // clients, hundreds of workgroups on the same lines, so such a client has several copies.
+  L.hist_copies = n >= 8u ? 1u : 8u / n;
+  L.hist_bins = off; off = align256(off + (size_t)n * L.hist_copies * kSelBins * sizeof(uint32_t));
   L.zero_bytes = off;
   L.params = off; off = align256(off + (size_t)n * sizeof(ClientParams));
   L.region_cnt = off; off = align256(off + (size_t)n * L.n_regions * sizeof(uint32_t));
@@ -137,8 +143,8 @@ EncodeLayout encode_layout(uint32_t d, uint32_t n, uint32_t cap) {
   L.span_first = off; off = align256(off + (size_t)n * (L.max_spans + 1) * sizeof(uint32_t));
   L.span_cnt = off; off = align256(off + (size_t)n * (L.max_spans + 1) * 32 * sizeof(uint32_t));
   L.group_info = off; off = align256(off + (size_t)n * sizeof(GroupInfo));
-  // twice what a list is expected to hold at most; three quarters shared out between the gather's workgroups
-  L.member_pool = std::min(kMemberPoolMin + L.dense_cap / 256u, kMemberPoolMax);
+  // several times what a list is expected to hold (a bin of bfloat16 values is one key, and a hundredth of them); three quarters shared out between the gather's workgroups
+  L.member_pool = std::min(kMemberPoolMin + L.dense_cap / 128u, kMemberPoolMax);
   L.members = off; off = align256(off + (size_t)n * kMemberSlots * L.member_pool * sizeof(uint2));
   L.seg_cnt = off; off = align256(off + (size_t)n * kMemberSlots * kGatherBlocksMax * sizeof(uint32_t));
   L.total = off;
@@ -160,10 +166,11 @@ struct Workspace {  // device pointers into the caller's workspace
   uint32_t* span_first;  // index (into the non-empty runs) of the run that holds candidate 512 s, per span s
   uint32_t* span_cnt;  // per span of 512 candidates: members of every group, then their exclusive prefix
   GroupInfo* group_info;
+  uint32_t* hist_bins; // per client, hist_copies times: candidates per selection bin (device-wide atomics from the filter, two counters each)
   uint2* members;      // per (client, boundary): the candidates in the boundary's selection bin, {number in the dense list, key}
   uint32_t* seg_cnt;   // ... and how many of them each of the gather's workgroups has seen
   unsigned long long* norm_limbs;  // QSGD: per (client, group) the exact sum of squares in 32-bit limbs
-  uint32_t d, region_shift, n_regions, max_spans, dense_cap, filter_blocks, gather_blocks, member_pool;
+  uint32_t d, region_shift, n_regions, max_spans, dense_cap, filter_blocks, gather_blocks, member_pool, hist_copies;
 };
 
 // ------------------------------------------------------------------ parameter upload
@@ -577,9 +584,11 @@ __global__ __launch_bounds__(kBlock) void filter_kernel(const ClientParams* __re
   if (w.nonfinite || tau_lo > 0x7F800000u) atomicOr(ws.status, CVLC_DEV_NONFINITE);
   __syncthreads();
   // two counters an atomic; no carry between them: a client has fewer than 2^32 candidates
+  unsigned long long* mine = reinterpret_cast<unsigned long long*>(
+      ws.hist_bins + ((size_t)client * ws.hist_copies + block_x % ws.hist_copies) * kSelBins);
   for (uint32_t i = threadIdx.x; i < kSelBins / 2u; i += kBlock) {
     const unsigned long long h = reinterpret_cast<const unsigned long long*>(s_hist)[i];
-    if (h) atomicAdd(reinterpret_cast<unsigned long long*>(ctl->hist_bin) + i, h);
+    if (h) atomicAdd(mine + i, h);
   }
 }
 
@@ -614,7 +623,14 @@ __global__ __launch_bounds__(kWideBlock) void scan_l1_kernel(const ClientParams*
   // requested before anything is waited for
   const uint32_t ahead0 = tid < n_regions ? cnt[tid] : 0u;
   const uint32_t ahead1 = tid + kWideBlock < n_regions ? cnt[tid + kWideBlock] : 0u;
-  const uint32_t bins_even = ctl->hist_bin[2u * tid], bins_odd = ctl->hist_bin[2u * tid + 1];
+  uint2 bins = make_uint2(0u, 0u);
+  const uint2* counted = reinterpret_cast<const uint2*>(ws.hist_bins + (size_t)client * ws.hist_copies * kSelBins);
+#pragma unroll 8
+  for (uint32_t c = 0; c < ws.hist_copies; ++c) {
+    const uint2 x = counted[c * (kSelBins / 2u) + tid];
+    bins.x += x.x;
+    bins.y += x.y;
+  }
   uint32_t run = 0, n_nz = 0;
   for (uint32_t base = 0; base < n_regions; base += kWideBlock) {
     const uint32_t j = base + tid;
@@ -653,8 +669,8 @@ __global__ __launch_bounds__(kWideBlock) void scan_l1_kernel(const ClientParams*
       ctl->n_cand = run;
       ctl->n_nz = n_nz;
     }
-    hist[2u * tid] = bins_even;
-    hist[2u * tid + 1] = bins_odd;
+    hist[2u * tid] = bins.x;
+    hist[2u * tid + 1] = bins.y;
   } else {
     const uint32_t d = ws.d;
     __syncthreads();  // the runs written above are overwritten
@@ -980,11 +996,13 @@ __global__ __launch_bounds__(kGatherBlock) void gather_kernel(const ClientParams
 }
 
 // One workgroup per (boundary, client); boundaries whose keys lie in one bin are
-// all served by the first of them.  A member is one 64-bit number, the key above
+// all served by the first of them, unless the bin's list was too short for it.  A member is one 64-bit number, the key above
 // the complement of its number in the dense list, so that members rank as the
 // coordinates do (larger keys first, earlier positions first) and no two are
 // alike.  Ten bits at a time below the highest bit in which the members differ
-// are counted, until a wavefront's worth of them is left.
+// are counted, until a wavefront's worth of them is left.  A bin that more keys lie in than its list has room for
+// (thousands of equal keys) is walked in the dense list, every boundary by its own workgroup, until LDS can hold
+// what is left of it.
 // All latency: one or two rounds of a handful of barriers each.
 constexpr uint32_t kSelectBlock = 512;
 constexpr uint32_t kSelectList = 2048;  // members kept in LDS; more are read again for every round
@@ -997,15 +1015,16 @@ __global__ __launch_bounds__(kSelectBlock) void select_kernel(const ClientParams
   __shared__ unsigned long long list[kSelectList];
   __shared__ uint32_t map[kMapBins];
   __shared__ uint32_t hist[kSelectDigits];
-  __shared__ uint32_t s_bin[32], s_rem[32], seg_first[kGatherBlocksMax + 1], scan_tmp[kSelectWaves];
+  __shared__ uint32_t s_bin[32], s_rem[32], s_over[32], seg_first[kGatherBlocksMax + 1], scan_tmp[kSelectWaves];
   __shared__ unsigned long long s_min, s_max, s_answer, few[kWave];
-  __shared__ uint32_t s_digit, s_left, s_in_digit, n_few;
+  __shared__ uint32_t s_digit, s_left, s_in_digit, s_larger, n_few;
   const uint32_t r = blockIdx.x, client = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wave = wave_id();
   const ClientParams& p = params[client];
   ClientCtl* ctl = ctls + client;
   // everything that is read from the control block is asked for together
-  const uint32_t dead = ctl->dead, R = p.R, n_cand = ctl->n_cand, over_cnt = ctl->over_cnt[r];
+  const uint32_t dead = ctl->dead, R = p.R, n_cand = ctl->n_cand;
   const uint32_t my_bin = tid < 32 ? ctl->sel_bin[tid] : kNoBin, my_rem = tid < 32 ? ctl->sel_rem[tid] : 0u;
+  const uint32_t my_over = tid < 32 ? ctl->over_cnt[tid] : 0u;
   uint32_t seen = 0;
   if (tid < ws.gather_blocks) seen = ws.seg_cnt[((size_t)client * kMemberSlots + r) * kGatherBlocksMax + tid];
   const MemberPieces mp = member_pieces(ws, n_cand);
@@ -1013,6 +1032,7 @@ __global__ __launch_bounds__(kSelectBlock) void select_kernel(const ClientParams
   if (tid < 32) {
     s_bin[tid] = my_bin;
     s_rem[tid] = my_rem;
+    s_over[tid] = my_over;
   }
   if (tid < kWave) {
     static_assert(kGatherBlocksMax <= kWave, "one lane per piece of a member list");
@@ -1023,10 +1043,12 @@ __global__ __launch_bounds__(kSelectBlock) void select_kernel(const ClientParams
   __syncthreads();
   const uint32_t bin = s_bin[r];
   if (bin == kNoBin) return;
-  for (uint32_t b = 0; b < r; ++b)
-    if (s_bin[b] == bin) return;  // uniform: served by the workgroup of boundary b
-  const bool walk_all = over_cnt > mp.over_room;  // some members were not stored
-  const uint32_t in_segs = seg_first[kWave], m = in_segs + min(over_cnt, mp.over_room);
+  uint32_t first = 0;  // the first boundary with this bin: the list is its
+  while (s_bin[first] != bin) ++first;
+  bool walk_all = s_over[first] > mp.over_room;  // some members were not stored
+  if (first != r && !walk_all) return;           // uniform: served by the workgroup of that boundary
+  const uint32_t in_segs = seg_first[kWave];
+  uint32_t m = in_segs + min(s_over[first], mp.over_room);
   auto member_of = [](uint32_t dense_i, uint32_t key) { return ((unsigned long long)key << 32) | (uint32_t)~dense_i; };
   const uint2* __restrict__ src = ws.members + ((size_t)client * kMemberSlots + r) * ws.member_pool;
   auto stored_member = [&](uint32_t e) {
@@ -1041,7 +1063,7 @@ __global__ __launch_bounds__(kSelectBlock) void select_kernel(const ClientParams
     const uint2 x = src[at];
     return member_of(x.x, x.y);
   };
-  const bool in_lds = m <= kSelectList;
+  const bool in_lds = walk_all || m <= kSelectList;
   if (walk_all) {
     for (uint32_t i = tid; i < kMapBins; i += kSelectBlock) map[i] = ctl->bin_map[i];
   } else if (in_lds) {
@@ -1050,33 +1072,40 @@ __global__ __launch_bounds__(kSelectBlock) void select_kernel(const ClientParams
   const uint32_t anchor = ctl->anchor;
   const uint32_t* __restrict__ val = ws.dense_val + (size_t)client * ws.dense_cap;
   auto each_member = [&](auto visit) {
-    if (!walk_all) {  // entries of `list` that this thread has written itself
+    if (!walk_all) {
       for (uint32_t e = tid; e < m; e += kSelectBlock) visit(in_lds ? list[e] : stored_member(e));
-    } else {  // next to never: a bin with thousands of equal keys
-      for (uint32_t base = 0; base < n_cand; base += kSelectBlock * 8u) {
-        uint32_t v[8];
+    } else {
+      constexpr uint32_t kDeep = 16;
+      for (uint32_t base = 0; base < n_cand; base += kSelectBlock * kDeep) {
+        uint32_t v[kDeep];
 #pragma unroll
-        for (uint32_t u = 0; u < 8; ++u) v[u] = val[min(base + u * kSelectBlock + tid, n_cand - 1u)];
+        for (uint32_t u = 0; u < kDeep; ++u) v[u] = val[min(base + u * kSelectBlock + tid, n_cand - 1u)];
 #pragma unroll
-        for (uint32_t u = 0; u < 8; ++u) {
+        for (uint32_t u = 0; u < kDeep; ++u) {
           const uint32_t i = base + u * kSelectBlock + tid, key = v[u] & 0x7FFFFFFFu;
           if (i < n_cand && selection_bin(map, anchor, key) == bin) visit(member_of(i, key));
         }
       }
     }
   };
-  for (uint32_t b = r; b < R; ++b) {
+  const uint32_t b_end = walk_all ? r + 1u : R;
+  for (uint32_t b = r; b < b_end; ++b) {
     if (s_bin[b] != bin) continue;  // uniform
     uint32_t rem = s_rem[b];
     unsigned long long prefix = 0;  // members at hand: those whose bits from `known` up are `prefix`
     uint32_t known = 63;            // keys have 31 bits
     bool found = false;
+    // A list overflows where thousands of keys are equal: the first walk counts the members above the key of some
+    // member and sorts those with that very key by their numbers; the boundary is nearly always among them.
+    bool guess = walk_all;
+    const uint32_t likely = guess ? src[mp.over_first].y : 0u;
     while (!found) {
-      __syncthreads();  // the map is in place; the round before is done with what is written below
+      __syncthreads();  // the map or the list is in place; the round before is done with what is written below
       if (tid == 0) {
         s_min = ~0ull;
         s_max = 0;
         s_in_digit = 0;
+        s_larger = 0;
         n_few = 0;
         s_answer = ~0ull;
       }
@@ -1084,35 +1113,50 @@ __global__ __launch_bounds__(kSelectBlock) void select_kernel(const ClientParams
       hist[tid + kSelectBlock] = 0;
       __syncthreads();
       unsigned long long lo = ~0ull, hi = 0;
-      each_member([&](unsigned long long c) {
-        if ((c >> known) != prefix) return;
-        lo = c < lo ? c : lo;
-        hi = c > hi ? c : hi;
-      });
+      uint32_t shift = 0;
+      if (guess) {
+        lo = member_of(0u, likely);  // any number: they differ below the digit and in it
+        const uint32_t bits = n_cand > 1u ? 32u - (uint32_t)__builtin_clz(n_cand - 1u) : 1u;
+        shift = bits > 10u ? bits - 10u : 0u;
+        uint32_t larger = 0;
+        each_member([&](unsigned long long c) {
+          const uint32_t key = (uint32_t)(c >> 32);
+          larger += key > likely ? 1u : 0u;
+          if (key == likely) atomicAdd(&hist[(uint32_t)(c >> shift) & (kSelectDigits - 1u)], 1u);
+        });
+        larger = wave_sum_u32(larger);
+        if (lane == 0 && larger) atomicAdd(&s_larger, larger);
+      } else {
+        each_member([&](unsigned long long c) {
+          if ((c >> known) != prefix) return;
+          lo = c < lo ? c : lo;
+          hi = c > hi ? c : hi;
+        });
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        const unsigned long long lo2 = __shfl_xor(lo, o, 64), hi2 = __shfl_xor(hi, o, 64);
-        lo = lo2 < lo ? lo2 : lo;
-        hi = hi2 > hi ? hi2 : hi;
+        for (int o = 32; o > 0; o >>= 1) {
+          const unsigned long long lo2 = __shfl_xor(lo, o, 64), hi2 = __shfl_xor(hi, o, 64);
+          lo = lo2 < lo ? lo2 : lo;
+          hi = hi2 > hi ? hi2 : hi;
+        }
+        if (lane == 0 && lo <= hi) {
+          atomicMin(&s_min, lo);
+          atomicMax(&s_max, hi);
+        }
+        __syncthreads();
+        lo = s_min;
+        hi = s_max;
+        if (lo > hi) break;  // uniform: no member at hand (cannot happen; reported below)
+        const uint32_t top_bit = lo == hi ? 0u : 63u - (uint32_t)__builtin_clzll(lo ^ hi);
+        shift = top_bit > 9u ? top_bit - 9u : 0u;
+        each_member([&](unsigned long long c) {
+          if ((c >> known) == prefix) atomicAdd(&hist[(uint32_t)(c >> shift) & (kSelectDigits - 1u)], 1u);
+        });
       }
-      if (lane == 0 && lo <= hi) {
-        atomicMin(&s_min, lo);
-        atomicMax(&s_max, hi);
-      }
-      __syncthreads();
-      lo = s_min;
-      hi = s_max;
-      if (lo > hi) break;  // uniform: no member at hand (cannot happen; reported below)
-      const uint32_t top_bit = lo == hi ? 0u : 63u - (uint32_t)__builtin_clzll(lo ^ hi);
-      const uint32_t shift = top_bit > 9u ? top_bit - 9u : 0u;
-      each_member([&](unsigned long long c) {
-        if ((c >> known) == prefix) atomicAdd(&hist[(uint32_t)(c >> shift) & (kSelectDigits - 1u)], 1u);
-      });
       __syncthreads();
       const uint32_t digit = kSelectDigits - 1u - 2u * tid;  // and the one below; larger digits first
       const uint32_t h0 = hist[digit], h1 = hist[digit - 1u];
       uint32_t total;
-      const uint32_t above = block_excl_scan<kSelectWaves>(h0 + h1, scan_tmp, &total);
+      const uint32_t above = s_larger + block_excl_scan<kSelectWaves>(h0 + h1, scan_tmp, &total);
       if (above < rem && rem <= above + h0 + h1) {  // exactly one thread
         const bool second = rem > above + h0;
         s_digit = second ? digit - 1u : digit;
@@ -1120,6 +1164,11 @@ __global__ __launch_bounds__(kSelectBlock) void select_kernel(const ClientParams
         s_in_digit = second ? h1 : h0;
       }
       __syncthreads();
+      if (guess && s_in_digit == 0) {  // uniform: the guess was no use
+        guess = false;
+        continue;
+      }
+      guess = false;
       if (s_in_digit == 0) break;  // uniform: fewer members than the rank (cannot happen; reported below)
       prefix = ((lo >> shift) & ~(unsigned long long)(kSelectDigits - 1u)) | s_digit;  // the bits above the digit are common to all
       known = shift;
@@ -1137,6 +1186,12 @@ __global__ __launch_bounds__(kSelectBlock) void select_kernel(const ClientParams
         }
         __syncthreads();
         found = true;
+      } else if (walk_all && s_in_digit <= kSelectList) {  // LDS holds what is left
+        each_member([&](unsigned long long c) {
+          if ((c >> known) == prefix) list[atomicAdd(&n_few, 1u)] = c;
+        });
+        m = s_in_digit;
+        walk_all = false;
       }
     }
     if (tid == 0) {
@@ -2096,6 +2151,7 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
   ws.span_first = reinterpret_cast<uint32_t*>(base + L.span_first);
   ws.span_cnt = reinterpret_cast<uint32_t*>(base + L.span_cnt);
   ws.group_info = reinterpret_cast<GroupInfo*>(base + L.group_info);
+  ws.hist_bins = reinterpret_cast<uint32_t*>(base + L.hist_bins);
   ws.members = reinterpret_cast<uint2*>(base + L.members);
   ws.seg_cnt = reinterpret_cast<uint32_t*>(base + L.seg_cnt);
   ws.norm_limbs = reinterpret_cast<unsigned long long*>(base + L.norm_limbs);
@@ -2107,6 +2163,7 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
   ws.filter_blocks = filter_blocks_per_client(L.n_regions, n, filter_resident_blocks());
   ws.gather_blocks = L.gather_blocks;
   ws.member_pool = L.member_pool;
+  ws.hist_copies = L.hist_copies;
 
   // sample geometry: 256-byte pieces spread evenly; all of them when the vector is short
   const uint32_t n_src = d / kSamplePiece;
