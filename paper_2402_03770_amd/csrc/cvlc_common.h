@@ -64,6 +64,17 @@ struct ClientParams {
 };
 static_assert(sizeof(ClientParams) % 8 == 0, "ClientParams must stay 8-byte granular");
 
+// Statistics of a client's groups as the counting pass's workgroups leave them; entry R: the candidates below the
+// last boundary.
+struct SegPartial {
+  double sumsq[32];          // energy
+  uint32_t max_enc[32];      // max of ordered(x); 0 = empty
+  uint32_t negmin_enc[32];   // max of ~ordered(x); 0 = empty
+};
+// Atomics queue up at each cache line, so the workgroups of a client share out several copies (one client of
+// 11.2 M, 100 workgroups: count 17.7 -> 9.2 us with eight).
+constexpr uint32_t kSegCopies = 8;
+
 // Per-client scratch state, zero-filled at the start of every encode call.
 struct ClientCtl {
   uint32_t tau_lo;           // candidate threshold key from the sample (0: keep every coordinate)
@@ -73,15 +84,13 @@ struct ClientCtl {
   uint32_t dead;             // 1: more candidates than the workspace has room for; nothing further is done for the client
   uint32_t claim;            // regions of the filter's claimed part taken so far
   uint32_t emit_claim;       // chunks of the packing pass taken beyond every workgroup's first
-  double seg_sumsq[32];      // energy of every coded group; entry R: candidates below the last boundary (atomic)
+  SegPartial seg[kSegCopies];
   uint32_t over_cnt[32];     // members of a boundary's bin that found no room in the share of their workgroup
   uint32_t sel_bin[32];      // selection bin that holds boundary r's key; kNoBin: Z_r = 0
   uint32_t sel_rem[32];      // rank of the boundary element inside that bin, 1-based from the largest key
   uint32_t anchor;           // first sample bin of the window that has fine selection bins
   uint32_t tau[32];          // Z_r-th largest key (0xFFFFFFFF: Z_r = 0)
   uint32_t iota[32];         // last of the key == tau_r candidates inside the top Z_r, by its number in the position-ordered list
-  uint32_t seg_max_enc[32];  // max over the group of ordered(x); 0 = empty
-  uint32_t seg_negmin_enc[32];  // max over the group of ~ordered(x); 0 = empty
   uint32_t hist_sample[kSampleBins];  // sample histogram, accumulated with device-wide atomics
   uint32_t bin_map[kMapBins];         // per sample bin of the window: its first selection bin, and above 16 bits the shift that finds the others
 };

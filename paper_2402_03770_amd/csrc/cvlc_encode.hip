@@ -58,6 +58,8 @@ constexpr uint32_t kGatherWaves = kGatherBlock / kWave;
 constexpr uint32_t kGatherResident = 512;   // gather workgroups the device holds
 constexpr uint32_t kGatherBlocksMax = 64;   // ... and of one client's
 
+constexpr uint32_t kHistCopiesMax = 8;
+
 // ------------------------------------------------------------------ workspace layout
 // Per-client, per-group constants of the last stages, written by the layout kernel.
 struct GroupInfo {
@@ -127,8 +129,9 @@ EncodeLayout encode_layout(uint32_t d, uint32_t n, uint32_t cap) {
   L.ctl = off; off = align256(off + (size_t)n * sizeof(ClientCtl));
   L.norm_limbs = off; off = align256(off + (size_t)n * 32 * kNormLimbs * sizeof(uint64_t));
   // The filter's workgroups add their counts to the client's by atomics, which queue up at each cache line: with few
-  // clients, hundreds of workgroups on the same lines, so such a client has several copies.
-  L.hist_copies = n >= 8u ? 1u : 8u / n;
+  // clients, hundreds of workgroups on the same lines, so such a client has several copies, one for about 32 workgroups
+  // (one client of 11.2 M: filter 30.6 -> 15.6 us; 8 of them: no difference).
+  L.hist_copies = n >= kHistCopiesMax ? 1u : std::max(1u, std::min(kHistCopiesMax / n, L.n_regions / (32u * kWavesPerBlock)));
   L.hist_bins = off; off = align256(off + (size_t)n * L.hist_copies * kSelBins * sizeof(uint32_t));
   L.zero_bytes = off;
   L.params = off; off = align256(off + (size_t)n * sizeof(ClientParams));
@@ -623,14 +626,8 @@ __global__ __launch_bounds__(kWideBlock) void scan_l1_kernel(const ClientParams*
   // requested before anything is waited for
   const uint32_t ahead0 = tid < n_regions ? cnt[tid] : 0u;
   const uint32_t ahead1 = tid + kWideBlock < n_regions ? cnt[tid + kWideBlock] : 0u;
-  uint2 bins = make_uint2(0u, 0u);
   const uint2* counted = reinterpret_cast<const uint2*>(ws.hist_bins + (size_t)client * ws.hist_copies * kSelBins);
-#pragma unroll 8
-  for (uint32_t c = 0; c < ws.hist_copies; ++c) {
-    const uint2 x = counted[c * (kSelBins / 2u) + tid];
-    bins.x += x.x;
-    bins.y += x.y;
-  }
+  uint2 bins = counted[tid];
   uint32_t run = 0, n_nz = 0;
   for (uint32_t base = 0; base < n_regions; base += kWideBlock) {
     const uint32_t j = base + tid;
@@ -668,6 +665,16 @@ __global__ __launch_bounds__(kWideBlock) void scan_l1_kernel(const ClientParams*
       nz_off[n_nz] = run;
       ctl->n_cand = run;
       ctl->n_nz = n_nz;
+    }
+    if (ws.hist_copies > 1u) {  // a few clients at most
+      uint2 more[kHistCopiesMax - 1u];
+#pragma unroll
+      for (uint32_t c = 1; c < kHistCopiesMax; ++c) more[c - 1u] = counted[min(c, ws.hist_copies - 1u) * (kSelBins / 2u) + tid];
+#pragma unroll
+      for (uint32_t c = 1; c < kHistCopiesMax; ++c) {
+        bins.x += c < ws.hist_copies ? more[c - 1u].x : 0u;
+        bins.y += c < ws.hist_copies ? more[c - 1u].y : 0u;
+      }
     }
     hist[2u * tid] = bins.x;
     hist[2u * tid + 1] = bins.y;
@@ -1460,9 +1467,10 @@ __global__ __launch_bounds__(kEmitBlock) void count_kernel(const ClientParams* _
     const uint32_t ng = wave_max_u32(s_negmin[g][lane]);
     const double sq = wave_sum_f64(s_sq[g][lane]);
     if (lane == 0 && mx != 0) {
-      atomicMax(&ctl->seg_max_enc[g], mx);
-      atomicMax(&ctl->seg_negmin_enc[g], ng);
-      atomicAdd(&ctl->seg_sumsq[g], sq);
+      SegPartial* part = &ctl->seg[blockIdx.x % kSegCopies];
+      atomicMax(&part->max_enc[g], mx);
+      atomicMax(&part->negmin_enc[g], ng);
+      atomicAdd(&part->sumsq[g], sq);
     }
   }
 }
@@ -1480,7 +1488,7 @@ typedef uint32_t __attribute__((address_space(1))) * GlobalWordPtr;
 __global__ __launch_bounds__(kWideBlock) void layout_kernel(const ClientParams* __restrict__ params,
                                                             ClientCtl* __restrict__ ctls, Workspace ws,
                                                             cvlc_seg_stats_t* __restrict__ stats_out, uint32_t quant) {
-  __shared__ double s_tail[kWideWaves];
+  __shared__ double s_tail[kWideWaves], s_dropped;
   __shared__ uint32_t s_sum[32][kNormLimbs];  // QSGD: a group's sum of squares, limbs below 2^32
   __shared__ uint32_t s_payload[32];
   __shared__ uint32_t s_tot[kWideWaves][32];
@@ -1496,9 +1504,15 @@ __global__ __launch_bounds__(kWideBlock) void layout_kernel(const ClientParams* 
   // What the headers and the statistics at the end need from memory is asked for here: this kernel is one
   // workgroup per client and all latency.
   uint32_t enc_max = 0, enc_negmin = 0;
-  if (tid < R) {
-    enc_max = ctl->seg_max_enc[tid];
-    enc_negmin = ctl->seg_negmin_enc[tid];
+  double enc_sumsq = 0.0;
+  if (tid <= R) {  // entry R: the candidates below the last boundary
+#pragma unroll
+    for (uint32_t c = 0; c < kSegCopies; ++c) {
+      enc_max = max(enc_max, ctl->seg[c].max_enc[tid]);
+      enc_negmin = max(enc_negmin, ctl->seg[c].negmin_enc[tid]);
+      enc_sumsq += ctl->seg[c].sumsq[tid];
+    }
+    if (tid == R) s_dropped = enc_sumsq;
   }
   const double* rsq = ws.region_sumsq + (size_t)client * ws.n_regions;  // energy the filter dropped, region by region
   const double tail0 = tid < ws.n_regions ? rsq[tid] : 0.0;
@@ -1680,7 +1694,7 @@ __global__ __launch_bounds__(kWideBlock) void layout_kernel(const ClientParams* 
     hdr[3] = quant == CVLC_QUANT_QSGD ? 0u : __float_as_uint(M);
     if (stats_out) {
       cvlc_seg_stats_t* st = stats_out + (size_t)client * kStatsStride + r;
-      st->min = m; st->max = M; st->sumsq = ctl->seg_sumsq[r]; st->count = P; st->reserved = 0;
+      st->min = m; st->max = M; st->sumsq = enc_sumsq; st->count = P; st->reserved = 0;
       st->errsq = 0.0;  // the pack kernel adds the group's error energy when asked to
     }
     GroupInfo* gi = ws.group_info + client;
@@ -1712,7 +1726,7 @@ __global__ __launch_bounds__(kWideBlock) void layout_kernel(const ClientParams* 
       double tail = 0.0;
       for (uint32_t w = 0; w < kWideWaves; ++w) tail += s_tail[w];
       cvlc_seg_stats_t* st = stats_out + (size_t)client * kStatsStride + R;
-      st->min = 0.0f; st->max = 0.0f; st->sumsq = tail + ctl->seg_sumsq[R]; st->count = ws.d - p.k; st->reserved = 0;
+      st->min = 0.0f; st->max = 0.0f; st->sumsq = tail + s_dropped; st->count = ws.d - p.k; st->reserved = 0;
       st->errsq = st->sumsq;  // dropped whole
     }
   }
