@@ -16,6 +16,7 @@
 //                  instance splits QSGD's sign bit from the level)
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -27,7 +28,6 @@ namespace {
 
 constexpr uint32_t kListsPerClient = 32;   // descriptor slots per client (CVLC_MAX_CODED used)
 constexpr uint32_t kTabChunk = 512;        // records per tile_table work item (one wavefront, eight a lane)
-constexpr uint32_t kListBatch = 512;       // lists a decode workgroup handles per sweep
 
 struct CompactDesc {  // one non-empty (client, group) record list, 32 bytes
   const uint32_t* payload;
@@ -82,20 +82,6 @@ struct ParseChunk {
   StreamArg args[kParseStreams];
 };
 static_assert(sizeof(ParseChunk) <= 3800, "kernel arguments are limited to 4 KB");
-
-// Bits [bit, bit + W) of a little-endian word array, W <= 63.  Reads the three
-// words the field can touch; `n_words` bounds the reads.
-template <typename WordPtr>
-__device__ __forceinline__ uint64_t read_bits(WordPtr words, uint64_t n_words, uint64_t bit, uint32_t W) {
-  const uint64_t w = bit >> 5;
-  const uint32_t sh = (uint32_t)(bit & 31u);
-  const uint64_t a = words[w];
-  const uint64_t b = (w + 1 < n_words) ? words[w + 1] : 0u;
-  const uint64_t c = (w + 2 < n_words) ? words[w + 2] : 0u;
-  uint64_t v = ((a | (b << 32)) >> sh);
-  if (sh) v |= c << (64u - sh);
-  return v & ((1ull << W) - 1ull);
-}
 
 // ------------------------------------------------------------------ 1. headers
 // One wavefront per stream; lane r reads and checks the header of group r, so
@@ -240,8 +226,10 @@ __global__ __launch_bounds__(1024) void compact_lists_kernel(const ListDesc* __r
   compact_lists(descs, n_lists, cdesc, item_start, ctl, stream_bad, n, status, scan_tmp);
 }
 
-// Both steps in one launch, for calls whose streams fit one set of kernel arguments: the sixteen wavefronts
+// Both steps in one launch, for calls of a few streams: the sixteen wavefronts
 // share out the streams, then the workgroup numbers the lists it has just described.
+constexpr uint32_t kFusedStreams = kParseStreams;
+static_assert(kFusedStreams <= kParseStreams, "one set of arguments");
 __global__ __launch_bounds__(1024) void setup_kernel(ParseChunk chunk, ListDesc* descs, uint32_t d, uint32_t quant,
                                                      CompactDesc* __restrict__ cdesc, uint32_t* __restrict__ item_start,
                                                      DecodeCtl* ctl, uint32_t* stream_bad, uint32_t* status) {
@@ -411,80 +399,59 @@ __global__ __launch_bounds__(kBlock, 8) void tile_table_kernel(const CompactDesc
 // non-empty slices that start inside the turn set a bit at their first record's
 // place in a 64-bit mask, and a lane counts the bits at or below its own place;
 // only the wavefront's first record needs a search.  List descriptors sit in LDS.
-constexpr uint32_t kDecBlock = 512;  // threads of a decode workgroup
-constexpr uint32_t kDecWaves = kDecBlock / kWave;
-constexpr uint32_t kDecTurns = 6;    // turns of 64 records a wavefront works on together
 constexpr uint32_t kChunkTiles = 16; // consecutive tiles decoded side by side on one XCD (more: less refetching, less even load)
 constexpr uint32_t kFirstBits = 22;  // a tile's records over one batch of lists are numbered below 2^22 ...
 constexpr uint32_t kFirstMask = (1u << kFirstBits) - 1u;
-static_assert((uint64_t)kListBatch * kDecTile < (1ull << kFirstBits) && kListBatch <= (1u << (32 - kFirstBits)),
-              "... and the list of a slice fits above that number in one word");
-static_assert(kListBatch == kDecBlock, "one list per thread and batch");
+constexpr uint32_t kListBits = 32u - kFirstBits;  // ... and the list of a slice fits above that number in one word
 
+// BLOCK: threads of a decode workgroup.  LISTS: lists it handles per sweep, one per thread.  TURNS: turns of 64
+// records a wavefront works on together.
+template <uint32_t BLOCK, uint32_t LISTS>
 struct DecodeShared {
+  static constexpr uint32_t kWaves = BLOCK / kWave;
+  static_assert(LISTS <= BLOCK && (uint64_t)LISTS * kDecTile < (1ull << kFirstBits) && LISTS <= (1u << kListBits), "see kFirstBits");
   double acc[kDecTile];
-  uint4 desc[kListBatch][2];       // CompactDesc, as loaded
+  uint4 desc[LISTS][2];            // CompactDesc, as loaded, but with the payload's words in the place of P
   // per non-empty slice of the batch, in list order
-  uint32_t begin[kListBatch];      // first record of the slice inside its list
-  uint32_t first[kListBatch + 1];  // number of the slice's first record in the tile | list << kFirstBits; then the total
-  unsigned long long turn_mask[kDecWaves][kDecTurns];  // per wavefront: starts of slices inside each of its current turns
-  uint32_t scan_a[kDecWaves], scan_b[kDecWaves];
+  uint32_t begin[LISTS];           // first record of the slice inside its list
+  uint32_t first[LISTS + 1];       // number of the slice's first record in the tile | list << kFirstBits; then the total
+  uint32_t scan_a[kWaves], scan_b[kWaves];
 };
-
-// Exclusive prefix sums of two values per thread over the workgroup, in thread order.
-__device__ __forceinline__ void block_excl_scan2(uint32_t va, uint32_t vb, uint32_t* sa, uint32_t* sb, uint32_t* before_a,
-                                                 uint32_t* before_b, uint32_t* total_a, uint32_t* total_b) {
-  const uint32_t ia = wave_incl_scan_u32(va), ib = wave_incl_scan_u32(vb);
-  const uint32_t wave = threadIdx.x / kWave;
-  __syncthreads();
-  if (lane_id() == kWave - 1) {
-    sa[wave] = ia;
-    sb[wave] = ib;
-  }
-  __syncthreads();
-  uint32_t ba = 0, bb = 0, ta = 0, tb = 0;
-#pragma unroll
-  for (uint32_t w = 0; w < kDecWaves; ++w) {
-    const uint32_t xa = sa[w], xb = sb[w];
-    if (w < wave) { ba += xa; bb += xb; }
-    ta += xa;
-    tb += xb;
-  }
-  *before_a = ba + ia - va;
-  *before_b = bb + ib - vb;
-  *total_a = ta;
-  *total_b = tb;
-}
 
 // LDS accesses of one wavefront complete in order; this keeps the compiler from
 // moving them across the point where lanes read what other lanes wrote.
 __device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // SIGNED: the streams' codes hold a sign bit above the level (QSGD).
-template <bool SIGNED>
-__global__ __launch_bounds__(kDecBlock, 6) void decode_tiles_kernel(const CompactDesc* __restrict__ cdesc,
+// WIDE: positions of more than 25 bits, which with a raw 32-bit code may not lie in eight bytes from the one they start in.
+template <bool SIGNED, bool WIDE, uint32_t BLOCK, uint32_t LISTS, uint32_t TURNS, uint32_t PER_SIMD>
+__global__ __launch_bounds__(BLOCK, PER_SIMD) void decode_tiles_kernel(const CompactDesc* __restrict__ cdesc,
                                                               const DecodeCtl* __restrict__ ctl,
                                                               const uint32_t* __restrict__ table, float* out,
                                                               uint32_t d, uint32_t n_tiles, uint32_t accumulate,
                                                               uint32_t* status) {
-  __shared__ DecodeShared S;
+  __shared__ DecodeShared<BLOCK, LISTS> S;
+  __shared__ unsigned long long turn_mask[BLOCK / kWave][TURNS];  // per wavefront: starts of slices inside each of its current turns
+  constexpr uint32_t kWaves = BLOCK / kWave;
   const uint32_t tid = threadIdx.x, lane = lane_id();
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const uint32_t n_active = ctl->n_active;
-  const bool one_batch = n_active <= kListBatch;
-  bool bad = false;
-  auto load_descs = [&](uint32_t l0, uint32_t nl) {
-    const uint4* src = reinterpret_cast<const uint4*>(cdesc + l0);
-    for (uint32_t i = tid; i < nl * 2u; i += kDecBlock) (&S.desc[0][0])[i] = src[i];
+  const bool one_batch = n_active <= LISTS;
+  bool bad = false, fresh = true;
+  // What a thread needs of its list of the batch at l0: the descriptor, and the two table entries for a tile.  Both
+  // are asked for a batch ahead (a batch of few records is otherwise little but the chain of waits for descriptors,
+  // then table entries, then records).
+  auto request_desc = [&](uint32_t l0, uint4 (&dd)[2]) {
+    const uint4* src = reinterpret_cast<const uint4*>(cdesc + min(l0 + tid, n_active - 1u));
+    dd[0] = src[0];
+    dd[1] = src[1];
   };
-  if (one_batch) load_descs(0, n_active);
-  // the two table entries of this thread's list (first batch) for the next tile, asked for a tile ahead
-  auto request_rows = [&](uint32_t tile) {
+  auto request_rows = [&](uint32_t tile, uint32_t l0) {
     uint2 r = make_uint2(0u, 0u);
-    if (tile < n_tiles && tid < min(n_active, kListBatch)) {
-      const uint32_t* row = table + (size_t)tid * (n_tiles + 1) + tile;
-      r.x = row[0];
-      r.y = row[1];
+    if (tile < n_tiles && tid < min(n_active - l0, LISTS)) {
+      const uint64_t two = load8((GlobalBytePtr)(table + (size_t)(l0 + tid) * (n_tiles + 1) + tile));
+      r.x = (uint32_t)two;
+      r.y = (uint32_t)(two >> 32);
     }
     return r;
   };
@@ -499,45 +466,63 @@ __global__ __launch_bounds__(kDecBlock, 6) void decode_tiles_kernel(const Compac
     return chunked ? ((seat / kChunkTiles + chunks_at_once * r) * 8u + xcd) * kChunkTiles + seat % kChunkTiles
                    : blockIdx.x + r * gridDim.x;
   };
-  uint32_t round = 0;
-  uint2 next_rows = request_rows(tile_of(0));
-  for (uint32_t tile = tile_of(0); tile < n_tiles; tile = tile_of(++round)) {
+  uint32_t round = 0, l0 = 0;
+  uint2 next_rows = make_uint2(0u, 0u);
+  uint4 next_desc[2] = {make_uint4(0u, 0u, 0u, 0u), make_uint4(0u, 0u, 0u, 0u)};
+  uint32_t my_P = 0;  // records of this thread's list
+  if (n_active) {
+    next_rows = request_rows(tile_of(0), 0);
+    request_desc(0, next_desc);
+  }
+  for (uint32_t i = tid; i < kDecTile; i += BLOCK) S.acc[i] = 0.0;
+  for (uint32_t tile = tile_of(0); tile < n_tiles;) {
     const uint32_t lo = tile * kDecTile;
-    const uint2 rows = next_rows;
-    next_rows = request_rows(tile_of(round + 1u));
-    __syncthreads();  // the tile before is written out; the descriptors are in place
-    for (uint32_t i = tid; i < kDecTile; i += kDecBlock) S.acc[i] = 0.0;
-    for (uint32_t l0 = 0; l0 < n_active; l0 += kListBatch) {
-      const uint32_t nl = min(n_active - l0, kListBatch);
-      if (!one_batch) {
-        __syncthreads();
-        load_descs(l0, nl);
-        __syncthreads();
-      }
-      // this thread's list: its slice [begin, end) from two neighbouring table entries
-      uint32_t len = 0, begin = 0;
-      if (tid < nl) {
-        const uint32_t P = S.desc[tid][1].x;
-        uint32_t end;
-        if (l0 == 0) {
-          begin = rows.x;
-          end = rows.y;
-        } else {
-          const uint32_t* row = table + (size_t)(l0 + tid) * (n_tiles + 1) + tile;
-          begin = row[0];
-          end = row[1];
+    const bool last_batch = n_active - l0 <= LISTS;  // of the tile
+    const uint32_t next_tile = last_batch ? tile_of(++round) : tile, next_l0 = last_batch ? 0u : l0 + LISTS;
+    if (n_active) {  // uniform
+      const uint32_t nl = min(n_active - l0, LISTS);
+      const uint2 rows = next_rows;
+      if (!one_batch || fresh) {  // one batch: its descriptors stay in LDS
+        if (tid < LISTS) {
+          // in the place of the number of records, which only this thread needs: the payload's words
+          uint4 d1 = next_desc[1];
+          d1.x = (uint32_t)payload_words(next_desc[1].x, next_desc[1].y & 0xFFu);
+          S.desc[tid][0] = next_desc[0];
+          S.desc[tid][1] = d1;
         }
-        if (begin > P) begin = P;  // table entries of a malformed list may hold anything
-        if (end > P) end = P;
+        my_P = next_desc[1].x;
+        if (!one_batch) request_desc(next_l0, next_desc);
+        fresh = false;
+      }
+      next_rows = request_rows(next_tile, next_l0);
+      // this thread's list: its slice [begin, end) from two neighbouring table entries
+      uint32_t len = 0, begin = rows.x;
+      if (tid < nl) {
+        uint32_t end = rows.y;
+        if (begin > my_P) begin = my_P;  // table entries of a malformed list may hold anything
+        if (end > my_P) end = my_P;
         if (end > begin) len = end - begin;
         if (len > kDecTile) {  // positions ascend strictly: a tile holds at most one record per coordinate
           bad = true;
           len = 0;
         }
       }
-      uint32_t before, j, total, n_live;
-      // (its barriers also separate the writes below from the reads of the batch before)
-      block_excl_scan2(len, len ? 1u : 0u, S.scan_a, S.scan_b, &before, &j, &total, &n_live);
+      // the slices' records numbered through, the slices that hold any compacted
+      const uint32_t incl = wave_incl_scan_u32(len);
+      const uint64_t live = __ballot(len != 0u);
+      if (lane == kWave - 1) {
+        S.scan_a[wave] = incl;
+        S.scan_b[wave] = (uint32_t)__popcll(live);
+      }
+      __syncthreads();
+      uint32_t before = incl - len, j = lanes_below(live), total = 0, n_live = 0;
+#pragma unroll
+      for (uint32_t w = 0; w < kWaves; ++w) {
+        const uint32_t xa = S.scan_a[w], xb = S.scan_b[w];
+        if (w < wave) { before += xa; j += xb; }
+        total += xa;
+        n_live += xb;
+      }
       if (len) {
         S.first[j] = before | (tid << kFirstBits);
         S.begin[j] = begin;
@@ -545,7 +530,7 @@ __global__ __launch_bounds__(kDecBlock, 6) void decode_tiles_kernel(const Compac
       if (tid == 0) S.first[n_live] = total;
       __syncthreads();
       // the wavefront's share of the records, a multiple of 64
-      const uint32_t share = ((total + kDecBlock - 1) / kDecBlock) * kWave;
+      const uint32_t share = ((total + BLOCK - 1) / BLOCK) * kWave;
       const uint32_t q_begin = min(wave * share, total), q_end = min(q_begin + share, total);
       if (q_begin < q_end) {  // uniform per wavefront
         // last slice whose first record is at or before the first record of the turns at hand (uniform): the
@@ -554,47 +539,53 @@ __global__ __launch_bounds__(kDecBlock, 6) void decode_tiles_kernel(const Compac
         {
           uint32_t at_or_before = 0;
 #pragma unroll
-          for (uint32_t k = 0; k < kListBatch / kWave; ++k) {
+          for (uint32_t k = 0; k < (LISTS + kWave - 1) / kWave; ++k) {
             const uint32_t i = k * kWave + lane;
             const bool hit = i < n_live && (S.first[min(i, n_live)] & kFirstMask) <= q_begin;
             at_or_before += (uint32_t)__popcll(__ballot(hit));
           }
           cur = __builtin_amdgcn_readfirstlane(at_or_before) - 1u;
         }
-        // kDecTurns turns at a time.  First the start masks of all of them; then, turn by turn but without one
+        // TURNS turns at a time.  First the start masks of all of them; then, turn by turn but without one
         // turn waiting for another, list and record number from LDS; then all record loads together, so that their
         // latencies overlap.  Nothing in this half branches on data (a lane past the end works on the last record
-        // again, the words after a record's first are clamped to the record's last), so that no load has to be
-        // waited for before the next one is issued.
-        unsigned long long* masks = S.turn_mask[wave];
-        for (uint32_t q0 = q_begin; q0 < q_end; q0 += kWave * kDecTurns) {
-          const uint32_t n_turns = __builtin_amdgcn_readfirstlane(min((q_end - q0 + kWave - 1u) / kWave, kDecTurns));
+        // again), so that no load has to be waited for before the next one is issued.  A record is read by one load of
+        // eight bytes from the byte it starts in (from the payload's last eight bytes where it would reach past them):
+        // lanes of a turn read from a dozen lists and more, an instruction costs the address unit a cycle or more per
+        // cache line, and that is what bounds this kernel (three aligned words a record and two loads per pair of table
+        // entries: 53 us instead of 47 for 32 streams of 11.2 M
+        // coordinates, 540 instead of 459 for 100 of 25.6 M).
+        unsigned long long* masks = turn_mask[wave];
+        for (uint32_t q0 = q_begin; q0 < q_end; q0 += kWave * TURNS) {
+          const uint32_t n_turns = __builtin_amdgcn_readfirstlane(min((q_end - q0 + kWave - 1u) / kWave, TURNS));
           // slices after `cur` that start inside the turns: first[] ascends strictly, first[n_live] = total.
           // 64 slices are looked at per round; more start inside the turns only when most hold a few records.
-          if (lane < kDecTurns) masks[lane] = 0ull;
+          if (lane < TURNS) masks[lane] = 0ull;
           wave_lds_fence();
           for (uint32_t seen = 0;; seen += kWave) {  // uniform
             const uint32_t idx = cur + 1u + seen + lane;
             const uint32_t f = (S.first[min(idx, n_live)] & kFirstMask) - q0;  // >= 0
-            if (idx <= n_live && f < kWave * kDecTurns) atomicOr(&masks[f >> 6], 1ull << (f & 63u));
+            if (idx <= n_live && f < kWave * TURNS) atomicOr(&masks[f >> 6], 1ull << (f & 63u));
             // done when the last one looked at lies past the turns at hand, or nothing is left to look at
             if (cur + seen + kWave >= n_live || __builtin_amdgcn_readlane(f, kWave - 1) >= kWave * n_turns) break;
           }
           wave_lds_fence();
-          uint32_t base_of[kDecTurns], w0[kDecTurns], w1[kDecTurns], w2[kDecTurns], at[kDecTurns];  // at: list | bit inside the first word << 9
-          unsigned long long starts[kDecTurns];
+          uint64_t bits_of[TURNS];
+          uint32_t tail_of[WIDE ? TURNS : 1];  // the byte behind those eight
+          uint32_t base_of[TURNS], at[TURNS];  // at: list | bit inside the first word << kListBits
+          unsigned long long starts[TURNS];
 #pragma unroll
-          for (uint32_t u = 0; u < kDecTurns; ++u) starts[u] = masks[u];
+          for (uint32_t u = 0; u < TURNS; ++u) starts[u] = masks[u];
 #pragma unroll
-          for (uint32_t u = 0; u < kDecTurns; ++u) {
+          for (uint32_t u = 0; u < TURNS; ++u) {
             base_of[u] = cur;
             if (u < n_turns)  // uniform; the sentinel's bit lies in the last turn at hand or past it
               cur += (uint32_t)__popc((uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)starts[u])) +
                      (uint32_t)__popc((uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(starts[u] >> 32)));
           }
-          uint32_t x_of[kDecTurns], e_of[kDecTurns];
+          uint32_t x_of[TURNS], e_of[TURNS];
 #pragma unroll
-          for (uint32_t u = 0; u < kDecTurns; ++u) {
+          for (uint32_t u = 0; u < TURNS; ++u) {
             x_of[u] = e_of[u] = 0;
             if (u >= n_turns) continue;          // uniform
             const uint32_t qt = q0 + u * kWave;  // the turn's first record (uniform)
@@ -604,35 +595,35 @@ __global__ __launch_bounds__(kDecBlock, 6) void decode_tiles_kernel(const Compac
             e_of[u] = S.begin[a] + (qt + place);
           }
 #pragma unroll
-          for (uint32_t u = 0; u < kDecTurns; ++u) {
-            w0[u] = w1[u] = w2[u] = at[u] = 0;
+          for (uint32_t u = 0; u < TURNS; ++u) {
+            bits_of[u] = 0;
+            at[u] = 0;
             if (u >= n_turns) continue;  // uniform
             const uint32_t li = x_of[u] >> kFirstBits;
             const uint32_t e = e_of[u] - (x_of[u] & kFirstMask);
             const uint2 ptr = *reinterpret_cast<const uint2*>(&S.desc[li][0]);  // payload
-            const uint32_t W = S.desc[li][1].y & 0xFFu;
-            GlobalConstWordPtr pay = (GlobalConstWordPtr)(((uint64_t)ptr.y << 32) | ptr.x);
-            const uint64_t bit = (uint64_t)e * W;
-            const uint32_t w = (uint32_t)(bit >> 5), sh = (uint32_t)bit & 31u;  // payloads have fewer than 2^32 words
-            const uint32_t w_end = w + ((sh + W - 1u) >> 5);                   // the word that holds the record's last bit
-            at[u] = li | (sh << 9);
-            w0[u] = pay[w];
-            w1[u] = pay[min(w + 1u, w_end)];
-            w2[u] = pay[min(w + 2u, w_end)];
+            const uint2 size = *reinterpret_cast<const uint2*>(&S.desc[li][1]);  // its words; W | s << 8 | y << 16
+            // from eight bytes in front of the payload (a stream's headers lie there), so that nothing is negative
+            GlobalBytePtr src = (GlobalBytePtr)((((uint64_t)ptr.y << 32) | ptr.x) - 8u);
+            const uint64_t bit = (uint64_t)e * (size.y & 0xFFu), end = (uint64_t)size.x * 4u;
+            const uint64_t byte = min((bit >> 3) + 8u, end);
+            at[u] = li | (((uint32_t)bit + 64u - (uint32_t)byte * 8u) << kListBits);  // bits in front of the record: at most 63
+            bits_of[u] = load8(src + byte);
+            if (WIDE) tail_of[u] = *(src + min(byte + 8u, end + 7u));
           }
 #pragma unroll
-          for (uint32_t u = 0; u < kDecTurns; ++u) {
+          for (uint32_t u = 0; u < TURNS; ++u) {
             if (u >= n_turns) continue;  // uniform
             if (q0 + u * kWave + lane >= q_end) continue;
-            const uint32_t li = at[u] & 511u, sh = at[u] >> 9;
+            const uint32_t li = at[u] & ((1u << kListBits) - 1u), sh = at[u] >> kListBits;
             const uint4 d0 = S.desc[li][0], d1 = S.desc[li][1];
             const uint32_t s = (d1.y >> 8) & 0xFFu, y = (d1.y >> 16) & 0xFFu;
             const double weight = __hiloint2double((int)d0.w, (int)d0.z);
-            const uint32_t lo32 = __builtin_amdgcn_alignbit(w1[u], w0[u], sh);  // bits [sh, sh + 32) of the three words
-            const uint32_t hi32 = __builtin_amdgcn_alignbit(w2[u], w1[u], sh);  // bits [sh + 32, sh + 64)
-            const uint32_t pid = lo32 & (s >= 32 ? 0xFFFFFFFFu : (1u << s) - 1u);
+            uint64_t rec = bits_of[u] >> sh;
+            if (WIDE && sh) rec |= (uint64_t)tail_of[u] << (64u - sh);
+            const uint32_t pid = (uint32_t)rec & ((1u << s) - 1u);  // s <= 31
             const uint32_t code_mask = y >= 32 ? 0xFFFFFFFFu : (1u << y) - 1u;
-            const uint32_t cid = __builtin_amdgcn_alignbit(hi32, lo32, s & 31u) & code_mask;  // s <= 31
+            const uint32_t cid = (uint32_t)(rec >> s) & code_mask;
             if (pid - lo >= kDecTile || pid >= d) { bad = true; continue; }  // a position below the tile wraps to a large value
             float xhat;
             if (y == 32) {
@@ -648,18 +639,22 @@ __global__ __launch_bounds__(kDecBlock, 6) void decode_tiles_kernel(const Compac
         }
       }
     }
-    __syncthreads();
-    // four pairs of coordinates per thread, neighbouring lanes neighbouring pairs (LDS reads without bank
-    // conflicts, 512-byte stores per wavefront): all reads first, then the stores
-    static_assert(kDecTile == kDecBlock * 8u, "four pairs of coordinates per thread");
-    {
-      double2 v[4];
+    __syncthreads();  // the batch's records are added up; its descriptors and slices may be overwritten
+    if (last_batch) {
+      // pairs of coordinates, neighbouring lanes neighbouring pairs (LDS reads without bank conflicts, 512-byte
+      // stores per wavefront): all reads first, then the stores.  The thread leaves zeros for the next tile.
+      constexpr uint32_t kPairs = kDecTile / (2u * BLOCK);
+      double2 v[kPairs];
 #pragma unroll
-      for (uint32_t c = 0; c < 4u; ++c) v[c] = *reinterpret_cast<const double2*>(&S.acc[c * (2u * kDecBlock) + tid * 2u]);
+      for (uint32_t c = 0; c < kPairs; ++c) {
+        double2* mine = reinterpret_cast<double2*>(&S.acc[c * (2u * BLOCK) + tid * 2u]);
+        v[c] = *mine;
+        *mine = make_double2(0.0, 0.0);
+      }
       const bool aligned = (reinterpret_cast<uintptr_t>(out + lo) & 7u) == 0;  // uniform
 #pragma unroll
-      for (uint32_t c = 0; c < 4u; ++c) {
-        const uint32_t j0 = lo + c * (2u * kDecBlock) + tid * 2u;
+      for (uint32_t c = 0; c < kPairs; ++c) {
+        const uint32_t j0 = lo + c * (2u * BLOCK) + tid * 2u;
         if (aligned && j0 + 2u <= d) {
           float2* dst = reinterpret_cast<float2*>(out + j0);
           if (accumulate) {
@@ -674,6 +669,8 @@ __global__ __launch_bounds__(kDecBlock, 6) void decode_tiles_kernel(const Compac
         }
       }
     }
+    tile = next_tile;
+    l0 = next_l0;
   }
   if (bad) atomicOr(status, CVLC_DEV_STREAM);
 }
@@ -749,7 +746,9 @@ int cvlc_decode_aggregate(uint32_t n, const void* const* d_streams, const size_t
   {
     ParseChunk chunk;
     chunk.pad[0] = chunk.pad[1] = 0;
-    const bool fused = n > 0 && n <= kParseStreams;  // one launch parses and numbers
+    // one launch parses and numbers, while the one workgroup has a wavefront for every stream (100 streams:
+    // 35 us against 4.8 + 10.8 for two launches, the first with a workgroup per stream; 32 streams: 11.5 against 4.7 + 4.8)
+    const bool fused = n > 0 && n <= kFusedStreams;
     for (uint32_t first = 0; first < n; first += kParseStreams) {
       chunk.first = first;
       chunk.count = (n - first < kParseStreams) ? n - first : kParseStreams;
@@ -782,9 +781,12 @@ int cvlc_decode_aggregate(uint32_t n, const void* const* d_streams, const size_t
   }
   {
     StageScope scope(CVLC_STAGE_DEC_TILES, stream);
-    const uint32_t g = L.n_tiles < 768u ? L.n_tiles : 768u;  // three workgroups per CU
-    auto kernel = quant == CVLC_QUANT_QSGD ? decode_tiles_kernel<true> : decode_tiles_kernel<false>;
-    hipLaunchKernelGGL(kernel, dim3(g), dim3(kDecBlock), 0, stream, cdesc, ctl, table, d_out, d, L.n_tiles,
+    const uint32_t g = std::min(L.n_tiles, 768u);  // three workgroups per CU
+    const bool qsgd = quant == CVLC_QUANT_QSGD;
+    const bool wide = position_bits(d) > 25u;
+    auto kernel = qsgd ? (wide ? decode_tiles_kernel<true, true, 512, 512, 6, 6> : decode_tiles_kernel<true, false, 512, 512, 6, 6>)
+                       : (wide ? decode_tiles_kernel<false, true, 512, 512, 6, 6> : decode_tiles_kernel<false, false, 512, 512, 6, 6>);
+    hipLaunchKernelGGL(kernel, dim3(g), dim3(512), 0, stream, cdesc, ctl, table, d_out, d, L.n_tiles,
                        flags & CVLC_DECODE_ACCUMULATE, status);
   }
   return hip_check(hipGetLastError());
