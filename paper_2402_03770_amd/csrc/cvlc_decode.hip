@@ -228,7 +228,7 @@ __global__ __launch_bounds__(1024) void compact_lists_kernel(const ListDesc* __r
 
 // Both steps in one launch, for calls of a few streams: the sixteen wavefronts
 // share out the streams, then the workgroup numbers the lists it has just described.
-constexpr uint32_t kFusedStreams = kParseStreams;
+constexpr uint32_t kFusedStreams = 1024u / kWave;
 static_assert(kFusedStreams <= kParseStreams, "one set of arguments");
 __global__ __launch_bounds__(1024) void setup_kernel(ParseChunk chunk, ListDesc* descs, uint32_t d, uint32_t quant,
                                                      CompactDesc* __restrict__ cdesc, uint32_t* __restrict__ item_start,
