@@ -847,6 +847,25 @@ def test_packets_at_the_benchmark_size():
     assert status == 0 and np.array_equal(out.cpu().numpy().view(np.uint32), words[0])
 
 
+@pytest.mark.parametrize("k,mtu", [(6 * 1024, 64), (6 * 1024 + 1, 64), (40_000, 64), (1_700_000, 64)])
+def test_packets_more_than_threads_and_more_than_bits_in_lds(k, mtu):
+    """The receiver keeps the headers of its first 1024 packets in registers and ticks off up to 262 144 in LDS: counts
+    at and beyond both, in reverse order; one packet replaced by a copy of another is refused."""
+    d = 1 << 22
+    U = np.random.default_rng(k).standard_normal(d).astype(np.float32)
+    po = orc.plan_manual(d, [10], [k])            # 32-bit records, six to a packet of 64 bytes
+    words, _, status, streams = gpu_encode([U], [po], 3, [1], want_stats=False)
+    assert status == 0
+    buf, n = gpu_packetize(to_lib_plan(po), streams[0], mtu)
+    assert n == -(-k // 6)
+    packets = buf.view(n, mtu // 4).flip(0).contiguous()
+    out, status = gpu_depacketize(packets, n, d, mtu, words[0].size)
+    assert status == 0 and np.array_equal(out.cpu().numpy().view(np.uint32), words[0])
+    packets[n // 2] = packets[n // 2 - 1]
+    _, status = gpu_depacketize(packets, n, d, mtu, words[0].size)
+    assert status & cv.DEV_STREAM
+
+
 # --------------------------------------------------------------------------- power-law exponent (Algorithm 1, first step)
 def gpu_fit_alpha(host_updates, two_passes=True):
     """two_passes: in the workspace that has room for the keys set aside by the second pass; else in the
