@@ -31,8 +31,20 @@
 //               wavefront's list (rows of 64 through LDS) and are counted on
 //               their next 9 bits (level 2)
 //   walk<2>, pass<3>, walk<3>   as above, the pass reading the lists
+//
+// Large calls do not even need the second pass: a sample says in which level-1
+// bins the ranks can lie, give or take, and the first pass sets those bins' keys
+// aside while it counts.
+//   sample, guess   histogram of 4096 pieces of 256 bytes, and per rank the bins
+//                   within 4.5 standard deviations of its place in it
+//   stream      all keys: counts of key >> 18; keys of the guessed bins go to
+//               the wavefronts' lists
+//   walk<1>, pass<2>, walk<2>, pass<3>, walk<3>   as above, the passes reading
+//               the lists; a client with a rank outside the guessed bins (the
+//               walk knows, from the exact counts) is read from its vector
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "cvlc_common.h"
@@ -69,7 +81,9 @@ struct RankCtl {
   uint32_t cls[kRanksMax];              // class of rank j: classes number the distinct prefixes, largest first
   uint32_t cls_prefix[kRanksMax];
   uint32_t n_cls;
-  uint32_t pad[3];
+  uint32_t missed;                      // a rank lies outside the guessed bins: the lists do not hold its class
+  uint32_t pad[2];
+  uint8_t guess[kTopBins / 8u];         // level-1 bins whose keys the lists hold, a bit each
 };
 
 struct RankLayout {
@@ -239,7 +253,7 @@ __global__ __launch_bounds__(kRankBlock) void rank_pass_kernel(const float* cons
         }
     }
   };
-  if (LISTS) list_keys(kl, visit); else stream_keys(updates[blockIdx.y], d, visit);
+  if (LISTS && !ctl->missed) list_keys(kl, visit); else stream_keys(updates[blockIdx.y], d, visit);
   __syncthreads();
   for (uint32_t i = threadIdx.x; i < n_cls * kSubBins; i += kRankBlock) {
     const uint32_t h = hist[i];
@@ -306,14 +320,21 @@ __device__ __forceinline__ void level1_walk(const RankCtl* ctl, const RankSet& r
   }
 }
 
-// (The three-pass path; with room for the key lists the collecting pass does this walk itself.)
-__global__ __launch_bounds__(kRankBlock) void rank_walk1_kernel(RankCtl* __restrict__ ctls, RankSet ranks) {
+// (The collecting pass does this walk itself.)  guessed: the lists hold the keys of the guessed bins; see whether all ranks lie in those.
+__global__ __launch_bounds__(kRankBlock) void rank_walk1_kernel(RankCtl* __restrict__ ctls, RankSet ranks, bool guessed) {
   __shared__ uint32_t scan_tmp[kRankWaves];
   __shared__ uint32_t s_prefix[kRanksMax], s_rem[kRanksMax];
   RankCtl* ctl = ctls + blockIdx.x;
   level1_walk(ctl, ranks, scan_tmp, s_prefix, s_rem);
   __syncthreads();
-  if (threadIdx.x < kWave) write_classes(ctl, s_prefix, s_rem, ranks.n);
+  if (threadIdx.x < kWave) {
+    write_classes(ctl, s_prefix, s_rem, ranks.n);
+    if (guessed) {
+      const uint32_t bin = threadIdx.x < ranks.n ? s_prefix[threadIdx.x] : 0u;
+      const bool outside = threadIdx.x < ranks.n && !((ctl->guess[bin >> 3] >> (bin & 7u)) & 1u);
+      if (__ballot(outside) && threadIdx.x == 0) ctl->missed = 1u;
+    }
+  }
 }
 
 // Ordinary least squares of ln(magnitude) on ln(rank) over the keys (in LDS) of the ranks: the logarithms
@@ -520,6 +541,167 @@ __global__ __launch_bounds__(kRankBlock) void rank_collect_kernel(const float* c
   }
 }
 
+// ------------------------------------------------------------------ one pass: sample, guess, stream
+constexpr uint32_t kPieceQuads = 16;       // a piece of the sample: 256 bytes
+constexpr uint32_t kSamplePieces = 4096;
+constexpr uint32_t kSampleWgs = 16;        // workgroups per client
+
+// Counts go to `sub`, which the guess leaves cleared.
+__global__ __launch_bounds__(256) void rank_sample_kernel(const float* const* __restrict__ updates, RankCtl* __restrict__ ctls,
+                                                          uint32_t n_pieces) {
+  __shared__ uint32_t hist[kTopBins];
+  for (uint32_t i = threadIdx.x; i < kTopBins; i += 256u) hist[i] = 0;
+  __syncthreads();
+  GlobalFloat4Ptr src = (GlobalFloat4Ptr)updates[blockIdx.y];
+  constexpr uint32_t kQuads = kSamplePieces * kPieceQuads / kSampleWgs, kTurn = 256u * 8u;
+  static_assert(kQuads % kTurn == 0, "whole turns");
+  for (uint32_t base = blockIdx.x * kQuads; base < (blockIdx.x + 1u) * kQuads; base += kTurn) {
+    Float4V v[8];
+#pragma unroll
+    for (uint32_t u = 0; u < 8; ++u) {
+      const uint32_t q = base + u * 256u + threadIdx.x;
+      const uint64_t piece = (uint64_t)(q / kPieceQuads) * n_pieces / kSamplePieces;  // evenly spread
+      v[u] = src[piece * kPieceQuads + q % kPieceQuads];
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < 8; ++u)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) atomicAdd(&hist[(__float_as_uint(v[u][c]) & 0x7FFFFFFFu) >> kTopShift], 1u);
+  }
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < kTopBins; i += 256u) {
+    const uint32_t h = hist[i];
+    if (h) atomicAdd(&ctls[blockIdx.y].sub[i], h);
+  }
+}
+static_assert(kTopBins <= kRanksMax * kSubBins, "the sample's counts fit where the second level's will stand");
+
+// A rank's place in the sample is binomial: bins that hold a place within 4.5 standard deviations (and three more,
+// for the ends) of the expected one are guessed.  Wrong only costs time.
+__global__ __launch_bounds__(kRankBlock) void rank_guess_kernel(RankCtl* __restrict__ ctls, RankSet ranks, uint32_t d) {
+  __shared__ uint32_t scan_tmp[kRankWaves];
+  __shared__ float s_lo[kRanksMax], s_hi[kRanksMax];
+  RankCtl* ctl = ctls + blockIdx.x;
+  constexpr uint32_t per = kTopBins / kRankBlock;
+  static_assert(per == 8u, "a byte of the bit set per thread");
+  const uint32_t first = kTopBins - per * (threadIdx.x + 1u);  // thread 0 owns the largest keys
+  uint32_t h[per], mine = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < per; ++i) {
+    h[i] = ctl->sub[first + i];
+    ctl->sub[first + i] = 0;
+    mine += h[i];
+  }
+  if (threadIdx.x < ranks.n) {
+    const double size = (double)kSamplePieces * kPieceQuads * 4.0, p = (double)ranks.rank[threadIdx.x] / (double)d;
+    const double margin = 4.5 * sqrt(size * p * (1.0 - p)) + 3.0;
+    s_lo[threadIdx.x] = (float)(size * p - margin);
+    s_hi[threadIdx.x] = (float)(size * p + margin);
+  }
+  uint32_t total;
+  uint32_t above = block_excl_scan<kRankWaves>(mine, scan_tmp, &total);  // (its barriers also publish s_lo and s_hi)
+  // bin i holds the sample's places from[i] .. to[i], and the borders of both sides: an empty bin lies between two
+  float from[per], to[per];
+#pragma unroll
+  for (int i = (int)per - 1; i >= 0; --i) {
+    from[i] = (float)above;
+    above += h[i];
+    to[i] = (float)(above + 1u);
+  }
+  uint32_t bits = 0;
+  for (uint32_t j = 0; j < ranks.n; ++j) {
+    const float lo = s_lo[j], hi = s_hi[j];
+    if (from[per - 1u] > hi || to[0] < lo) continue;
+#pragma unroll
+    for (uint32_t i = 0; i < per; ++i) bits |= (from[i] <= hi && to[i] >= lo ? 1u : 0u) << i;
+  }
+  ctl->guess[first / 8u] = (uint8_t)bits;
+}
+
+// Counts all keys (level 1) and sets the keys of the guessed bins aside, in rows of 64 through LDS.  Bound by HBM:
+// the vectors once, and the writes mixed into them (8 % of the keys).  32 vectors of 11.2 M: 302 us where the counting
+// pass and the collecting pass took 223 + 272; the call 512 -> 396 us.
+__global__ __launch_bounds__(kRankBlock) void rank_stream_kernel(const float* const* __restrict__ updates,
+                                                                 RankCtl* __restrict__ ctls, uint32_t d,
+                                                                 uint32_t* __restrict__ lists,
+                                                                 uint32_t* __restrict__ list_cnt, uint32_t wave_cap,
+                                                                 uint32_t* status) {
+  __shared__ uint32_t hist[kTopBins];
+  __shared__ uint32_t guess[kTopBins / 32u];
+  __shared__ uint32_t stage[kRankWaves][kCollectStage];
+  RankCtl* ctl = ctls + blockIdx.y;
+  for (uint32_t i = threadIdx.x; i < kTopBins; i += kRankBlock) hist[i] = 0;
+  if (threadIdx.x < kTopBins / 32u) guess[threadIdx.x] = reinterpret_cast<const uint32_t*>(ctl->guess)[threadIdx.x];
+  __syncthreads();
+  const uint32_t lane = lane_id(), wave = wave_id();
+  const size_t list = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kRankWaves + wave;
+  uint32_t* __restrict__ out = lists + list * wave_cap;
+  uint32_t* mine = stage[wave];
+  uint32_t fill = 0, run = 0;  // staged keys, keys already written (uniform over the wavefront)
+  bool nonfinite = false;
+  // LDS accesses of a wavefront complete in order; the fences keep the compiler from moving them.
+  auto lds_fence = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
+  auto flush = [&](bool all) {
+    lds_fence();
+    uint32_t g = 0;
+    for (; g + kWave <= fill; g += kWave) out[run + g + lane] = mine[g + lane];
+    const uint32_t left = fill - g;
+    if (left) {
+      const uint32_t k = lane < left ? mine[g + lane] : 0u;
+      if (all) {
+        if (lane < left) out[run + g + lane] = k;
+        g += left;
+      } else if (g) {  // the partial row moves to the front
+        lds_fence();
+        if (lane < left) mine[lane] = k;
+      }
+    }
+    run += g;
+    fill -= g;
+    lds_fence();
+  };
+  auto take = [&](uint32_t key, bool valid) {
+    const uint32_t bin = key >> kTopShift;
+    if (valid) atomicAdd(&hist[bin], 1u);
+    nonfinite |= valid && key >= 0x7F800000u;
+    const bool keep = valid && ((guess[bin >> 5] >> (bin & 31u)) & 1u);
+    const uint64_t m = __ballot(keep);
+    if (keep) mine[fill + lanes_below(m)] = key;
+    fill += (uint32_t)__popcll(m);
+  };
+  const float* update = updates[blockIdx.y];
+  const uint32_t n_quads = d / 4u;
+  GlobalFloat4Ptr src = (GlobalFloat4Ptr)update;
+  constexpr uint32_t kTileQuads = kRankBlock * kDeep;
+  for (uint32_t q0 = blockIdx.x * kTileQuads; q0 < n_quads; q0 += gridDim.x * kTileQuads) {
+    Float4V v[kDeep];
+#pragma unroll
+    for (uint32_t u = 0; u < kDeep; ++u) {
+      const uint32_t q = q0 + u * kRankBlock + threadIdx.x;
+      v[u] = __builtin_nontemporal_load(src + min(q, n_quads - 1u));
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kDeep; ++u) {
+      const bool valid = q0 + u * kRankBlock + threadIdx.x < n_quads;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) take(__float_as_uint(v[u][c]) & 0x7FFFFFFFu, valid);
+      if (fill > kCollectStage - 4u * kWave) flush(false);  // room for the next four keys of every lane
+    }
+  }
+  if (blockIdx.x == 0 && wave == 0) {  // the last d % 4 coordinates
+    const bool valid = lane < d - n_quads * 4u;
+    take(valid ? __float_as_uint(update[n_quads * 4u + lane]) & 0x7FFFFFFFu : 0u, valid);
+  }
+  flush(true);
+  if (lane == 0) list_cnt[list] = run;
+  const int any_nonfinite = __syncthreads_or((int)nonfinite);
+  if (any_nonfinite && threadIdx.x == 0) atomicOr(status, CVLC_DEV_NONFINITE);
+  for (uint32_t i = threadIdx.x; i < kTopBins; i += kRankBlock) {
+    const uint32_t h = hist[i];
+    if (h) atomicAdd(&ctl->top[i], h);
+  }
+}
+
 // Workgroups per client in a streaming pass: per_cu 1024-thread workgroups on every CU, never more than
 // there are tiles.
 uint32_t pass_blocks_per_client(uint32_t d, uint32_t n, uint32_t per_cu) {
@@ -595,8 +777,17 @@ int cvlc_fit_alpha(uint32_t n, const float* const* d_updates, uint32_t d, double
     }
   }
   const dim3 pass_grid(pass_blocks_per_client(d, n, 2u), n);
-  hipLaunchKernelGGL(rank_hist1_kernel, pass_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, status);
   KeyLists kl = {nullptr, nullptr, 0u, 0u};
+  // One pass fewer over the vectors for three small launches and longer lists: level at 77 M coordinates (3 vectors of
+  // 25.6 M: 208 us both ways), ahead at 90 M (8 of 11.2 M: 173 -> 157 us); for vectors that have the sample's pieces
+  // several times over.
+  const bool one_pass = L.wave_cap && (uint64_t)n * d >= (5u << 24) && d >= (1u << 20);
+  if (one_pass) {
+    hipLaunchKernelGGL(rank_sample_kernel, dim3(kSampleWgs, n), dim3(256), 0, stream, ptrs, ctls, d / (4u * kPieceQuads));
+    hipLaunchKernelGGL(rank_guess_kernel, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks, d);
+  } else {
+    hipLaunchKernelGGL(rank_hist1_kernel, pass_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, status);
+  }
   if (L.wave_cap) {  // two passes: the keys of the class bins are set aside, levels 2 and 3 count among those
     uint32_t* lists = reinterpret_cast<uint32_t*>(base + L.lists);
     uint32_t* list_cnt = reinterpret_cast<uint32_t*>(base + L.list_cnt);
@@ -604,17 +795,24 @@ int cvlc_fit_alpha(uint32_t n, const float* const* d_updates, uint32_t d, double
     kl.list_cnt = list_cnt;
     kl.per_client = L.blocks * kRankWaves;
     kl.wave_cap = L.wave_cap;
-    hipLaunchKernelGGL(rank_collect_kernel, dim3(L.blocks, n), dim3(kRankBlock), 0, stream, ptrs, ctls, ranks, d, lists,
-                       list_cnt, L.wave_cap);
-    // a few workgroups per client: their cost is clearing and adding up the counters, not reading the keys
-    const dim3 list_grid(L.blocks < 16u ? L.blocks : 16u, n);
+    // a few workgroups per client: their cost is clearing and adding up the counters, and less so reading the keys
+    const dim3 list_grid(std::min(L.blocks, 16u), n);
+    if (one_pass) {
+      hipLaunchKernelGGL(rank_stream_kernel, dim3(L.blocks, n), dim3(kRankBlock), 0, stream, ptrs, ctls, d, lists, list_cnt,
+                         L.wave_cap, status);
+      hipLaunchKernelGGL(rank_walk1_kernel, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks, true);
+      hipLaunchKernelGGL((rank_pass_kernel<2, true>), list_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl);
+    } else {
+      hipLaunchKernelGGL(rank_collect_kernel, dim3(L.blocks, n), dim3(kRankBlock), 0, stream, ptrs, ctls, ranks, d, lists,
+                         list_cnt, L.wave_cap);
+    }
     hipLaunchKernelGGL(rank_walk_kernel<2>, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks, (uint32_t*)nullptr,
                        (double*)nullptr);
     hipLaunchKernelGGL((rank_pass_kernel<3, true>), list_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl);
     hipLaunchKernelGGL(rank_walk_kernel<3>, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks, d_keys_out, d_alpha_out);
     return hip_check(hipGetLastError());
   }
-  hipLaunchKernelGGL(rank_walk1_kernel, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks);
+  hipLaunchKernelGGL(rank_walk1_kernel, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks, false);
   hipLaunchKernelGGL((rank_pass_kernel<2, false>), pass_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl);
   hipLaunchKernelGGL(rank_walk_kernel<2>, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks, (uint32_t*)nullptr,
                      (double*)nullptr);

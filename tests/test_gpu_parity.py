@@ -944,6 +944,27 @@ def test_fit_alpha_more_clients_than_one_upload_holds():
     check_fit([(rng.standard_t(3, 5000) * 1e-3).astype(np.float32) for _ in range(600)])
 
 
+@pytest.mark.parametrize("d", [2_100_003, 2_097_152])
+def test_fit_alpha_in_one_pass(d):
+    """From 5 x 2^24 coordinates on the level-1 bins of the ranks are guessed from a sample: ordinary vectors, tied ones, and
+    one whose sampled pieces hold what the rest does not, so that the guess is wrong and the vector is read again."""
+    rng = np.random.default_rng(d)
+    planted = (rng.standard_normal(d) * 1e-4).astype(np.float32)
+    plant_on_the_sampled_pieces(planted, rng)
+    tied = (2.0 ** rng.integers(-3, 4, d)).astype(np.float32)
+    host = [planted, syn.update_vector(3, 1, d=d), tied, (rng.standard_normal(d) * 1e-3).astype(np.float32)]
+    n = 40
+    assert n * d >= 5 << 24
+    refs = [(orc.fit_points(u)[1], orc.fit_alpha(u)) for u in host]
+    alpha, keys, status = gpu_fit_alpha([host[c % 4] for c in range(n)])
+    assert status == 0
+    for c in range(n):
+        ref_keys, ref_alpha = refs[c % 4]
+        assert keys[c, : ref_keys.size].tolist() == ref_keys.tolist(), c
+        assert not keys[c, ref_keys.size:].any()
+        assert alpha[c] == pytest.approx(ref_alpha, rel=1e-11, abs=1e-11), c
+
+
 def test_fit_alpha_flags_non_finite_input():
     U = syn.update_vector(1, 0).copy()
     U[777] = np.float32("inf")
