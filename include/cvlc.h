@@ -242,10 +242,10 @@ uint32_t cvlc_fit_ranks(uint32_t d, uint32_t* ranks_out);
 
 /* Scratch bytes for cvlc_fit_alpha.  cvlc_fit_workspace_bytes(n): the least it
  * runs in, independent of d (about 100 KB per client); it then reads the vectors
- * three times.  cvlc_fit_workspace_bytes_for(n, d): with room for the keys the
- * second pass sets aside (4 bytes per coordinate in the worst case, every
- * wavefront owning room for all it reads); given that much, cvlc_fit_alpha reads
- * the vectors twice.  Same results either way.  0 for n = 0 or d outside
+ * three times.  cvlc_fit_workspace_bytes_for(n, d): with room for the keys that
+ * are set aside (4 bytes per coordinate in the worst case, every wavefront
+ * owning room for all it reads); given that much, cvlc_fit_alpha reads the
+ * vectors twice, a large call's once.  Same results either way.  0 for n = 0 or d outside
  * 1 .. 2^31-1. */
 size_t cvlc_fit_workspace_bytes(uint32_t n_clients);
 size_t cvlc_fit_workspace_bytes_for(uint32_t n_clients, uint32_t d);
@@ -323,7 +323,7 @@ enum {
   CVLC_STAGE_ENC_SETUP = 0,    /* clear scratch, upload per-client parameters   */
   CVLC_STAGE_ENC_SAMPLE = 1,   /* sample histogram -> candidate threshold       */
   CVLC_STAGE_ENC_FILTER = 2,   /* the full pass over the update vectors         */
-  CVLC_STAGE_ENC_REFILTER = 3, /* prefix of the kept runs, level-1 boundaries;  */
+  CVLC_STAGE_ENC_REFILTER = 3, /* prefix of the kept runs, boundaries' bins; */
                                /* keep-all second pass if the sample misjudged  */
   CVLC_STAGE_ENC_SELECT = 4,   /* dense candidate list, exact boundary keys, ties */
   CVLC_STAGE_ENC_CLASSIFY = 5, /* group counts and statistics                   */
