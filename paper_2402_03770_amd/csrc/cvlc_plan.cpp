@@ -10,7 +10,6 @@
 #include <cmath>
 #include <cstring>
 #include <limits>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -261,8 +260,8 @@ int plan_algorithm1(uint32_t d, uint64_t budget, uint32_t R, double alpha, float
     const unsigned cpus = std::thread::hardware_concurrency();
     try {
       for (unsigned t = 0; t + 1u < cpus && t < (unsigned)(kThreads - 1); ++t) helpers[t] = std::thread(search);
-    } catch (const std::system_error&) {
-      // no more threads to be had: those that run and this one do the work
+    } catch (...) {
+      // no more threads (or no memory for them) to be had: those that run and this one do the work
     }
   }
   search();
