@@ -101,15 +101,24 @@ uint32_t filter_blocks_per_client(uint32_t n_regions, uint32_t n, uint32_t resid
 // filter: 20.6 -> 5.8 us for one client of 65 536 coordinates, 20.6 -> 14.4 us for 8 of 1.2 M.  One client of
 // 11.2 M: filter 27.8 -> 20.6 us with regions of 4096 (scan_l1 and the gather 1.5 and 1.2 us more); with regions of
 // 2048 scan_l1 takes 13.1 us and more is lost than won.
+uint32_t regions_of(uint32_t d, uint32_t shift) { return (uint32_t)(((uint64_t)d + (1u << shift) - 1u) >> shift); }
+
+// Regions a client of n may have while they are shorter than the longest.
+uint32_t short_regions_max(uint32_t n) {
+  constexpr uint32_t kWavesCounted = 256u * 24u, kScanRounds = 3u * kWideBlock;
+  return std::min(kScanRounds, kWavesCounted / n);
+}
+
 uint32_t region_shift_for(uint32_t d, uint32_t n) {
-  constexpr uint64_t kWavesCounted = 256u * 24u, kScanRounds = 3u * kWideBlock;
   uint32_t shift = kRegionShiftMax;
-  while (shift > kRegionShiftMin) {
-    const uint64_t regions = ((uint64_t)d + (1u << (shift - 1u)) - 1u) >> (shift - 1u);
-    if (regions > kScanRounds || regions * n > kWavesCounted) break;
-    --shift;
-  }
+  while (shift > kRegionShiftMin && regions_of(d, shift - 1u) <= short_regions_max(n)) --shift;
   return shift;
+}
+
+// The most regions that a vector of up to d coordinates has.  The number itself falls by half wherever the length of
+// a region doubles; the workspace is sized by this one, so that a workspace for one d holds every smaller one too.
+uint32_t region_room_for(uint32_t d, uint32_t n) {
+  return std::max(regions_of(d, kRegionShiftMax), std::min(regions_of(d, kRegionShiftMin), short_regions_max(n)));
 }
 
 // `cap`: candidates (coordinates at or above the sampled threshold) a client may have; the filter's own
@@ -117,7 +126,8 @@ uint32_t region_shift_for(uint32_t d, uint32_t n) {
 EncodeLayout encode_layout(uint32_t d, uint32_t n, uint32_t cap) {
   EncodeLayout L;
   L.region_shift = region_shift_for(d, n);
-  L.n_regions = (uint32_t)(((uint64_t)d + (1u << L.region_shift) - 1) >> L.region_shift);
+  L.n_regions = regions_of(d, L.region_shift);
+  const uint32_t region_room = region_room_for(d, n);
   L.dense_cap = cap < d ? cap : d;
   L.max_spans = (uint32_t)(((uint64_t)L.dense_cap + kSpan - 1) / kSpan);
   {
@@ -131,18 +141,18 @@ EncodeLayout encode_layout(uint32_t d, uint32_t n, uint32_t cap) {
   // The filter's workgroups add their counts to the client's by atomics, which queue up at each cache line: with few
   // clients, hundreds of workgroups on the same lines, so such a client has several copies, one for about 32 workgroups
   // (one client of 11.2 M: filter 30.6 -> 15.6 us; 8 of them: no difference).
-  L.hist_copies = n >= kHistCopiesMax ? 1u : std::max(1u, std::min(kHistCopiesMax / n, L.n_regions / (32u * kWavesPerBlock)));
+  L.hist_copies = n >= kHistCopiesMax ? 1u : std::max(1u, std::min(kHistCopiesMax / n, region_room / (32u * kWavesPerBlock)));
   L.hist_bins = off; off = align256(off + (size_t)n * L.hist_copies * kSelBins * sizeof(uint32_t));
   L.zero_bytes = off;
   L.params = off; off = align256(off + (size_t)n * sizeof(ClientParams));
-  L.region_cnt = off; off = align256(off + (size_t)n * L.n_regions * sizeof(uint32_t));
-  L.region_sumsq = off; off = align256(off + (size_t)n * L.n_regions * sizeof(double));
+  L.region_cnt = off; off = align256(off + (size_t)n * region_room * sizeof(uint32_t));
+  L.region_sumsq = off; off = align256(off + (size_t)n * region_room * sizeof(double));
   L.cand_idx = off; off = align256(off + (size_t)n * d * sizeof(uint16_t));
   L.cand_val = off; off = align256(off + (size_t)n * d * sizeof(uint32_t));
   L.dense_idx = off; off = align256(off + (size_t)n * L.dense_cap * sizeof(uint32_t));
   L.dense_val = off; off = align256(off + (size_t)n * L.dense_cap * sizeof(uint32_t));
-  L.nz_off = off; off = align256(off + (size_t)n * (L.n_regions + 1) * sizeof(uint32_t));
-  L.nz_run = off; off = align256(off + (size_t)n * (L.n_regions + 1) * sizeof(uint32_t));
+  L.nz_off = off; off = align256(off + (size_t)n * (region_room + 1) * sizeof(uint32_t));
+  L.nz_run = off; off = align256(off + (size_t)n * (region_room + 1) * sizeof(uint32_t));
   L.span_first = off; off = align256(off + (size_t)n * (L.max_spans + 1) * sizeof(uint32_t));
   L.span_cnt = off; off = align256(off + (size_t)n * (L.max_spans + 1) * 32 * sizeof(uint32_t));
   L.group_info = off; off = align256(off + (size_t)n * sizeof(GroupInfo));

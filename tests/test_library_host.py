@@ -134,6 +134,20 @@ def test_encode_workspace_sized_to_the_candidates():
     assert cv.encode_workspace_bytes_for(0, 1, 5) == 0 and cv.encode_workspace_bytes_for(5, 0, 5) == 0
 
 
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 7, 8, 32, 100, 7000])
+def test_encode_workspace_for_one_length_holds_every_smaller_one(n):
+    """Buffers are sized for the largest model and used for all: the size never falls as d grows, the steps at which
+    the encoder takes longer regions included, nor as n does."""
+    steps = [(m << s) + e for s in range(10, 15) for m in {3072, 6144 // n, 1} for e in (-1, 0, 1)]
+    rng = np.random.default_rng(n)
+    lengths = sorted({v for v in steps + rng.integers(1, 40_000_000, 300).tolist() if v >= 1})
+    for cap in (1, 300_000, 0xFFFFFFFF):
+        sizes = [cv.encode_workspace_bytes_for(v, n, cap) for v in lengths]
+        assert sizes == sorted(sizes)
+    for v in lengths[::10]:
+        assert cv.encode_workspace_bytes(v, n) < cv.encode_workspace_bytes(v, n + 1)
+
+
 def test_fit_ranks_and_argument_errors():
     """The ranks of the power-law fit (doubling ranks, then d) and cvlc_fit_alpha's host-side checks."""
     for d in (1, 2, 3, 4, 5, 1000, 65536, 11_200_000, 2**31 - 1):
