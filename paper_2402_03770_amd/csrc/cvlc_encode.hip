@@ -1113,9 +1113,10 @@ __global__ __launch_bounds__(kSelectBlock) void select_kernel(const ClientParams
     uint32_t known = 63;            // keys have 31 bits
     bool found = false;
     // A list overflows where thousands of keys are equal: the first walk counts the members above the key of some
-    // member and sorts those with that very key by their numbers; the boundary is nearly always among them.
+    // member (the list is the first boundary's of those with this bin, and its shared rest is full) and sorts those
+    // with that very key by their numbers; the boundary is nearly always among them.
     bool guess = walk_all;
-    const uint32_t likely = guess ? src[mp.over_first].y : 0u;
+    const uint32_t likely = guess ? ws.members[((size_t)client * kMemberSlots + first) * ws.member_pool + mp.over_first].y : 0u;
     while (!found) {
       __syncthreads();  // the map or the list is in place; the round before is done with what is written below
       if (tid == 0) {

@@ -275,6 +275,30 @@ def test_selection_bins(d, kind, share):
     check_encode([U], [p], 17, [4])
 
 
+def encode_stage_us(update, plan, stage, repeats=5):
+    """Shortest time of a stage of an encode call, on a workspace full of ones: what the call before left there must not matter."""
+    ws = cv.new_workspace(cv.encode_workspace_bytes(plan.d, 1), DEV)
+    stream = cv.new_stream_buffer(plan, DEV)
+    best = float("inf")
+    for _ in range(repeats):
+        ws.fill_(255)
+        cv.profile_start([stage])
+        cv.encode_batch([plan], [update], 3, [1], [stream], ws)
+        best = min(best, cv.profile_stop()[stage][0] * 1e3)
+        assert cv.device_status(ws) == 0
+    return best
+
+
+def test_boundaries_that_share_a_tied_bin_cost_what_one_does():
+    """Seven magnitudes: the boundaries cut one class of a million equal keys, and every boundary's workgroup starts from
+    a member of the class.  (From anything else the walk takes twice as long.)"""
+    d = 8_000_000
+    U = torch.from_numpy((2.0 ** np.random.default_rng(1).integers(-3, 4, d)).astype(np.float32)).to(DEV)
+    one = encode_stage_us(U, cv.plan_manual(d, [8], [80_000]), "enc_select")
+    three = encode_stage_us(U, cv.plan_manual(d, [8, 6, 4], [20_000, 20_000, 40_000]), "enc_select")
+    assert three < 1.25 * one, (one, three)
+
+
 # --------------------------------------------------------------------------- batches of clients with different plans
 def test_batch_with_mixed_plans():
     d = 150_000
