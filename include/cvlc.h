@@ -174,6 +174,8 @@ uint32_t cvlc_plan_candidates_hint(const cvlc_plan_t* plan);
  *   client_ids[i]    host; written to the header and mixed into the generator
  *   d_streams_out[i] host array of device pointers, 4-byte aligned, each at
  *                    least capacities[i] >= cvlc_stream_capacity(&plans[i]) bytes
+ *                    (the call may use those bytes as scratch before it writes the
+ *                    stream there)
  *   d_workspace      device, 256-byte aligned, ws_bytes >= cvlc_encode_workspace_bytes(d, n),
  *                    or less as cvlc_encode_workspace_bytes_for describes
  *   d_stats_out      device or NULL: n * CVLC_STATS_STRIDE cvlc_seg_stats_t

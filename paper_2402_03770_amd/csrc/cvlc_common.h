@@ -30,10 +30,11 @@ constexpr uint32_t kChunkSpans = 8;        // spans per emit chunk (4096 candida
 constexpr uint32_t kSampleBins = 8192;     // sample histogram on key >> 18 (8 exponent + 5 mantissa bits)
 constexpr uint32_t kSampleShift = 18;
 // Selection bins: a window of kMapBins sample bins, each cut into 1 .. 1024 fine bins by its share of the sample,
-// so that no fine bin holds much more than 2 / (number aimed at) of the candidates; outside the window one bin per octave.
+// so that no fine bin holds much more than 2 / (number aimed at) of the candidates, unless keys are equal; outside the
+// window one bin per octave.
 constexpr uint32_t kMapBins = 512;         // 16 octaves
 constexpr uint32_t kFineMin = 128, kFineMax = 1024;  // fine bins aimed at ...
-constexpr uint32_t kFineShare = 256;       // ... so that one holds about this many of the k kept coordinates
+constexpr uint32_t kFineShare = 256;       // ... so that one holds about this many of the k kept coordinates, more once kFineMax is reached
 constexpr uint32_t kOctaves = 256;         // values of the exponent field
 constexpr uint32_t kFineBins = kFineMax + kMapBins;  // at most: the shares add up to the number aimed at, every sample bin has one fine bin at least
 constexpr uint32_t kSelBins = kOctaves + kFineBins + kOctaves;  // below the window, the window, above it: ascending with the key
@@ -75,6 +76,14 @@ struct SegPartial {
 // 11.2 M, 100 workgroups: count 17.7 -> 9.2 us with eight).
 constexpr uint32_t kSegCopies = 8;
 
+// Where the gather sets the members of a boundary's selection bin aside: pieces of `cap` entries for its workgroups, and
+// behind the pieces room for what found its piece full.
+struct MemberList {
+  uint64_t entries;          // address; 0: the bin has no list
+  uint32_t cap, over_first, over_room;
+  uint32_t members;          // candidates in the bin
+};
+
 // Per-client scratch state, zero-filled at the start of every encode call.
 struct ClientCtl {
   uint32_t tau_lo;           // candidate threshold key from the sample (0: keep every coordinate)
@@ -85,9 +94,10 @@ struct ClientCtl {
   uint32_t claim;            // regions of the filter's claimed part taken so far
   uint32_t emit_claim;       // chunks of the packing pass taken beyond every workgroup's first
   SegPartial seg[kSegCopies];
-  uint32_t over_cnt[32];     // members of a boundary's bin that found no room in the share of their workgroup
+  uint32_t over_cnt[32];     // members of a boundary's bin that found no room in the piece of their workgroup
   uint32_t sel_bin[32];      // selection bin that holds boundary r's key; kNoBin: Z_r = 0
   uint32_t sel_rem[32];      // rank of the boundary element inside that bin, 1-based from the largest key
+  MemberList list[32];       // that bin's list
   uint32_t anchor;           // first sample bin of the window that has fine selection bins
   uint32_t tau[32];          // Z_r-th largest key (0xFFFFFFFF: Z_r = 0)
   uint32_t iota[32];         // last of the key == tau_r candidates inside the top Z_r, by its number in the position-ordered list

@@ -156,9 +156,9 @@ EncodeLayout encode_layout(uint32_t d, uint32_t n, uint32_t cap) {
   L.span_first = off; off = align256(off + (size_t)n * (L.max_spans + 1) * sizeof(uint32_t));
   L.span_cnt = off; off = align256(off + (size_t)n * (L.max_spans + 1) * 32 * sizeof(uint32_t));
   L.group_info = off; off = align256(off + (size_t)n * sizeof(GroupInfo));
-  // several times what a list is expected to hold (a bin of bfloat16 values is one key, and a hundredth of them); three quarters shared out between the gather's workgroups
+  // Twice what a bin holds of up to 2 M candidates, give or take the sample's error; larger bins have their lists elsewhere.
   L.member_pool = std::min(kMemberPoolMin + L.dense_cap / 128u, kMemberPoolMax);
-  L.members = off; off = align256(off + (size_t)n * kMemberSlots * L.member_pool * sizeof(uint2));
+  L.members = off; off = align256(off + (size_t)n * kMemberSlots * L.member_pool * sizeof(uint64_t));
   L.seg_cnt = off; off = align256(off + (size_t)n * kMemberSlots * kGatherBlocksMax * sizeof(uint32_t));
   L.total = off;
   return L;
@@ -180,7 +180,7 @@ struct Workspace {  // device pointers into the caller's workspace
   uint32_t* span_cnt;  // per span of 512 candidates: members of every group, then their exclusive prefix
   GroupInfo* group_info;
   uint32_t* hist_bins; // per client, hist_copies times: candidates per selection bin (device-wide atomics from the filter, two counters each)
-  uint2* members;      // per (client, boundary): the candidates in the boundary's selection bin, {number in the dense list, key}
+  unsigned long long* members;  // per (client, boundary): the candidates in the boundary's selection bin, as member_of() gives them
   uint32_t* seg_cnt;   // ... and how many of them each of the gather's workgroups has seen
   unsigned long long* norm_limbs;  // QSGD: per (client, group) the exact sum of squares in 32-bit limbs
   uint32_t d, region_shift, n_regions, max_spans, dense_cap, filter_blocks, gather_blocks, member_pool, hist_copies;
@@ -605,6 +605,67 @@ __global__ __launch_bounds__(kBlock) void filter_kernel(const ClientParams* __re
   }
 }
 
+// ---- member lists
+// The gather sets the members of the boundaries' selection bins aside for the select kernel.  How many a bin has is
+// known by then, so a list has room for all of them: a piece for every gather workgroup that has spans to go through,
+// and behind the pieces room for what found its piece full, all members if need be.  Bins grow with the candidates
+// (one to two 1024ths of them from 262 144 kept coordinates on): a list of up to half the boundary's pool lies there,
+// a larger one in the client's own stream buffer, which nothing is written to before the layout and which has
+// three bytes and more for every kept coordinate.  For a client whose sample misjudged it lies in the filter's
+// output, which is not looked at then.  Boundaries that share a bin share the list of the first of them.  A bin that
+// holds a large part of all candidates (equal magnitudes) has no list, the select kernel walks the candidates for it.
+constexpr uint32_t kWalkShare = 16;  // more than this part of the candidates: no list
+typedef unsigned long long __attribute__((address_space(1))) * GlobalU64Ptr;
+
+// A member as one number: members rank as the coordinates do (larger keys first, earlier positions first), no two are alike.
+__device__ __forceinline__ unsigned long long member_of(uint32_t dense_i, uint32_t key) {
+  return ((unsigned long long)key << 32) | (uint32_t)~dense_i;
+}
+
+// Workgroups of a client's gather that have spans to go through.
+__device__ __forceinline__ uint32_t gather_workgroups(const Workspace& ws, uint32_t n_cand) {
+  return max(1u, min(ws.gather_blocks, (n_cand + kSpan * kGatherWaves - 1u) / (kSpan * kGatherWaves)));
+}
+
+// One whole wavefront, lane b = boundary b: the list of its bin.
+__device__ __forceinline__ MemberList place_member_list(const Workspace& ws, const ClientParams& p, uint32_t client, bool keep_all,
+                                                        uint32_t n_cand, uint32_t bin, uint32_t members) {
+  const uint32_t lane = lane_id();
+  const uint32_t blocks = gather_workgroups(ws, n_cand);
+  MemberList l = {0u, 0u, 0u, 0u, members};
+  const bool valid = bin != kNoBin, large = valid && members > ws.member_pool / 2u;
+  if (valid && !large) {
+    l.entries = (uint64_t)(ws.members + ((size_t)client * kMemberSlots + lane) * ws.member_pool);
+    l.cap = (ws.member_pool - members) / blocks;
+    l.over_first = blocks * l.cap;
+    l.over_room = ws.member_pool - l.over_first;
+  }
+  if (!__ballot(large)) return l;  // (a small list is looked for in the place of the first of its boundaries only)
+  uint32_t first = lane;
+#pragma unroll
+  for (int j = (int)kMemberSlots - 1; j >= 0; --j)
+    if ((uint32_t)j < lane && (uint32_t)__builtin_amdgcn_readlane(bin, j) == bin) first = (uint32_t)j;
+  // the area of the larger lists, 8-byte aligned
+  const uint64_t at = keep_all ? (uint64_t)(ws.cand_val + (size_t)client * ws.d) : (uint64_t)p.stream;
+  const uint32_t words = keep_all ? ws.d : p.total_words, skip = (uint32_t)(at >> 2) & 1u;
+  const uint32_t room = (max(words, skip) - skip) / 2u;
+  uint32_t need = 0;
+  if (large && members <= n_cand / kWalkShare) {
+    l.cap = members / blocks + members / (4u * blocks) + 16u;  // a quarter more than the workgroups' equal shares
+    l.over_first = blocks * l.cap;
+    l.over_room = members;
+    if (first == lane) need = l.over_first + l.over_room;  // below 2^29
+  }
+  uint32_t used = 0;
+  for (uint32_t b = 0; b < kMemberSlots; ++b) {
+    const uint32_t n = __builtin_amdgcn_readlane(need, b);
+    if (n == 0 || n > room - used) continue;  // uniform
+    if (first == b && large) l.entries = at + 4u * skip + 8ull * used;
+    used += n;
+  }
+  return l;
+}
+
 // ------------------------------------------------------------------ 3. region prefix + the boundaries' selection bins
 // One workgroup per client.  Turns the region counts into exclusive offsets
 // and lists the non-empty runs with the number of their first candidate (the
@@ -751,8 +812,8 @@ __global__ __launch_bounds__(kWideBlock) void scan_l1_kernel(const ClientParams*
   incl[top] = above + h0;
   incl[top - 1] = above + h0 + h1;
   __syncthreads();
-  if (tid < 32) {
-    uint32_t bin = kNoBin, rem = 0;
+  if (tid < kWave) {  // lane b = boundary b
+    uint32_t bin = kNoBin, rem = 0, members = 0;
     if (tid < p.R) {
       const uint32_t Z = p.Z[tid];
       if (Z > total) atomicOr(ws.status, CVLC_DEV_INTERNAL);  // cannot happen once the filter kept >= k
@@ -764,12 +825,18 @@ __global__ __launch_bounds__(kWideBlock) void scan_l1_kernel(const ClientParams*
         }
         bin = lo;
         rem = Z - (incl[lo] - hist[lo]);
+        members = hist[lo];
       }
     }
-    ctl->sel_bin[tid] = bin;
-    ctl->sel_rem[tid] = rem;
-    ctl->tau[tid] = 0xFFFFFFFFu;  // boundaries with Z_r = 0 keep "nothing inside"
-    ctl->iota[tid] = 0u;
+    const uint32_t n_cand = keep_all ? ws.d : run;
+    const MemberList list = place_member_list(ws, p, client, keep_all, n_cand, bin, members);
+    if (tid < 32) {
+      ctl->sel_bin[tid] = bin;
+      ctl->sel_rem[tid] = rem;
+      ctl->list[tid] = list;
+      ctl->tau[tid] = 0xFFFFFFFFu;  // boundaries with Z_r = 0 keep "nothing inside"
+      ctl->iota[tid] = 0u;
+    }
   }
 }
 
@@ -777,7 +844,7 @@ __global__ __launch_bounds__(kWideBlock) void scan_l1_kernel(const ClientParams*
 // scan_l1 has left, for every boundary, the selection bin its key lies in and
 // the boundary's rank inside that bin.  A bin holds about a thousandth of the
 // candidates, so the gather, which reads every candidate anyway, sets the
-// members of the boundaries' bins aside ({number in the dense list, key}), and
+// members of the boundaries' bins aside (key and number in the dense list), and
 // the select kernel finds each boundary's element among them.  Its number in the
 // dense list cuts a class of equal keys (ties rank by position, and that
 // numbering preserves positions): keys above tau are inside, and so are those
@@ -890,27 +957,15 @@ __device__ __forceinline__ void span_slots(const CandView& cv, uint32_t span, co
   for (uint32_t j = 0; j < kPerLane; ++j) slot[j] += begin + j * kWave + lane;  // meaningless for i >= n, never used there
 }
 
-// How a client's member lists are laid out: a piece for every gather workgroup that has spans to go through, three
-// quarters of the list in all, and behind them the room for what found its piece full.
-struct MemberPieces {
-  uint32_t blocks, cap, over_first, over_room;
-};
-__device__ __forceinline__ MemberPieces member_pieces(const Workspace& ws, uint32_t n_cand) {
-  MemberPieces mp;
-  mp.blocks = max(1u, min(ws.gather_blocks, (n_cand + kSpan * kGatherWaves - 1u) / (kSpan * kGatherWaves)));
-  mp.cap = ws.member_pool / 4u * 3u / mp.blocks;
-  mp.over_first = mp.blocks * mp.cap;
-  mp.over_room = ws.member_pool - mp.over_first;
-  return mp;
-}
-
 // What the wavefronts of a gather workgroup share.
 struct GatherShared {
   uint32_t map[kMapBins];
   uint8_t tag[kSelBins];       // per selection bin: 1 + the first boundary whose key lies in it, 0: none
-  uint32_t seen[kMemberSlots + 1];  // members of every boundary's bin met by this workgroup
-  uint32_t full[kMemberSlots + 1];  // the bin's list has no room left
   uint32_t bin[32];
+  // per boundary
+  uint32_t seen[32];           // members of its bin met by this workgroup
+  uint4 list[32];              // the bin's list: address of its entries, cap, over_first
+  uint32_t over_room[32];
 };
 
 // Every wavefront takes spans of 512 candidates (gw, gw + wavefronts, ...), collects
@@ -918,61 +973,66 @@ struct GatherShared {
 // dense position-ordered candidate list and sets the members of the boundaries'
 // bins aside.  Every span is the same amount of work wherever its candidates lie,
 // and the wavefronts do not wait for each other.
-// Bound by its mixed traffic (6 bytes read and 8 written per candidate).  A member list is shared out: every
-// workgroup has a piece of its own, so that a member takes its place with an LDS atomic; only what a piece has no
-// room for takes one with a device-wide atomic, behind the pieces, and what finds that full too is not stored
-// (the select kernel then walks the dense list).
-__global__ __launch_bounds__(kGatherBlock) void gather_kernel(const ClientParams* __restrict__ params,
+// Bound by its mixed traffic (6 bytes read and 8 written per candidate).  A member takes its place in its workgroup's
+// piece of the list with an LDS atomic; only what the piece has no room for takes one with a device-wide atomic,
+// behind the pieces.
+// (Past 80 scalar registers a CU takes one workgroup of 1024 threads instead of two, 565 us instead of 466 for
+// 100 x 25.6 M: capped.)
+__global__ __launch_bounds__(kGatherBlock) __attribute__((amdgpu_num_sgpr(80))) void gather_kernel(const ClientParams* __restrict__ params,
                                                               ClientCtl* __restrict__ ctls, Workspace ws) {
   __shared__ GatherShared S;
   const uint32_t client = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
   const ClientParams& p = params[client];
   ClientCtl* ctl = ctls + client;
-  if (ctl->dead) return;  // the workspace was too short for this client (whole workgroup)
   const uint32_t R = p.R, anchor = ctl->anchor;
-  for (uint32_t i = tid; i < kMapBins; i += kGatherBlock) S.map[i] = ctl->bin_map[i];
-  for (uint32_t i = tid; i < kSelBins / 4u; i += kGatherBlock) reinterpret_cast<uint32_t*>(S.tag)[i] = 0;
+  const CandView cv = cand_view(ws, ctl, client);
+  static_assert(kMapBins <= kGatherBlock && kSelBins / 4u <= kGatherBlock, "one entry per thread");
+  // everything that is read from the control block is asked for together
+  const uint32_t my_map = ctl->bin_map[min(tid, kMapBins - 1u)], b = min(tid, kMemberSlots - 1u);
+  const uint32_t my_bin = tid < R ? ctl->sel_bin[b] : kNoBin;
+  const uint64_t my_entries = ctl->list[b].entries;
+  const uint32_t my_cap = ctl->list[b].cap, my_over_first = ctl->list[b].over_first, my_over_room = ctl->list[b].over_room;
+  if (ctl->dead) return;  // the workspace was too short for this client (whole workgroup)
+  if (tid < kMapBins) S.map[tid] = my_map;
+  if (tid < kSelBins / 4u) reinterpret_cast<uint32_t*>(S.tag)[tid] = 0;
   if (tid < 32) {
-    S.bin[tid] = tid < R ? ctl->sel_bin[tid] : kNoBin;
+    S.bin[tid] = my_bin;
     S.seen[tid] = 0;
-    S.full[tid] = 0;
+    S.list[tid] = make_uint4((uint32_t)my_entries, (uint32_t)(my_entries >> 32), my_cap, my_over_first);
+    S.over_room[tid] = my_over_room;
   }
   __syncthreads();
   if (tid < R) {
-    const uint32_t bin = S.bin[tid];
-    bool first = bin != kNoBin;
-    for (uint32_t b = 0; b < tid; ++b) first = first && S.bin[b] != bin;
-    if (first) S.tag[bin] = (uint8_t)(tid + 1u);
+    bool first = my_entries != 0;
+    for (uint32_t o = 0; o < tid; ++o) first = first && S.bin[o] != my_bin;
+    if (first) S.tag[my_bin] = (uint8_t)(tid + 1u);
   }
   __syncthreads();
-  const CandView cv = cand_view(ws, ctl, client);
+  const uint32_t blocks = gather_workgroups(ws, cv.n);
+  if (blockIdx.x >= blocks) return;  // no span is left for this workgroup
   uint32_t* __restrict__ dst_idx = ws.dense_idx + (size_t)client * ws.dense_cap;
   uint32_t* __restrict__ dst_val = ws.dense_val + (size_t)client * ws.dense_cap;
-  uint2* __restrict__ members = ws.members + (size_t)client * kMemberSlots * ws.member_pool;
-  const MemberPieces mp = member_pieces(ws, cv.n);
-  if (blockIdx.x >= mp.blocks) return;  // no span is left for this workgroup
-  const uint32_t piece = blockIdx.x * mp.cap;
+  auto entries_of = [](const uint4& l) { return (GlobalU64Ptr)(((uint64_t)l.y << 32) | l.x); };
   // slot: 1 + boundary, 0: in no boundary's bin
   auto set_aside = [&](uint32_t slot, uint32_t dense_i, uint32_t key) {
     bool over = false;
     if (slot) {
       const uint32_t place = atomicAdd(&S.seen[slot - 1u], 1u);
-      if (place < mp.cap) members[(slot - 1u) * ws.member_pool + piece + place] = make_uint2(dense_i, key);
-      else over = S.full[slot - 1u] == 0;
+      const uint4 l = S.list[slot - 1u];
+      if (place < l.z) entries_of(l)[blockIdx.x * l.z + place] = member_of(dense_i, key);
+      else over = true;
     }
     uint64_t todo = __ballot(over);
     while (todo) {  // one device-wide atomic per boundary and row
       const uint32_t leader = (uint32_t)__builtin_ctzll(todo), q = __builtin_amdgcn_readlane(slot, leader) - 1u;
       const uint64_t peers = __ballot(over && slot == q + 1u);
       uint32_t base = 0;
-      if (lane == leader) {
-        base = atomicAdd(&ctl->over_cnt[q], (uint32_t)__popcll(peers));
-        if (base >= mp.over_room) S.full[q] = 1u;  // the count is past the room for good: stop adding to it
-      }
+      if (lane == leader) base = atomicAdd(&ctl->over_cnt[q], (uint32_t)__popcll(peers));
       base = __builtin_amdgcn_readlane(base, leader);
       if (over && slot == q + 1u) {
         const uint32_t place = base + lanes_below(peers);
-        if (place < mp.over_room) members[q * ws.member_pool + mp.over_first + place] = make_uint2(dense_i, key);
+        if (place < S.over_room[q])  // always: a list has room for all members
+          entries_of(S.list[q])[S.list[q].w + place] = member_of(dense_i, key);
       }
       todo &= ~peers;
     }
@@ -981,7 +1041,7 @@ __global__ __launch_bounds__(kGatherBlock) void gather_kernel(const ClientParams
   // keep_all: a slot is a region of the vector itself and a candidate's place in it its position
   auto copy_spans = [&](auto keep_all) {
     const uint32_t* __restrict__ src_val = keep_all.value ? reinterpret_cast<const uint32_t*>(p.update) : cv.val;
-    for (uint32_t span = blockIdx.x * kGatherWaves + wave; span < n_spans; span += mp.blocks * kGatherWaves) {
+    for (uint32_t span = blockIdx.x * kGatherWaves + wave; span < n_spans; span += blocks * kGatherWaves) {
       uint32_t slot[kPerLane], v[kPerLane], x[kPerLane];
       span_slots(cv, span, span_window(cv, span), slot);
 #pragma unroll
@@ -1013,13 +1073,10 @@ __global__ __launch_bounds__(kGatherBlock) void gather_kernel(const ClientParams
 }
 
 // One workgroup per (boundary, client); boundaries whose keys lie in one bin are
-// all served by the first of them, unless the bin's list was too short for it.  A member is one 64-bit number, the key above
-// the complement of its number in the dense list, so that members rank as the
-// coordinates do (larger keys first, earlier positions first) and no two are
-// alike.  Ten bits at a time below the highest bit in which the members differ
-// are counted, until a wavefront's worth of them is left.  A bin that more keys lie in than its list has room for
-// (thousands of equal keys) is walked in the dense list, every boundary by its own workgroup, until LDS can hold
-// what is left of it.
+// all served by the first of them while the bin's list fits LDS, each by its own workgroup otherwise.  Members are
+// 64-bit numbers of which no two are alike (see member_of).  Ten bits at a time below the highest bit in which the
+// members differ are counted, until a wavefront's worth of them is left.  A bin without a list
+// (equal keys) is walked in the dense list, until LDS can hold what is left of it.
 // All latency: one or two rounds of a handful of barriers each.
 constexpr uint32_t kSelectBlock = 512;
 constexpr uint32_t kSelectList = 2048;  // members kept in LDS; more are read again for every round
@@ -1032,7 +1089,7 @@ __global__ __launch_bounds__(kSelectBlock) void select_kernel(const ClientParams
   __shared__ unsigned long long list[kSelectList];
   __shared__ uint32_t map[kMapBins];
   __shared__ uint32_t hist[kSelectDigits];
-  __shared__ uint32_t s_bin[32], s_rem[32], s_over[32], seg_first[kGatherBlocksMax + 1], scan_tmp[kSelectWaves];
+  __shared__ uint32_t s_bin[32], s_rem[32], seg_first[kGatherBlocksMax + 1], scan_tmp[kSelectWaves];
   __shared__ unsigned long long s_min, s_max, s_answer, few[kWave];
   __shared__ uint32_t s_digit, s_left, s_in_digit, s_larger, n_few;
   const uint32_t r = blockIdx.x, client = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wave = wave_id();
@@ -1041,56 +1098,82 @@ __global__ __launch_bounds__(kSelectBlock) void select_kernel(const ClientParams
   // everything that is read from the control block is asked for together
   const uint32_t dead = ctl->dead, R = p.R, n_cand = ctl->n_cand;
   const uint32_t my_bin = tid < 32 ? ctl->sel_bin[tid] : kNoBin, my_rem = tid < 32 ? ctl->sel_rem[tid] : 0u;
-  const uint32_t my_over = tid < 32 ? ctl->over_cnt[tid] : 0u;
-  uint32_t seen = 0;
-  if (tid < ws.gather_blocks) seen = ws.seg_cnt[((size_t)client * kMemberSlots + r) * kGatherBlocksMax + tid];
-  const MemberPieces mp = member_pieces(ws, n_cand);
+  const uint32_t my_over = ctl->over_cnt[r];
+  const MemberList l = ctl->list[r];
+  const uint32_t blocks = gather_workgroups(ws, n_cand);
+  auto seen_of = [&](uint32_t b) {
+    return tid < blocks ? ws.seg_cnt[((size_t)client * kMemberSlots + b) * kGatherBlocksMax + tid] : 0u;
+  };
+  uint32_t seen = seen_of(r);
   if (dead || r >= R) return;  // uniform (dead: the workspace was too short for this client)
   if (tid < 32) {
     s_bin[tid] = my_bin;
     s_rem[tid] = my_rem;
-    s_over[tid] = my_over;
-  }
-  if (tid < kWave) {
-    static_assert(kGatherBlocksMax <= kWave, "one lane per piece of a member list");
-    const uint32_t here = tid < mp.blocks ? min(seen, mp.cap) : 0u, incl = wave_incl_scan_u32(here);
-    seg_first[tid] = incl - here;
-    if (tid == kWave - 1u) seg_first[kWave] = incl;
   }
   __syncthreads();
   const uint32_t bin = s_bin[r];
   if (bin == kNoBin) return;
   uint32_t first = 0;  // the first boundary with this bin: the list is its
   while (s_bin[first] != bin) ++first;
-  bool walk_all = s_over[first] > mp.over_room;  // some members were not stored
-  if (first != r && !walk_all) return;           // uniform: served by the workgroup of that boundary
-  const uint32_t in_segs = seg_first[kWave];
-  uint32_t m = in_segs + min(s_over[first], mp.over_room);
-  auto member_of = [](uint32_t dense_i, uint32_t key) { return ((unsigned long long)key << 32) | (uint32_t)~dense_i; };
-  const uint2* __restrict__ src = ws.members + ((size_t)client * kMemberSlots + r) * ws.member_pool;
-  auto stored_member = [&](uint32_t e) {
-    uint32_t at = mp.over_first + e - in_segs;
-    if (e < in_segs) {  // a thread finds its member's piece by the pieces' first places: six probes
-      uint32_t s = 0;
-#pragma unroll
-      for (uint32_t step = kWave / 2u; step; step >>= 1)
-        if (seg_first[s + step] <= e) s += step;
-      at = s * mp.cap + e - seg_first[s];
-    }
-    const uint2 x = src[at];
-    return member_of(x.x, x.y);
-  };
-  const bool in_lds = walk_all || m <= kSelectList;
+  bool walk_all = l.entries == 0;
+  const bool in_lds = walk_all || l.members <= kSelectList;
+  GlobalU64Ptr entries = (GlobalU64Ptr)l.entries;
+  if (first != r && in_lds && !walk_all) return;  // uniform: served by the workgroup of that boundary
+  uint32_t m = 0;
   if (walk_all) {
     for (uint32_t i = tid; i < kMapBins; i += kSelectBlock) map[i] = ctl->bin_map[i];
-  } else if (in_lds) {
-    for (uint32_t e = tid; e < m; e += kSelectBlock) list[e] = stored_member(e);
+  } else {
+    uint32_t over = my_over;
+    if (first != r) {
+      seen = seen_of(first);
+      over = ctl->over_cnt[first];
+    }
+    if (tid < kWave) {
+      static_assert(kGatherBlocksMax <= kWave, "one lane per piece of a member list");
+      const uint32_t here = min(seen, l.cap), incl = wave_incl_scan_u32(here);
+      seg_first[tid] = incl - here;
+      if (tid == kWave - 1u) seg_first[kWave] = incl;
+    }
+    __syncthreads();
+    m = seg_first[kWave] + min(over, l.over_room);
+  }
+  const uint32_t in_segs = m ? seg_first[kWave] : 0u;
+  if (!walk_all && in_lds) {
+    for (uint32_t e = tid; e < min(m, kSelectList); e += kSelectBlock) {
+      uint32_t at = l.over_first + e - in_segs;
+      if (e < in_segs) {  // a thread finds its member's piece by the pieces' first places: six probes
+        uint32_t s = 0;
+#pragma unroll
+        for (uint32_t step = kWave / 2u; step; step >>= 1)
+          if (seg_first[s + step] <= e) s += step;
+        at = s * l.cap + e - seg_first[s];
+      }
+      list[e] = entries[at];
+    }
+    m = min(m, kSelectList);  // m = l.members, no more than that
   }
   const uint32_t anchor = ctl->anchor;
   const uint32_t* __restrict__ val = ws.dense_val + (size_t)client * ws.dense_cap;
   auto each_member = [&](auto visit) {
-    if (!walk_all) {
-      for (uint32_t e = tid; e < m; e += kSelectBlock) visit(in_lds ? list[e] : stored_member(e));
+    if (!walk_all && in_lds) {
+      for (uint32_t e = tid; e < m; e += kSelectBlock) visit(list[e]);
+    } else if (!walk_all) {
+      // a wavefront takes piece after piece, then all of them go through what lies behind the pieces; eight rows are
+      // asked for together
+      constexpr uint32_t kRows = 8;
+      auto visit_run = [&](uint32_t at, uint32_t count, uint32_t begin, uint32_t step) {
+        for (uint32_t base = begin; base < count; base += step) {
+          unsigned long long c[kRows];
+#pragma unroll
+          for (uint32_t u = 0; u < kRows; ++u) c[u] = entries[at + min(base + u * kWave + lane, count - 1u)];
+#pragma unroll
+          for (uint32_t u = 0; u < kRows; ++u)
+            if (base + u * kWave + lane < count) visit(c[u]);
+        }
+      };
+      for (uint32_t s = wave; s < blocks; s += kSelectWaves)
+        visit_run(s * l.cap, seg_first[s + 1u] - seg_first[s], 0u, kRows * kWave);
+      visit_run(l.over_first, m - in_segs, wave * kRows * kWave, kSelectWaves * kRows * kWave);
     } else {
       constexpr uint32_t kDeep = 16;
       for (uint32_t base = 0; base < n_cand; base += kSelectBlock * kDeep) {
@@ -1105,18 +1188,27 @@ __global__ __launch_bounds__(kSelectBlock) void select_kernel(const ClientParams
       }
     }
   };
-  const uint32_t b_end = walk_all ? r + 1u : R;
+  const uint32_t b_end = walk_all || !in_lds ? r + 1u : R;
   for (uint32_t b = r; b < b_end; ++b) {
     if (s_bin[b] != bin) continue;  // uniform
     uint32_t rem = s_rem[b];
     unsigned long long prefix = 0;  // members at hand: those whose bits from `known` up are `prefix`
     uint32_t known = 63;            // keys have 31 bits
     bool found = false;
-    // A list overflows where thousands of keys are equal: the first walk counts the members above the key of some
-    // member (the list is the first boundary's of those with this bin, and its shared rest is full) and sorts those
-    // with that very key by their numbers; the boundary is nearly always among them.
+    // A bin has no list where a large part of the keys are equal: the first walk counts the members above the key of
+    // some member, the first of 512 candidates spread over the list, and sorts those with that very key by their
+    // numbers; the boundary is nearly always among them.
     bool guess = walk_all;
-    const uint32_t likely = guess ? ws.members[((size_t)client * kMemberSlots + first) * ws.member_pool + mp.over_first].y : 0u;
+    uint32_t likely = 0;
+    if (guess) {
+      if (tid == 0) s_digit = n_cand;
+      __syncthreads();  // the map is in place too
+      const uint32_t i = (uint32_t)((uint64_t)tid * n_cand / kSelectBlock);
+      if (selection_bin(map, anchor, val[i] & 0x7FFFFFFFu) == bin) atomicMin(&s_digit, i);
+      __syncthreads();
+      guess = s_digit < n_cand;
+      if (guess) likely = val[s_digit] & 0x7FFFFFFFu;
+    }
     while (!found) {
       __syncthreads();  // the map or the list is in place; the round before is done with what is written below
       if (tid == 0) {
@@ -2177,7 +2269,7 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
   ws.span_cnt = reinterpret_cast<uint32_t*>(base + L.span_cnt);
   ws.group_info = reinterpret_cast<GroupInfo*>(base + L.group_info);
   ws.hist_bins = reinterpret_cast<uint32_t*>(base + L.hist_bins);
-  ws.members = reinterpret_cast<uint2*>(base + L.members);
+  ws.members = reinterpret_cast<unsigned long long*>(base + L.members);
   ws.seg_cnt = reinterpret_cast<uint32_t*>(base + L.seg_cnt);
   ws.norm_limbs = reinterpret_cast<unsigned long long*>(base + L.norm_limbs);
   ws.d = d;

@@ -299,6 +299,28 @@ def test_boundaries_that_share_a_tied_bin_cost_what_one_does():
     assert three < 1.25 * one, (one, three)
 
 
+@pytest.mark.parametrize("kind", ["laplace", "fp16", "sorted"])
+def test_half_of_a_large_vector_kept(kind):
+    """Bins grow with the candidates, and so do the lists of the boundaries' bins: with six million candidates and keys
+    that are not all equal no boundary's search goes through all of them (which took a hundred times as long)."""
+    rng = np.random.default_rng(6)
+
+    def vector(d):
+        U = (rng.laplace(size=d) * 1e-3).astype(np.float32)
+        if kind == "fp16":      # a handful of equal keys to a bin
+            U = U.astype(np.float16).astype(np.float32)
+        return np.sort(np.abs(U)) if kind == "sorted" else U
+
+    fractions, y = (0.10, 0.15, 0.25), [8, 4, 2]
+    U = vector(12_000_037)
+    po = orc.plan_manual(U.size, y, [int(f * U.size) for f in fractions])
+    check_encode([U], [po], 9, [5])
+    small = vector(3_000_000)
+    t = [encode_stage_us(torch.from_numpy(u).to(DEV), cv.plan_manual(u.size, y, [int(f * u.size) for f in fractions]), "enc_select")
+         for u in (small, U)]
+    assert t[1] < 10 * t[0], t      # four times the candidates
+
+
 # --------------------------------------------------------------------------- batches of clients with different plans
 def test_batch_with_mixed_plans():
     d = 150_000
