@@ -291,7 +291,7 @@ def encode_stage_us(update, plan, stage, repeats=5):
 
 def test_boundaries_that_share_a_tied_bin_cost_what_one_does():
     """Seven magnitudes: the boundaries cut one class of a million equal keys, and every boundary's workgroup starts from
-    a member of the class.  (From anything else the walk takes twice as long.)"""
+    a member of the class.  (From anything else the search takes twice as long.)"""
     d = 8_000_000
     U = torch.from_numpy((2.0 ** np.random.default_rng(1).integers(-3, 4, d)).astype(np.float32)).to(DEV)
     one = encode_stage_us(U, cv.plan_manual(d, [8], [80_000]), "enc_select")
@@ -319,6 +319,38 @@ def test_half_of_a_large_vector_kept(kind):
     t = [encode_stage_us(torch.from_numpy(u).to(DEV), cv.plan_manual(u.size, y, [int(f * u.size) for f in fractions]), "enc_select")
          for u in (small, U)]
     assert t[1] < 10 * t[0], t      # four times the candidates
+
+
+@pytest.mark.parametrize("kind", ["neighbours", "low octave", "signs", "late class"])
+def test_bins_that_hold_a_large_part_of_all_candidates(kind):
+    """Such a bin has no list, its boundaries are looked for in the dense list: two classes of equal keys one apart among
+    close ones (the key counted by itself may be the wrong one), half a million different keys of one octave far below the
+    window of fine bins, one magnitude for all, and a class that begins late in the vector."""
+    rng = np.random.default_rng(8)
+    d = 700_001
+    bits = np.full(d, 0x3F800000, np.uint32)
+    if kind == "neighbours":
+        u = rng.random(d)
+        bits = np.where(u < 0.3, 0x3F800040, np.where(u < 0.6, 0x3F800041, 0x3F800000 + rng.integers(0, 400, d))).astype(np.uint32)
+    if kind == "low octave":
+        bits = np.where(rng.random(d) < 0.05, 0x3F800000 + rng.integers(0, 1 << 23, d), 0x20000000 + rng.integers(0, 1 << 23, d)).astype(np.uint32)
+    if kind == "late class":
+        bits = np.where(np.arange(d) < 9 * d // 10, 0x3F800000 + rng.integers(0, 3, d), 0x3F900000).astype(np.uint32)
+    U = (bits | np.where(rng.random(d) < 0.5, 0x80000000, 0).astype(np.uint32)).view(np.float32)
+    for share in (0.03, 0.4, 1.0):
+        counts = [1, int(0.1 * share * d), int(0.2 * share * d), 0, int(0.3 * share * d), 2]
+        counts.append(int(share * d) - sum(counts))
+        check_encode([U], [orc.plan_manual(d, [12, 10, 8, 6, 6, 4, 1], counts)], 17, [4])
+
+
+def test_a_class_of_equal_keys_is_cut_in_few_passes():
+    """(A hundred times the time of the smooth vector before the passes were made to use the CU's bandwidth.)"""
+    d = 8_000_000
+    rng = np.random.default_rng(2)
+    p = cv.plan_manual(d, [8, 6, 4], [800_000, 800_000, 2_000_000])
+    smooth, tied = (torch.from_numpy(u.astype(np.float32)).to(DEV) for u in (rng.laplace(size=d), 2.0 ** rng.integers(-3, 4, d)))
+    t = [encode_stage_us(u, p, "enc_select") for u in (smooth, tied)]
+    assert t[1] < 20 * t[0], t
 
 
 # --------------------------------------------------------------------------- batches of clients with different plans
