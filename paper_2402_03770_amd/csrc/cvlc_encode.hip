@@ -288,6 +288,30 @@ __global__ __launch_bounds__(kBlock) void sample_hist_kernel(const ClientParams*
   }
 }
 
+// A wavefront's visit to the keys begin .. end - 1 of a list of values: visit(number, key, valid), all lanes
+// together.  One workgroup has a CU's share of the bandwidth at best, so eight 16-byte loads a lane go out together.
+template <class Visit>
+__device__ __forceinline__ void visit_keys(const uint32_t* __restrict__ val, uint32_t begin, uint32_t end, Visit visit) {
+  typedef uint32_t __attribute__((ext_vector_type(4), aligned(4))) Words4;
+  typedef const Words4 __attribute__((address_space(1))) * Words4Ptr;
+  constexpr uint32_t kDeep = 8, kStep = kDeep * 4u * kWave;
+  const uint32_t lane = lane_id();
+  uint32_t base = begin;
+  for (; base + kStep <= end; base += kStep) {
+    Words4 v[kDeep];
+#pragma unroll
+    for (uint32_t u = 0; u < kDeep; ++u) v[u] = *((Words4Ptr)(val + base) + u * kWave + lane);
+#pragma unroll
+    for (uint32_t u = 0; u < kDeep; ++u)
+#pragma unroll
+      for (uint32_t c = 0; c < 4u; ++c) visit(base + (u * kWave + lane) * 4u + c, v[u][c] & 0x7FFFFFFFu, true);
+  }
+  for (; base < end; base += kWave) {
+    const uint32_t i = base + lane;
+    visit(i, val[min(i, end - 1u)] & 0x7FFFFFFFu, i < end);
+  }
+}
+
 // ---- selection bins
 constexpr uint32_t kNoBin = 0xFFFFFFFFu;
 
@@ -677,7 +701,7 @@ __device__ __forceinline__ MemberList place_member_list(const Workspace& ws, con
 // misjudged: six standard deviations, or a vector built against the sampling
 // pattern), every coordinate becomes a candidate: the runs are then the regions
 // themselves, read from the vector, and this workgroup draws up the bin map again, from
-// the whole vector, and counts its selection bins on its own: slow, and next to never needed.
+// the whole vector, and counts its selection bins on its own: slow, and next to never needed (1 x 11.2 M: 0.8 ms).
 __global__ __launch_bounds__(kWideBlock) void scan_l1_kernel(const ClientParams* __restrict__ params,
                                                              ClientCtl* __restrict__ ctls, Workspace ws) {
   __shared__ uint32_t hist[kSelBins];
@@ -769,40 +793,56 @@ __global__ __launch_bounds__(kWideBlock) void scan_l1_kernel(const ClientParams*
     hist[2u * tid + 1] = 0;
     for (uint32_t i = tid; i < kSampleBins; i += kWideBlock) top_hist[i] = 0;
     __syncthreads();
+    // What one workgroup has of the memory's bandwidth bounds this (60 GB/s), and the LDS atomics, which hit few
+    // counters: one pass, if it can be, of the keys at or above the sample's key of four times the rank that was too
+    // low; all of them if they are fewer than k (at once all of them where the sample is wide of the mark).  The bins
+    // are the sample bins themselves, from the one that holds the k-th key on: finer ones would take a second pass,
+    // the longer member lists cost less.
     const uint32_t* __restrict__ bits = reinterpret_cast<const uint32_t*>(p.update);
-    auto each_key = [&](auto visit) {
-      for (uint32_t base = 0; base < d; base += kWideBlock * 8u) {
-        uint32_t v[8];
-#pragma unroll
-        for (uint32_t u = 0; u < 8; ++u) v[u] = bits[min(base + u * kWideBlock + tid, d - 1u)];
-#pragma unroll
-        for (uint32_t u = 0; u < 8; ++u)
-          if (base + u * kWideBlock + tid < d) visit(v[u] & 0x7FFFFFFFu);
-      }
-    };
-    bool nonfinite = false;
-    each_key([&](uint32_t key) {
-      nonfinite |= key >= 0x7F800000u;
-      atomicAdd(&top_hist[key >> kSampleShift], 1u);
-    });
-    if (nonfinite) atomicOr(ws.status, CVLC_DEV_NONFINITE);
-    __syncthreads();
-    uint32_t h[kWalkBins], mine = 0;
+    const uint32_t share = (d + kWideBlock - 1u) / kWideBlock * kWave;
+    const uint32_t w_begin = min(tid / kWave * share, d), w_end = min(w_begin + share, d);
+    uint32_t h[kWalkBins], mine = 0, all, above;
 #pragma unroll
     for (uint32_t i = 0; i < kWalkBins; ++i) {
-      h[i] = top_hist[kSampleBins - 1 - kWalkBins * tid - i];
+      h[i] = ctl->hist_sample[kSampleBins - 1 - kWalkBins * tid - i];
       mine += h[i];
     }
-    uint32_t all;
-    const uint32_t above = block_excl_scan<kWideWaves>(mine, scan_tmp, &all);
+    if (tid == 0) s_bin = 0;
+    above = block_excl_scan<kWideWaves>(mine, scan_tmp, &all);
+    if (run >= p.k / 4u) find_sample_bin(h, above, 4u * p.sample_rank, &s_bin, &s_reached);
+    __syncthreads();
+    constexpr uint32_t kNonfiniteBin = 0x7F800000u >> kSampleShift;  // the first that only Inf and NaN lie in
+    for (uint32_t floor_bin = min(s_bin, kNonfiniteBin);; floor_bin = 0) {
+      auto count_top = [&](auto floored) {
+        visit_keys(bits, w_begin, w_end, [&](uint32_t, uint32_t key, bool valid) {
+          const uint32_t b = key >> kSampleShift;
+          if (valid && (!floored.value || b >= floor_bin)) atomicAdd(&top_hist[b], 1u);
+        });
+      };
+      if (floor_bin) count_top(std::true_type{}); else count_top(std::false_type{});
+      __syncthreads();
+      mine = 0;
+#pragma unroll
+      for (uint32_t i = 0; i < kWalkBins; ++i) {
+        h[i] = top_hist[kSampleBins - 1 - kWalkBins * tid - i];
+        mine += h[i];
+      }
+      above = block_excl_scan<kWideWaves>(mine, scan_tmp, &all);
+      if (all >= p.k || floor_bin == 0) break;  // uniform
+      __syncthreads();
+      for (uint32_t i = tid; i < kSampleBins; i += kWideBlock) top_hist[i] = 0;
+      __syncthreads();
+    }
+    if (tid < kSampleBins - kNonfiniteBin && top_hist[kNonfiniteBin + tid]) atomicOr(ws.status, CVLC_DEV_NONFINITE);
     find_sample_bin(h, above, p.k, &s_bin, &s_reached);  // 1 <= k <= d here: fewer than k were kept
     __syncthreads();
     const uint32_t anchor = s_bin;
-    const uint32_t entry = build_bin_map(ctl, p.k, anchor, s_reached, scan_tmp, [&](uint32_t b) { return top_hist[b]; });
-    uint32_t* map = incl;  // not yet in use
-    if (tid < kMapBins) map[tid] = entry;
-    __syncthreads();
-    each_key([&](uint32_t key) { atomicAdd(&hist[selection_bin(map, anchor, key)], 1u); });
+    build_bin_map(ctl, p.k, anchor, 1u, scan_tmp, [](uint32_t) { return 0u; });
+    if (tid < kMapBins && anchor + tid < kSampleBins) hist[kOctaves + tid] = top_hist[anchor + tid];
+    for (uint32_t b = anchor + kMapBins + tid; b < kSampleBins; b += kWideBlock) {
+      const uint32_t n = top_hist[b];
+      if (n) atomicAdd(&hist[kOctaves + kFineBins + (b >> (23u - kSampleShift))], n);
+    }
   }
   __syncthreads();
   const uint32_t top = kSelBins - 1 - 2u * tid;
@@ -1109,30 +1149,6 @@ __device__ __forceinline__ void find_digit(SelectShared& S, uint32_t rem) {
   __syncthreads();
 }
 
-// A wavefront's visit to the candidates begin .. end - 1 of the dense list: visit(number, key, valid), all lanes
-// together.  One workgroup has a CU's share of the bandwidth at best, so eight 16-byte loads a lane go out together.
-template <class Visit>
-__device__ __forceinline__ void visit_candidates(const uint32_t* __restrict__ val, uint32_t begin, uint32_t end, Visit visit) {
-  typedef uint32_t __attribute__((ext_vector_type(4), aligned(4))) Words4;
-  typedef const Words4 __attribute__((address_space(1))) * Words4Ptr;
-  constexpr uint32_t kDeep = 8, kStep = kDeep * 4u * kWave;
-  const uint32_t lane = lane_id();
-  uint32_t base = begin;
-  for (; base + kStep <= end; base += kStep) {
-    Words4 v[kDeep];
-#pragma unroll
-    for (uint32_t u = 0; u < kDeep; ++u) v[u] = *((Words4Ptr)(val + base) + u * kWave + lane);
-#pragma unroll
-    for (uint32_t u = 0; u < kDeep; ++u)
-#pragma unroll
-      for (uint32_t c = 0; c < 4u; ++c) visit(base + (u * kWave + lane) * 4u + c, v[u][c] & 0x7FFFFFFFu, true);
-  }
-  for (; base < end; base += kWave) {
-    const uint32_t i = base + lane;
-    visit(i, val[min(i, end - 1u)] & 0x7FFFFFFFu, i < end);
-  }
-}
-
 // Range of the keys that lie in a selection bin, into S.lo and S.hi.  Whole workgroup; ends with a barrier.
 __device__ __forceinline__ void bin_keys(SelectShared& S, const ClientCtl* ctl, uint32_t bin) {
   static_assert(kMapBins <= kSelectBlock, "one entry per thread");
@@ -1174,7 +1190,7 @@ __device__ __forceinline__ bool search_candidates(SelectShared& S, const ClientC
     if (count <= kSelectList) {
       if (tid == 0) S.n_few = 0;
       __syncthreads();
-      visit_candidates(val, w_begin, w_end, [&](uint32_t i, uint32_t key, bool valid) {
+      visit_keys(val, w_begin, w_end, [&](uint32_t i, uint32_t key, bool valid) {
         if (valid && key - lo <= hi - lo) {
           const uint32_t at = atomicAdd(&S.n_few, 1u);
           if (at < kSelectList) S.list[at] = member_of(i, key);  // always
@@ -1202,7 +1218,7 @@ __device__ __forceinline__ bool search_candidates(SelectShared& S, const ClientC
     const uint32_t likely = S.digit < n ? val[S.digit] & 0x7FFFFFFFu : 0xFFFFFFFFu;
     const uint32_t bits = 32u - (uint32_t)__builtin_clz(hi - lo), shift = bits > 10u ? bits - 10u : 0u;
     uint32_t larger = 0, equal = 0;
-    visit_candidates(val, w_begin, w_end, [&](uint32_t, uint32_t key, bool valid) {
+    visit_keys(val, w_begin, w_end, [&](uint32_t, uint32_t key, bool valid) {
       const uint64_t same = __ballot(valid && key == likely);
       const bool other = valid && key != likely && key - lo <= hi - lo;
       equal += (uint32_t)__popcll(same);
@@ -1249,7 +1265,7 @@ __device__ __forceinline__ bool search_candidates(SelectShared& S, const ClientC
     if (!counted) {
       const uint32_t b = min(begin + wave * part, end), e = min(b + part, end);
       uint32_t equal = 0;
-      visit_candidates(val, b, e, [&](uint32_t, uint32_t key, bool valid) {
+      visit_keys(val, b, e, [&](uint32_t, uint32_t key, bool valid) {
         equal += (uint32_t)__popcll(__ballot(valid && key == tau));
       });
       __syncthreads();  // the counts before have been read

@@ -343,6 +343,19 @@ def test_bins_that_hold_a_large_part_of_all_candidates(kind):
         check_encode([U], [orc.plan_manual(d, [12, 10, 8, 6, 6, 4, 1], counts)], 17, [4])
 
 
+def test_a_misjudged_sample_costs_one_pass_of_one_workgroup():
+    """Every coordinate is then a candidate and one workgroup counts them all, once; the vector's other pass, by
+    the whole device, is the measure (a factor of 50 here; 330 with two passes and an LDS atomic for every key)."""
+    d = 8_000_000
+    rng = np.random.default_rng(3)
+    U = (rng.standard_normal(d) * 1e-4).astype(np.float32)
+    plant_on_the_sampled_pieces(U, rng)
+    p = cv.plan_manual(d, [8, 4], [100_000, 140_000])
+    update = torch.from_numpy(U).to(DEV)
+    t = [encode_stage_us(update, p, stage) for stage in ("enc_filter", "enc_refilter")]
+    assert t[1] < 120 * t[0], t
+
+
 def test_a_class_of_equal_keys_is_cut_in_few_passes():
     """(A hundred times the time of the smooth vector before the passes were made to use the CU's bandwidth.)"""
     d = 8_000_000
