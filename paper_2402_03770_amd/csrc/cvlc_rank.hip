@@ -35,13 +35,16 @@
 // Large calls do not even need the second pass: a sample says in which level-1
 // bins the ranks can lie, give or take, and the first pass sets those bins' keys
 // aside while it counts.
-//   sample, guess   histogram of 4096 pieces of 256 bytes, and per rank the bins
-//                   within 4.5 standard deviations of its place in it
+//   sample, guess   histograms of 4096 to 12288 pieces of 256 bytes in sixteen interleaved
+//                   parts, and per rank the bins within 4.5 standard deviations
+//                   of its place in their sum; the parts tell how far a place
+//                   strays where the coordinates of a piece are alike
 //   stream      all keys: counts of key >> 18; keys of the guessed bins go to
 //               the wavefronts' lists
-//   walk<1>, pass<2>, walk<2>, pass<3>, walk<3>   as above, the passes reading
-//               the lists; a client with a rank outside the guessed bins (the
-//               walk knows, from the exact counts) is read from its vector
+//   pass<2>, walk<2>, pass<3>, walk<3>   as above, the passes reading the lists, the
+//               first after the level-1 walk; for a client with a rank outside the
+//               guessed bins (known then, from the exact counts) collect
+//               writes the lists anew
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -217,50 +220,6 @@ __device__ __forceinline__ void list_keys(const KeyLists& kl, Visit visit) {
   }
 }
 
-template <int LEVEL, bool LISTS>
-__global__ __launch_bounds__(kRankBlock) void rank_pass_kernel(const float* const* __restrict__ updates,
-                                                               RankCtl* __restrict__ ctls, uint32_t d, KeyLists kl) {
-  __shared__ uint32_t hist[kRanksMax * kSubBins];
-  __shared__ alignas(16) uint8_t first_cls[kTopBins];
-  __shared__ uint32_t cls_prefix[kRanksMax + 1];
-  RankCtl* ctl = ctls + blockIdx.y;
-  const uint32_t n_cls = ctl->n_cls;
-  for (uint32_t i = threadIdx.x; i < n_cls * kSubBins; i += kRankBlock) hist[i] = 0;
-  for (uint32_t i = threadIdx.x; i < kTopBins / 4u; i += kRankBlock)
-    reinterpret_cast<uint32_t*>(first_cls)[i] = 0xFFFFFFFFu;
-  if (threadIdx.x <= kRanksMax) cls_prefix[threadIdx.x] = threadIdx.x < n_cls ? ctl->cls_prefix[threadIdx.x] : 0xFFFFFFFFu;
-  __syncthreads();
-  if (threadIdx.x < n_cls) {
-    const uint32_t c = threadIdx.x;
-    const uint32_t bin = LEVEL == 2 ? cls_prefix[c] : cls_prefix[c] >> kSubBits;
-    const uint32_t before = c == 0 ? 0xFFFFFFFFu : (LEVEL == 2 ? cls_prefix[c - 1] : cls_prefix[c - 1] >> kSubBits);
-    if (bin != before) first_cls[bin] = (uint8_t)c;
-  }
-  __syncthreads();
-  auto visit = [&](uint32_t key) {
-    const uint32_t bin = key >> kTopShift;
-    uint32_t c = first_cls[bin];
-    if (c == kNoClass) return;
-    if (LEVEL == 2) {
-      atomicAdd(&hist[c * kSubBins + ((key >> kSubBits) & (kSubBins - 1u))], 1u);
-    } else {
-      const uint32_t mine = key >> kSubBits;
-      // the entry after the last class never starts with a level-1 bin, so the walk ends
-      for (uint32_t p = cls_prefix[c]; (p >> kSubBits) == bin; p = cls_prefix[++c])
-        if (p == mine) {
-          atomicAdd(&hist[c * kSubBins + (key & (kSubBins - 1u))], 1u);
-          break;
-        }
-    }
-  };
-  if (LISTS && !ctl->missed) list_keys(kl, visit); else stream_keys(updates[blockIdx.y], d, visit);
-  __syncthreads();
-  for (uint32_t i = threadIdx.x; i < n_cls * kSubBins; i += kRankBlock) {
-    const uint32_t h = hist[i];
-    if (h) atomicAdd(&ctl->sub[i], h);
-  }
-}
-
 // ------------------------------------------------------------------ the walks
 // Ranks ascend, so their prefixes never increase: classes are runs of equal
 // prefixes.  Called by the first 32 threads of a workgroup with the new prefix
@@ -320,21 +279,88 @@ __device__ __forceinline__ void level1_walk(const RankCtl* ctl, const RankSet& r
   }
 }
 
-// (The collecting pass does this walk itself.)  guessed: the lists hold the keys of the guessed bins; see whether all ranks lie in those.
-__global__ __launch_bounds__(kRankBlock) void rank_walk1_kernel(RankCtl* __restrict__ ctls, RankSet ranks, bool guessed) {
+// WALK: the keys come from the lists of the guessed bins, and every workgroup does the level-1 walk for itself (a launch of
+// its own for it takes 11 us), workgroup 0 of a client leaves its result, and whether a rank lies outside
+// the guessed bins, where the later kernels look for them; a client whose guess missed has its level 2 counted by the
+// collecting pass.
+template <int LEVEL, bool LISTS, bool WALK>
+__global__ __launch_bounds__(kRankBlock) void rank_pass_kernel(const float* const* __restrict__ updates,
+                                                               RankCtl* __restrict__ ctls, uint32_t d, KeyLists kl,
+                                                               RankSet ranks) {
+  __shared__ uint32_t hist[kRanksMax * kSubBins];
+  __shared__ alignas(16) uint8_t first_cls[kTopBins];
+  __shared__ uint32_t cls_prefix[kRanksMax + 1];
+  __shared__ uint32_t scan_tmp[kRankWaves], s_prefix[kRanksMax], s_rem[kRanksMax], s_n_cls, s_missed;  // WALK
+  RankCtl* ctl = ctls + blockIdx.y;
+  uint32_t n_cls;
+  if constexpr (WALK) {
+    if (threadIdx.x <= kRanksMax) cls_prefix[threadIdx.x] = 0xFFFFFFFFu;
+    level1_walk(ctl, ranks, scan_tmp, s_prefix, s_rem);
+    __syncthreads();
+    if (threadIdx.x < kWave) {
+      const uint32_t bin = threadIdx.x < ranks.n ? s_prefix[threadIdx.x] : 0u;
+      const bool outside = threadIdx.x < ranks.n && !((ctl->guess[bin >> 3] >> (bin & 7u)) & 1u);
+      const uint32_t missed = __ballot(outside) ? 1u : 0u;
+      uint32_t c;
+      bool opens;
+      const uint32_t n = write_classes(blockIdx.x == 0 ? ctl : nullptr, s_prefix, s_rem, ranks.n, &c, &opens);
+      if (opens) cls_prefix[c] = bin;
+      if (threadIdx.x == 0) {
+        s_n_cls = n;
+        s_missed = missed;
+        if (blockIdx.x == 0) ctl->missed = missed;
+      }
+    }
+    __syncthreads();
+    if (s_missed) return;  // uniform
+    n_cls = s_n_cls;
+  } else {
+    n_cls = ctl->n_cls;
+    if (threadIdx.x <= kRanksMax) cls_prefix[threadIdx.x] = threadIdx.x < n_cls ? ctl->cls_prefix[threadIdx.x] : 0xFFFFFFFFu;
+  }
+  for (uint32_t i = threadIdx.x; i < n_cls * kSubBins; i += kRankBlock) hist[i] = 0;
+  for (uint32_t i = threadIdx.x; i < kTopBins / 4u; i += kRankBlock)
+    reinterpret_cast<uint32_t*>(first_cls)[i] = 0xFFFFFFFFu;
+  __syncthreads();
+  if (threadIdx.x < n_cls) {
+    const uint32_t c = threadIdx.x;
+    const uint32_t bin = LEVEL == 2 ? cls_prefix[c] : cls_prefix[c] >> kSubBits;
+    const uint32_t before = c == 0 ? 0xFFFFFFFFu : (LEVEL == 2 ? cls_prefix[c - 1] : cls_prefix[c - 1] >> kSubBits);
+    if (bin != before) first_cls[bin] = (uint8_t)c;
+  }
+  __syncthreads();
+  auto visit = [&](uint32_t key) {
+    const uint32_t bin = key >> kTopShift;
+    uint32_t c = first_cls[bin];
+    if (c == kNoClass) return;
+    if (LEVEL == 2) {
+      atomicAdd(&hist[c * kSubBins + ((key >> kSubBits) & (kSubBins - 1u))], 1u);
+    } else {
+      const uint32_t mine = key >> kSubBits;
+      // the entry after the last class never starts with a level-1 bin, so the walk ends
+      for (uint32_t p = cls_prefix[c]; (p >> kSubBits) == bin; p = cls_prefix[++c])
+        if (p == mine) {
+          atomicAdd(&hist[c * kSubBins + (key & (kSubBins - 1u))], 1u);
+          break;
+        }
+    }
+  };
+  if (LISTS) list_keys(kl, visit); else stream_keys(updates[blockIdx.y], d, visit);
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < n_cls * kSubBins; i += kRankBlock) {
+    const uint32_t h = hist[i];
+    if (h) atomicAdd(&ctl->sub[i], h);
+  }
+}
+
+// (The three-pass path; with room for the key lists the passes behind do this walk themselves.)
+__global__ __launch_bounds__(kRankBlock) void rank_walk1_kernel(RankCtl* __restrict__ ctls, RankSet ranks) {
   __shared__ uint32_t scan_tmp[kRankWaves];
   __shared__ uint32_t s_prefix[kRanksMax], s_rem[kRanksMax];
   RankCtl* ctl = ctls + blockIdx.x;
   level1_walk(ctl, ranks, scan_tmp, s_prefix, s_rem);
   __syncthreads();
-  if (threadIdx.x < kWave) {
-    write_classes(ctl, s_prefix, s_rem, ranks.n);
-    if (guessed) {
-      const uint32_t bin = threadIdx.x < ranks.n ? s_prefix[threadIdx.x] : 0u;
-      const bool outside = threadIdx.x < ranks.n && !((ctl->guess[bin >> 3] >> (bin & 7u)) & 1u);
-      if (__ballot(outside) && threadIdx.x == 0) ctl->missed = 1u;
-    }
-  }
+  if (threadIdx.x < kWave) write_classes(ctl, s_prefix, s_rem, ranks.n);
 }
 
 // Ordinary least squares of ln(magnitude) on ln(rank) over the keys (in LDS) of the ranks: the logarithms
@@ -427,10 +453,12 @@ constexpr uint32_t kCollectStage = 512;  // keys a wavefront stages in LDS; rows
 // more), workgroup 0 of a client also leaves the result where the later kernels look for it.  The keys it
 // collects are counted on their next 9 bits as they pass (level 2, per class, 64 KB of LDS).  With its 104 KB
 // of LDS one workgroup has a CU to itself, which suits a streaming pass (241 against 252 us with two).
+// guessed: only the clients whose guess missed.
 __global__ __launch_bounds__(kRankBlock) void rank_collect_kernel(const float* const* __restrict__ updates,
                                                                   RankCtl* __restrict__ ctls, RankSet ranks,
                                                                   uint32_t d, uint32_t* __restrict__ lists,
-                                                                  uint32_t* __restrict__ list_cnt, uint32_t wave_cap) {
+                                                                  uint32_t* __restrict__ list_cnt, uint32_t wave_cap,
+                                                                  bool guessed) {
   __shared__ alignas(16) uint8_t first_cls[kTopBins];
   __shared__ uint32_t stage[kRankWaves][kCollectStage];
   __shared__ uint32_t s_fill[kRankWaves];  // keys a wavefront has staged
@@ -439,6 +467,7 @@ __global__ __launch_bounds__(kRankBlock) void rank_collect_kernel(const float* c
   __shared__ uint32_t s_prefix[kRanksMax], s_rem[kRanksMax];
   __shared__ uint32_t s_n_cls;
   RankCtl* ctl = ctls + blockIdx.y;
+  if (guessed && !ctl->missed) return;  // uniform
   for (uint32_t i = threadIdx.x; i < kTopBins / 4u; i += kRankBlock)
     reinterpret_cast<uint32_t*>(first_cls)[i] = 0xFFFFFFFFu;
   level1_walk(ctl, ranks, scan_tmp, s_prefix, s_rem);
@@ -543,63 +572,148 @@ __global__ __launch_bounds__(kRankBlock) void rank_collect_kernel(const float* c
 
 // ------------------------------------------------------------------ one pass: sample, guess, stream
 constexpr uint32_t kPieceQuads = 16;       // a piece of the sample: 256 bytes
-constexpr uint32_t kSamplePieces = 4096;
+constexpr uint32_t kSamplePiecesMin = 4096, kSamplePiecesMax = 12288;  // by the length, see sample_pieces
 constexpr uint32_t kSampleWgs = 16;        // workgroups per client
 
-// Counts go to `sub`, which the guess leaves cleared.
-__global__ __launch_bounds__(256) void rank_sample_kernel(const float* const* __restrict__ updates, RankCtl* __restrict__ ctls,
-                                                          uint32_t n_pieces) {
+// Workgroup g takes pieces g, g + 16, ...: its counts are those of an evenly spread sample of its own.  The sum of the
+// parts goes to `sub`, which the guess leaves cleared, the parts' counts of key >> 21 to parts, 16 a client and bin.
+constexpr uint32_t kPartShift = 21, kPartBins = 1u << (31u - kPartShift), kPartStep = kTopBins / kPartBins;
+static_assert(kSamplePiecesMax / kSampleWgs * kPieceQuads * 4u < (1u << 16), "a part's counts and their sums fit 16 bits");
+static_assert(kTopBins <= kRanksMax * kSubBins, "the sample's counts fit where the second level's will stand");
+// The more pieces, the nearer the margins (32 x 11.2 M: lists of 6 % of the keys instead of 8, of 9 % for vectors of rows
+// instead of 17); an eighth of the vector is read at most.
+constexpr uint32_t kSampleDeep = 4, kSampleTurn = kRankBlock * kSampleDeep;  // float4 a workgroup asks for together
+uint32_t sample_pieces(uint32_t d) {
+  const uint32_t eighth = d / (4u * kPieceQuads * 8u) / kSampleTurn * kSampleTurn;
+  return std::min(kSamplePiecesMax, std::max(kSamplePiecesMin, eighth));
+}
+static_assert(kSampleWgs == kPieceQuads && kSamplePiecesMin % kSampleTurn == 0 && kSamplePiecesMax % kSampleTurn == 0, "whole turns");
+
+__global__ __launch_bounds__(kRankBlock) void rank_sample_kernel(const float* const* __restrict__ updates, RankCtl* __restrict__ ctls,
+                                                                 uint16_t* __restrict__ parts, uint32_t n_pieces, uint32_t sampled) {
   __shared__ uint32_t hist[kTopBins];
-  for (uint32_t i = threadIdx.x; i < kTopBins; i += 256u) hist[i] = 0;
+  for (uint32_t i = threadIdx.x; i < kTopBins; i += kRankBlock) hist[i] = 0;
   __syncthreads();
   GlobalFloat4Ptr src = (GlobalFloat4Ptr)updates[blockIdx.y];
-  constexpr uint32_t kQuads = kSamplePieces * kPieceQuads / kSampleWgs, kTurn = 256u * 8u;
-  static_assert(kQuads % kTurn == 0, "whole turns");
-  for (uint32_t base = blockIdx.x * kQuads; base < (blockIdx.x + 1u) * kQuads; base += kTurn) {
-    Float4V v[8];
+  const uint32_t quads = sampled * kPieceQuads / kSampleWgs;
+  for (uint32_t base = 0; base < quads; base += kSampleTurn) {
+    Float4V v[kSampleDeep];
 #pragma unroll
-    for (uint32_t u = 0; u < 8; ++u) {
-      const uint32_t q = base + u * 256u + threadIdx.x;
-      const uint64_t piece = (uint64_t)(q / kPieceQuads) * n_pieces / kSamplePieces;  // evenly spread
+    for (uint32_t u = 0; u < kSampleDeep; ++u) {
+      const uint32_t q = base + u * kRankBlock + threadIdx.x;
+      const uint64_t piece = (uint64_t)(q / kPieceQuads * kSampleWgs + blockIdx.x) * n_pieces / sampled;  // evenly spread
       v[u] = src[piece * kPieceQuads + q % kPieceQuads];
     }
 #pragma unroll
-    for (uint32_t u = 0; u < 8; ++u)
+    for (uint32_t u = 0; u < kSampleDeep; ++u)
 #pragma unroll
       for (int c = 0; c < 4; ++c) atomicAdd(&hist[(__float_as_uint(v[u][c]) & 0x7FFFFFFFu) >> kTopShift], 1u);
   }
   __syncthreads();
-  for (uint32_t i = threadIdx.x; i < kTopBins; i += 256u) {
+  for (uint32_t i = threadIdx.x; i < kTopBins; i += kRankBlock) {
     const uint32_t h = hist[i];
     if (h) atomicAdd(&ctls[blockIdx.y].sub[i], h);
   }
+  static_assert(kPartBins == kRankBlock, "one bin of a part per thread");
+  uint32_t sum = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < kPartStep; ++i) sum += hist[threadIdx.x * kPartStep + i];
+  parts[((size_t)blockIdx.y * kPartBins + threadIdx.x) * kSampleWgs + blockIdx.x] = (uint16_t)sum;
 }
-static_assert(kTopBins <= kRanksMax * kSubBins, "the sample's counts fit where the second level's will stand");
 
-// A rank's place in the sample is binomial: bins that hold a place within 4.5 standard deviations (and three more,
-// for the ends) of the expected one are guessed.  Wrong only costs time.
-__global__ __launch_bounds__(kRankBlock) void rank_guess_kernel(RankCtl* __restrict__ ctls, RankSet ranks, uint32_t d) {
-  __shared__ uint32_t scan_tmp[kRankWaves];
-  __shared__ float s_lo[kRanksMax], s_hi[kRanksMax];
-  RankCtl* ctl = ctls + blockIdx.x;
-  constexpr uint32_t per = kTopBins / kRankBlock;
+// A rank's place in the sample of n coordinates is binomial if they are drawn one by one: bins that hold a place within
+// 4.5 standard deviations (and three more, for the ends) of the expected one are guessed.  They are drawn in pieces of
+// 64 neighbours, though, and where neighbours are alike (a scale of its own per row, rows that are zero) a place
+// strays up to eight times as far.  How far is measured: the variance of the sixteen parts' places over the
+// binomial one, averaged over the bins of key >> 21 where that is not small.  (Binomial alone missed a rank in five of
+// six vectors of rows of 64, and the call took 1.8 to 3 times as long; with the factor none of 66, the lists
+// half as long again.)  Where the margins, beyond the bins of the expected places themselves, hold more than a seventh
+// of the sample, the lists would cost more than the second pass they save: nothing is guessed.
+// Wrong only costs time: the second pass.
+__global__ __launch_bounds__(kRankBlock) void rank_guess_kernel(RankCtl* __restrict__ ctls, const uint16_t* __restrict__ parts,
+                                                                RankSet ranks, uint32_t d, uint32_t sampled) {
+  constexpr uint32_t per = kTopBins / kRankBlock, kPairs = kSampleWgs / 2u;
+  const float size = (float)(sampled * kPieceQuads * 4u);
   static_assert(per == 8u, "a byte of the bit set per thread");
+  __shared__ uint32_t s_pair[kPairs][kRankWaves], scan_tmp[kRankWaves], s_extra[kRankWaves];
+  __shared__ float s_factor[kRankWaves], s_bins[kRankWaves], s_place[kRanksMax], s_spread[kRanksMax], s_margin[kRanksMax];
+  RankCtl* ctl = ctls + blockIdx.x;
+  const uint32_t lane = lane_id(), wave = wave_id();
   const uint32_t first = kTopBins - per * (threadIdx.x + 1u);  // thread 0 owns the largest keys
   uint32_t h[per], mine = 0;
 #pragma unroll
+  for (uint32_t i = 0; i < per; ++i) h[i] = ctl->sub[first + i];
+  const uint4* __restrict__ part = reinterpret_cast<const uint4*>(parts + ((size_t)blockIdx.x * kPartBins + (kPartBins - 1u - threadIdx.x)) * kSampleWgs);
+  const uint4 p0 = part[0], p1 = part[1];
+  if (threadIdx.x < ranks.n) {
+    const double p = (double)ranks.rank[threadIdx.x] / (double)d;
+    s_place[threadIdx.x] = (float)((double)size * p);
+    s_spread[threadIdx.x] = (float)((double)size * p * (1.0 - p));
+  }
+#pragma unroll
   for (uint32_t i = 0; i < per; ++i) {
-    h[i] = ctl->sub[first + i];
     ctl->sub[first + i] = 0;
     mine += h[i];
   }
-  if (threadIdx.x < ranks.n) {
-    const double size = (double)kSamplePieces * kPieceQuads * 4.0, p = (double)ranks.rank[threadIdx.x] / (double)d;
-    const double margin = 4.5 * sqrt(size * p * (1.0 - p)) + 3.0;
-    s_lo[threadIdx.x] = (float)(size * p - margin);
-    s_hi[threadIdx.x] = (float)(size * p + margin);
-  }
   uint32_t total;
-  uint32_t above = block_excl_scan<kRankWaves>(mine, scan_tmp, &total);  // (its barriers also publish s_lo and s_hi)
+  uint32_t above = block_excl_scan<kRankWaves>(mine, scan_tmp, &total);
+  // the parts' places at the lower end of the thread's bin, two to a word
+  uint32_t at[kPairs] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
+#pragma unroll
+  for (uint32_t j = 0; j < kPairs; ++j) {
+    at[j] = wave_incl_scan_u32(at[j]);  // no carry between the halves
+    if (lane == kWave - 1u) s_pair[j][wave] = at[j];
+  }
+  __syncthreads();
+  if (threadIdx.x < kPairs * kRankWaves) {  // sixteen lanes per pair: the sums of the wavefronts before
+    uint32_t* word = &s_pair[0][0] + threadIdx.x;
+    const uint32_t own = *word;
+    uint32_t sum = own;
+#pragma unroll
+    for (int o = 1; o < (int)kRankWaves; o <<= 1) {
+      const uint32_t t = (uint32_t)__shfl_up((int)sum, o, (int)kRankWaves);
+      if (threadIdx.x % kRankWaves >= (uint32_t)o) sum += t;
+    }
+    *word = sum - own;
+  }
+  __syncthreads();
+  uint32_t place = 0;
+#pragma unroll
+  for (uint32_t j = 0; j < kPairs; ++j) {
+    at[j] += s_pair[j][wave];
+    place += (at[j] & 0xFFFFu) + (at[j] >> 16);
+  }
+  const float mean = (float)place * (1.0f / kSampleWgs), binomial = (float)place * (1.0f - (float)place / size);
+  float squares = 0.0f;
+#pragma unroll
+  for (uint32_t j = 0; j < kPairs; ++j) {
+    const float a = (float)(at[j] & 0xFFFFu) - mean, b = (float)(at[j] >> 16) - mean;
+    squares += a * a + b * b;
+  }
+  const bool counts = binomial > 1024.0f;
+  float factor = counts ? fminf(fmaxf(squares * ((float)kSampleWgs / (kSampleWgs - 1.0f)) / binomial, 1.0f), (float)(4u * kPieceQuads)) : 0.0f;
+  float bins = counts ? 1.0f : 0.0f;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    factor += __shfl_xor(factor, o, kWave);
+    bins += __shfl_xor(bins, o, kWave);
+  }
+  if (lane == 0) {
+    s_factor[wave] = factor;
+    s_bins[wave] = bins;
+  }
+  __syncthreads();
+  factor = bins = 0.0f;
+#pragma unroll
+  for (uint32_t w = 0; w < kRankWaves; ++w) {
+    factor += s_factor[w];
+    bins += s_bins[w];
+  }
+  if (threadIdx.x < ranks.n) {
+    factor = bins > 0.0f ? factor / bins : 1.0f;
+    s_margin[threadIdx.x] = 4.5f * sqrtf(factor * s_spread[threadIdx.x]) + 3.0f * factor;
+  }
+  __syncthreads();
   // bin i holds the sample's places from[i] .. to[i], and the borders of both sides: an empty bin lies between two
   float from[per], to[per];
 #pragma unroll
@@ -608,19 +722,33 @@ __global__ __launch_bounds__(kRankBlock) void rank_guess_kernel(RankCtl* __restr
     above += h[i];
     to[i] = (float)(above + 1u);
   }
-  uint32_t bits = 0;
-  for (uint32_t j = 0; j < ranks.n; ++j) {
-    const float lo = s_lo[j], hi = s_hi[j];
+  uint32_t bits = 0, expected = 0;
+  for (uint32_t j = 0; j < ranks.n; ++j) {  // uniform
+    const float middle = s_place[j], margin = s_margin[j];
+    const float lo = middle - margin, hi = middle + margin;
     if (from[per - 1u] > hi || to[0] < lo) continue;
 #pragma unroll
-    for (uint32_t i = 0; i < per; ++i) bits |= (from[i] <= hi && to[i] >= lo ? 1u : 0u) << i;
+    for (uint32_t i = 0; i < per; ++i) {
+      bits |= (from[i] <= hi && to[i] >= lo ? 1u : 0u) << i;
+      expected |= (from[i] <= middle && to[i] >= middle ? 1u : 0u) << i;
+    }
   }
-  ctl->guess[first / 8u] = (uint8_t)bits;
+  uint32_t extra = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < per; ++i)
+    if (((bits & ~expected) >> i) & 1u) extra += h[i];
+  extra = wave_sum_u32(extra);
+  if (lane == 0) s_extra[wave] = extra;
+  __syncthreads();
+  extra = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < kRankWaves; ++w) extra += s_extra[w];
+  ctl->guess[first / 8u] = (uint8_t)((float)extra > size / 7.0f ? 0u : bits);
 }
 
 // Counts all keys (level 1) and sets the keys of the guessed bins aside, in rows of 64 through LDS.  Bound by HBM:
-// the vectors once, and the writes mixed into them (8 % of the keys).  32 vectors of 11.2 M: 302 us where the counting
-// pass and the collecting pass took 223 + 272; the call 512 -> 396 us.
+// the vectors once, and the writes mixed into them (6 % of the keys).  32 vectors of 11.2 M: 290 us where the counting
+// pass and the collecting pass took 223 + 272.
 __global__ __launch_bounds__(kRankBlock) void rank_stream_kernel(const float* const* __restrict__ updates,
                                                                  RankCtl* __restrict__ ctls, uint32_t d,
                                                                  uint32_t* __restrict__ lists,
@@ -778,13 +906,16 @@ int cvlc_fit_alpha(uint32_t n, const float* const* d_updates, uint32_t d, double
   }
   const dim3 pass_grid(pass_blocks_per_client(d, n, 2u), n);
   KeyLists kl = {nullptr, nullptr, 0u, 0u};
-  // One pass fewer over the vectors for three small launches and longer lists: level at 77 M coordinates (3 vectors of
-  // 25.6 M: 208 us both ways), ahead at 90 M (8 of 11.2 M: 173 -> 157 us); for vectors that have the sample's pieces
-  // several times over.
-  const bool one_pass = L.wave_cap && (uint64_t)n * d >= (5u << 24) && d >= (1u << 20);
+  // One pass fewer over the vectors for three small launches and longer lists, which are longest for vectors of rows with
+  // a scale of their own.  4 vectors of 25.6 M: 222 -> 217 us, of rows 211 -> 263; 12 of 11.2 M: 315 -> 254, of rows 290 ->
+  // 275; 32 of 11.2 M: 540 -> 431, of rows 528 -> 462.  For vectors that have the sample's pieces several times over.
+  const bool one_pass = L.wave_cap && (uint64_t)n * d >= (7u << 24) && d >= (1u << 20);
   if (one_pass) {
-    hipLaunchKernelGGL(rank_sample_kernel, dim3(kSampleWgs, n), dim3(256), 0, stream, ptrs, ctls, d / (4u * kPieceQuads));
-    hipLaunchKernelGGL(rank_guess_kernel, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks, d);
+    // the parts' counts lie where the lists will: 32 KB a client of at least 4 MB
+    uint16_t* parts = reinterpret_cast<uint16_t*>(base + L.lists);
+    const uint32_t sampled = sample_pieces(d);
+    hipLaunchKernelGGL(rank_sample_kernel, dim3(kSampleWgs, n), dim3(kRankBlock), 0, stream, ptrs, ctls, parts, d / (4u * kPieceQuads), sampled);
+    hipLaunchKernelGGL(rank_guess_kernel, dim3(n), dim3(kRankBlock), 0, stream, ctls, parts, ranks, d, sampled);
   } else {
     hipLaunchKernelGGL(rank_hist1_kernel, pass_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, status);
   }
@@ -800,23 +931,21 @@ int cvlc_fit_alpha(uint32_t n, const float* const* d_updates, uint32_t d, double
     if (one_pass) {
       hipLaunchKernelGGL(rank_stream_kernel, dim3(L.blocks, n), dim3(kRankBlock), 0, stream, ptrs, ctls, d, lists, list_cnt,
                          L.wave_cap, status);
-      hipLaunchKernelGGL(rank_walk1_kernel, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks, true);
-      hipLaunchKernelGGL((rank_pass_kernel<2, true>), list_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl);
-    } else {
-      hipLaunchKernelGGL(rank_collect_kernel, dim3(L.blocks, n), dim3(kRankBlock), 0, stream, ptrs, ctls, ranks, d, lists,
-                         list_cnt, L.wave_cap);
+      hipLaunchKernelGGL((rank_pass_kernel<2, true, true>), list_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl, ranks);
     }
+    hipLaunchKernelGGL(rank_collect_kernel, dim3(L.blocks, n), dim3(kRankBlock), 0, stream, ptrs, ctls, ranks, d, lists,
+                       list_cnt, L.wave_cap, one_pass);
     hipLaunchKernelGGL(rank_walk_kernel<2>, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks, (uint32_t*)nullptr,
                        (double*)nullptr);
-    hipLaunchKernelGGL((rank_pass_kernel<3, true>), list_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl);
+    hipLaunchKernelGGL((rank_pass_kernel<3, true, false>), list_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl, ranks);
     hipLaunchKernelGGL(rank_walk_kernel<3>, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks, d_keys_out, d_alpha_out);
     return hip_check(hipGetLastError());
   }
-  hipLaunchKernelGGL(rank_walk1_kernel, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks, false);
-  hipLaunchKernelGGL((rank_pass_kernel<2, false>), pass_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl);
+  hipLaunchKernelGGL(rank_walk1_kernel, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks);
+  hipLaunchKernelGGL((rank_pass_kernel<2, false, false>), pass_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl, ranks);
   hipLaunchKernelGGL(rank_walk_kernel<2>, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks, (uint32_t*)nullptr,
                      (double*)nullptr);
-  hipLaunchKernelGGL((rank_pass_kernel<3, false>), pass_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl);
+  hipLaunchKernelGGL((rank_pass_kernel<3, false, false>), pass_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl, ranks);
   hipLaunchKernelGGL(rank_walk_kernel<3>, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks, d_keys_out, d_alpha_out);
   return hip_check(hipGetLastError());
 }

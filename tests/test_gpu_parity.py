@@ -1037,23 +1037,55 @@ def test_fit_alpha_more_clients_than_one_upload_holds():
 
 @pytest.mark.parametrize("d", [2_100_003, 2_097_152])
 def test_fit_alpha_in_one_pass(d):
-    """From 5 x 2^24 coordinates on the level-1 bins of the ranks are guessed from a sample: ordinary vectors, tied ones, and
+    """From 7 x 2^24 coordinates on the level-1 bins of the ranks are guessed from a sample: ordinary vectors, tied ones, and
     one whose sampled pieces hold what the rest does not, so that the guess is wrong and the vector is read again."""
     rng = np.random.default_rng(d)
     planted = (rng.standard_normal(d) * 1e-4).astype(np.float32)
     plant_on_the_sampled_pieces(planted, rng)
     tied = (2.0 ** rng.integers(-3, 4, d)).astype(np.float32)
     host = [planted, syn.update_vector(3, 1, d=d), tied, (rng.standard_normal(d) * 1e-3).astype(np.float32)]
-    n = 40
-    assert n * d >= 5 << 24
+    n = 56
+    assert n * d >= 7 << 24
     refs = [(orc.fit_points(u)[1], orc.fit_alpha(u)) for u in host]
-    alpha, keys, status = gpu_fit_alpha([host[c % 4] for c in range(n)])
-    assert status == 0
+    dev = [torch.from_numpy(u).to(DEV) for u in host]
+    ws = cv.new_workspace(cv.fit_workspace_bytes_for(n, d), DEV)
+    alpha_dev = torch.zeros(n, dtype=torch.float64, device=DEV)
+    keys_dev = torch.zeros((n, cv.FIT_RANKS_MAX), dtype=torch.int32, device=DEV)
+    cv.fit_alpha([dev[c % 4] for c in range(n)], alpha_dev, ws, keys_dev)
+    assert cv.device_status(ws) == 0
+    alpha, keys = alpha_dev.cpu().numpy(), keys_dev.cpu().numpy().view(np.uint32)
+    # A client's state lies behind the status word's 256 bytes and ends in {missed, 8 bytes, 1024 bytes of guessed bins}.
+    size = (cv.fit_workspace_bytes(512) - cv.fit_workspace_bytes(256)) // 256 - 8
+    state = ws[256:256 + n * size].view(n, size).cpu().numpy()
+    guessed, missed = state[:, -1024:].any(axis=1), state[:, -1036:-1032].any(axis=1)
+    assert guessed.all() and missed[0::4].all() and not missed[1::2].any()
     for c in range(n):
         ref_keys, ref_alpha = refs[c % 4]
         assert keys[c, : ref_keys.size].tolist() == ref_keys.tolist(), c
         assert not keys[c, ref_keys.size:].any()
         assert alpha[c] == pytest.approx(ref_alpha, rel=1e-11, abs=1e-11), c
+
+
+def test_fit_alpha_of_vectors_of_rows():
+    """Rows of 64 with a scale of their own: the sample's pieces are as alike as rows are, the margins of the guess take
+    that in, and the call costs a little more than for coordinates drawn one by one (twice as much when rows were
+    missed as a rule and their vectors read twice more by few workgroups)."""
+    n, d = 12, 11_200_000
+    gen = torch.Generator(device=DEV).manual_seed(9)
+    plain = [torch.randn(d, device=DEV, generator=gen) for _ in range(n)]
+    rows = [(u.view(-1, 64) * torch.exp(torch.randn(d // 64, 1, device=DEV, generator=gen))).view(-1) for u in plain]
+    ws = cv.new_workspace(cv.fit_workspace_bytes_for(n, d), DEV)
+    alpha = torch.zeros(n, dtype=torch.float64, device=DEV)
+    best = []
+    for updates in (plain, rows):
+        times = []
+        for _ in range(7):
+            cv.profile_start(["fit_alpha"])
+            cv.fit_alpha(updates, alpha, ws)
+            times.append(cv.profile_stop()["fit_alpha"][0])
+        best.append(min(times))
+    assert best[1] < 1.35 * best[0], best
+    assert alpha[3].item() == pytest.approx(orc.fit_alpha(rows[3].cpu().numpy()), rel=1e-11, abs=1e-11)
 
 
 def test_fit_alpha_flags_non_finite_input():
