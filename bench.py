@@ -273,7 +273,7 @@ def main() -> int:
                      "launch_ms": filter_ms},
     }
     result["fit_alpha"] = {"ms": t_fit * 1e3, "g_coords_s": n * d / t_fit / 1e9, "algorithmic_gb": 4.0 * n * d / 1e9,
-                           "hbm_frac": 4.0 * n * d / t_fit / 1e9 / HBM_PEAK_GBS, "passes_over_input": 1 if n * d >= 5 << 24 else 2,
+                           "hbm_frac": 4.0 * n * d / t_fit / 1e9 / HBM_PEAK_GBS, "passes_over_input": 1 if n * d >= 7 << 24 and d >= 1 << 20 else 2,
                            "in_step": False,
                            # a round whose planner refits the exponent first: the fit, then the step
                            "step_plus_fit_ms": (t_step + t_fit) * 1e3,
