@@ -102,6 +102,9 @@ uint32_t cvlc_position_bits(uint32_t d);
  *   both NULL: Algorithm 1 -- enumerate k, sweep the atomic operation of Eq. (6)
  *       over adjacent groups, pick the plan minimising gamma of Eq. (5) for the
  *       power-law exponent alpha of Definition 1 (alpha < 0).
+ *       It searches on the caller's thread and up to 15 helpers, which end
+ *       before it returns; helpers of all calls of a process together are at
+ *       most one fewer than the CPUs the process may use.
  * The stream layout charges a 256-bit global header and H = 128 bits per group.
  * Returns CVLC_ERR_BUDGET when the budget cannot hold one update per group. */
 int cvlc_plan(uint32_t d, uint64_t budget_bits, uint32_t n_coded, const uint32_t* code_len,

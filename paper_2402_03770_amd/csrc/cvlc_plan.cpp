@@ -6,6 +6,9 @@
 // paper's equal packet size, scaled up to a run of packets), pays H = 128 bits
 // for its header and (s + y_r) bits per update; the stream adds one 256-bit
 // global header.
+#include <sched.h>
+
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstring>
@@ -225,6 +228,35 @@ class Algorithm1 {
   double y_min_;
 };
 
+// CPUs the calling thread may run on.
+int cpus() {
+  cpu_set_t set;
+  if (sched_getaffinity(0, sizeof set, &set) == 0) return CPU_COUNT(&set);
+  return (int)std::thread::hardware_concurrency();  // more of them than the set can name
+}
+
+// Helper threads of all planner calls that run at the same time: as many as there are CPUs left besides the caller's,
+// however many threads plan for their clients at once.
+class Helpers {
+ public:
+  explicit Helpers(int most) {
+    const int room = cpus() - 1;
+    int running = running_.load();
+    do {
+      taken_ = std::max(0, std::min(most, room - running));
+    } while (taken_ && !running_.compare_exchange_weak(running, running + taken_));
+  }
+  ~Helpers() { running_.fetch_sub(taken_); }
+  Helpers(const Helpers&) = delete;
+  Helpers& operator=(const Helpers&) = delete;
+  int taken() const { return taken_; }
+
+ private:
+  static std::atomic<int> running_;
+  int taken_;
+};
+std::atomic<int> Helpers::running_{0};
+
 int plan_algorithm1(uint32_t d, uint64_t budget, uint32_t R, double alpha, float B, uint32_t quant,
                     cvlc_plan_t* out) {
   if (R < 1 || !std::isfinite(alpha) || quant > CVLC_QUANT_QSGD) return CVLC_ERR_ARG;
@@ -255,18 +287,18 @@ int plan_algorithm1(uint32_t d, uint64_t budget, uint32_t R, double alpha, float
       found[g].gamma = alg.solve(k, found[g].y, found[g].P);
     }
   };
-  std::thread helpers[kThreads - 1];
-  if (R > 1) {  // one group: nothing to balance, microseconds in all
-    const unsigned cpus = std::thread::hardware_concurrency();
+  {
+    const Helpers room(R > 1 ? kThreads - 1 : 0);  // one group: nothing to balance, microseconds in all
+    std::thread helpers[kThreads - 1];
     try {
-      for (unsigned t = 0; t + 1u < cpus && t < (unsigned)(kThreads - 1); ++t) helpers[t] = std::thread(search);
+      for (int t = 0; t < room.taken(); ++t) helpers[t] = std::thread(search);
     } catch (...) {
       // no more threads (or no memory for them) to be had: those that run and this one do the work
     }
+    search();
+    for (std::thread& t : helpers)
+      if (t.joinable()) t.join();
   }
-  search();
-  for (std::thread& t : helpers)
-    if (t.joinable()) t.join();
   double best = std::numeric_limits<double>::infinity();
   for (const Candidate& c : found) {
     if (c.gamma < best) {

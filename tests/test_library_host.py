@@ -4,6 +4,8 @@ argument errors are reported before anything is launched."""
 import ctypes as C
 import os
 import re
+import threading
+from concurrent.futures import ThreadPoolExecutor
 
 import numpy as np
 import pytest
@@ -43,6 +45,27 @@ def test_planner_matches_oracle_on_the_workloads():
             assert _same(pg, po), cfg
             assert w.mode == "fractions" or pg.total_bits <= w.budget_bits(3)
             assert cv.plan_gamma(pg, alpha) == pytest.approx(orc.gamma(po, alpha), rel=1e-12)
+
+
+def test_planner_threads_of_concurrent_calls():
+    """Many threads plan at once: the same plans, and all calls together start no more helpers than there are CPUs."""
+    alone = cv.plan(1_200_000, 1_800_000, n_coded=7, alpha=-0.5)
+    before, most, done = len(os.listdir("/proc/self/task")), 0, threading.Event()
+
+    def watch():
+        nonlocal most
+        while not done.is_set():
+            most = max(most, len(os.listdir("/proc/self/task")))
+
+    watcher = threading.Thread(target=watch)
+    watcher.start()
+    callers = 24
+    with ThreadPoolExecutor(callers) as pool:
+        plans = list(pool.map(lambda _: cv.plan(1_200_000, 1_800_000, n_coded=7, alpha=-0.5), range(4 * callers)))
+    done.set()
+    watcher.join()
+    assert all(bytes(p) == bytes(alone) for p in plans)
+    assert most <= before + 1 + callers + len(os.sched_getaffinity(0)) - 1, (before, most)
 
 
 def test_planner_matches_oracle_on_random_inputs():
