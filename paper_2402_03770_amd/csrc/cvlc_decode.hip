@@ -404,18 +404,18 @@ constexpr uint32_t kFirstBits = 22;  // a tile's records over one batch of lists
 constexpr uint32_t kFirstMask = (1u << kFirstBits) - 1u;
 constexpr uint32_t kListBits = 32u - kFirstBits;  // ... and the list of a slice fits above that number in one word
 
-// BLOCK: threads of a decode workgroup.  LISTS: lists it handles per sweep, one per thread.  TURNS: turns of 64
-// records a wavefront works on together.
-template <uint32_t BLOCK, uint32_t LISTS>
+constexpr uint32_t kDecBlock = 512;  // threads of a decode workgroup, three to a CU
+constexpr uint32_t kDecWaves = kDecBlock / kWave;
+constexpr uint32_t kDecLists = kDecBlock;  // lists it handles per sweep, one per thread
+constexpr uint32_t kDecTurns = 6;    // turns of 64 records a wavefront works on together
 struct DecodeShared {
-  static constexpr uint32_t kWaves = BLOCK / kWave;
-  static_assert(LISTS <= BLOCK && (uint64_t)LISTS * kDecTile < (1ull << kFirstBits) && LISTS <= (1u << kListBits), "see kFirstBits");
+  static_assert(kDecLists <= kDecBlock && (uint64_t)kDecLists * kDecTile < (1ull << kFirstBits) && kDecLists <= (1u << kListBits), "see kFirstBits");
   double acc[kDecTile];
-  uint4 desc[LISTS][2];            // CompactDesc, as loaded, but with the payload's words in the place of P
+  uint4 desc[kDecLists][2];            // CompactDesc, as loaded, but with the payload's words in the place of P
   // per non-empty slice of the batch, in list order
-  uint32_t begin[LISTS];           // first record of the slice inside its list
-  uint32_t first[LISTS + 1];       // number of the slice's first record in the tile | list << kFirstBits; then the total
-  uint32_t scan_a[kWaves], scan_b[kWaves];
+  uint32_t begin[kDecLists];           // first record of the slice inside its list
+  uint32_t first[kDecLists + 1];       // number of the slice's first record in the tile | list << kFirstBits; then the total
+  uint32_t scan_a[kDecWaves], scan_b[kDecWaves];
 };
 
 // LDS accesses of one wavefront complete in order; this keeps the compiler from
@@ -424,19 +424,18 @@ __device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOM
 
 // SIGNED: the streams' codes hold a sign bit above the level (QSGD).
 // WIDE: positions of more than 25 bits, which with a raw 32-bit code may not lie in eight bytes from the one they start in.
-template <bool SIGNED, bool WIDE, uint32_t BLOCK, uint32_t LISTS, uint32_t TURNS, uint32_t PER_SIMD>
-__global__ __launch_bounds__(BLOCK, PER_SIMD) void decode_tiles_kernel(const CompactDesc* __restrict__ cdesc,
+template <bool SIGNED, bool WIDE>
+__global__ __launch_bounds__(kDecBlock, 6) void decode_tiles_kernel(const CompactDesc* __restrict__ cdesc,
                                                               const DecodeCtl* __restrict__ ctl,
                                                               const uint32_t* __restrict__ table, float* out,
                                                               uint32_t d, uint32_t n_tiles, uint32_t accumulate,
                                                               uint32_t* status) {
-  __shared__ DecodeShared<BLOCK, LISTS> S;
-  __shared__ unsigned long long turn_mask[BLOCK / kWave][TURNS];  // per wavefront: starts of slices inside each of its current turns
-  constexpr uint32_t kWaves = BLOCK / kWave;
+  __shared__ DecodeShared S;
+  __shared__ unsigned long long turn_mask[kDecBlock / kWave][kDecTurns];  // per wavefront: starts of slices inside each of its current turns
   const uint32_t tid = threadIdx.x, lane = lane_id();
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const uint32_t n_active = ctl->n_active;
-  const bool one_batch = n_active <= LISTS;
+  const bool one_batch = n_active <= kDecLists;
   bool bad = false, fresh = true;
   // What a thread needs of its list of the batch at l0: the descriptor, and the two table entries for a tile.  Both
   // are asked for a batch ahead (a batch of few records is otherwise little but the chain of waits for descriptors,
@@ -448,7 +447,7 @@ __global__ __launch_bounds__(BLOCK, PER_SIMD) void decode_tiles_kernel(const Com
   };
   auto request_rows = [&](uint32_t tile, uint32_t l0) {
     uint2 r = make_uint2(0u, 0u);
-    if (tile < n_tiles && tid < min(n_active - l0, LISTS)) {
+    if (tile < n_tiles && tid < min(n_active - l0, kDecLists)) {
       const uint64_t two = load8((GlobalBytePtr)(table + (size_t)(l0 + tid) * (n_tiles + 1) + tile));
       r.x = (uint32_t)two;
       r.y = (uint32_t)(two >> 32);
@@ -474,16 +473,16 @@ __global__ __launch_bounds__(BLOCK, PER_SIMD) void decode_tiles_kernel(const Com
     next_rows = request_rows(tile_of(0), 0);
     request_desc(0, next_desc);
   }
-  for (uint32_t i = tid; i < kDecTile; i += BLOCK) S.acc[i] = 0.0;
+  for (uint32_t i = tid; i < kDecTile; i += kDecBlock) S.acc[i] = 0.0;
   for (uint32_t tile = tile_of(0); tile < n_tiles;) {
     const uint32_t lo = tile * kDecTile;
-    const bool last_batch = n_active - l0 <= LISTS;  // of the tile
-    const uint32_t next_tile = last_batch ? tile_of(++round) : tile, next_l0 = last_batch ? 0u : l0 + LISTS;
+    const bool last_batch = n_active - l0 <= kDecLists;  // of the tile
+    const uint32_t next_tile = last_batch ? tile_of(++round) : tile, next_l0 = last_batch ? 0u : l0 + kDecLists;
     if (n_active) {  // uniform
-      const uint32_t nl = min(n_active - l0, LISTS);
+      const uint32_t nl = min(n_active - l0, kDecLists);
       const uint2 rows = next_rows;
       if (!one_batch || fresh) {  // one batch: its descriptors stay in LDS
-        if (tid < LISTS) {
+        if (tid < kDecLists) {
           // in the place of the number of records, which only this thread needs: the payload's words
           uint4 d1 = next_desc[1];
           d1.x = (uint32_t)payload_words(next_desc[1].x, next_desc[1].y & 0xFFu);
@@ -517,7 +516,7 @@ __global__ __launch_bounds__(BLOCK, PER_SIMD) void decode_tiles_kernel(const Com
       __syncthreads();
       uint32_t before = incl - len, j = lanes_below(live), total = 0, n_live = 0;
 #pragma unroll
-      for (uint32_t w = 0; w < kWaves; ++w) {
+      for (uint32_t w = 0; w < kDecWaves; ++w) {
         const uint32_t xa = S.scan_a[w], xb = S.scan_b[w];
         if (w < wave) { before += xa; j += xb; }
         total += xa;
@@ -530,7 +529,7 @@ __global__ __launch_bounds__(BLOCK, PER_SIMD) void decode_tiles_kernel(const Com
       if (tid == 0) S.first[n_live] = total;
       __syncthreads();
       // the wavefront's share of the records, a multiple of 64
-      const uint32_t share = ((total + BLOCK - 1) / BLOCK) * kWave;
+      const uint32_t share = ((total + kDecBlock - 1) / kDecBlock) * kWave;
       const uint32_t q_begin = min(wave * share, total), q_end = min(q_begin + share, total);
       if (q_begin < q_end) {  // uniform per wavefront
         // last slice whose first record is at or before the first record of the turns at hand (uniform): the
@@ -539,14 +538,14 @@ __global__ __launch_bounds__(BLOCK, PER_SIMD) void decode_tiles_kernel(const Com
         {
           uint32_t at_or_before = 0;
 #pragma unroll
-          for (uint32_t k = 0; k < (LISTS + kWave - 1) / kWave; ++k) {
+          for (uint32_t k = 0; k < (kDecLists + kWave - 1) / kWave; ++k) {
             const uint32_t i = k * kWave + lane;
             const bool hit = i < n_live && (S.first[min(i, n_live)] & kFirstMask) <= q_begin;
             at_or_before += (uint32_t)__popcll(__ballot(hit));
           }
           cur = __builtin_amdgcn_readfirstlane(at_or_before) - 1u;
         }
-        // TURNS turns at a time.  First the start masks of all of them; then, turn by turn but without one
+        // kDecTurns turns at a time.  First the start masks of all of them; then, turn by turn but without one
         // turn waiting for another, list and record number from LDS; then all record loads together, so that their
         // latencies overlap.  Nothing in this half branches on data (a lane past the end works on the last record
         // again), so that no load has to be waited for before the next one is issued.  A record is read by one load of
@@ -556,36 +555,36 @@ __global__ __launch_bounds__(BLOCK, PER_SIMD) void decode_tiles_kernel(const Com
         // entries: 53 us instead of 47 for 32 streams of 11.2 M
         // coordinates, 540 instead of 459 for 100 of 25.6 M).
         unsigned long long* masks = turn_mask[wave];
-        for (uint32_t q0 = q_begin; q0 < q_end; q0 += kWave * TURNS) {
-          const uint32_t n_turns = __builtin_amdgcn_readfirstlane(min((q_end - q0 + kWave - 1u) / kWave, TURNS));
+        for (uint32_t q0 = q_begin; q0 < q_end; q0 += kWave * kDecTurns) {
+          const uint32_t n_turns = __builtin_amdgcn_readfirstlane(min((q_end - q0 + kWave - 1u) / kWave, kDecTurns));
           // slices after `cur` that start inside the turns: first[] ascends strictly, first[n_live] = total.
           // 64 slices are looked at per round; more start inside the turns only when most hold a few records.
-          if (lane < TURNS) masks[lane] = 0ull;
+          if (lane < kDecTurns) masks[lane] = 0ull;
           wave_lds_fence();
           for (uint32_t seen = 0;; seen += kWave) {  // uniform
             const uint32_t idx = cur + 1u + seen + lane;
             const uint32_t f = (S.first[min(idx, n_live)] & kFirstMask) - q0;  // >= 0
-            if (idx <= n_live && f < kWave * TURNS) atomicOr(&masks[f >> 6], 1ull << (f & 63u));
+            if (idx <= n_live && f < kWave * kDecTurns) atomicOr(&masks[f >> 6], 1ull << (f & 63u));
             // done when the last one looked at lies past the turns at hand, or nothing is left to look at
             if (cur + seen + kWave >= n_live || __builtin_amdgcn_readlane(f, kWave - 1) >= kWave * n_turns) break;
           }
           wave_lds_fence();
-          uint64_t bits_of[TURNS];
-          uint32_t tail_of[WIDE ? TURNS : 1];  // the byte behind those eight
-          uint32_t base_of[TURNS], at[TURNS];  // at: list | bit inside the first word << kListBits
-          unsigned long long starts[TURNS];
+          uint64_t bits_of[kDecTurns];
+          uint32_t tail_of[WIDE ? kDecTurns : 1];  // the byte behind those eight
+          uint32_t base_of[kDecTurns], at[kDecTurns];  // at: list | bit inside the first word << kListBits
+          unsigned long long starts[kDecTurns];
 #pragma unroll
-          for (uint32_t u = 0; u < TURNS; ++u) starts[u] = masks[u];
+          for (uint32_t u = 0; u < kDecTurns; ++u) starts[u] = masks[u];
 #pragma unroll
-          for (uint32_t u = 0; u < TURNS; ++u) {
+          for (uint32_t u = 0; u < kDecTurns; ++u) {
             base_of[u] = cur;
             if (u < n_turns)  // uniform; the sentinel's bit lies in the last turn at hand or past it
               cur += (uint32_t)__popc((uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)starts[u])) +
                      (uint32_t)__popc((uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(starts[u] >> 32)));
           }
-          uint32_t x_of[TURNS], e_of[TURNS];
+          uint32_t x_of[kDecTurns], e_of[kDecTurns];
 #pragma unroll
-          for (uint32_t u = 0; u < TURNS; ++u) {
+          for (uint32_t u = 0; u < kDecTurns; ++u) {
             x_of[u] = e_of[u] = 0;
             if (u >= n_turns) continue;          // uniform
             const uint32_t qt = q0 + u * kWave;  // the turn's first record (uniform)
@@ -595,7 +594,7 @@ __global__ __launch_bounds__(BLOCK, PER_SIMD) void decode_tiles_kernel(const Com
             e_of[u] = S.begin[a] + (qt + place);
           }
 #pragma unroll
-          for (uint32_t u = 0; u < TURNS; ++u) {
+          for (uint32_t u = 0; u < kDecTurns; ++u) {
             bits_of[u] = 0;
             at[u] = 0;
             if (u >= n_turns) continue;  // uniform
@@ -612,7 +611,7 @@ __global__ __launch_bounds__(BLOCK, PER_SIMD) void decode_tiles_kernel(const Com
             if (WIDE) tail_of[u] = *(src + min(byte + 8u, end + 7u));
           }
 #pragma unroll
-          for (uint32_t u = 0; u < TURNS; ++u) {
+          for (uint32_t u = 0; u < kDecTurns; ++u) {
             if (u >= n_turns) continue;  // uniform
             if (q0 + u * kWave + lane >= q_end) continue;
             const uint32_t li = at[u] & ((1u << kListBits) - 1u), sh = at[u] >> kListBits;
@@ -643,18 +642,18 @@ __global__ __launch_bounds__(BLOCK, PER_SIMD) void decode_tiles_kernel(const Com
     if (last_batch) {
       // pairs of coordinates, neighbouring lanes neighbouring pairs (LDS reads without bank conflicts, 512-byte
       // stores per wavefront): all reads first, then the stores.  The thread leaves zeros for the next tile.
-      constexpr uint32_t kPairs = kDecTile / (2u * BLOCK);
+      constexpr uint32_t kPairs = kDecTile / (2u * kDecBlock);
       double2 v[kPairs];
 #pragma unroll
       for (uint32_t c = 0; c < kPairs; ++c) {
-        double2* mine = reinterpret_cast<double2*>(&S.acc[c * (2u * BLOCK) + tid * 2u]);
+        double2* mine = reinterpret_cast<double2*>(&S.acc[c * (2u * kDecBlock) + tid * 2u]);
         v[c] = *mine;
         *mine = make_double2(0.0, 0.0);
       }
       const bool aligned = (reinterpret_cast<uintptr_t>(out + lo) & 7u) == 0;  // uniform
 #pragma unroll
       for (uint32_t c = 0; c < kPairs; ++c) {
-        const uint32_t j0 = lo + c * (2u * BLOCK) + tid * 2u;
+        const uint32_t j0 = lo + c * (2u * kDecBlock) + tid * 2u;
         if (aligned && j0 + 2u <= d) {
           float2* dst = reinterpret_cast<float2*>(out + j0);
           if (accumulate) {
@@ -784,9 +783,9 @@ int cvlc_decode_aggregate(uint32_t n, const void* const* d_streams, const size_t
     const uint32_t g = std::min(L.n_tiles, 768u);  // three workgroups per CU
     const bool qsgd = quant == CVLC_QUANT_QSGD;
     const bool wide = position_bits(d) > 25u;
-    auto kernel = qsgd ? (wide ? decode_tiles_kernel<true, true, 512, 512, 6, 6> : decode_tiles_kernel<true, false, 512, 512, 6, 6>)
-                       : (wide ? decode_tiles_kernel<false, true, 512, 512, 6, 6> : decode_tiles_kernel<false, false, 512, 512, 6, 6>);
-    hipLaunchKernelGGL(kernel, dim3(g), dim3(512), 0, stream, cdesc, ctl, table, d_out, d, L.n_tiles,
+    auto kernel = qsgd ? (wide ? decode_tiles_kernel<true, true> : decode_tiles_kernel<true, false>)
+                       : (wide ? decode_tiles_kernel<false, true> : decode_tiles_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, dim3(g), dim3(kDecBlock), 0, stream, cdesc, ctl, table, d_out, d, L.n_tiles,
                        flags & CVLC_DECODE_ACCUMULATE, status);
   }
   return hip_check(hipGetLastError());
