@@ -49,6 +49,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "cvlc_common.h"
 
@@ -283,10 +284,11 @@ __device__ __forceinline__ void level1_walk(const RankCtl* ctl, const RankSet& r
 // its own for it takes 11 us), workgroup 0 of a client leaves its result, and whether a rank lies outside
 // the guessed bins, where the later kernels look for them; a client whose guess missed has its level 2 counted by the
 // collecting pass.
+struct NoRanks {};  // (132 bytes of kernel arguments cost the small calls 0.3 us)
 template <int LEVEL, bool LISTS, bool WALK>
 __global__ __launch_bounds__(kRankBlock) void rank_pass_kernel(const float* const* __restrict__ updates,
                                                                RankCtl* __restrict__ ctls, uint32_t d, KeyLists kl,
-                                                               RankSet ranks) {
+                                                               std::conditional_t<WALK, RankSet, NoRanks> ranks) {
   __shared__ uint32_t hist[kRanksMax * kSubBins];
   __shared__ alignas(16) uint8_t first_cls[kTopBins];
   __shared__ uint32_t cls_prefix[kRanksMax + 1];
@@ -453,12 +455,12 @@ constexpr uint32_t kCollectStage = 512;  // keys a wavefront stages in LDS; rows
 // more), workgroup 0 of a client also leaves the result where the later kernels look for it.  The keys it
 // collects are counted on their next 9 bits as they pass (level 2, per class, 64 KB of LDS).  With its 104 KB
 // of LDS one workgroup has a CU to itself, which suits a streaming pass (241 against 252 us with two).
-// guessed: only the clients whose guess missed.
+// GUESSED: only the clients whose guess missed.
+template <bool GUESSED>
 __global__ __launch_bounds__(kRankBlock) void rank_collect_kernel(const float* const* __restrict__ updates,
                                                                   RankCtl* __restrict__ ctls, RankSet ranks,
                                                                   uint32_t d, uint32_t* __restrict__ lists,
-                                                                  uint32_t* __restrict__ list_cnt, uint32_t wave_cap,
-                                                                  bool guessed) {
+                                                                  uint32_t* __restrict__ list_cnt, uint32_t wave_cap) {
   __shared__ alignas(16) uint8_t first_cls[kTopBins];
   __shared__ uint32_t stage[kRankWaves][kCollectStage];
   __shared__ uint32_t s_fill[kRankWaves];  // keys a wavefront has staged
@@ -467,7 +469,7 @@ __global__ __launch_bounds__(kRankBlock) void rank_collect_kernel(const float* c
   __shared__ uint32_t s_prefix[kRanksMax], s_rem[kRanksMax];
   __shared__ uint32_t s_n_cls;
   RankCtl* ctl = ctls + blockIdx.y;
-  if (guessed && !ctl->missed) return;  // uniform
+  if (GUESSED && !ctl->missed) return;  // uniform
   for (uint32_t i = threadIdx.x; i < kTopBins / 4u; i += kRankBlock)
     reinterpret_cast<uint32_t*>(first_cls)[i] = 0xFFFFFFFFu;
   level1_walk(ctl, ranks, scan_tmp, s_prefix, s_rem);
@@ -933,19 +935,19 @@ int cvlc_fit_alpha(uint32_t n, const float* const* d_updates, uint32_t d, double
                          L.wave_cap, status);
       hipLaunchKernelGGL((rank_pass_kernel<2, true, true>), list_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl, ranks);
     }
-    hipLaunchKernelGGL(rank_collect_kernel, dim3(L.blocks, n), dim3(kRankBlock), 0, stream, ptrs, ctls, ranks, d, lists,
-                       list_cnt, L.wave_cap, one_pass);
+    auto collect = one_pass ? rank_collect_kernel<true> : rank_collect_kernel<false>;
+    hipLaunchKernelGGL(collect, dim3(L.blocks, n), dim3(kRankBlock), 0, stream, ptrs, ctls, ranks, d, lists, list_cnt, L.wave_cap);
     hipLaunchKernelGGL(rank_walk_kernel<2>, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks, (uint32_t*)nullptr,
                        (double*)nullptr);
-    hipLaunchKernelGGL((rank_pass_kernel<3, true, false>), list_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl, ranks);
+    hipLaunchKernelGGL((rank_pass_kernel<3, true, false>), list_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl, NoRanks{});
     hipLaunchKernelGGL(rank_walk_kernel<3>, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks, d_keys_out, d_alpha_out);
     return hip_check(hipGetLastError());
   }
   hipLaunchKernelGGL(rank_walk1_kernel, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks);
-  hipLaunchKernelGGL((rank_pass_kernel<2, false, false>), pass_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl, ranks);
+  hipLaunchKernelGGL((rank_pass_kernel<2, false, false>), pass_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl, NoRanks{});
   hipLaunchKernelGGL(rank_walk_kernel<2>, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks, (uint32_t*)nullptr,
                      (double*)nullptr);
-  hipLaunchKernelGGL((rank_pass_kernel<3, false, false>), pass_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl, ranks);
+  hipLaunchKernelGGL((rank_pass_kernel<3, false, false>), pass_grid, dim3(kRankBlock), 0, stream, ptrs, ctls, d, kl, NoRanks{});
   hipLaunchKernelGGL(rank_walk_kernel<3>, dim3(n), dim3(kRankBlock), 0, stream, ctls, ranks, d_keys_out, d_alpha_out);
   return hip_check(hipGetLastError());
 }
