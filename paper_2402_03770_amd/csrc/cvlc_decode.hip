@@ -550,10 +550,11 @@ __global__ __launch_bounds__(kDecBlock, 6) void decode_tiles_kernel(const Compac
         // latencies overlap.  Nothing in this half branches on data (a lane past the end works on the last record
         // again), so that no load has to be waited for before the next one is issued.  A record is read by one load of
         // eight bytes from the byte it starts in (from the payload's last eight bytes where it would reach past them):
-        // lanes of a turn read from a dozen lists and more, an instruction costs the address unit a cycle or more per
-        // cache line, and that is what bounds this kernel (three aligned words a record and two loads per pair of table
-        // entries: 53 us instead of 47 for 32 streams of 11.2 M
-        // coordinates, 540 instead of 459 for 100 of 25.6 M).
+        // lanes of a turn read from a dozen lists and more, 48 cache lines to a load on average, and every one of them is
+        // a cycle or more of the address unit (three aligned words a record and two loads per pair of table
+        // entries, 2.7 times the loads: 53 us instead of 47 for 32 streams of 11.2 M coordinates, 540 instead of 459
+        // for 100 of 25.6 M).  Now no unit is the bound by itself: the address units are busy for 38 % of the launch, the vector
+        // units for 36 %.
         unsigned long long* masks = turn_mask[wave];
         for (uint32_t q0 = q_begin; q0 < q_end; q0 += kWave * kDecTurns) {
           const uint32_t n_turns = __builtin_amdgcn_readfirstlane(min((q_end - q0 + kWave - 1u) / kWave, kDecTurns));

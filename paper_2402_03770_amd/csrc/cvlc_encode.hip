@@ -26,9 +26,10 @@
 //   gather        copies the runs into one dense, position-ordered candidate
 //                 list, spans of 512 candidates per wavefront, and sets the
 //                 members of the boundaries' bins aside
-//   select        finds every boundary's element among the members of its bin:
-//                 its key, and its number in the dense list, which cuts a class
-//                 of equal magnitudes
+//   select        finds every boundary's element among the members of its bin (in
+//                 the dense list where equal magnitudes make that a large part of
+//                 it): its key, and its number in the dense list, which cuts a
+//                 class of equal magnitudes
 //   count         per span: group of every candidate and its number among the
 //                 span's members of that group (left for emit, 16 bits per
 //                 candidate), per-group count, min/max/sum of squares; for the
