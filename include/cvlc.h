@@ -260,8 +260,8 @@ size_t cvlc_fit_workspace_bytes_for(uint32_t n_clients, uint32_t d);
  * largest magnitude.  alpha is the ordinary-least-squares slope of ln|U{l}| on
  * ln l over the ranks of cvlc_fit_ranks(d), ranks whose magnitude is zero left
  * out; fewer than two usable ranks give alpha = -1.  The magnitudes are exact
- * order statistics of the whole vector (two or three passes over it, by the
- * size of the workspace).
+ * order statistics of the whole vector (one to three passes over it, by the
+ * size of the workspace and of the call).
  *   d_updates[i]  host array of device pointers, each d fp32, 16-byte aligned
  *   d_alpha_out   device, n doubles
  *   d_keys_out    device or NULL: n * CVLC_FIT_RANKS_MAX words; word j of client
