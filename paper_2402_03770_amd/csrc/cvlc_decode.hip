@@ -228,7 +228,7 @@ __global__ __launch_bounds__(1024) void compact_lists_kernel(const ListDesc* __r
 
 // Both steps in one launch, for calls of a few streams: the sixteen wavefronts
 // share out the streams, then the workgroup numbers the lists it has just described.
-constexpr uint32_t kFusedStreams = 1024u / kWave;
+constexpr uint32_t kFusedStreams = 24;
 static_assert(kFusedStreams <= kParseStreams, "one set of arguments");
 __global__ __launch_bounds__(1024) void setup_kernel(ParseChunk chunk, ListDesc* descs, uint32_t d, uint32_t quant,
                                                      CompactDesc* __restrict__ cdesc, uint32_t* __restrict__ item_start,
@@ -746,8 +746,9 @@ int cvlc_decode_aggregate(uint32_t n, const void* const* d_streams, const size_t
   {
     ParseChunk chunk;
     chunk.pad[0] = chunk.pad[1] = 0;
-    // one launch parses and numbers, while the one workgroup has a wavefront for every stream (100 streams:
-    // 35 us against 4.8 + 10.8 for two launches, the first with a workgroup per stream; 32 streams: 11.5 against 4.7 + 4.8)
+    // One launch parses and numbers, 3.5 us for every 16 streams; two launches, the first with a workgroup per stream, take
+    // 4.2 + 3.8 for 17 and 4.8 + 10.8 for 100 (35 us in one).  The second launch costs a small call 2 us on the host:
+    // a call of 17 streams of 20 000 coordinates takes 20.5 us with one and 22.6 with two, of 32 25 either way.
     const bool fused = n > 0 && n <= kFusedStreams;
     for (uint32_t first = 0; first < n; first += kParseStreams) {
       chunk.first = first;
