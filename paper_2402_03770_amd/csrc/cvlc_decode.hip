@@ -263,37 +263,64 @@ typedef const unsigned char __attribute__((address_space(1))) * GlobalBytePtr;
 __device__ __forceinline__ uint32_t load4(GlobalBytePtr p) { return ((const Bytes4 __attribute__((address_space(1)))*)p)->v; }
 __device__ __forceinline__ uint64_t load8(GlobalBytePtr p) { return ((const Bytes8 __attribute__((address_space(1)))*)p)->v; }
 
-// The list that owns item q (last list with item_start <= q), whole wavefront, 64 probes a round: two rounds for up
-// to 4096 lists.  (A binary search by every lane costs log2 rounds, in LDS a copy of item_start per workgroup first:
-// beyond 2048 lists, where the copy did not fit, it was twelve dependent loads per item and two thirds of the kernel.)
-__device__ __forceinline__ uint32_t owner_of(const uint32_t* __restrict__ item_start, uint32_t n_active, uint32_t q) {
+// The list that owns item q: the last one with item_start <= q; its first item and the next list's.
+struct ItemOwner {
+  uint32_t list, first_item, next_list;
+};
+// Whole wavefront, 64 probes a round: one round for up to 64 lists, two for up to 4096.  lead: in a call of up to
+// kLeadLists lists lane l holds item_start[l], asked for before the number of non-empty lists is known (beyond that the
+// load is in the way of 8192 wavefronts).  The last round's lanes hold the two starts: a load that waits for
+// the one before is half a microsecond at the head of a small call's kernel.  (A binary search by every lane costs log2 rounds, in
+// LDS a copy of item_start per workgroup first: beyond 2048 lists, where the copy did not fit, it was twelve dependent
+// loads per item and two thirds of the kernel.)
+constexpr uint32_t kLeadLists = 512;
+__device__ __forceinline__ ItemOwner owner_of(const uint32_t* __restrict__ item_start, uint32_t lead, uint32_t n_lists,
+                                              uint32_t n_active, uint32_t n_items, uint32_t q) {
   const uint32_t lane = lane_id();
   uint32_t a = 0, len = n_active;  // the owner is one of a .. a + len - 1
-  while (len > 1) {
-    const uint32_t step = (len + kWave - 1u) / kWave;
-    const uint32_t at = a + lane * step;
-    const bool hit = lane * step < len && item_start[min(at, n_active)] <= q;
-    const uint32_t last = (uint32_t)__popcll(__ballot(hit)) - 1u;  // item_start ascends and its first entry is 0: the hits are a prefix
-    a += last * step;
-    len = min(step, len - last * step);
+  uint32_t start = lane < n_active ? lead : n_items;
+  if (n_lists > kLeadLists || len > kWave) {  // uniform
+    while (len > kWave) {
+      const uint32_t step = (len + kWave - 1u) / kWave;
+      const bool hit = lane * step < len && item_start[min(a + lane * step, n_active)] <= q;
+      const uint32_t last = (uint32_t)__popcll(__ballot(hit)) - 1u;  // item_start ascends and its first entry is 0: the hits are a prefix
+      a += last * step;
+      len = min(step, len - last * step);
+    }
+    start = item_start[min(a + lane, n_active)];
   }
-  return __builtin_amdgcn_readfirstlane(a);
+  const uint32_t last = (uint32_t)__popcll(__ballot(lane < len && start <= q)) - 1u;
+  ItemOwner o;
+  o.list = __builtin_amdgcn_readfirstlane(a + last);
+  o.first_item = __builtin_amdgcn_readlane(start, last);
+  o.next_list = __builtin_amdgcn_readlane(start, min(last + 1u, kWave - 1u));
+  if (last == kWave - 1u) o.next_list = item_start[o.list + 1u];  // uniform
+  return o;
 }
+constexpr uint32_t kTableBlocks = 2048;  // workgroups of tile_table, eight per CU
 
 // WIDE: positions of more than 25 bits, which need not lie in the four bytes from the one they start in.
 template <bool WIDE>
 __global__ __launch_bounds__(kBlock, 8) void tile_table_kernel(const CompactDesc* __restrict__ cdesc,
                                                          const uint32_t* __restrict__ item_start,
                                                          const DecodeCtl* __restrict__ ctl, uint32_t* table,
-                                                         uint32_t d, uint32_t n_tiles, uint32_t* status) {
+                                                         uint32_t d, uint32_t n_tiles, uint32_t n_lists, uint32_t* status) {
   const uint32_t tid = threadIdx.x, lane = lane_id();
+  const uint32_t lead = n_lists <= kLeadLists ? item_start[min(lane, n_lists)] : 0u;  // the array has room for n_lists + 1
   const uint32_t n_active = ctl->n_active, n_items = ctl->n_items;
   // A wavefront takes neighbouring items, so that it looks for the owner of the first one only and then walks on.
-  const uint64_t n_waves = gridDim.x * kWavesPerBlock, me = blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(tid / kWave);
-  const uint32_t q_begin = (uint32_t)(me * n_items / n_waves), q_end = (uint32_t)((me + 1u) * n_items / n_waves);
+  constexpr uint64_t n_waves = kTableBlocks * kWavesPerBlock;
+  const uint64_t me = blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(tid / kWave);
+  // Few items go to the first workgroups, which start a microsecond before the last ones (one stream of 2000 coordinates:
+  // 2.1 us; 3.9 with its three items in the middle and at the end of the launch and two loads more in a chain).
+  uint32_t q_begin = (uint32_t)(me * n_items / n_waves), q_end = (uint32_t)((me + 1u) * n_items / n_waves);
+  if (n_items <= n_waves) {
+    q_begin = min((uint32_t)me, n_items);
+    q_end = min((uint32_t)me + 1u, n_items);
+  }
   if (q_begin >= q_end) return;  // uniform
-  uint32_t a = owner_of(item_start, n_active, q_begin);
-  uint32_t first_item = item_start[a], next_list = item_start[a + 1u];  // uniform
+  const ItemOwner owner = owner_of(item_start, lead, n_lists, n_active, n_items, q_begin);
+  uint32_t a = owner.list, first_item = owner.first_item, next_list = owner.next_list;  // uniform
   bool bad = false;
   for (uint32_t q = q_begin; q < q_end; ++q) {  // uniform per wavefront
     while (q >= next_list) {  // every list has an item: one step at most
@@ -776,9 +803,10 @@ int cvlc_decode_aggregate(uint32_t n, const void* const* d_streams, const size_t
   profile_mark(CVLC_STAGE_DEC_SETUP, false, stream);
   if (n > 0) {
     StageScope scope(CVLC_STAGE_DEC_TABLE, stream);
-    // the number of work items is only known on the device: 2048 workgroups (eight per CU) walk them
+    // the number of work items is only known on the device
     auto kernel = position_bits(d) > 25u ? tile_table_kernel<true> : tile_table_kernel<false>;
-    hipLaunchKernelGGL(kernel, dim3(2048), dim3(kBlock), 0, stream, cdesc, item_start, ctl, table, d, L.n_tiles, status);
+    hipLaunchKernelGGL(kernel, dim3(kTableBlocks), dim3(kBlock), 0, stream, cdesc, item_start, ctl, table, d, L.n_tiles, n_lists,
+                       status);
   }
   {
     StageScope scope(CVLC_STAGE_DEC_TILES, stream);
