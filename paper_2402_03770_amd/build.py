@@ -19,7 +19,7 @@ FLAGS = [
 
 def build(force: bool = True, extra_flags=()) -> str:
     srcs = [os.path.join(CSRC, s) for s in SOURCES]
-    deps = srcs + [os.path.join(CSRC, "cvlc_common.h"), os.path.join(ROOT, "include", "cvlc.h")]
+    deps = srcs + [os.path.join(CSRC, "cvlc_common.h"), os.path.join(CSRC, "cvlc_select.h"), os.path.join(ROOT, "include", "cvlc.h")]
     if not force and os.path.exists(LIB) and all(os.path.getmtime(LIB) >= os.path.getmtime(f) for f in deps):
         return LIB
     cmd = ["hipcc", *FLAGS, *extra_flags, "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-x", "hip", *srcs, "-o", LIB]

@@ -92,6 +92,7 @@ struct ClientCtl {
   uint32_t n_nz;             // regions that kept at least one coordinate
   uint32_t dead;             // 1: more candidates than the workspace has room for; nothing further is done for the client
   uint32_t claim;            // regions of the filter's claimed part taken so far
+  uint32_t flags;            // short vectors: status bits that the selection found, reported by the packing pass
   uint32_t emit_claim;       // chunks of the packing pass taken beyond every workgroup's first
   SegPartial seg[kSegCopies];
   uint32_t over_cnt[32];     // members of a boundary's bin that found no room in the piece of their workgroup

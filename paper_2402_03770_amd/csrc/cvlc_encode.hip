@@ -9,6 +9,7 @@
 // position.  Launch chain per batch of clients (no kernel waits on another
 // workgroup and none needs a memory fence; every dependency is a kernel
 // boundary):
+// (short vectors, up to 65 536 coordinates: short_select, count and emit only)
 //   upload        per-client parameters as kernel arguments; clears the
 //                 call's control blocks
 //   sample_hist   strided sample of |U| -> histogram of the top 13 key bits
@@ -48,6 +49,7 @@
 #include <type_traits>
 
 #include "cvlc_common.h"
+#include "cvlc_select.h"
 
 namespace cvlc {
 namespace {
@@ -187,6 +189,28 @@ struct Workspace {  // device pointers into the caller's workspace
   uint32_t d, region_shift, n_regions, max_spans, dense_cap, filter_blocks, gather_blocks, member_pool, hist_copies;
 };
 
+// Short vectors: their selection, count and emit work on the vector itself, its coordinates take the place of the
+// candidates.  Less than any workspace that the general layout fits: that one has 6 bytes per coordinate and 500 KB per client more.
+struct ShortLayout {
+  size_t status, ctl, norm_limbs, params, places, span_cnt, total;
+  uint32_t max_spans;
+};
+
+ShortLayout short_layout(uint32_t d, uint32_t n) {
+  ShortLayout L;
+  L.max_spans = (d + kSpan - 1u) / kSpan;
+  size_t off = 0;
+  L.status = off; off = align256(off + 256);
+  L.ctl = off; off = align256(off + (size_t)n * sizeof(ClientCtl));
+  L.norm_limbs = off; off = align256(off + (size_t)n * 32 * kNormLimbs * sizeof(uint64_t));
+  L.params = off; off = align256(off + (size_t)n * sizeof(ClientParams));
+  L.places = off; off = align256(off + (size_t)n * d * sizeof(uint16_t));
+  L.span_cnt = off; off = align256(off + (size_t)n * (L.max_spans + 1) * 32 * sizeof(uint32_t));
+  L.total = off;
+  return L;
+}
+static_assert(kSpan >= 2u * 32u, "a span's counts take no more room than its candidates in the general layout");
+
 // ------------------------------------------------------------------ parameter upload
 // The per-client parameter blocks travel as kernel arguments (no pinned memory,
 // no synchronisation).  Clients of a batch mostly share a plan, so a chunk holds
@@ -203,6 +227,12 @@ struct UploadChunk {
   uint32_t data[kUploadWords];  // n_templates parameter blocks, then n_clients references
 };
 
+// Word w of the parameter block of the chunk's client-th client.
+__device__ __forceinline__ uint32_t param_word(const UploadChunk& c, uint32_t client, uint32_t w) {
+  const uint32_t* ref = c.data + c.n_templates * kParamWords + client * kRefWords;
+  return w < 5 ? ref[w] : c.data[ref[5] * kParamWords + w];
+}
+
 // Workgroup 0 expands the chunk into the clients' parameter blocks; all
 // workgroups clear zero_n16 16-byte pieces from `zero` on (the call's state that
 // starts at zero, in the call's first launch; a plain kernel, so that a caller
@@ -211,12 +241,9 @@ __global__ __launch_bounds__(256) void upload_kernel(uint32_t* dst, UploadChunk 
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < zero_n16; i += gridDim.x * blockDim.x)
     zero[i] = make_uint4(0u, 0u, 0u, 0u);
   if (blockIdx.x == 0) {
-    const uint32_t* refs = c.data + c.n_templates * kParamWords;
     for (uint32_t i = threadIdx.x; i < c.n_clients * kParamWords; i += blockDim.x) {
       const uint32_t client = i / kParamWords, w = i % kParamWords;
-      const uint32_t* ref = refs + client * kRefWords;
-      const uint32_t v = w < 5 ? ref[w] : c.data[ref[5] * kParamWords + w];
-      dst[(size_t)(c.first_client + client) * kParamWords + w] = v;
+      dst[(size_t)(c.first_client + client) * kParamWords + w] = param_word(c, client, w);
     }
   }
 }
@@ -238,6 +265,8 @@ __device__ __forceinline__ uint32_t lanes_below4(uint64_t m0, uint64_t m1, uint6
 // Pointers read from the parameter block are generic; the update vectors live in
 // global memory, and saying so lets the loads be issued as global loads.
 typedef const float __attribute__((address_space(1))) * GlobalFloatPtr;
+typedef uint32_t __attribute__((address_space(1))) * GlobalWordPtr;
+typedef const uint32_t __attribute__((address_space(1))) * GlobalConstWordPtr;
 typedef float __attribute__((ext_vector_type(4))) Float4V;
 typedef const Float4V __attribute__((address_space(1))) * GlobalFloat4Ptr;
 
@@ -1456,6 +1485,118 @@ __global__ __launch_bounds__(kSelectBlock) void select_kernel(const ClientParams
   }
 }
 
+// ------------------------------------------------------------------ 4b. short vectors: the whole selection in one workgroup
+// What the seven launches before this find for a long vector one workgroup per client finds for a short one
+// (cvlc_select.h): exact keys of all boundaries, and where a boundary cuts a class of equal keys the position
+// of the last one inside.  There are no candidates: the counting and packing passes go through the vector itself, a
+// coordinate's number is its position.  The kernel also puts the client's parameters and control block in place.
+// All latency (and what one CU gets of the memory's bandwidth).
+
+// The parameters come as kernel arguments, or have been uploaded before (batches of many different plans).
+struct ParamsUploaded {
+  const ClientParams* params;
+};
+__device__ __forceinline__ uint32_t short_client(const UploadChunk& c) { return c.first_client + blockIdx.x; }
+__device__ __forceinline__ uint32_t short_client(const ParamsUploaded&) { return blockIdx.x; }
+__device__ __forceinline__ uint32_t short_param(const UploadChunk& c, uint32_t w) { return param_word(c, blockIdx.x, w); }
+__device__ __forceinline__ uint32_t short_param(const ParamsUploaded& u, uint32_t w) {
+  return reinterpret_cast<const uint32_t*>(u.params + blockIdx.x)[w];
+}
+
+// Whether a vector would have more candidates than the caller's workspace has room for (`room` < d): what the
+// general path refuses is refused here too.  Its candidates are the keys at or above the lower edge of the 13-bit bin that
+// holds the sample's rank-th largest key, and the sample of a short vector is all of it but the last d mod kSamplePiece
+// coordinates.  So that key lies between the vector's rank-th and (rank + missing)-th (the extra rank).  Whole
+// workgroup, after locate_short; leaves S.top and S.upto as they were.
+static_assert(kSampleShift == kTopShift + 1u && kShortMax <= kSampleChunksMax * kSamplePiece, "two bins to a sample bin, all pieces sampled");
+__device__ __forceinline__ uint32_t short_missing(uint32_t d) { return d % kSamplePiece; }
+__device__ __forceinline__ bool short_of_room(ShortSelect& S, const float* update, uint32_t d, uint32_t room, uint32_t rank) {
+  if (rank == 0u) return true;  // no threshold: all d are candidates
+  const uint32_t missing = short_missing(d);
+  const uint32_t upto = S.extra - S.extra_rem + S.top[S.extra_bin] + ((S.extra_bin & 1u) ? S.top[S.extra_bin - 1u] : 0u);
+  if (upto <= room || missing == 0u) return upto > room;  // uniform
+  // next to never: the counts without the last coordinates decide
+  auto last_ones = [&](uint32_t by) {
+    __syncthreads();
+    if (threadIdx.x < missing) atomicAdd(&S.top[(__float_as_uint(((ShortFloatPtr)update)[d - missing + threadIdx.x]) & 0x7FFFFFFFu) >> kTopShift], by);
+    __syncthreads();
+  };
+  last_ones(~0u);
+  constexpr uint32_t kBins = kTopBins / kShortBlock;
+  const uint32_t largest = kTopBins - 1u - kBins * threadIdx.x;
+  uint32_t mine = 0, total;
+  for (uint32_t i = 0; i < kBins; ++i) mine += S.top[largest - i];
+  uint32_t above = block_excl_scan<kShortWaves>(mine, S.scan_tmp, &total);
+  if (above < rank && rank <= above + mine) {  // one thread
+    uint32_t bin = largest + 1u;
+    while (above < rank) {
+      bin -= 2u;
+      above += S.top[bin] + S.top[bin + 1u];
+    }
+    S.extra_bin = bin;
+  }
+  last_ones(1u);
+  const uint32_t from = S.extra_bin, t = (kTopBins - 1u - from) / kBins;
+  uint32_t all = t ? S.upto[t - 1u] : 0u;
+  for (uint32_t b = from; b < kTopBins - kBins * t; ++b) all += S.top[b];
+  return all > room;
+}
+
+template <class Params>
+__global__ __launch_bounds__(kShortBlock) void short_select_kernel(Params source, ClientParams* params, ClientCtl* ctls, Workspace ws,
+                                                                   cvlc_seg_stats_t* stats_out, uint32_t first_launch) {
+  __shared__ ShortSelect S;
+  __shared__ uint32_t s_params[kParamWords];
+  const uint32_t client = short_client(source), tid = threadIdx.x;
+  const uint32_t d = ws.d;
+  ClientCtl* ctl = ctls + client;
+  if (tid < kParamWords) {
+    const uint32_t word = short_param(source, tid);
+    s_params[tid] = word;
+    reinterpret_cast<uint32_t*>(params + client)[tid] = word;
+  }
+  if (first_launch && blockIdx.x == 0 && tid == 0) *ws.status = 0u;  // this kernel reports through ctl->flags
+  clear_short(S);
+  __syncthreads();
+  const ClientParams& p = *reinterpret_cast<const ClientParams*>(s_params);
+  const uint32_t R = p.R;
+  const float* update = p.update;
+  if (tid < R) S.rank[tid] = p.Z[tid];  // (cleared by the same thread)
+  const bool check_room = ws.dense_cap < d;
+  if (tid == 0) {
+    S.n_ranks = R;
+    S.extra = check_room && p.sample_rank ? p.sample_rank + short_missing(d) : 0u;
+  }
+  count_top(S, update, d);
+  // the control block, as far as the later kernels read it, and what this kernel counts in
+  static_assert(sizeof(SegPartial) * kSegCopies == kShortBlock * 4u, "a word per thread");
+  reinterpret_cast<uint32_t*>(ctl->seg)[tid] = 0;
+  for (uint32_t i = tid; i < 32u * kNormLimbs; i += kShortBlock) ws.norm_limbs[(size_t)client * 32u * kNormLimbs + i] = 0;
+  if (stats_out && tid < R) stats_out[(size_t)client * kStatsStride + tid].errsq = 0.0;  // the pack kernel adds to it when asked to
+  const uint32_t flags = tid < kTopBins - (0x7F800000u >> kTopShift) ? S.top[(0x7F800000u >> kTopShift) + tid] : 0u;
+  locate_short(S);
+  const bool dead = check_room && short_of_room(S, update, d, ws.dense_cap, p.sample_rank);  // uniform
+  const uint64_t flagged = __ballot(flags != 0u);  // the first wavefront looks at the bins of Inf and NaN
+  static_assert(kTopBins - (0x7F800000u >> kTopShift) <= kWave, "a bin per lane");
+  if (tid == 0) {
+    ctl->n_cand = d;
+    ctl->dead = dead ? 1u : 0u;
+    ctl->flags = (flagged ? CVLC_DEV_NONFINITE : 0u) | (dead ? CVLC_DEV_WORKSPACE : 0u);
+    ctl->emit_claim = 0;
+    if (dead) p.stream[0] = 0u;  // not a stream header
+  }
+  if (dead) return;
+  select_short(S, update, d);
+  if (tid < 32u) {
+    const bool none = tid >= R || S.rank[tid] == 0u;
+    ctl->tau[tid] = none ? 0xFFFFFFFFu : S.prefix[tid];
+    if (none || S.rem[tid] == S.equal[tid]) ctl->iota[tid] = none ? 0u : 0xFFFFFFFFu;  // the whole class is inside
+  }
+  visit_ties(S, update, d, [&](uint32_t r, uint32_t at) {
+    if (r < R) ctl->iota[r] = at;
+  });
+}
+
 // ------------------------------------------------------------------ 5. classification of the candidates
 struct Thresholds {  // group boundaries in LDS
   uint32_t tau[32];
@@ -1607,7 +1748,10 @@ constexpr uint32_t kLimbBanks = 2;  // copies of a workgroup's limb counters, to
 // collide; they are reduced once at the end.  Wavefronts do not wait for each
 // other before that.
 // QSGD: also the exact sum of squares of every group (see above).
-template <bool QSGD>
+// SHORT: the coordinates of a short vector take the candidates' place (short_select_kernel); most may be dropped, so
+// those are neither numbered nor kept in the columns, their energy stays in a register.  The pass also clears the
+// stream, whose words the packing pass ORs into.
+template <bool QSGD, bool SHORT>
 __global__ __launch_bounds__(kEmitBlock) void count_kernel(const ClientParams* __restrict__ params,
                                                            ClientCtl* __restrict__ ctls, Workspace ws) {
   __shared__ Thresholds thr;
@@ -1621,8 +1765,10 @@ __global__ __launch_bounds__(kEmitBlock) void count_kernel(const ClientParams* _
   if (ctl->dead) return;  // the workspace was too short for this client (whole workgroup)
   const uint32_t R = p.R, n = ctl->n_cand;
   const uint32_t n_spans = (n + kSpan - 1) / kSpan;
-  const uint32_t* __restrict__ val = ws.dense_val + (size_t)client * ws.dense_cap;
+  const uint32_t* __restrict__ val = SHORT ? (const uint32_t*)(GlobalConstWordPtr)p.update : ws.dense_val + (size_t)client * ws.dense_cap;
   uint32_t* __restrict__ span_cnt = ws.span_cnt + (size_t)client * (ws.max_spans + 1) * 32;
+  if (SHORT)
+    for (uint32_t i = blockIdx.x * kEmitBlock + tid; i < p.total_words; i += gridDim.x * kEmitBlock) ((GlobalWordPtr)p.stream)[i] = 0;
   load_thresholds(thr, ctl, R);
   if (tid < kEmitWaves * 32) (&s_cnt[0][0])[tid] = 0;
   for (uint32_t i = tid; i < 33 * kWave; i += kEmitBlock) {
@@ -1636,6 +1782,7 @@ __global__ __launch_bounds__(kEmitBlock) void count_kernel(const ClientParams* _
   uint16_t* __restrict__ place = span_places(ws, client);
   uint32_t* running = s_cnt[wave];  // members of every group (the dropped ones last) in the rows so far
   const uint32_t span_step = gridDim.x * kEmitWaves;
+  double tail = 0.0;  // SHORT: energy of the dropped
   uint32_t ahead[kPerLane];  // the next span's value bits, asked for before the current span is worked on
   if (blockIdx.x * kEmitWaves + wave < n_spans) load_span(val, n, blockIdx.x * kEmitWaves + wave, ahead);
   for (uint32_t span = blockIdx.x * kEmitWaves + wave; span < n_spans; span += span_step) {
@@ -1644,6 +1791,14 @@ __global__ __launch_bounds__(kEmitBlock) void count_kernel(const ClientParams* _
     for (uint32_t j = 0; j < kPerLane; ++j) v[j] = ahead[j];
     if (span + span_step < n_spans) load_span(val, n, span + span_step, ahead);
     classify_loaded(thr, R, n, span, v, grp);
+    if (SHORT) {
+#pragma unroll
+      for (uint32_t j = 0; j < kPerLane; ++j) {
+        const double x = grp[j] == R ? (double)__uint_as_float(v[j]) : 0.0;
+        tail = fma(x, x, tail);
+        if (grp[j] == R) grp[j] = kNoGroup;
+      }
+    }
     // Every candidate's number among the span's members of its group (row after row, lanes in order): a
     // row's members of a group read the group's running number and the lowest of them adds the row's
     // members to it.  This wavefront alone touches the counters and its LDS accesses complete in the order
@@ -1653,9 +1808,10 @@ __global__ __launch_bounds__(kEmitBlock) void count_kernel(const ClientParams* _
     auto number_rows = [&](auto id_bits) {
 #pragma unroll
       for (uint32_t j = 0; j < kPerLane; ++j) {
+        start[j] = below[j] = 0;
+        if (SHORT && !__ballot(grp[j] != kNoGroup)) continue;  // uniform
         const uint64_t same = same_group_lanes<decltype(id_bits)::value>(grp[j]);
         below[j] = lanes_below(same);
-        start[j] = 0;
         if (grp[j] != kNoGroup) {
           start[j] = running[grp[j]];
           if (below[j] == 0) atomicAdd(&running[grp[j]], (uint32_t)__popcll(same));
@@ -1696,6 +1852,10 @@ __global__ __launch_bounds__(kEmitBlock) void count_kernel(const ClientParams* _
       }
     }
   }
+  if (SHORT) {
+    tail = wave_sum_f64(tail);
+    if (lane == 0) atomicAdd(&ctl->seg[blockIdx.x % kSegCopies].sumsq[R], tail);
+  }
   __syncthreads();
   if (QSGD) {  // a workgroup sees fewer than 2^31 candidates, so no counter has wrapped
     unsigned long long* dst = ws.norm_limbs + (size_t)client * 32 * kNormLimbs;
@@ -1706,7 +1866,7 @@ __global__ __launch_bounds__(kEmitBlock) void count_kernel(const ClientParams* _
     }
   }
   // group g's columns are reduced by wavefront g mod 8; finite values never code to 0, so 0 = no member here
-  for (uint32_t g = wave; g <= R; g += kEmitWaves) {
+  for (uint32_t g = wave; SHORT ? g < R : g <= R; g += kEmitWaves) {
     const uint32_t mx = wave_max_u32(s_max[g][lane]);
     const uint32_t ng = wave_max_u32(s_negmin[g][lane]);
     const double sq = wave_sum_f64(s_sq[g][lane]);
@@ -1720,7 +1880,128 @@ __global__ __launch_bounds__(kEmitBlock) void count_kernel(const ClientParams* _
 }
 
 // ------------------------------------------------------------------ 7. layout: prefix, headers, statistics
-typedef uint32_t __attribute__((address_space(1))) * GlobalWordPtr;
+// What the packing pass and the headers need to know of a group.
+struct GroupValues {
+  uint32_t P, y;
+  float m, M, norm;    // smallest and largest value; QSGD: the l2-norm of the header
+  float low, inv, step;  // first centroid, reciprocal spacing and spacing of the centroids
+};
+
+// One thread per group.  P, y: its size and code length (read from the parameters well before: a load in the middle of this
+// is half a microsecond of a small call); enc_max, enc_negmin: as the counting pass leaves them; limbs: QSGD, the group's exact sum of
+// squares in 64-bit counters; sum: room for it in LDS.  Status bits go to *flags.
+__device__ __forceinline__ GroupValues group_values(uint32_t P, uint32_t y, uint32_t enc_max, uint32_t enc_negmin, uint32_t quant,
+                                                    const unsigned long long* limbs, uint32_t (&sum)[kNormLimbs], uint32_t* flags) {
+  GroupValues v;
+  v.P = P;
+  v.y = y;
+  v.m = v.M = v.norm = 0.0f;
+  if (v.P > 0 && enc_max != 0) {
+    v.M = from_ordered_bits(enc_max);
+    v.m = from_ordered_bits(~enc_negmin);
+  } else if (v.P > 0) {
+    *flags |= CVLC_DEV_INTERNAL;
+  }
+  if (!(fabsf(v.M - v.m) <= 3.4028234664e38f)) *flags |= CVLC_DEV_NONFINITE;
+  if (quant == CVLC_QUANT_QSGD) {
+    // carry the 64-bit counters into 32-bit limbs, then look for the smallest fp32 value whose
+    // square reaches the sum: squares grow with the bit pattern, so a binary search over it
+    unsigned long long carry = 0;
+    int top = -1;  // highest limb that is not zero
+    for (uint32_t i = 0; i < kNormLimbs; ++i) {
+      const unsigned long long t = limbs[i] + carry;
+      sum[i] = (uint32_t)t;
+      if ((uint32_t)t) top = (int)i;
+      carry = t >> 32;
+    }
+    auto reaches = [&](uint32_t key) {  // key^2 >= sum, compared limb by limb from the top
+      const SquareLimbs sl = square_limbs(key);
+      const int from = max(top, (int)sl.word + 2);
+      for (int i = from; i >= 0; --i) {
+        const uint32_t j = (uint32_t)i - sl.word;  // wraps to a large value below sl.word
+        const uint32_t mine = j == 0u ? sl.part[0] : (j == 1u ? sl.part[1] : (j == 2u ? sl.part[2] : 0u));
+        const uint32_t theirs = sum[i];
+        if (mine != theirs) return mine > theirs;
+      }
+      return true;
+    };
+    uint32_t lo = 0, hi = 0x7F7FFFFFu;
+    if (!reaches(hi)) {
+      *flags |= CVLC_DEV_NONFINITE;  // the norm overflows fp32
+      lo = hi;
+    } else if (top >= 0) {
+      // a floating-point estimate from the three top limbs brackets the answer within a few
+      // patterns; the exact comparison decides, and the full range stays as the fallback
+      double head = (double)sum[top];
+      if (top >= 1) head = head * 4294967296.0 + (double)sum[top - 1];
+      if (top >= 2) head = head * 4294967296.0 + (double)sum[top - 2];
+      const float guess = (float)sqrt(ldexp(head, 32 * (top - (top >= 2 ? 2 : top)) - 298));
+      const uint32_t g = min(__float_as_uint(guess), 0x7F7FFFFFu);
+      const uint32_t glo = g > 2u ? g - 2u : 0u, ghi = g < 0x7F7FFFFDu ? g + 2u : 0x7F7FFFFFu;
+      if (reaches(ghi) && (glo == 0u || !reaches(glo - 1u))) {
+        lo = glo;
+        hi = ghi;
+      }
+    } else {
+      hi = 0;  // an all-zero group
+    }
+    while (lo < hi) {
+      const uint32_t mid = lo + (hi - lo) / 2u;
+      if (reaches(mid)) hi = mid; else lo = mid + 1u;
+    }
+    v.norm = __uint_as_float(lo);
+  }
+  if (quant == CVLC_QUANT_QSGD) {  // levels 0 .. s on [0, norm]: the same spacing rule with s = 2^(y-1) - 1 steps
+    centroid_spacing(0.0f, v.norm, y == 32 ? 1u : y - 1u, &v.step, &v.inv);
+    v.low = 0.0f;
+  } else {
+    centroid_spacing(v.m, v.M, y == 32 ? 1u : y, &v.step, &v.inv);
+    v.low = v.m;
+  }
+  return v;
+}
+
+// A group's header, and its statistics but for the error energy, which the packing pass adds to.
+__device__ __forceinline__ void write_group(const ClientParams& p, uint32_t client, uint32_t r, const GroupValues& v, double sumsq, uint32_t quant,
+                                            cvlc_seg_stats_t* stats_out) {
+  GlobalWordPtr hdr = (GlobalWordPtr)p.stream + kGlobalHeaderWords + kSegHeaderWords * r;
+  hdr[0] = v.y;
+  hdr[1] = v.P;
+  hdr[2] = quant == CVLC_QUANT_QSGD ? __float_as_uint(v.norm) : __float_as_uint(v.m);
+  hdr[3] = quant == CVLC_QUANT_QSGD ? 0u : __float_as_uint(v.M);
+  if (stats_out) {
+    cvlc_seg_stats_t* st = stats_out + (size_t)client * kStatsStride + r;
+    st->min = v.m; st->max = v.M; st->sumsq = sumsq; st->count = v.P; st->reserved = 0;
+  }
+}
+
+// One thread: the stream's header, and the statistics of what is dropped.
+__device__ __forceinline__ void write_global(const ClientParams& p, uint32_t client, uint32_t d, double dropped, uint32_t quant,
+                                             cvlc_seg_stats_t* stats_out) {
+  GlobalWordPtr stream = (GlobalWordPtr)p.stream;
+  stream[0] = kMagic;
+  stream[1] = kVersion | (quant << 16);
+  stream[2] = d;
+  stream[3] = p.R;
+  stream[4] = position_bits(d);
+  stream[5] = __float_as_uint(p.B);
+  stream[6] = p.client_id;
+  stream[7] = p.total_words;
+  if (stats_out) {
+    cvlc_seg_stats_t* st = stats_out + (size_t)client * kStatsStride + p.R;
+    st->min = 0.0f; st->max = 0.0f; st->sumsq = dropped; st->count = d - p.k; st->reserved = 0;
+    st->errsq = dropped;  // dropped whole
+  }
+}
+
+// One whole wavefront, lanes 0 .. 31: first stream word of a group's records, the exclusive prefix of the payload sizes.
+__device__ __forceinline__ uint32_t group_payload(const ClientParams& p, uint32_t sbits) {
+  const uint32_t r = lane_id();
+  uint32_t words = 0;
+  if (r < p.R) words = (uint32_t)payload_words(p.Z[r] - (r ? p.Z[r - 1] : 0u), sbits + p.y[r]);
+  const uint32_t incl = wave_incl_scan_u32(words);
+  return kGlobalHeaderWords + kSegHeaderWords * p.R + incl - words;
+}
 
 // One workgroup of 1024 threads per client.  Turns the per-span counts of the
 // groups into exclusive prefixes (in place; the row after the last span
@@ -1758,14 +2039,14 @@ __global__ __launch_bounds__(kWideBlock) void layout_kernel(const ClientParams* 
     }
     if (tid == R) s_dropped = enc_sumsq;
   }
+  const uint32_t my_group = min(tid, CVLC_MAX_CODED - 1u), my_y = p.y[my_group];
+  const uint32_t my_P = p.Z[my_group] - (my_group ? p.Z[my_group - 1u] : 0u);
   const double* rsq = ws.region_sumsq + (size_t)client * ws.n_regions;  // energy the filter dropped, region by region
   const double tail0 = tid < ws.n_regions ? rsq[tid] : 0.0;
   const double tail1 = tid + kWideBlock < ws.n_regions ? rsq[tid + kWideBlock] : 0.0;
-  if (tid < 32) {  // first stream word of every group's records: exclusive prefix of the payload sizes
-    uint32_t words = 0;
-    if (tid < R) words = (uint32_t)payload_words(p.Z[tid] - (tid ? p.Z[tid - 1] : 0u), sbits + p.y[tid]);
-    const uint32_t incl = wave_incl_scan_u32(words);
-    s_payload[tid] = kGlobalHeaderWords + kSegHeaderWords * R + incl - words;
+  if (wave == 0) {
+    const uint32_t payload = group_payload(p, sbits);
+    if (lane < 32u) s_payload[lane] = payload;
   }
   __syncthreads();
   // Exclusive prefix of the per-span counts over the spans, per group, in place.
@@ -1872,107 +2153,24 @@ __global__ __launch_bounds__(kWideBlock) void layout_kernel(const ClientParams* 
 
   if (tid < R) {
     const uint32_t r = tid;
-    const uint32_t P = p.Z[r] - (r ? p.Z[r - 1] : 0u);
-    float m = 0.0f, M = 0.0f;
-    if (P > 0 && enc_max != 0) {
-      M = from_ordered_bits(enc_max);
-      m = from_ordered_bits(~enc_negmin);
-    } else if (P > 0) {
-      atomicOr(ws.status, CVLC_DEV_INTERNAL);
-    }
-    if (!(fabsf(M - m) <= 3.4028234664e38f)) atomicOr(ws.status, CVLC_DEV_NONFINITE);
-    float norm = 0.0f;
-    if (quant == CVLC_QUANT_QSGD) {
-      // carry the 64-bit counters into 32-bit limbs, then look for the smallest fp32 value whose
-      // square reaches the sum: squares grow with the bit pattern, so a binary search over it
-      const unsigned long long* src = ws.norm_limbs + ((size_t)client * 32 + r) * kNormLimbs;
-      unsigned long long carry = 0;
-      int top = -1;  // highest limb that is not zero
-      for (uint32_t i = 0; i < kNormLimbs; ++i) {
-        const unsigned long long t = src[i] + carry;
-        s_sum[r][i] = (uint32_t)t;
-        if ((uint32_t)t) top = (int)i;
-        carry = t >> 32;
-      }
-      auto reaches = [&](uint32_t key) {  // key^2 >= sum, compared limb by limb from the top
-        const SquareLimbs sl = square_limbs(key);
-        const int from = max(top, (int)sl.word + 2);
-        for (int i = from; i >= 0; --i) {
-          const uint32_t j = (uint32_t)i - sl.word;  // wraps to a large value below sl.word
-          const uint32_t mine = j < 3u ? sl.part[j] : 0u;
-          const uint32_t theirs = s_sum[r][i];
-          if (mine != theirs) return mine > theirs;
-        }
-        return true;
-      };
-      uint32_t lo = 0, hi = 0x7F7FFFFFu;
-      if (!reaches(hi)) {
-        atomicOr(ws.status, CVLC_DEV_NONFINITE);  // the norm overflows fp32
-        lo = hi;
-      } else if (top >= 0) {
-        // a floating-point estimate from the three top limbs brackets the answer within a few
-        // patterns; the exact comparison decides, and the full range stays as the fallback
-        double head = (double)s_sum[r][top];
-        if (top >= 1) head = head * 4294967296.0 + (double)s_sum[r][top - 1];
-        if (top >= 2) head = head * 4294967296.0 + (double)s_sum[r][top - 2];
-        const float guess = (float)sqrt(ldexp(head, 32 * (top - (top >= 2 ? 2 : top)) - 298));
-        const uint32_t g = min(__float_as_uint(guess), 0x7F7FFFFFu);
-        const uint32_t glo = g > 2u ? g - 2u : 0u, ghi = g < 0x7F7FFFFDu ? g + 2u : 0x7F7FFFFFu;
-        if (reaches(ghi) && (glo == 0u || !reaches(glo - 1u))) {
-          lo = glo;
-          hi = ghi;
-        }
-      } else {
-        hi = 0;  // an all-zero group
-      }
-      while (lo < hi) {
-        const uint32_t mid = lo + (hi - lo) / 2u;
-        if (reaches(mid)) hi = mid; else lo = mid + 1u;
-      }
-      norm = __uint_as_float(lo);
-    }
-    GlobalWordPtr hdr = stream + kGlobalHeaderWords + kSegHeaderWords * r;
-    hdr[0] = p.y[r];
-    hdr[1] = P;
-    hdr[2] = quant == CVLC_QUANT_QSGD ? __float_as_uint(norm) : __float_as_uint(m);
-    hdr[3] = quant == CVLC_QUANT_QSGD ? 0u : __float_as_uint(M);
-    if (stats_out) {
-      cvlc_seg_stats_t* st = stats_out + (size_t)client * kStatsStride + r;
-      st->min = m; st->max = M; st->sumsq = enc_sumsq; st->count = P; st->reserved = 0;
-      st->errsq = 0.0;  // the pack kernel adds the group's error energy when asked to
-    }
+    uint32_t flags = 0;
+    const GroupValues v = group_values(my_P, my_y, enc_max, enc_negmin, quant, ws.norm_limbs + ((size_t)client * 32 + r) * kNormLimbs, s_sum[r], &flags);
+    write_group(p, client, r, v, enc_sumsq, quant, stats_out);
+    if (stats_out) stats_out[(size_t)client * kStatsStride + r].errsq = 0.0;  // the pack kernel adds the group's error energy when asked to
     GroupInfo* gi = ws.group_info + client;
-    float step, inv;
-    if (quant == CVLC_QUANT_QSGD) {  // levels 0 .. s on [0, norm]: the same spacing rule with s = 2^(y-1) - 1 steps
-      centroid_spacing(0.0f, norm, p.y[r] == 32 ? 1u : p.y[r] - 1u, &step, &inv);
-      m = 0.0f;
-    } else {
-      centroid_spacing(m, M, p.y[r] == 32 ? 1u : p.y[r], &step, &inv);
-    }
     gi->payload[r] = s_payload[r];
-    gi->P[r] = P;
-    gi->W[r] = sbits + p.y[r];
-    gi->y[r] = p.y[r];
-    gi->m[r] = m;
-    gi->inv[r] = inv;
-    gi->step[r] = step;
+    gi->P[r] = v.P;
+    gi->W[r] = sbits + v.y;
+    gi->y[r] = v.y;
+    gi->m[r] = v.low;
+    gi->inv[r] = v.inv;
+    gi->step[r] = v.step;
+    if (flags) atomicOr(ws.status, flags);
   }
   if (tid == 32) {
-    stream[0] = kMagic;
-    stream[1] = kVersion | (quant << 16);
-    stream[2] = ws.d;
-    stream[3] = R;
-    stream[4] = sbits;
-    stream[5] = __float_as_uint(p.B);
-    stream[6] = p.client_id;
-    stream[7] = p.total_words;
-    if (stats_out) {
-      double tail = 0.0;
-      for (uint32_t w = 0; w < kWideWaves; ++w) tail += s_tail[w];
-      cvlc_seg_stats_t* st = stats_out + (size_t)client * kStatsStride + R;
-      st->min = 0.0f; st->max = 0.0f; st->sumsq = tail + s_dropped; st->count = ws.d - p.k; st->reserved = 0;
-      st->errsq = st->sumsq;  // dropped whole
-    }
+    double dropped = s_dropped;
+    for (uint32_t w = 0; w < kWideWaves; ++w) dropped += s_tail[w];
+    write_global(p, client, ws.d, dropped, quant, stats_out);
   }
 }
 
@@ -2021,6 +2219,8 @@ __device__ __forceinline__ uint32_t quantise(float x, float m, float inv, uint32
 
 
 constexpr uint32_t kChunkCands = kSpan * kChunkSpans;         // 4096
+constexpr uint32_t kShortSpans = kShortMax / kSpan;
+static_assert(kShortSpans % (kEmitBlock / 32u) == 0, "a short vector's spans are dealt out to the threads evenly");
 constexpr uint32_t kEdgeChunks = 8;                           // chunks whose shared stream words a workgroup holds back
 constexpr uint32_t kStageWords = kChunkCands * 2 + 2 * 32;    // every record is < 64 bits; two edge words per group
 
@@ -2043,8 +2243,10 @@ struct alignas(16) EmitGroup {  // per (chunk, group)
 // the statistics block (Lemma 1's left side for this draw), xtilde being the
 // centroid value the decoder will compute from the header.
 // QSGD: the code is the level of |x| on [0, norm] with the sign bit above it.
-template <bool ERR, bool QSGD>
-__global__ __launch_bounds__(kEmitBlock, 6) void emit_kernel(const ClientParams* __restrict__ params,
+// SHORT: a short vector's coordinates in the candidates' place.  There is no layout launch: every workgroup adds up the
+// spans' counts and the groups' statistics for itself (a few KB), a client's first one also writes its headers.
+template <bool ERR, bool QSGD, bool SHORT>
+__global__ __launch_bounds__(kEmitBlock, SHORT ? 4 : 6) void emit_kernel(const ClientParams* __restrict__ params,
                                                           ClientCtl* __restrict__ ctls, Workspace ws, uint64_t seed,
                                                           cvlc_seg_stats_t* __restrict__ stats_out) {
   __shared__ double s_err[ERR ? kEmitWaves : 1][32];  // per wavefront, per group
@@ -2063,6 +2265,9 @@ __global__ __launch_bounds__(kEmitBlock, 6) void emit_kernel(const ClientParams*
   // issued together.
   __shared__ uint32_t s_edge_word[kEdgeChunks][32][2];  // the bits; 0: nothing to OR
   __shared__ uint32_t s_edge_at[kEdgeChunks][32][2];    // the stream word they belong to
+  __shared__ uint32_t s_prefix[SHORT ? kShortSpans + 1u : 1u][32];  // members of every group in the spans before
+  __shared__ uint32_t s_part[SHORT ? kEmitBlock / 32u : 1u][32];
+  __shared__ uint32_t s_sum[SHORT && QSGD ? 32 : 1][kNormLimbs];
   // Workgroups are dispatched in the order of their linear index and a CU serves its oldest first: the
   // clients' workgroups are interleaved in that order, so that every client has workgroups of every age.
   const uint32_t linear = blockIdx.y * gridDim.x + blockIdx.x;
@@ -2070,11 +2275,12 @@ __global__ __launch_bounds__(kEmitBlock, 6) void emit_kernel(const ClientParams*
   const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
   const ClientParams& p = params[client];
   ClientCtl* ctl = ctls + client;
+  if (SHORT && block_x == 0 && tid == 0 && ctl->flags) atomicOr(ws.status, ctl->flags);
   if (ctl->dead) return;  // the workspace was too short for this client (whole workgroup)
-  const uint32_t n = ctl->n_cand;
+  const uint32_t n = SHORT ? ws.d : ctl->n_cand;
   const uint32_t n_spans = (n + kSpan - 1) / kSpan;
   const uint32_t R = p.R, sbits = position_bits(ws.d);
-  const uint32_t* __restrict__ val = ws.dense_val + (size_t)client * ws.dense_cap;
+  const uint32_t* __restrict__ val = SHORT ? (const uint32_t*)(GlobalConstWordPtr)p.update : ws.dense_val + (size_t)client * ws.dense_cap;
   const uint32_t* __restrict__ idx = ws.dense_idx + (size_t)client * ws.dense_cap;
   const uint16_t* __restrict__ place = span_places(ws, client);
   const uint32_t* __restrict__ prefix = ws.span_cnt + (size_t)client * (ws.max_spans + 1) * 32;
@@ -2083,7 +2289,60 @@ __global__ __launch_bounds__(kEmitBlock, 6) void emit_kernel(const ClientParams*
 
   uint32_t my_P = 0, my_W = 0, my_y = 0;
   float my_m = 0.0f, my_inv = 0.0f, my_step = 0.0f;
-  if (tid < 32 && tid < R) {
+  if constexpr (SHORT) {
+    // the spans' counts: a thread takes group tid mod 32 of eight neighbouring spans
+    constexpr uint32_t kSpansEach = kShortSpans / (kEmitBlock / 32u);
+    const uint32_t g = tid % 32u, part = tid / 32u;
+    uint32_t c[kSpansEach], sum = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kSpansEach; ++i) {
+      const uint32_t span = part * kSpansEach + i;
+      c[i] = prefix[(size_t)min(span, n_spans - 1u) * 32 + g];
+      c[i] = span < n_spans ? c[i] : 0u;
+    }
+    const uint32_t my_group = min(tid, CVLC_MAX_CODED - 1u), y = p.y[my_group], P = p.Z[my_group] - (my_group ? p.Z[my_group - 1u] : 0u);
+    uint32_t enc_max = 0, enc_negmin = 0, flags = 0;
+    double sumsq = 0.0;
+    if (tid <= R) {  // entry R: what is dropped
+#pragma unroll
+      for (uint32_t i = 0; i < kSegCopies; ++i) {
+        enc_max = max(enc_max, ctl->seg[i].max_enc[tid]);
+        enc_negmin = max(enc_negmin, ctl->seg[i].negmin_enc[tid]);
+        sumsq += ctl->seg[i].sumsq[tid];
+      }
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < kSpansEach; ++i) sum += c[i];
+    s_part[part][g] = sum;
+    if (wave == 0) {
+      const uint32_t payload = group_payload(p, sbits);
+      if (lane < 32u) s_payload[lane] = payload;
+    }
+    __syncthreads();
+    uint32_t run = 0;
+    for (uint32_t i = 0; i < part; ++i) run += s_part[i][g];
+#pragma unroll
+    for (uint32_t i = 0; i < kSpansEach; ++i) {
+      s_prefix[part * kSpansEach + i][g] = run;
+      run += c[i];
+    }
+    if (part == kEmitBlock / 32u - 1u) s_prefix[kShortSpans][g] = run;
+    if (tid < R) {
+      const GroupValues gv = group_values(P, y, enc_max, enc_negmin, QSGD ? CVLC_QUANT_QSGD : CVLC_QUANT_PQ,
+                                          ws.norm_limbs + ((size_t)client * 32 + tid) * kNormLimbs, s_sum[QSGD ? tid : 0u], &flags);
+      my_P = gv.P;
+      my_W = sbits + y;
+      my_y = y;
+      my_m = gv.low;
+      my_inv = gv.inv;
+      my_step = gv.step;
+      if (block_x == 0) write_group(p, client, tid, gv, sumsq, QSGD ? CVLC_QUANT_QSGD : CVLC_QUANT_PQ, stats_out);
+    }
+    if (block_x == 0 && tid == R) write_global(p, client, ws.d, sumsq, QSGD ? CVLC_QUANT_QSGD : CVLC_QUANT_PQ, stats_out);
+    __syncthreads();
+    if (tid < R && s_prefix[kShortSpans][tid] != my_P) flags |= CVLC_DEV_INTERNAL;  // spans past the last are empty
+    if (block_x == 0 && flags) atomicOr(ws.status, flags);
+  } else if (tid < 32 && tid < R) {
     const GroupInfo* gi = ws.group_info + client;
     my_P = gi->P[tid];
     my_W = gi->W[tid];
@@ -2102,11 +2361,12 @@ __global__ __launch_bounds__(kEmitBlock, 6) void emit_kernel(const ClientParams*
   auto ask_prefix = [&](uint32_t c) {
     if (!chunk_exists(c)) return;  // uniform
     const uint32_t span = c * kChunkSpans + wave;
-    if (lane < 32) ahead_row = span < n_spans ? prefix[(size_t)span * 32 + lane] : 0u;
+    auto row = [&](uint32_t sp, uint32_t g) { return SHORT ? s_prefix[sp][g] : prefix[(size_t)sp * 32 + g]; };
+    if (lane < 32) ahead_row = span < n_spans ? row(span, lane) : 0u;
     if (tid < R && tid < 32) {
       const uint32_t last_span = min((c + 1) * kChunkSpans, n_spans);
-      ahead_first = prefix[(size_t)c * kChunkSpans * 32 + tid];
-      ahead_last = prefix[(size_t)last_span * 32 + tid];
+      ahead_first = row(c * kChunkSpans, tid);
+      ahead_last = row(last_span, tid);
     }
   };
   // Value bits, position and place of the candidates of the wavefront's span.  Unconditional loads (a
@@ -2119,7 +2379,7 @@ __global__ __launch_bounds__(kEmitBlock, 6) void emit_kernel(const ClientParams*
       const uint32_t i = (c * kChunkSpans + wave) * kSpan + j * kWave + lane;
       const uint32_t at = min(i, n - 1u);
       v[j] = val[at];
-      pid[j] = idx[at];
+      pid[j] = SHORT ? i : idx[at];
       plc[j] = i < n ? (uint32_t)place[at] : (uint32_t)kNoPlace;
     }
   };
@@ -2393,6 +2653,11 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const uint32_t d = plans[0].d;
   const EncodeLayout L = encode_layout(d, n, candidate_room(d, n, ws_bytes));
+  const ShortLayout SL = short_layout(d, n);
+  // Short vectors take three launches instead of ten, whatever their number: 1 x 2000 52 -> 25 us, 1 x 65 536 59 -> 40 (31
+  // groups 64 -> 48), 32 x 65 536 76 -> 46, 100 x 65 536 116 -> 82, 1000 x 65 536 707 -> 563 (3 % kept: 516 either way).  Beyond
+  // 65 536 coordinates a position takes more than 16 bits in the list, and two passes of one workgroup 10 us more for every 65 536.
+  const bool is_short = d <= kShortMax && SL.total <= ws_bytes;
   char* base = static_cast<char*>(d_workspace);
   Workspace ws;
   ws.status = reinterpret_cast<uint32_t*>(base + L.status);
@@ -2422,6 +2687,15 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
   ws.gather_blocks = L.gather_blocks;
   ws.member_pool = L.member_pool;
   ws.hist_copies = L.hist_copies;
+  if (is_short) {
+    ws.status = reinterpret_cast<uint32_t*>(base + SL.status);
+    ws.params = reinterpret_cast<ClientParams*>(base + SL.params);
+    ws.ctl = reinterpret_cast<ClientCtl*>(base + SL.ctl);
+    ws.norm_limbs = reinterpret_cast<unsigned long long*>(base + SL.norm_limbs);
+    ws.cand_idx = reinterpret_cast<uint16_t*>(base + SL.places);
+    ws.span_cnt = reinterpret_cast<uint32_t*>(base + SL.span_cnt);
+    ws.max_spans = SL.max_spans;
+  }
 
   // sample geometry: 256-byte pieces spread evenly; all of them when the vector is short
   const uint32_t n_src = d / kSamplePiece;
@@ -2429,7 +2703,11 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
 
   profile_mark(CVLC_STAGE_ENC_SETUP, true, stream);
   // the status word and the control blocks start every call at zero
-  uint32_t zero_n16 = (uint32_t)(L.zero_bytes / 16u);  // n <= 65535 clients: below 2^32 pieces
+  uint32_t zero_n16 = (uint32_t)((is_short ? SL.ctl : L.zero_bytes) / 16u);  // n <= 65535 clients: below 2^32 pieces
+  auto short_select = [&](auto source, uint32_t clients, bool first) {
+    hipLaunchKernelGGL(short_select_kernel<decltype(source)>, dim3(clients), dim3(kShortBlock), 0, stream, source, ws.params, ws.ctl, ws,
+                       d_stats_out, first ? 1u : 0u);
+  };
 
   // per-client parameters, shipped as kernel arguments
   uint32_t max_R = 0;
@@ -2440,8 +2718,14 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
     chunk.n_templates = 0;
     chunk.pad = 0;
     uint32_t refs[kUploadWords];  // the chunk's references, appended behind its templates when it is sent
-    auto send = [&]() {
+    bool one_chunk = true;  // all clients' parameters fit one launch's arguments
+    auto send = [&](bool last) {
       std::memcpy(&chunk.data[chunk.n_templates * kParamWords], refs, (size_t)chunk.n_clients * kRefWords * 4u);
+      one_chunk = one_chunk && last;
+      if (is_short && one_chunk) {
+        short_select(chunk, chunk.n_clients, true);
+        return;
+      }
       const uint32_t blocks = zero_n16 ? (zero_n16 + 1023u) / 1024u : 1u;
       hipLaunchKernelGGL(upload_kernel, dim3(blocks < 512u ? blocks : 512u), dim3(256), 0, stream,
                          reinterpret_cast<uint32_t*>(ws.params), chunk, reinterpret_cast<uint4*>(base + L.status),
@@ -2472,7 +2756,7 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
         while (t < chunk.n_templates && std::memcmp(&chunk.data[t * kParamWords], &cp, sizeof(cp)) != 0) ++t;
         const uint32_t templates = t == chunk.n_templates ? t + 1 : chunk.n_templates;
         if (templates * kParamWords + (chunk.n_clients + 1) * kRefWords > kUploadWords) {
-          send();  // no room: this client opens the next chunk (which always has room for one)
+          send(false);  // no room: this client opens the next chunk (which always has room for one)
           continue;
         }
         if (t == chunk.n_templates) {
@@ -2491,44 +2775,46 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
         break;
       }
     }
-    if (chunk.n_clients) send();
+    if (chunk.n_clients) send(true);
+    if (is_short && !one_chunk) short_select(ParamsUploaded{ws.params}, n, false);
   }
   profile_mark(CVLC_STAGE_ENC_SETUP, false, stream);
 
-  {
-    StageScope scope(CVLC_STAGE_ENC_SAMPLE, stream);
-    // also for plans that keep everything: the selection bins are laid out by the sample.  n_src < 2^26 and n_s <= 2^12: the step is below 2^58 / n_s and j * step below 2^58
-    if (n_s)
-      hipLaunchKernelGGL(sample_hist_kernel, dim3(kSampleBlocks, n), dim3(kBlock), 0, stream, ws.params, ws.ctl, n_s,
-                         ((uint64_t)n_src << 32) / n_s);
-    hipLaunchKernelGGL(sample_walk_kernel, dim3(n), dim3(kWideBlock), 0, stream, ws.params, ws.ctl);
-  }
-  {
-    StageScope scope(CVLC_STAGE_ENC_FILTER, stream);
-    hipLaunchKernelGGL(filter_kernel, dim3(ws.filter_blocks, n), dim3(kBlock), 0, stream, ws.params, ws.ctl, ws);
-  }
-  {
-    StageScope scope(CVLC_STAGE_ENC_REFILTER, stream);
-    hipLaunchKernelGGL(scan_l1_kernel, dim3(n), dim3(kWideBlock), 0, stream, ws.params, ws.ctl, ws);
-  }
-  {
-    StageScope scope(CVLC_STAGE_ENC_SELECT, stream);
-    // the gather also builds the dense candidate list (also when nothing is coded)
-    hipLaunchKernelGGL(gather_kernel, dim3(L.gather_blocks, n), dim3(kGatherBlock), 0, stream, ws.params, ws.ctl, ws);
-    if (max_R)
-      hipLaunchKernelGGL(select_kernel, dim3(max_R, n), dim3(kSelectBlock), 0, stream, ws.params, ws.ctl, ws);
+  if (!is_short) {
+    {
+      StageScope scope(CVLC_STAGE_ENC_SAMPLE, stream);
+      // also for plans that keep everything: the selection bins are laid out by the sample.  n_src < 2^26 and n_s <= 2^12: the step is below 2^58 / n_s and j * step below 2^58
+      if (n_s)
+        hipLaunchKernelGGL(sample_hist_kernel, dim3(kSampleBlocks, n), dim3(kBlock), 0, stream, ws.params, ws.ctl, n_s,
+                           ((uint64_t)n_src << 32) / n_s);
+      hipLaunchKernelGGL(sample_walk_kernel, dim3(n), dim3(kWideBlock), 0, stream, ws.params, ws.ctl);
+    }
+    {
+      StageScope scope(CVLC_STAGE_ENC_FILTER, stream);
+      hipLaunchKernelGGL(filter_kernel, dim3(ws.filter_blocks, n), dim3(kBlock), 0, stream, ws.params, ws.ctl, ws);
+    }
+    {
+      StageScope scope(CVLC_STAGE_ENC_REFILTER, stream);
+      hipLaunchKernelGGL(scan_l1_kernel, dim3(n), dim3(kWideBlock), 0, stream, ws.params, ws.ctl, ws);
+    }
+    {
+      StageScope scope(CVLC_STAGE_ENC_SELECT, stream);
+      // the gather also builds the dense candidate list (also when nothing is coded)
+      hipLaunchKernelGGL(gather_kernel, dim3(L.gather_blocks, n), dim3(kGatherBlock), 0, stream, ws.params, ws.ctl, ws);
+      if (max_R)
+        hipLaunchKernelGGL(select_kernel, dim3(max_R, n), dim3(kSelectBlock), 0, stream, ws.params, ws.ctl, ws);
+    }
   }
   // count: wavefronts walk the spans; about what the device holds at once (four workgroups per CU)
   uint32_t g_count = (1024u + n - 1) / n;
-  if (g_count > (L.max_spans + kEmitWaves - 1) / kEmitWaves) g_count = (L.max_spans + kEmitWaves - 1) / kEmitWaves;
+  if (g_count > (ws.max_spans + kEmitWaves - 1) / kEmitWaves) g_count = (ws.max_spans + kEmitWaves - 1) / kEmitWaves;
   {
     StageScope scope(CVLC_STAGE_ENC_CLASSIFY, stream);
-    if (quant == CVLC_QUANT_QSGD)
-      hipLaunchKernelGGL(count_kernel<true>, dim3(g_count, n), dim3(kEmitBlock), 0, stream, ws.params, ws.ctl, ws);
-    else
-      hipLaunchKernelGGL(count_kernel<false>, dim3(g_count, n), dim3(kEmitBlock), 0, stream, ws.params, ws.ctl, ws);
+    auto kernel = quant == CVLC_QUANT_QSGD ? (is_short ? count_kernel<true, true> : count_kernel<true, false>)
+                                           : (is_short ? count_kernel<false, true> : count_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, dim3(g_count, n), dim3(kEmitBlock), 0, stream, ws.params, ws.ctl, ws);
   }
-  {
+  if (!is_short) {
     StageScope scope(CVLC_STAGE_ENC_LAYOUT, stream);
     hipLaunchKernelGGL(layout_kernel, dim3(n), dim3(kWideBlock), 0, stream, ws.params, ws.ctl, ws, d_stats_out, quant);
   }
@@ -2536,11 +2822,15 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
     // emit: workgroups walk the chunks; about what the device holds at once (three per CU)
     StageScope scope(CVLC_STAGE_ENC_EMIT, stream);
     uint32_t g_emit = (768u + n - 1) / n;
-    const uint32_t max_chunks = (L.max_spans + kChunkSpans - 1) / kChunkSpans;
+    const uint32_t max_chunks = (ws.max_spans + kChunkSpans - 1) / kChunkSpans;
     if (g_emit > max_chunks) g_emit = max_chunks;
     const bool err = flags & CVLC_ENCODE_ERROR_STATS, qsgd = quant == CVLC_QUANT_QSGD;
-    auto kernel = err ? (qsgd ? emit_kernel<true, true> : emit_kernel<true, false>)
-                      : (qsgd ? emit_kernel<false, true> : emit_kernel<false, false>);
+    auto choose = [&](auto short_vectors) {
+      constexpr bool kShort = decltype(short_vectors)::value;
+      return err ? (qsgd ? emit_kernel<true, true, kShort> : emit_kernel<true, false, kShort>)
+                 : (qsgd ? emit_kernel<false, true, kShort> : emit_kernel<false, false, kShort>);
+    };
+    auto kernel = is_short ? choose(std::true_type{}) : choose(std::false_type{});
     hipLaunchKernelGGL(kernel, dim3(g_emit, n), dim3(kEmitBlock), 0, stream, ws.params, ws.ctl, ws, seed, d_stats_out);
   }
   return hip_check(hipGetLastError());

@@ -275,6 +275,58 @@ def test_selection_bins(d, kind, share):
     check_encode([U], [p], 17, [4])
 
 
+SHORT_MAX = 65_536  # vectors up to here are selected by one workgroup
+
+
+@pytest.mark.parametrize("R", [1, 7, 31])
+@pytest.mark.parametrize("kind", ["plain", "bfloat16", "few values", "zeros", "one outlier"])
+@pytest.mark.parametrize("d", [4097, 40_003, SHORT_MAX - 1, SHORT_MAX, SHORT_MAX + 1])
+def test_short_vectors(d, kind, R):
+    """Half of the coordinates kept: boundaries among distinct keys, pairs of equal ones, and classes larger than what is
+    set aside, which are counted by parts of the vector."""
+    U = _selection_vectors(kind, d, np.random.default_rng(d + R))
+    counts = [max(1, d * (r + 1) // (R * (R + 1))) for r in range(R)]
+    p = orc.plan_manual(d, [max(1, 14 - r // 2) for r in range(R)], counts)
+    check_encode([U], [p], 19, [6])
+    q = orc.plan_manual(d, [max(2, 14 - r // 2) for r in range(R)], counts, quant=orc.QSGD)
+    words, _, status, _ = gpu_encode([U], [q], 20, [7], error_stats=True)
+    assert status == 0
+    assert_stream_equal(words[0], orc.encode(U, q, 20, 7).words)
+
+
+def test_short_vectors_of_many_plans():
+    """More different plans than one launch's arguments hold, groups of no coordinates among them."""
+    d, n = 3001, 45
+    rng = np.random.default_rng(9)
+    host = [_selection_vectors("plain", d, rng) for _ in range(n)]
+    plans = [orc.plan_manual(d, [9, 6, 3], [0 if c % 5 == 0 else c, 40 + c, 0 if c % 7 == 0 else 300]) for c in range(n)]
+    check_encode(host, plans, 23, list(range(n)))
+
+
+def test_short_vectors_are_refused_by_the_same_rule():
+    """A vector has as many candidates as it has keys at or above the lower edge of the 13-bit bin that holds the sample's
+    rank-th largest, the sample being all but the last d mod 64 coordinates; a workspace with less room refuses it."""
+    d, k = 50_047, 9_000
+    rng = np.random.default_rng(31)
+    U = rng.standard_normal(d).astype(np.float32)
+    key = U.view(np.uint32) & np.uint32(0x7FFFFFFF)
+    sampled = d // 64 * 64
+    E = k * sampled / d
+    rank = int(np.ceil(E + 6.0 * np.sqrt(E) + 16.0))
+    edge = (np.sort(key[:sampled])[::-1][rank - 1] >> 18) << 18
+    c = int(np.count_nonzero(key >= edge))
+    p = to_lib_plan(orc.plan_manual(d, [8, 4], [k // 3, k - k // 3]))
+    slack = 512  # a workspace of so many bytes has room for a few hundred candidates more than it was asked for
+    for room, expected in ((c, 0), (c - slack, cv.DEV_WORKSPACE)):
+        stream = cv.new_stream_buffer(p, DEV)
+        stream.fill_(-1)
+        ws = cv.new_workspace(cv.encode_workspace_bytes_for(d, 1, room), DEV)
+        ws.fill_(255)
+        cv.encode_batch([p], [torch.from_numpy(U).to(DEV)], 21, [3], [stream], ws)
+        assert cv.device_status(ws) == expected
+        assert (int(stream[0].item()) == 0) == (expected != 0)
+
+
 def encode_stage_us(update, plan, stage, repeats=5):
     """Shortest time of a stage of an encode call, on a workspace full of ones: what the call before left there must not matter."""
     ws = cv.new_workspace(cv.encode_workspace_bytes(plan.d, 1), DEV)
