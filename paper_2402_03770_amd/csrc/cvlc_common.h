@@ -107,7 +107,10 @@ struct ClientCtl {
 };
 
 // ---- decoder -------------------------------------------------------------------
-constexpr uint32_t kDecTile = 4096;  // output coordinates per decode workgroup
+// A decode workgroup's tile has 4096 output coordinates, or 8192 in long vectors.
+constexpr uint32_t kDecShiftMin = 12, kDecShiftMax = 13;
+constexpr uint32_t kDecLargeFrom = 1u << 23;
+static_assert(kDecLargeFrom < (1u << 25), "positions of more than 25 bits: large tiles only");
 
 struct ListDesc {       // one (client, coded group) record list
   const uint32_t* payload;

@@ -20,6 +20,7 @@
 #include <cmath>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 
 #include "cvlc_common.h"
 
@@ -36,7 +37,7 @@ struct CompactDesc {  // one non-empty (client, group) record list, 32 bytes
   uint32_t wsy;   // W | s << 8 | y << 16
   float m, step;
 };
-static_assert(sizeof(CompactDesc) == 32, "CompactDesc is copied to LDS as two 16-byte pieces");
+static_assert(sizeof(CompactDesc) == 32, "CompactDesc is read as two 16-byte pieces");
 
 struct DecodeCtl {  // written by compact_lists
   uint32_t n_active;  // non-empty lists
@@ -45,7 +46,7 @@ struct DecodeCtl {  // written by compact_lists
 
 struct DecodeLayout {
   size_t status, ctl, stream_bad, desc, cdesc, item_start, table, total;
-  uint32_t n_tiles, n_lists;
+  uint32_t n_lists;
 };
 
 size_t align256(size_t v) { return (v + 255u) & ~(size_t)255u; }
@@ -58,9 +59,12 @@ struct StreamArg {  // per-stream inputs, passed as kernel arguments
   uint32_t pad;
 };
 
+uint32_t tiles_of(uint32_t d, uint32_t shift) { return (uint32_t)(((uint64_t)d + (1u << shift) - 1u) >> shift); }
+
+uint32_t tile_shift_for(uint32_t d) { return d >= kDecLargeFrom ? kDecShiftMax : kDecShiftMin; }
+
 DecodeLayout decode_layout(uint32_t d, uint32_t n) {
   DecodeLayout L;
-  L.n_tiles = (uint32_t)(((uint64_t)d + kDecTile - 1) / kDecTile);
   L.n_lists = n * kListsPerClient;
   size_t off = 0;
   L.status = off; off = align256(off + 256);
@@ -69,7 +73,7 @@ DecodeLayout decode_layout(uint32_t d, uint32_t n) {
   L.desc = off; off = align256(off + (size_t)L.n_lists * sizeof(ListDesc));
   L.cdesc = off; off = align256(off + (size_t)L.n_lists * sizeof(CompactDesc));
   L.item_start = off; off = align256(off + ((size_t)L.n_lists + 1) * sizeof(uint32_t));
-  L.table = off; off = align256(off + (size_t)(L.n_tiles + 1) * L.n_lists * sizeof(uint32_t));
+  L.table = off; off = align256(off + (size_t)(tiles_of(d, kDecShiftMin) + 1) * L.n_lists * sizeof(uint32_t));
   L.total = off;
   return L;
 }
@@ -304,7 +308,7 @@ template <bool WIDE>
 __global__ __launch_bounds__(kBlock, 8) void tile_table_kernel(const CompactDesc* __restrict__ cdesc,
                                                          const uint32_t* __restrict__ item_start,
                                                          const DecodeCtl* __restrict__ ctl, uint32_t* table,
-                                                         uint32_t d, uint32_t n_tiles, uint32_t n_lists, uint32_t* status) {
+                                                         uint32_t d, uint32_t tile_shift, uint32_t n_tiles, uint32_t n_lists, uint32_t* status) {
   const uint32_t tid = threadIdx.x, lane = lane_id();
   const uint32_t lead = n_lists <= kLeadLists ? item_start[min(lane, n_lists)] : 0u;  // the array has room for n_lists + 1
   const uint32_t n_active = ctl->n_active, n_items = ctl->n_items;
@@ -373,7 +377,7 @@ __global__ __launch_bounds__(kBlock, 8) void tile_table_kernel(const CompactDesc
       const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)carry, (int)pid, 0x138 /* wave_shr:1 */, 0xF, 0xF, false);
       carry = __builtin_amdgcn_readlane(pid, kWave - 1);
       // a position past the end (an error, reported below) counts as lying behind the last tile
-      const uint32_t t_cur = min(pid / kDecTile, n_tiles), t_prev = min(prev / kDecTile, n_tiles);
+      const uint32_t t_cur = min(pid >> tile_shift, n_tiles), t_prev = min(prev >> tile_shift, n_tiles);
       const bool first = e == 0, last = e == P - 1;
       bad |= live && ((!first && prev >= pid) || pid >= d);  // positions must ascend strictly and stay below d
       // entries (tile of record e-1, tile of record e] point at e; past the last record they hold P
@@ -418,32 +422,57 @@ __global__ __launch_bounds__(kBlock, 8) void tile_table_kernel(const CompactDesc
 
 // ------------------------------------------------------------------ 3. fused decode + accumulate
 // Persistent workgroups walk the output tiles, neighbouring tiles at the same
-// time on the same XCD (see tile_of below).  The records of a tile, over all lists, are numbered
-// 0..total-1 list by list (an exclusive scan of the slice lengths); every
-// wavefront takes a contiguous share of them, 64 at a time ("turn"), so the work
-// is even however the records are spread over the lists and neighbouring lanes
-// read neighbouring records.  Which list a lane's record belongs to: the
-// non-empty slices that start inside the turn set a bit at their first record's
-// place in a 64-bit mask, and a lane counts the bits at or below its own place;
-// only the wavefront's first record needs a search.  List descriptors sit in LDS.
+// time on the same XCD (see tile_of below).  The lists are dealt out to the wavefronts, up to 64 each, lane i the
+// list of one: lane i knows its list's descriptor and asks for the two table entries of its slice.  The
+// records of the wavefront's slices are numbered 0..total-1 (an exclusive scan of the slice lengths), and
+// the wavefront goes through them 64 at a time ("turn"), so that neighbouring lanes read neighbouring
+// records.  Which slice a lane's record belongs to: the slices that start inside the turn set a bit at their
+// first record's place in a 64-bit mask, and a lane counts the bits at or below its own place; what it needs of the
+// slice it reads from LDS.  Wavefronts wait for each other twice a tile only: before it is written out, and
+// before the next tile's first value is added.
+// What bounds it: latencies, and cache lines.  A pair of table entries, a descriptor and a slice's records are a line each,
+// however little of it is used, and a slice holds a handful of records.
+// Hence tiles of 8192 coordinates, two workgroups a CU, where they are enough to go round: from 2^23 coordinates on, two
+// tiles for every workgroup (us a call, tiles of 4096 and 8192: 100 x 25.6 M 550 and 407, 8 x 11.2 M 39.1 and 35.8, 32 x
+// 11.2 M Gauss 61.9 and 57.0, layers 68 and 68; 32 x 5 M 44 and 53, 8 x 5 M 24.7 and 26.3).  With the records shared out evenly
+// over all wavefronts, three barriers and a search a tile, and tiles of 4096: 600, 44.0, 69.3, 75, 48.5 and 28.7.
 constexpr uint32_t kChunkTiles = 16; // consecutive tiles decoded side by side on one XCD (more: less refetching, less even load)
-constexpr uint32_t kFirstBits = 22;  // a tile's records over one batch of lists are numbered below 2^22 ...
-constexpr uint32_t kFirstMask = (1u << kFirstBits) - 1u;
-constexpr uint32_t kListBits = 32u - kFirstBits;  // ... and the list of a slice fits above that number in one word
 
-constexpr uint32_t kDecBlock = 512;  // threads of a decode workgroup, three to a CU
+constexpr uint32_t kDecBlock = 512;  // threads of a decode workgroup
 constexpr uint32_t kDecWaves = kDecBlock / kWave;
-constexpr uint32_t kDecLists = kDecBlock;  // lists it handles per sweep, one per thread
-constexpr uint32_t kDecTurns = 6;    // turns of 64 records a wavefront works on together
-struct DecodeShared {
-  static_assert(kDecLists <= kDecBlock && (uint64_t)kDecLists * kDecTile < (1ull << kFirstBits) && kDecLists <= (1u << kListBits), "see kFirstBits");
-  double acc[kDecTile];
-  uint4 desc[kDecLists][2];            // CompactDesc, as loaded, but with the payload's words in the place of P
-  // per non-empty slice of the batch, in list order
-  uint32_t begin[kDecLists];           // first record of the slice inside its list
-  uint32_t first[kDecLists + 1];       // number of the slice's first record in the tile | list << kFirstBits; then the total
-  uint32_t scan_a[kDecWaves], scan_b[kDecWaves];
+constexpr uint32_t kWaveLists = 60;  // lists a wavefront has in a sweep at most (64 would not fit twice into a CU with the large tile)
+constexpr uint32_t kDecLists = kWaveLists * kDecWaves;  // ... and a workgroup
+
+// Turns of 64 records a wavefront works on together, in two halves: as many as the registers hold with three workgroups a CU
+// (small tiles) and with two (large ones, 64 KB of sums).
+constexpr uint32_t half_turns(uint32_t tile_shift) { return tile_shift == kDecShiftMin ? 3u : 4u; }
+
+// What the lanes need of a slice, set aside by the lane that owns its list.  `at` is a byte offset from `src`, eight
+// bytes before the byte in which the slice's first record starts (a stream's headers lie in front of its first payload, so the
+// bytes are there).
+struct SliceInfo {
+  uint4 where;  // src (two words); the bit offset from src of the record numbered 0; last `at` a load may use | W << 16 | y << 24
+  uint4 value;  // weight (two words), m, step
 };
+template <uint32_t SHIFT>
+struct DecodeShared {
+  double acc[1u << SHIFT];
+  SliceInfo slice[kDecWaves][kWaveLists];  // per wavefront: its non-empty slices, in order
+  unsigned long long turn_mask[kDecWaves][2u * half_turns(SHIFT)];  // ... and the starts of slices inside each of its current turns
+};
+static_assert(((1u << kDecShiftMax) + kWave) * 63u / 8u + 8u < (1u << 16), "a slice's bytes are counted in 16 bits");
+static_assert(((uint64_t)kWaveLists << kDecShiftMax) + kWave < (1u << 24), "a wavefront's records are numbered in 24 bits");
+
+// Inclusive prefix sum over the 64 lanes, all of them active: adds within rows of sixteen, then across (no LDS round trips).
+__device__ __forceinline__ uint32_t wave_incl_scan_rows(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111 /* row_shr:1 */, 0xF, 0xF, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112 /* row_shr:2 */, 0xF, 0xF, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114 /* row_shr:4 */, 0xF, 0xF, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118 /* row_shr:8 */, 0xF, 0xF, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142 /* row_bcast:15 */, 0xA, 0xF, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143 /* row_bcast:31 */, 0xC, 0xF, false);
+  return v;
+}
 
 // LDS accesses of one wavefront complete in order; this keeps the compiler from
 // moving them across the point where lanes read what other lanes wrote.
@@ -451,31 +480,43 @@ __device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOM
 
 // SIGNED: the streams' codes hold a sign bit above the level (QSGD).
 // WIDE: positions of more than 25 bits, which with a raw 32-bit code may not lie in eight bytes from the one they start in.
-template <bool SIGNED, bool WIDE>
-__global__ __launch_bounds__(kDecBlock, 6) void decode_tiles_kernel(const CompactDesc* __restrict__ cdesc,
+template <bool SIGNED, bool WIDE, uint32_t SHIFT>
+__global__ __launch_bounds__(kDecBlock, SHIFT == kDecShiftMin ? 6 : 4) void decode_tiles_kernel(const CompactDesc* __restrict__ cdesc,
                                                               const DecodeCtl* __restrict__ ctl,
                                                               const uint32_t* __restrict__ table, float* out,
-                                                              uint32_t d, uint32_t n_tiles, uint32_t accumulate,
+                                                              uint32_t d, uint32_t n_tiles, uint32_t s, uint32_t accumulate,
                                                               uint32_t* status) {
-  __shared__ DecodeShared S;
-  __shared__ unsigned long long turn_mask[kDecBlock / kWave][kDecTurns];  // per wavefront: starts of slices inside each of its current turns
+  constexpr uint32_t kTile = 1u << SHIFT, kHalf = half_turns(SHIFT), kTurns = 2u * kHalf;
+  __shared__ DecodeShared<SHIFT> S;
   const uint32_t tid = threadIdx.x, lane = lane_id();
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const uint32_t n_active = ctl->n_active;
-  const bool one_batch = n_active <= kDecLists;
-  bool bad = false, fresh = true;
-  // What a thread needs of its list of the batch at l0: the descriptor, and the two table entries for a tile.  Both
-  // are asked for a batch ahead (a batch of few records is otherwise little but the chain of waits for descriptors,
+  const uint32_t n_active = __builtin_amdgcn_readfirstlane(ctl->n_active);
+  // Sweeps over the lists, of equal length.  In a sweep the lists are dealt out to 1, 2, 4 or 8 groups of wavefronts so that no
+  // lane gets two, and wavefronts of the same group share out the records.  One by one where one sweep takes them all (clients
+  // differ in what they keep of a layer: four neighbouring lists at a time make a 4 us longer call of 32 streams of 11.2 M
+  // coordinates); in fours, a cache line of descriptors, where every sweep reads them anew.  The order turns by one from
+  // hand to hand, so that a wavefront does not get the same groups of every client.
+  const uint32_t n_sweeps = max((n_active + kDecLists - 1u) / kDecLists, 1u);
+  const uint32_t per_sweep = (n_active + n_sweeps - 1u) / n_sweeps;
+  const uint32_t group_bits = per_sweep <= kWaveLists ? 0u : per_sweep <= 2u * kWaveLists ? 1u : per_sweep <= 4u * kWaveLists ? 2u : 3u;
+  const uint32_t group_mask = (1u << group_bits) - 1u, group = wave & group_mask, part = wave >> group_bits;
+  const uint32_t part_records = kDecBlock >> group_bits;  // records of a turn of all the wavefronts of a group
+  const uint32_t deal_bits = n_sweeps > 1u ? 2u : 0u, hand = lane >> deal_bits;
+  const uint32_t mine = (((hand << group_bits) + ((group + hand) & group_mask)) << deal_bits) + (lane & ((1u << deal_bits) - 1u));  // the lane's list in a sweep
+  static_assert(kDecWaves == 8u && kWaveLists % 4u == 0u, "three bits of groups, whole fours");
+  bool bad = false;
+  // What a lane needs of its list of the sweep at l0: the descriptor, and the two table entries for a tile.  Both
+  // are asked for a sweep ahead (a sweep of few records is otherwise little but the chain of waits for descriptors,
   // then table entries, then records).
   auto request_desc = [&](uint32_t l0, uint4 (&dd)[2]) {
-    const uint4* src = reinterpret_cast<const uint4*>(cdesc + min(l0 + tid, n_active - 1u));
+    const uint4* src = reinterpret_cast<const uint4*>(cdesc + min(l0 + mine, n_active - 1u));
     dd[0] = src[0];
     dd[1] = src[1];
   };
   auto request_rows = [&](uint32_t tile, uint32_t l0) {
     uint2 r = make_uint2(0u, 0u);
-    if (tile < n_tiles && tid < min(n_active - l0, kDecLists)) {
-      const uint64_t two = load8((GlobalBytePtr)(table + (size_t)(l0 + tid) * (n_tiles + 1) + tile));
+    if (tile < n_tiles && mine < per_sweep && l0 + mine < n_active) {
+      const uint64_t two = load8((GlobalBytePtr)(table + (size_t)(l0 + mine) * (n_tiles + 1) + tile));
       r.x = (uint32_t)two;
       r.y = (uint32_t)(two >> 32);
     }
@@ -495,182 +536,145 @@ __global__ __launch_bounds__(kDecBlock, 6) void decode_tiles_kernel(const Compac
   uint32_t round = 0, l0 = 0;
   uint2 next_rows = make_uint2(0u, 0u);
   uint4 next_desc[2] = {make_uint4(0u, 0u, 0u, 0u), make_uint4(0u, 0u, 0u, 0u)};
-  uint32_t my_P = 0;  // records of this thread's list
   if (n_active) {
     next_rows = request_rows(tile_of(0), 0);
     request_desc(0, next_desc);
   }
-  for (uint32_t i = tid; i < kDecTile; i += kDecBlock) S.acc[i] = 0.0;
+  for (uint32_t i = tid; i < kTile; i += kDecBlock) S.acc[i] = 0.0;
+  SliceInfo* slices = S.slice[wave];
+  unsigned long long* masks = S.turn_mask[wave];
+  bool open = false;  // all wavefronts have cleared their part of the tile (uniform)
   for (uint32_t tile = tile_of(0); tile < n_tiles;) {
-    const uint32_t lo = tile * kDecTile;
-    const bool last_batch = n_active - l0 <= kDecLists;  // of the tile
-    const uint32_t next_tile = last_batch ? tile_of(++round) : tile, next_l0 = last_batch ? 0u : l0 + kDecLists;
+    const uint32_t lo = tile << SHIFT;
+    const uint32_t room = min(kTile, d - lo);  // coordinates of the tile
+    const bool last_sweep = l0 + per_sweep >= n_active;  // of the tile
+    const uint32_t next_tile = last_sweep ? tile_of(++round) : tile, next_l0 = last_sweep ? 0u : l0 + per_sweep;
     if (n_active) {  // uniform
-      const uint32_t nl = min(n_active - l0, kDecLists);
       const uint2 rows = next_rows;
-      if (!one_batch || fresh) {  // one batch: its descriptors stay in LDS
-        if (tid < kDecLists) {
-          // in the place of the number of records, which only this thread needs: the payload's words
-          uint4 d1 = next_desc[1];
-          d1.x = (uint32_t)payload_words(next_desc[1].x, next_desc[1].y & 0xFFu);
-          S.desc[tid][0] = next_desc[0];
-          S.desc[tid][1] = d1;
-        }
-        my_P = next_desc[1].x;
-        if (!one_batch) request_desc(next_l0, next_desc);
-        fresh = false;
-      }
+      const uint4 d0 = next_desc[0], d1 = next_desc[1];
+      if (n_sweeps > 1u) request_desc(next_l0, next_desc);
       next_rows = request_rows(next_tile, next_l0);
-      // this thread's list: its slice [begin, end) from two neighbouring table entries
-      uint32_t len = 0, begin = rows.x;
-      if (tid < nl) {
-        uint32_t end = rows.y;
-        if (begin > my_P) begin = my_P;  // table entries of a malformed list may hold anything
-        if (end > my_P) end = my_P;
-        if (end > begin) len = end - begin;
-        if (len > kDecTile) {  // positions ascend strictly: a tile holds at most one record per coordinate
-          bad = true;
-          len = 0;
-        }
+      // this lane's list: its slice [begin, end) from two neighbouring table entries (none: both are 0)
+      const uint32_t P = d1.x, W = d1.y & 0xFFu;
+      const uint32_t begin = min(rows.x, P), end = min(rows.y, P);  // table entries of a malformed list may hold anything
+      uint32_t len = end > begin ? end - begin : 0u;
+      if (len > kTile) {  // positions ascend strictly: a tile holds at most one record per coordinate
+        bad = true;
+        len = 0;
       }
-      // the slices' records numbered through, the slices that hold any compacted
-      const uint32_t incl = wave_incl_scan_u32(len);
+      const uint32_t incl = wave_incl_scan_rows(len), before = incl - len;
+      const uint32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
       const uint64_t live = __ballot(len != 0u);
-      if (lane == kWave - 1) {
-        S.scan_a[wave] = incl;
-        S.scan_b[wave] = (uint32_t)__popcll(live);
-      }
-      __syncthreads();
-      uint32_t before = incl - len, j = lanes_below(live), total = 0, n_live = 0;
-#pragma unroll
-      for (uint32_t w = 0; w < kDecWaves; ++w) {
-        const uint32_t xa = S.scan_a[w], xb = S.scan_b[w];
-        if (w < wave) { before += xa; j += xb; }
-        total += xa;
-        n_live += xb;
-      }
       if (len) {
-        S.first[j] = before | (tid << kFirstBits);
-        S.begin[j] = begin;
+        const uint64_t bit0 = (uint64_t)begin * W;
+        const uint64_t src = (((uint64_t)d0.y << 32) | d0.x) + (bit0 >> 3) - 8u;
+        const uint64_t left = payload_words(P, W) * 4u - (bit0 >> 3);  // bytes up to the payload's end: its last eight may be loaded
+        SliceInfo& info = slices[lanes_below(live)];
+        info.where = make_uint4((uint32_t)src, (uint32_t)(src >> 32), ((uint32_t)bit0 & 7u) + 64u - before * W,
+                                (uint32_t)(left < 0xFFFFu ? left : 0xFFFFu) | (W << 16) | ((d1.y >> 16) << 24));
+        info.value = make_uint4(d0.z, d0.w, d1.z, d1.w);
       }
-      if (tid == 0) S.first[n_live] = total;
-      __syncthreads();
       // the wavefront's share of the records, a multiple of 64
-      const uint32_t share = ((total + kDecBlock - 1) / kDecBlock) * kWave;
-      const uint32_t q_begin = min(wave * share, total), q_end = min(q_begin + share, total);
-      if (q_begin < q_end) {  // uniform per wavefront
-        // last slice whose first record is at or before the first record of the turns at hand (uniform): the
-        // lanes look at all slices of the batch at once (first[] ascends; slice 0 starts at record 0)
-        uint32_t cur = 0;
-        {
-          uint32_t at_or_before = 0;
+      const uint32_t share = ((total + part_records - 1u) / part_records) * kWave;
+      const uint32_t q_begin = min(part * share, total), q_end = min(q_begin + share, total);
+      // kTurns turns at a time.  First the start masks of all of them; then, half by half but without one
+      // turn waiting for another, the slice from LDS and the record's place; then all record loads together, so that their
+      // latencies overlap.  Nothing in a half branches on data or on the number of turns (a lane past the end reads the last
+      // record again), so that no load has to be waited for before the next one is issued.  A record is read by one load of
+      // eight bytes from the byte it starts in (from the payload's last eight bytes where it would reach past them).
+      for (uint32_t q0 = q_begin; q0 < q_end; q0 += kWave * kTurns) {
+        if (lane < kTurns) masks[lane] = 0ull;
+        wave_lds_fence();
+        const uint32_t f = before - q0;
+        if (len && f < kWave * kTurns) atomicOr(&masks[f >> 6], 1ull << (f & 63u));
+        uint32_t cur = (uint32_t)__popcll(__ballot(len && before < q0));  // slices that start before the turns at hand
+        wave_lds_fence();
+        uint64_t bits_of[kTurns];
+        uint32_t tail_of[WIDE ? kTurns : 1];  // the byte behind those eight
+        uint32_t at_of[kTurns];               // bits in front of the record, at most 63 | slice << 8 | y << 24
+        auto request = [&](auto half) {
+          constexpr uint32_t u0 = decltype(half)::value * kHalf;
+          uint32_t a_of[kHalf];
+          uint4 where[kHalf];
 #pragma unroll
-          for (uint32_t k = 0; k < (kDecLists + kWave - 1) / kWave; ++k) {
-            const uint32_t i = k * kWave + lane;
-            const bool hit = i < n_live && (S.first[min(i, n_live)] & kFirstMask) <= q_begin;
-            at_or_before += (uint32_t)__popcll(__ballot(hit));
-          }
-          cur = __builtin_amdgcn_readfirstlane(at_or_before) - 1u;
-        }
-        // kDecTurns turns at a time.  First the start masks of all of them; then, turn by turn but without one
-        // turn waiting for another, list and record number from LDS; then all record loads together, so that their
-        // latencies overlap.  Nothing in this half branches on data (a lane past the end works on the last record
-        // again), so that no load has to be waited for before the next one is issued.  A record is read by one load of
-        // eight bytes from the byte it starts in (from the payload's last eight bytes where it would reach past them):
-        // lanes of a turn read from a dozen lists and more, 48 cache lines to a load on average, and every one of them is
-        // a cycle or more of the address unit (three aligned words a record and two loads per pair of table
-        // entries, 2.7 times the loads: 53 us instead of 47 for 32 streams of 11.2 M coordinates, 540 instead of 459
-        // for 100 of 25.6 M).  Now no unit is the bound by itself: the address units are busy for 38 % of the launch, the vector
-        // units for 36 %.
-        unsigned long long* masks = turn_mask[wave];
-        for (uint32_t q0 = q_begin; q0 < q_end; q0 += kWave * kDecTurns) {
-          const uint32_t n_turns = __builtin_amdgcn_readfirstlane(min((q_end - q0 + kWave - 1u) / kWave, kDecTurns));
-          // slices after `cur` that start inside the turns: first[] ascends strictly, first[n_live] = total.
-          // 64 slices are looked at per round; more start inside the turns only when most hold a few records.
-          if (lane < kDecTurns) masks[lane] = 0ull;
-          wave_lds_fence();
-          for (uint32_t seen = 0;; seen += kWave) {  // uniform
-            const uint32_t idx = cur + 1u + seen + lane;
-            const uint32_t f = (S.first[min(idx, n_live)] & kFirstMask) - q0;  // >= 0
-            if (idx <= n_live && f < kWave * kDecTurns) atomicOr(&masks[f >> 6], 1ull << (f & 63u));
-            // done when the last one looked at lies past the turns at hand, or nothing is left to look at
-            if (cur + seen + kWave >= n_live || __builtin_amdgcn_readlane(f, kWave - 1) >= kWave * n_turns) break;
-          }
-          wave_lds_fence();
-          uint64_t bits_of[kDecTurns];
-          uint32_t tail_of[WIDE ? kDecTurns : 1];  // the byte behind those eight
-          uint32_t base_of[kDecTurns], at[kDecTurns];  // at: list | bit inside the first word << kListBits
-          unsigned long long starts[kDecTurns];
-#pragma unroll
-          for (uint32_t u = 0; u < kDecTurns; ++u) starts[u] = masks[u];
-#pragma unroll
-          for (uint32_t u = 0; u < kDecTurns; ++u) {
-            base_of[u] = cur;
-            if (u < n_turns)  // uniform; the sentinel's bit lies in the last turn at hand or past it
-              cur += (uint32_t)__popc((uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)starts[u])) +
-                     (uint32_t)__popc((uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(starts[u] >> 32)));
-          }
-          uint32_t x_of[kDecTurns], e_of[kDecTurns];
-#pragma unroll
-          for (uint32_t u = 0; u < kDecTurns; ++u) {
-            x_of[u] = e_of[u] = 0;
-            if (u >= n_turns) continue;          // uniform
-            const uint32_t qt = q0 + u * kWave;  // the turn's first record (uniform)
-            const uint32_t place = min(lane, q_end - 1u - qt);
-            const uint32_t a = base_of[u] + (uint32_t)__popcll(starts[u] & ((2ull << place) - 1ull));
-            x_of[u] = S.first[a];
-            e_of[u] = S.begin[a] + (qt + place);
+          for (uint32_t i = 0; i < kHalf; ++i) {
+            const unsigned long long m = masks[u0 + i];
+            const uint32_t m_lo = __builtin_amdgcn_readfirstlane((uint32_t)m), m_hi = __builtin_amdgcn_readfirstlane((uint32_t)(m >> 32));
+            const uint64_t starts = ((uint64_t)m_hi << 32) | m_lo;
+            // slices that start at or before the lane's record, less one; bit 0 counts for every lane
+            const uint64_t above = starts >> 1;
+            a_of[i] = __builtin_amdgcn_mbcnt_hi((uint32_t)(above >> 32),
+                                                __builtin_amdgcn_mbcnt_lo((uint32_t)above, cur + (m_lo & 1u) - 1u));
+            cur += (uint32_t)__popcll(starts);
           }
 #pragma unroll
-          for (uint32_t u = 0; u < kDecTurns; ++u) {
-            bits_of[u] = 0;
-            at[u] = 0;
-            if (u >= n_turns) continue;  // uniform
-            const uint32_t li = x_of[u] >> kFirstBits;
-            const uint32_t e = e_of[u] - (x_of[u] & kFirstMask);
-            const uint2 ptr = *reinterpret_cast<const uint2*>(&S.desc[li][0]);  // payload
-            const uint2 size = *reinterpret_cast<const uint2*>(&S.desc[li][1]);  // its words; W | s << 8 | y << 16
-            // from eight bytes in front of the payload (a stream's headers lie there), so that nothing is negative
-            GlobalBytePtr src = (GlobalBytePtr)((((uint64_t)ptr.y << 32) | ptr.x) - 8u);
-            const uint64_t bit = (uint64_t)e * (size.y & 0xFFu), end = (uint64_t)size.x * 4u;
-            const uint64_t byte = min((bit >> 3) + 8u, end);
-            at[u] = li | (((uint32_t)bit + 64u - (uint32_t)byte * 8u) << kListBits);  // bits in front of the record: at most 63
-            bits_of[u] = load8(src + byte);
-            if (WIDE) tail_of[u] = *(src + min(byte + 8u, end + 7u));
-          }
+          for (uint32_t i = 0; i < kHalf; ++i) where[i] = slices[a_of[i]].where;
 #pragma unroll
-          for (uint32_t u = 0; u < kDecTurns; ++u) {
-            if (u >= n_turns) continue;  // uniform
-            if (q0 + u * kWave + lane >= q_end) continue;
-            const uint32_t li = at[u] & ((1u << kListBits) - 1u), sh = at[u] >> kListBits;
-            const uint4 d0 = S.desc[li][0], d1 = S.desc[li][1];
-            const uint32_t s = (d1.y >> 8) & 0xFFu, y = (d1.y >> 16) & 0xFFu;
-            const double weight = __hiloint2double((int)d0.w, (int)d0.z);
+          for (uint32_t i = 0; i < kHalf; ++i) {
+            const uint32_t u = u0 + i, last = where[i].w & 0xFFFFu;
+            const uint32_t q = min(q0 + u * kWave + lane, q_end - 1u);
+            const uint32_t bit = __umul24(q, (where[i].w >> 16) & 0xFFu) + where[i].z;
+            const uint32_t at = min(bit >> 3, last);
+            at_of[u] = ((bit - at * 8u) & 63u) | (a_of[i] << 8) | (where[i].w & 0xFF000000u);
+            GlobalBytePtr src = (GlobalBytePtr)(((uint64_t)where[i].y << 32) | where[i].x);
+            bits_of[u] = load8(src + at);
+            if (WIDE) tail_of[u] = *(src + min(at + 8u, last + 7u));
+          }
+        };
+        auto add_up = [&](auto half) {
+          constexpr uint32_t u0 = decltype(half)::value * kHalf;
+          uint32_t pos[kHalf];
+          double val[kHalf];
+#pragma unroll
+          for (uint32_t i = 0; i < kHalf; ++i) {
+            const uint32_t u = u0 + i;
+            const uint4 v = slices[(at_of[u] >> 8) & 0xFFFFu].value;
+            const uint32_t sh = at_of[u] & 63u, y = at_of[u] >> 24;
             uint64_t rec = bits_of[u] >> sh;
             if (WIDE && sh) rec |= (uint64_t)tail_of[u] << (64u - sh);
-            const uint32_t pid = (uint32_t)rec & ((1u << s) - 1u);  // s <= 31
-            const uint32_t code_mask = y >= 32 ? 0xFFFFFFFFu : (1u << y) - 1u;
-            const uint32_t cid = (uint32_t)(rec >> s) & code_mask;
-            if (pid - lo >= kDecTile || pid >= d) { bad = true; continue; }  // a position below the tile wraps to a large value
+            pos[i] = ((uint32_t)rec & ((1u << s) - 1u)) - lo;  // s <= 31; a position below the tile wraps to a large value
+            const uint32_t code = (uint32_t)(rec >> s);
+            const uint32_t cid = __builtin_amdgcn_ubfe(code, 0u, y);  // a raw code, y = 32, is taken whole below
             float xhat;
-            if (y == 32) {
-              xhat = __uint_as_float(cid);
-            } else if (SIGNED) {
-              const float mag = __fmaf_rn((float)(cid & ((1u << (y - 1u)) - 1u)), __uint_as_float(d1.w), __uint_as_float(d1.z));
-              xhat = __uint_as_float(__float_as_uint(mag) ^ ((cid >> (y - 1u)) << 31));
+            if (SIGNED) {
+              const float mag = __fmaf_rn((float)__builtin_amdgcn_ubfe(code, 0u, y - 1u), __uint_as_float(v.w), __uint_as_float(v.z));
+              xhat = __uint_as_float(__float_as_uint(mag) ^ ((cid >> ((y - 1u) & 31u)) << 31));
             } else {
-              xhat = __fmaf_rn((float)cid, __uint_as_float(d1.w), __uint_as_float(d1.z));
+              xhat = __fmaf_rn((float)cid, __uint_as_float(v.w), __uint_as_float(v.z));
             }
-            atomicAdd(&S.acc[pid - lo], weight * (double)xhat);
+            if (y == 32u) xhat = __uint_as_float(code);
+            val[i] = __hiloint2double((int)v.y, (int)v.x) * (double)xhat;
           }
+#pragma unroll
+          for (uint32_t i = 0; i < kHalf; ++i) {
+            const bool live = q0 + (u0 + i) * kWave + lane < q_end, inside = pos[i] < room;
+            if (live && inside) atomicAdd(&S.acc[pos[i]], val[i]);
+            bad |= live && !inside;
+          }
+        };
+        using First = std::integral_constant<uint32_t, 0>;
+        using Second = std::integral_constant<uint32_t, 1>;
+        const bool both = q_end - q0 > kWave * kHalf;  // uniform
+        request(First{});
+        if (both) request(Second{});
+        if (!open) {  // uniform
+          __syncthreads();
+          open = true;
         }
+        add_up(First{});
+        if (both) add_up(Second{});
       }
+      wave_lds_fence();  // the slices may be overwritten
     }
-    __syncthreads();  // the batch's records are added up; its descriptors and slices may be overwritten
-    if (last_batch) {
+    if (last_sweep) {
+      if (!open) __syncthreads();  // uniform
+      open = false;
+      __syncthreads();  // the tile's records are added up
+    }
+    if (last_sweep) {
       // pairs of coordinates, neighbouring lanes neighbouring pairs (LDS reads without bank conflicts, 512-byte
       // stores per wavefront): all reads first, then the stores.  The thread leaves zeros for the next tile.
-      constexpr uint32_t kPairs = kDecTile / (2u * kDecBlock);
+      constexpr uint32_t kPairs = kTile / (2u * kDecBlock);
       double2 v[kPairs];
 #pragma unroll
       for (uint32_t c = 0; c < kPairs; ++c) {
@@ -768,6 +772,8 @@ int cvlc_decode_aggregate(uint32_t n, const void* const* d_streams, const size_t
   DecodeCtl* ctl = reinterpret_cast<DecodeCtl*>(base + L.ctl);
   uint32_t* table = reinterpret_cast<uint32_t*>(base + L.table);
   const uint32_t n_lists = n * kListsPerClient;
+  const bool wide = position_bits(d) > 25u;
+  const uint32_t shift = tile_shift_for(d), n_tiles = tiles_of(d, shift);
 
   profile_mark(CVLC_STAGE_DEC_SETUP, true, stream);
   {
@@ -804,18 +810,19 @@ int cvlc_decode_aggregate(uint32_t n, const void* const* d_streams, const size_t
   if (n > 0) {
     StageScope scope(CVLC_STAGE_DEC_TABLE, stream);
     // the number of work items is only known on the device
-    auto kernel = position_bits(d) > 25u ? tile_table_kernel<true> : tile_table_kernel<false>;
-    hipLaunchKernelGGL(kernel, dim3(kTableBlocks), dim3(kBlock), 0, stream, cdesc, item_start, ctl, table, d, L.n_tiles, n_lists,
-                       status);
+    auto kernel = wide ? tile_table_kernel<true> : tile_table_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(kTableBlocks), dim3(kBlock), 0, stream, cdesc, item_start, ctl, table, d, shift, n_tiles,
+                       n_lists, status);
   }
   {
     StageScope scope(CVLC_STAGE_DEC_TILES, stream);
-    const uint32_t g = std::min(L.n_tiles, 768u);  // three workgroups per CU
+    const bool large = shift == kDecShiftMax;
+    const uint32_t g = std::min(n_tiles, large ? 512u : 768u);  // two or three workgroups per CU
     const bool qsgd = quant == CVLC_QUANT_QSGD;
-    const bool wide = position_bits(d) > 25u;
-    auto kernel = qsgd ? (wide ? decode_tiles_kernel<true, true> : decode_tiles_kernel<true, false>)
-                       : (wide ? decode_tiles_kernel<false, true> : decode_tiles_kernel<false, false>);
-    hipLaunchKernelGGL(kernel, dim3(g), dim3(kDecBlock), 0, stream, cdesc, ctl, table, d_out, d, L.n_tiles,
+    auto kernel = wide    ? (qsgd ? decode_tiles_kernel<true, true, kDecShiftMax> : decode_tiles_kernel<false, true, kDecShiftMax>)
+                  : large ? (qsgd ? decode_tiles_kernel<true, false, kDecShiftMax> : decode_tiles_kernel<false, false, kDecShiftMax>)
+                          : (qsgd ? decode_tiles_kernel<true, false, kDecShiftMin> : decode_tiles_kernel<false, false, kDecShiftMin>);
+    hipLaunchKernelGGL(kernel, dim3(g), dim3(kDecBlock), 0, stream, cdesc, ctl, table, d_out, d, n_tiles, position_bits(d),
                        flags & CVLC_DECODE_ACCUMULATE, status);
   }
   return hip_check(hipGetLastError());

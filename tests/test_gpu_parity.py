@@ -430,6 +430,50 @@ def test_decode_at_the_steps_of_the_list_search(n, R):
     check_decode(refs, d, weights=rng.uniform(0.5, 1.5, n).tolist())
 
 
+# Lists are dealt out to 1, 2, 4 or 8 groups of wavefronts, 60 to each, and to several sweeps beyond 480: both sides of
+# every step, empty lists among them, with few records and with every coordinate kept (a wavefront's share is many turns).
+@pytest.mark.parametrize("quant", [cv.QUANT_PQ, cv.QUANT_QSGD])
+@pytest.mark.parametrize("n,R", [(1, 1), (1, 31), (12, 5), (61, 1), (15, 8), (11, 11), (16, 15), (241, 1), (32, 15), (37, 13), (70, 14)])
+def test_decode_at_the_steps_of_the_lists_share(n, R, quant):
+    rng = np.random.default_rng(n * 100 + R)
+    d = 9001                                       # two tiles and a part of a third
+    refs = []
+    for c in range(n):
+        full = c % 7 == 0
+        cnt = [d // R] * R if full else [int(v) for v in rng.integers(0, 1 + d // (8 * R), R)]
+        cnt[-1] = max(cnt[-1], 1)
+        ys = sorted((int(v) for v in rng.integers(2, 17, R)), reverse=True)
+        u = rng.standard_t(3, d).astype(np.float32)
+        refs.append(orc.encode(u, orc.plan_manual(d, ys, cnt, quant=quant), 5, c).words)
+    dev = [torch.from_numpy(s.view(np.int32)).to(DEV) for s in refs]
+    got, status = gpu_decode(dev, d, quant=quant)
+    assert status == 0
+    ref = orc.decode_aggregate(refs, d).astype(np.float64)
+    # fp64 sums in free order, rounded to fp32 once: half a unit of the last place on either side
+    assert np.all(np.abs(got - ref) <= 2.0 ** -23 * np.abs(ref) + 1e-12 * abs_terms(refs, d))
+
+
+# Tiles of 4096 coordinates below 2^23, of 8192 from there on.
+@pytest.mark.parametrize("d", [(1 << 23) - 1, 1 << 23, (1 << 23) + 4097])
+def test_decode_on_both_sides_of_the_large_tiles(d):
+    rng = np.random.default_rng(d)
+    refs = []
+    for c in range(3):
+        u = np.zeros(d, dtype=np.float32)
+        at = np.concatenate([rng.choice(d, 50_000, replace=False), np.arange(8192 * 3, 8192 * 4), np.arange(d - 5000, d)])
+        u[at] = rng.standard_t(3, at.size).astype(np.float32)
+        refs.append(orc.encode(u, orc.plan_manual(d, [32, 16, 3][: c + 1], [20_000, 10_000, 5_000][: c + 1]), 9, c).words)
+    check_decode(refs, d)
+    dev = [torch.from_numpy(s.view(np.int32)).to(DEV) for s in refs]
+    start = rng.standard_normal(d).astype(np.float32)
+    got, status = gpu_decode(dev, d, accumulate_into=torch.from_numpy(start.copy()).to(DEV))
+    assert status == 0
+    exact = start.astype(np.float64)
+    for s in refs:
+        exact += orc.decode_aggregate([s], d, weights=[1.0]).astype(np.float64) / 3.0
+    assert np.all(np.abs(got - exact) <= 2.0 ** -23 * np.abs(exact) + 1e-12)
+
+
 # --------------------------------------------------------------------------- batches of clients with different plans
 def test_batch_with_mixed_plans():
     d = 150_000
