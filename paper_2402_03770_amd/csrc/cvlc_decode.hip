@@ -303,7 +303,98 @@ __device__ __forceinline__ ItemOwner owner_of(const uint32_t* __restrict__ item_
 }
 constexpr uint32_t kTableBlocks = 2048;  // workgroups of tile_table, eight per CU
 
-// WIDE: positions of more than 25 bits, which need not lie in the four bytes from the one they start in.
+// Item q of list a (descriptor d0, d1, its first item `first_item`), whole wavefront.  Returns whether a lane's record is out of
+// order or of range.  WIDE: positions of more than 25 bits, which need not lie in the four bytes from the one they start in.
+template <bool WIDE>
+__device__ __forceinline__ bool table_item(uint4 d0, uint4 d1, uint32_t a, uint32_t first_item, uint32_t q, uint32_t* table,
+                                           uint32_t d, uint32_t tile_shift, uint32_t n_tiles) {
+  const uint32_t lane = lane_id();
+  bool bad = false;
+  // the list's descriptor is the same for all lanes: keeping it in scalar registers keeps the address
+  // arithmetic of the loads below off the vector unit
+  const uint64_t pay = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(d0.y) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane(d0.x);
+  const uint32_t P = __builtin_amdgcn_readfirstlane(d1.x), wsy = __builtin_amdgcn_readfirstlane(d1.y);
+  const uint32_t W = wsy & 0xFFu, s = (wsy >> 8) & 0xFFu;
+  const uint32_t pid_mask = (1u << s) - 1u;  // s <= 31
+  const uint32_t e0 = (q - first_item) * kTabChunk, cnt = min(P - e0, kTabChunk);
+  uint32_t* row = table + (size_t)a * (n_tiles + 1);
+  // The window of the item starts at the record before the run (the run's first record for the first
+  // item of a list); records are addressed by their number in the window, bits by their offset from the
+  // byte `src`, eight before the window's first word (a stream's headers lie in front of its first payload, so
+  // the bytes are there): everything stays far below 2^24.
+  const uint32_t lead = e0 ? 1u : 0u;
+  const uint64_t bit0 = (uint64_t)(e0 - lead) * W;
+  GlobalBytePtr src = (GlobalBytePtr)(pay + (bit0 >> 5) * 4u - 8u);
+  const uint32_t sh0 = ((uint32_t)bit0 & 31u) + 64u;
+  // the last place a whole load may start at: the list's payload ends there
+  const uint64_t left = (((uint64_t)P * W + 31u) >> 5) * 4u - (bit0 >> 5) * 4u + 8u - (WIDE ? 8u : 4u);
+  const uint32_t rel_last = left < (1u << 24) ? (uint32_t)left : 1u << 24;
+  // position field of record r of the window
+  auto request = [&](uint32_t r, uint32_t& sh) {
+    const uint32_t bit = sh0 + __umul24(r, W), at = min(bit >> 3, rel_last);
+    sh = bit - at * 8u;
+    if constexpr (WIDE) return load8(src + at); else return load4(src + at);
+  };
+  decltype(request(0u, a)) w[kTabTurns], c_w;
+  uint32_t sh[kTabTurns], c_sh;
+  c_w = request(0u, c_sh);  // the record before the run (uniform)
+#pragma unroll
+  for (uint32_t i = 0; i < kTabTurns; ++i)  // no branch: a lane past the end reads the last record again
+    w[i] = request(lead + min(i * kWave + lane, cnt - 1u), sh[i]);
+  uint32_t carry = (uint32_t)(c_w >> c_sh) & pid_mask;
+#pragma unroll
+  for (uint32_t i = 0; i < kTabTurns; ++i) {
+    if (i * kWave >= cnt) break;  // uniform
+    const uint32_t j = i * kWave + lane;
+    const bool live = j < cnt;
+    const uint32_t e = e0 + j;
+    const uint32_t pid = (uint32_t)(w[i] >> sh[i]) & pid_mask;
+    // the record before mine sits in the lane below; lane 0 takes the last one of the turn before
+    const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)carry, (int)pid, 0x138 /* wave_shr:1 */, 0xF, 0xF, false);
+    carry = __builtin_amdgcn_readlane(pid, kWave - 1);
+    // a position past the end (an error, reported below) counts as lying behind the last tile
+    const uint32_t t_cur = min(pid >> tile_shift, n_tiles), t_prev = min(prev >> tile_shift, n_tiles);
+    const bool first = e == 0, last = e == P - 1;
+    bad |= live && ((!first && prev >= pid) || pid >= d);  // positions must ascend strictly and stay below d
+    // entries (tile of record e-1, tile of record e] point at e; past the last record they hold P
+    const bool starts = live && (first || last || t_cur != t_prev);
+    if (!__ballot(starts)) continue;
+    const uint32_t t_first = first ? 0u : t_prev + 1u;
+    const bool single = starts && !last && t_first == t_cur;  // nearly always: the next tile, one entry
+    if (single) row[t_cur] = e;
+    if (!__ballot(starts && !single)) continue;
+    const bool run = starts && !single && t_cur >= t_first;
+    uint32_t tail_first = 1, tail_last = 0;
+    if (starts && last) {
+      tail_first = t_cur + 1;
+      tail_last = n_tiles;
+    }
+    // short runs of entries are written by the lane that found them, long ones (the stretch before a
+    // list's first record, after its last, or across a region it skips) by the whole wavefront
+    constexpr uint32_t kLong = 16;
+    const bool long_run = run && t_cur - t_first >= kLong;
+    const bool long_tail = tail_last >= tail_first;
+    if (run && !long_run)
+      for (uint32_t t = t_first; t <= t_cur; ++t) row[t] = e;
+    uint64_t todo = __ballot(long_run);
+    while (todo) {
+      const uint32_t from = (uint32_t)__builtin_ctzll(todo);
+      const uint32_t a0 = __builtin_amdgcn_readlane(t_first, from), a1 = __builtin_amdgcn_readlane(t_cur, from);
+      const uint32_t val = __builtin_amdgcn_readlane(e, from);
+      for (uint32_t t = a0 + lane; t <= a1; t += kWave) row[t] = val;
+      todo &= todo - 1;
+    }
+    todo = __ballot(long_tail);
+    while (todo) {
+      const uint32_t from = (uint32_t)__builtin_ctzll(todo);
+      const uint32_t a0 = __builtin_amdgcn_readlane(tail_first, from), a1 = __builtin_amdgcn_readlane(tail_last, from);
+      for (uint32_t t = a0 + lane; t <= a1; t += kWave) row[t] = P;
+      todo &= todo - 1;
+    }
+  }
+  return bad;
+}
+
 template <bool WIDE>
 __global__ __launch_bounds__(kBlock, 8) void tile_table_kernel(const CompactDesc* __restrict__ cdesc,
                                                          const uint32_t* __restrict__ item_start,
@@ -332,93 +423,100 @@ __global__ __launch_bounds__(kBlock, 8) void tile_table_kernel(const CompactDesc
       first_item = next_list;
       next_list = item_start[a + 1u];
     }
-    // the list's descriptor is the same for all lanes: keeping it in scalar registers keeps the address
-    // arithmetic of the loads below off the vector unit
     const uint4* dsrc = reinterpret_cast<const uint4*>(cdesc + a);
-    const uint4 d0 = dsrc[0], d1 = dsrc[1];
-    const uint64_t pay = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(d0.y) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane(d0.x);
-    const uint32_t P = __builtin_amdgcn_readfirstlane(d1.x), wsy = __builtin_amdgcn_readfirstlane(d1.y);
-    const uint32_t W = wsy & 0xFFu, s = (wsy >> 8) & 0xFFu;
-    const uint32_t pid_mask = (1u << s) - 1u;  // s <= 31
-    const uint32_t e0 = (q - first_item) * kTabChunk, cnt = min(P - e0, kTabChunk);
-    uint32_t* row = table + (size_t)a * (n_tiles + 1);
-    // The window of the item starts at the record before the run (the run's first record for the first
-    // item of a list); records are addressed by their number in the window, bits by their offset from the
-    // byte `src`, eight before the window's first word (a stream's headers lie in front of its first payload, so
-    // the bytes are there): everything stays far below 2^24.
-    const uint32_t lead = e0 ? 1u : 0u;
-    const uint64_t bit0 = (uint64_t)(e0 - lead) * W;
-    GlobalBytePtr src = (GlobalBytePtr)(pay + (bit0 >> 5) * 4u - 8u);
-    const uint32_t sh0 = ((uint32_t)bit0 & 31u) + 64u;
-    // the last place a whole load may start at: the list's payload ends there
-    const uint64_t left = (((uint64_t)P * W + 31u) >> 5) * 4u - (bit0 >> 5) * 4u + 8u - (WIDE ? 8u : 4u);
-    const uint32_t rel_last = left < (1u << 24) ? (uint32_t)left : 1u << 24;
-    // position field of record r of the window
-    auto request = [&](uint32_t r, uint32_t& sh) {
-      const uint32_t bit = sh0 + __umul24(r, W), at = min(bit >> 3, rel_last);
-      sh = bit - at * 8u;
-      if constexpr (WIDE) return load8(src + at); else return load4(src + at);
-    };
-    decltype(request(0u, a)) w[kTabTurns], c_w;
-    uint32_t sh[kTabTurns], c_sh;
-    c_w = request(0u, c_sh);  // the record before the run (uniform)
-#pragma unroll
-    for (uint32_t i = 0; i < kTabTurns; ++i)  // no branch: a lane past the end reads the last record again
-      w[i] = request(lead + min(i * kWave + lane, cnt - 1u), sh[i]);
-    uint32_t carry = (uint32_t)(c_w >> c_sh) & pid_mask;
-#pragma unroll
-    for (uint32_t i = 0; i < kTabTurns; ++i) {
-      if (i * kWave >= cnt) break;  // uniform
-      const uint32_t j = i * kWave + lane;
-      const bool live = j < cnt;
-      const uint32_t e = e0 + j;
-      const uint32_t pid = (uint32_t)(w[i] >> sh[i]) & pid_mask;
-      // the record before mine sits in the lane below; lane 0 takes the last one of the turn before
-      const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)carry, (int)pid, 0x138 /* wave_shr:1 */, 0xF, 0xF, false);
-      carry = __builtin_amdgcn_readlane(pid, kWave - 1);
-      // a position past the end (an error, reported below) counts as lying behind the last tile
-      const uint32_t t_cur = min(pid >> tile_shift, n_tiles), t_prev = min(prev >> tile_shift, n_tiles);
-      const bool first = e == 0, last = e == P - 1;
-      bad |= live && ((!first && prev >= pid) || pid >= d);  // positions must ascend strictly and stay below d
-      // entries (tile of record e-1, tile of record e] point at e; past the last record they hold P
-      const bool starts = live && (first || last || t_cur != t_prev);
-      if (!__ballot(starts)) continue;
-      const uint32_t t_first = first ? 0u : t_prev + 1u;
-      const bool single = starts && !last && t_first == t_cur;  // nearly always: the next tile, one entry
-      if (single) row[t_cur] = e;
-      if (!__ballot(starts && !single)) continue;
-      const bool run = starts && !single && t_cur >= t_first;
-      uint32_t tail_first = 1, tail_last = 0;
-      if (starts && last) {
-        tail_first = t_cur + 1;
-        tail_last = n_tiles;
-      }
-      // short runs of entries are written by the lane that found them, long ones (the stretch before a
-      // list's first record, after its last, or across a region it skips) by the whole wavefront
-      constexpr uint32_t kLong = 16;
-      const bool long_run = run && t_cur - t_first >= kLong;
-      const bool long_tail = tail_last >= tail_first;
-      if (run && !long_run)
-        for (uint32_t t = t_first; t <= t_cur; ++t) row[t] = e;
-      uint64_t todo = __ballot(long_run);
-      while (todo) {
-        const uint32_t from = (uint32_t)__builtin_ctzll(todo);
-        const uint32_t a0 = __builtin_amdgcn_readlane(t_first, from), a1 = __builtin_amdgcn_readlane(t_cur, from);
-        const uint32_t val = __builtin_amdgcn_readlane(e, from);
-        for (uint32_t t = a0 + lane; t <= a1; t += kWave) row[t] = val;
-        todo &= todo - 1;
-      }
-      todo = __ballot(long_tail);
-      while (todo) {
-        const uint32_t from = (uint32_t)__builtin_ctzll(todo);
-        const uint32_t a0 = __builtin_amdgcn_readlane(tail_first, from), a1 = __builtin_amdgcn_readlane(tail_last, from);
-        for (uint32_t t = a0 + lane; t <= a1; t += kWave) row[t] = P;
-        todo &= todo - 1;
-      }
-    }
+    bad |= table_item<WIDE>(dsrc[0], dsrc[1], a, first_item, q, table, d, tile_shift, n_tiles);
   }
   if (bad) atomicOr(status, CVLC_DEV_STREAM);
 }
+
+// ---- a few streams: headers, list numbers and table in one launch
+// A call of a few streams is little but launches and the latencies of its headers (8 streams of 1.2 M coordinates: header
+// kernel 6.2 us, table 4.3; the call 17.4 -> 14.1 us in one launch, 1 x 1.2 M 18.7 -> 13.9, 1 x 11.2 M 26.8 -> 23.8): every workgroup parses the streams for itself, a wavefront each, and numbers the lists, in LDS;
+// workgroup 0 leaves both where decode_tiles looks for them.  The status word starts in this launch, so that what the
+// workgroups find goes to a word of each, which decode_tiles adds to it.
+constexpr uint32_t kMergedBlock = 512, kMergedWaves = kMergedBlock / kWave;
+constexpr uint64_t kMergedBlocksMax = 1024;  // four to a CU, all resident
+constexpr uint32_t kMergedStreams = kMergedWaves, kMergedLists = kMergedStreams * kListsPerClient;
+static_assert(kMergedLists <= kMergedBlock, "a thread per list");
+struct MergedArgs {
+  uint32_t n, pad;
+  StreamArg args[kMergedStreams];
+};
+
+template <bool WIDE>
+__global__ __launch_bounds__(kMergedBlock, 8) void merged_table_kernel(MergedArgs in, uint32_t quant, CompactDesc* __restrict__ cdesc,
+                                                                       DecodeCtl* ctl, uint32_t* table, uint32_t d, uint32_t tile_shift,
+                                                                       uint32_t n_tiles, uint32_t* __restrict__ found, uint32_t* status) {
+  __shared__ ListDesc descs[kMergedLists];
+  __shared__ alignas(16) CompactDesc lists[kMergedLists];
+  __shared__ uint32_t item_start[kMergedLists + 1], stream_bad[kMergedStreams], scan_a[kMergedWaves], scan_b[kMergedWaves];
+  const uint32_t tid = threadIdx.x, lane = lane_id();
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  if (wave < in.n) parse_stream(in.args[wave], wave, descs, d, in.n, stream_bad, quant);
+  __syncthreads();
+  // the lists with records, numbered in (stream, group) order, and the items before each
+  const bool live = tid < in.n * kListsPerClient && descs[min(tid, kMergedLists - 1u)].P > 0u;
+  const uint32_t P = live ? descs[tid].P : 0u, items = (P + kTabChunk - 1u) / kTabChunk;
+  const uint32_t incl = wave_incl_scan_u32(items);
+  const uint64_t mask = __ballot(live);
+  if (lane == kWave - 1u) {
+    scan_a[wave] = incl;
+    scan_b[wave] = (uint32_t)__popcll(mask);
+  }
+  __syncthreads();
+  uint32_t first = incl - items, pos = lanes_below(mask), n_items = 0, n_active = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < kMergedWaves; ++w) {
+    const uint32_t xa = scan_a[w], xb = scan_b[w];
+    if (w < wave) { first += xa; pos += xb; }
+    n_items += xa;
+    n_active += xb;
+  }
+  if (live) {
+    const ListDesc ld = descs[tid];
+    CompactDesc c;
+    c.payload = ld.payload; c.weight = ld.weight; c.P = ld.P; c.wsy = ld.W | (ld.s << 8) | (ld.y << 16);
+    c.m = ld.m; c.step = ld.step;
+    lists[pos] = c;
+    item_start[pos] = first;
+    if (blockIdx.x == 0) cdesc[pos] = c;
+  }
+  if (tid == 0) {
+    item_start[n_active] = n_items;
+    if (blockIdx.x == 0) {
+      uint32_t any_bad = 0;
+      for (uint32_t i = 0; i < in.n; ++i) any_bad |= stream_bad[i];
+      *status = any_bad ? CVLC_DEV_STREAM : 0u;
+      ctl->n_active = n_active;
+      ctl->n_items = n_items;
+    }
+  }
+  __syncthreads();
+  // neighbouring items to a wavefront; few of them to the workgroups that start first
+  const uint64_t n_waves = (uint64_t)gridDim.x * kMergedWaves, me = (uint64_t)blockIdx.x * kMergedWaves + wave;
+  n_items = __builtin_amdgcn_readfirstlane(n_items);
+  n_active = __builtin_amdgcn_readfirstlane(n_active);
+  uint32_t q_begin = (uint32_t)(me * n_items / n_waves), q_end = (uint32_t)((me + 1u) * n_items / n_waves);
+  if (n_items <= n_waves) {
+    q_begin = min((uint32_t)me, n_items);
+    q_end = min((uint32_t)me + 1u, n_items);
+  }
+  bool bad = false;
+  if (q_begin < q_end) {  // uniform per wavefront
+    uint32_t before = 0;  // lists that start at or before the first item: their starts ascend
+    for (uint32_t base = 0; base < n_active; base += kWave)
+      before += (uint32_t)__popcll(__ballot(base + lane < n_active && item_start[min(base + lane, n_active)] <= q_begin));
+    uint32_t a = before - 1u;
+    for (uint32_t q = q_begin; q < q_end; ++q) {
+      while (q >= (uint32_t)__builtin_amdgcn_readfirstlane(item_start[a + 1u])) ++a;  // every list has an item: one step at most
+      const uint4* dsrc = reinterpret_cast<const uint4*>(lists + a);
+      bad |= table_item<WIDE>(dsrc[0], dsrc[1], a, __builtin_amdgcn_readfirstlane(item_start[a]), q, table, d, tile_shift, n_tiles);
+    }
+  }
+  const int any = __syncthreads_or((int)bad);
+  if (tid == 0) found[blockIdx.x] = any ? 1u : 0u;
+}
+
 
 // ------------------------------------------------------------------ 3. fused decode + accumulate
 // Persistent workgroups walk the output tiles, neighbouring tiles at the same
@@ -485,6 +583,7 @@ __global__ __launch_bounds__(kDecBlock, SHIFT == kDecShiftMin ? 6 : 4) void deco
                                                               const DecodeCtl* __restrict__ ctl,
                                                               const uint32_t* __restrict__ table, float* out,
                                                               uint32_t d, uint32_t n_tiles, uint32_t s, uint32_t accumulate,
+                                                              const uint32_t* __restrict__ found, uint32_t n_found,
                                                               uint32_t* status) {
   constexpr uint32_t kTile = 1u << SHIFT, kHalf = half_turns(SHIFT), kTurns = 2u * kHalf;
   __shared__ DecodeShared<SHIFT> S;
@@ -703,6 +802,8 @@ __global__ __launch_bounds__(kDecBlock, SHIFT == kDecShiftMin ? 6 : 4) void deco
     tile = next_tile;
     l0 = next_l0;
   }
+  if (blockIdx.x == 0)  // what the table's workgroups found, where the status word started in their launch
+    for (uint32_t i = tid; i < n_found; i += kDecBlock) bad |= found[i] != 0u;
   if (bad) atomicOr(status, CVLC_DEV_STREAM);
 }
 
@@ -775,44 +876,68 @@ int cvlc_decode_aggregate(uint32_t n, const void* const* d_streams, const size_t
   const bool wide = position_bits(d) > 25u;
   const uint32_t shift = tile_shift_for(d), n_tiles = tiles_of(d, shift);
 
-  profile_mark(CVLC_STAGE_DEC_SETUP, true, stream);
-  {
-    ParseChunk chunk;
-    chunk.pad[0] = chunk.pad[1] = 0;
-    // One launch parses and numbers, 3.5 us for every 16 streams; two launches, the first with a workgroup per stream, take
-    // 4.2 + 3.8 for 17 and 4.8 + 10.8 for 100 (35 us in one).  The second launch costs a small call 2 us on the host:
-    // a call of 17 streams of 20 000 coordinates takes 20.5 us with one and 22.6 with two, of 32 25 either way.
-    const bool fused = n > 0 && n <= kFusedStreams;
-    for (uint32_t first = 0; first < n; first += kParseStreams) {
-      chunk.first = first;
-      chunk.count = (n - first < kParseStreams) ? n - first : kParseStreams;
-      for (uint32_t i = 0; i < chunk.count; ++i) {
-        StreamArg& sa = chunk.args[i];
-        sa.words = static_cast<const uint32_t*>(d_streams[first + i]);
-        sa.n_words = stream_bytes[first + i] / 4u;
-        sa.weight = weights ? (double)weights[first + i] : 0.0;
-        sa.has_weight = weights ? 1u : 0u;
-        sa.pad = 0;
-      }
-      if (fused)
-        hipLaunchKernelGGL(setup_kernel, dim3(1), dim3(1024), 0, stream, chunk, descs, d, quant, cdesc, item_start, ctl,
-                           stream_bad, status);
-      else
-        hipLaunchKernelGGL(parse_headers_kernel, dim3(chunk.count), dim3(64), 0, stream, chunk, descs, d, n, stream_bad,
-                           quant);
-    }
-    // also for n = 0: writes the (empty) list counts and the status word
-    if (!fused)
-      hipLaunchKernelGGL(compact_lists_kernel, dim3(1), dim3(1024), 0, stream, descs, n_lists, cdesc, item_start, ctl,
-                         stream_bad, n, status);
-  }
-  profile_mark(CVLC_STAGE_DEC_SETUP, false, stream);
-  if (n > 0) {
+  auto stream_arg = [&](uint32_t i) {
+    StreamArg sa;
+    sa.words = static_cast<const uint32_t*>(d_streams[i]);
+    sa.n_words = stream_bytes[i] / 4u;
+    sa.weight = weights ? (double)weights[i] : 0.0;
+    sa.has_weight = weights ? 1u : 0u;
+    sa.pad = 0;
+    return sa;
+  };
+  // The most items that the streams can hold (a record has a code bit at least): a wavefront each, all of them resident, or the
+  // general path, whose table kernel starts without a prologue (8 x 25.6 M: 50.2 us, merged 53.4; 8 x 11.2 M, within the limit:
+  // 35.6 and 34.4).
+  uint64_t items_most = 0;
+  for (uint32_t i = 0; i < n && n <= kMergedStreams; ++i)
+    items_most += (uint64_t)stream_bytes[i] * 8u / ((position_bits(d) + 1u) * kTabChunk) + CVLC_MAX_CODED;
+  const bool merged = n > 0 && n <= kMergedStreams && items_most <= kMergedBlocksMax * kMergedWaves;
+  // a word for every workgroup in the place of the list descriptors, of which there is room for 320 a stream
+  uint32_t* found = reinterpret_cast<uint32_t*>(descs);
+  const uint32_t merged_blocks = (uint32_t)std::min<uint64_t>((items_most + kMergedWaves - 1u) / kMergedWaves,
+                                                              (uint64_t)n_lists * sizeof(ListDesc) / sizeof(uint32_t));
+  if (merged) {
     StageScope scope(CVLC_STAGE_DEC_TABLE, stream);
-    // the number of work items is only known on the device
-    auto kernel = wide ? tile_table_kernel<true> : tile_table_kernel<false>;
-    hipLaunchKernelGGL(kernel, dim3(kTableBlocks), dim3(kBlock), 0, stream, cdesc, item_start, ctl, table, d, shift, n_tiles,
-                       n_lists, status);
+    MergedArgs in;
+    in.n = n;
+    in.pad = 0;
+    for (uint32_t i = 0; i < kMergedStreams; ++i) in.args[i] = i < n ? stream_arg(i) : StreamArg{};
+    auto kernel = wide ? merged_table_kernel<true> : merged_table_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(merged_blocks), dim3(kMergedBlock), 0, stream, in, quant, cdesc, ctl, table, d, shift, n_tiles,
+                       found, status);
+  } else {
+    profile_mark(CVLC_STAGE_DEC_SETUP, true, stream);
+    {
+      ParseChunk chunk;
+      chunk.pad[0] = chunk.pad[1] = 0;
+      // One launch parses and numbers, 3.5 us for every 16 streams; two launches, the first with a workgroup per stream, take
+      // 4.2 + 3.8 for 17 and 4.8 + 10.8 for 100 (35 us in one).  The second launch costs a small call 2 us on the host:
+      // a call of 17 streams of 20 000 coordinates takes 20.5 us with one and 22.6 with two, of 32 25 either way.
+      const bool fused = n > 0 && n <= kFusedStreams;
+      for (uint32_t first = 0; first < n; first += kParseStreams) {
+        chunk.first = first;
+        chunk.count = (n - first < kParseStreams) ? n - first : kParseStreams;
+        for (uint32_t i = 0; i < chunk.count; ++i) chunk.args[i] = stream_arg(first + i);
+        if (fused)
+          hipLaunchKernelGGL(setup_kernel, dim3(1), dim3(1024), 0, stream, chunk, descs, d, quant, cdesc, item_start, ctl,
+                             stream_bad, status);
+        else
+          hipLaunchKernelGGL(parse_headers_kernel, dim3(chunk.count), dim3(64), 0, stream, chunk, descs, d, n, stream_bad,
+                             quant);
+      }
+      // also for n = 0: writes the (empty) list counts and the status word
+      if (!fused)
+        hipLaunchKernelGGL(compact_lists_kernel, dim3(1), dim3(1024), 0, stream, descs, n_lists, cdesc, item_start, ctl,
+                           stream_bad, n, status);
+    }
+    profile_mark(CVLC_STAGE_DEC_SETUP, false, stream);
+    if (n > 0) {
+      StageScope scope(CVLC_STAGE_DEC_TABLE, stream);
+      // the number of work items is only known on the device
+      auto kernel = wide ? tile_table_kernel<true> : tile_table_kernel<false>;
+      hipLaunchKernelGGL(kernel, dim3(kTableBlocks), dim3(kBlock), 0, stream, cdesc, item_start, ctl, table, d, shift, n_tiles,
+                         n_lists, status);
+    }
   }
   {
     StageScope scope(CVLC_STAGE_DEC_TILES, stream);
@@ -823,7 +948,7 @@ int cvlc_decode_aggregate(uint32_t n, const void* const* d_streams, const size_t
                   : large ? (qsgd ? decode_tiles_kernel<true, false, kDecShiftMax> : decode_tiles_kernel<false, false, kDecShiftMax>)
                           : (qsgd ? decode_tiles_kernel<true, false, kDecShiftMin> : decode_tiles_kernel<false, false, kDecShiftMin>);
     hipLaunchKernelGGL(kernel, dim3(g), dim3(kDecBlock), 0, stream, cdesc, ctl, table, d_out, d, n_tiles, position_bits(d),
-                       flags & CVLC_DECODE_ACCUMULATE, status);
+                       flags & CVLC_DECODE_ACCUMULATE, found, merged ? merged_blocks : 0u, status);
   }
   return hip_check(hipGetLastError());
 }

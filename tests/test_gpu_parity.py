@@ -433,7 +433,7 @@ def test_decode_at_the_steps_of_the_list_search(n, R):
 # Lists are dealt out to 1, 2, 4 or 8 groups of wavefronts, 60 to each, and to several sweeps beyond 480: both sides of
 # every step, empty lists among them, with few records and with every coordinate kept (a wavefront's share is many turns).
 @pytest.mark.parametrize("quant", [cv.QUANT_PQ, cv.QUANT_QSGD])
-@pytest.mark.parametrize("n,R", [(1, 1), (1, 31), (12, 5), (61, 1), (15, 8), (11, 11), (16, 15), (241, 1), (32, 15), (37, 13), (70, 14)])
+@pytest.mark.parametrize("n,R", [(1, 1), (1, 31), (8, 31), (9, 31), (12, 5), (61, 1), (15, 8), (11, 11), (16, 15), (241, 1), (32, 15), (37, 13), (70, 14)])
 def test_decode_at_the_steps_of_the_lists_share(n, R, quant):
     rng = np.random.default_rng(n * 100 + R)
     d = 9001                                       # two tiles and a part of a third
