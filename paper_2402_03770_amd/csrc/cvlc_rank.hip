@@ -100,6 +100,13 @@ struct RankLayout {
 size_t align256(size_t v) { return (v + 255u) & ~(size_t)255u; }
 
 uint32_t pass_blocks_per_client(uint32_t d, uint32_t n, uint32_t per_cu);
+uint32_t list_blocks_per_client(uint32_t d, uint32_t n);
+uint32_t wave_cap_for(uint32_t d, uint32_t blocks);
+
+// One pass fewer over the vectors for three small launches and longer lists, which are longest for vectors of rows with
+// a scale of their own.  4 vectors of 25.6 M: 222 -> 217 us, of rows 211 -> 263; 12 of 11.2 M: 315 -> 254, of rows 290 ->
+// 275; 32 of 11.2 M: 540 -> 431, of rows 528 -> 462.  For vectors that have the sample's pieces several times over.
+bool one_pass_for(uint32_t n, uint32_t d) { return (uint64_t)n * d >= (7u << 24) && d >= (1u << 20); }
 
 // d = 0: the layout without lists.  With lists, every wavefront of the collecting pass owns room for all
 // the keys it reads (whole tiles, plus the last d % 4 coordinates), so nothing has to be counted first.
@@ -114,10 +121,8 @@ RankLayout rank_layout(uint32_t n, uint32_t d) {
   L.blocks = 0;
   L.wave_cap = 0;
   if (d) {
-    L.blocks = pass_blocks_per_client(d, n, 2u);
-    const uint32_t tiles = (d / 4u + kRankBlock * kDeep - 1) / (kRankBlock * kDeep);
-    const uint32_t tiles_per_block = (tiles + L.blocks - 1) / L.blocks;
-    L.wave_cap = tiles_per_block * (kDeep * kWave * 4u) + kWave;
+    L.blocks = list_blocks_per_client(d, n);
+    L.wave_cap = wave_cap_for(d, L.blocks);
     const size_t n_lists = (size_t)n * L.blocks * kRankWaves;
     L.list_cnt = off; off = align256(off + n_lists * sizeof(uint32_t));
     L.lists = off; off = align256(off + n_lists * L.wave_cap * sizeof(uint32_t));
@@ -832,9 +837,7 @@ __global__ __launch_bounds__(kRankBlock) void rank_stream_kernel(const float* co
   }
 }
 
-// Workgroups per client in a streaming pass: per_cu 1024-thread workgroups on every CU, never more than
-// there are tiles.
-uint32_t pass_blocks_per_client(uint32_t d, uint32_t n, uint32_t per_cu) {
+uint32_t cu_count() {
   static int cus = 0;
   if (cus == 0) {
     int dev = 0, found = 0;
@@ -843,10 +846,31 @@ uint32_t pass_blocks_per_client(uint32_t d, uint32_t n, uint32_t per_cu) {
         hipDeviceGetAttribute(&found, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && found > 0)
       cus = found;
   }
-  const uint32_t tiles = (d / 4u + kRankBlock * kDeep - 1) / (kRankBlock * kDeep);
-  uint32_t b = ((uint32_t)cus * per_cu + n - 1) / n;
-  if (b > tiles) b = tiles;
-  return b < 1 ? 1u : b;
+  return (uint32_t)cus;
+}
+
+uint32_t tiles_of(uint32_t d) { return std::max(1u, (d / 4u + kRankBlock * kDeep - 1) / (kRankBlock * kDeep)); }
+
+// Workgroups per client in a streaming pass: per_cu 1024-thread workgroups on every CU, never more than
+// there are tiles.
+uint32_t pass_blocks_per_client(uint32_t d, uint32_t n, uint32_t per_cu) {
+  return std::max(1u, std::min((cu_count() * per_cu + n - 1) / n, tiles_of(d)));
+}
+
+// Keys that a wavefront reads of a client whose tiles are dealt round `blocks` workgroups: whole tiles, and the last d % 4.
+uint32_t wave_cap_for(uint32_t d, uint32_t blocks) { return (tiles_of(d) + blocks - 1) / blocks * (kDeep * kWave * 4u) + kWave; }
+
+// ... in the pass that writes the lists.  One pass: two for every CU.  Two passes: of the collecting one a CU holds one at a
+// time, so as many as are held at once, that the prologue and the counters added up at the end (10 us of a small call) are paid
+// once; twice as many where a client's whole number of them would leave more than an eighth of the CUs idle.  (Two for every CU,
+// rounded up: 1 x 11.2 M 72 us instead of 59, 8 x 1.2 M 71 and 57, 8 x 11.2 M 181 and 164; one, rounded up: 12 x 9.6 M 256
+// instead of 239, the last eight of 264 alone.)  Where few tiles a workgroup make such lists need more room than two for every CU
+// do, it is those.
+uint32_t list_blocks_per_client(uint32_t d, uint32_t n) {
+  const uint32_t cus = cu_count(), twice = pass_blocks_per_client(d, n, 2u), once = cus / n;
+  if (one_pass_for(n, d)) return twice;
+  const uint32_t held = std::max(1u, std::min(once * n >= cus - cus / 8u ? once : 2u * cus / n, tiles_of(d)));
+  return (uint64_t)held * wave_cap_for(d, held) <= (uint64_t)twice * wave_cap_for(d, twice) ? held : twice;
 }
 
 }  // namespace
@@ -908,10 +932,7 @@ int cvlc_fit_alpha(uint32_t n, const float* const* d_updates, uint32_t d, double
   }
   const dim3 pass_grid(pass_blocks_per_client(d, n, 2u), n);
   KeyLists kl = {nullptr, nullptr, 0u, 0u};
-  // One pass fewer over the vectors for three small launches and longer lists, which are longest for vectors of rows with
-  // a scale of their own.  4 vectors of 25.6 M: 222 -> 217 us, of rows 211 -> 263; 12 of 11.2 M: 315 -> 254, of rows 290 ->
-  // 275; 32 of 11.2 M: 540 -> 431, of rows 528 -> 462.  For vectors that have the sample's pieces several times over.
-  const bool one_pass = L.wave_cap && (uint64_t)n * d >= (7u << 24) && d >= (1u << 20);
+  const bool one_pass = L.wave_cap && one_pass_for(n, d);
   if (one_pass) {
     // the parts' counts lie where the lists will: 32 KB a client of at least 4 MB
     uint16_t* parts = reinterpret_cast<uint16_t*>(base + L.lists);
@@ -928,8 +949,10 @@ int cvlc_fit_alpha(uint32_t n, const float* const* d_updates, uint32_t d, double
     kl.list_cnt = list_cnt;
     kl.per_client = L.blocks * kRankWaves;
     kl.wave_cap = L.wave_cap;
-    // a few workgroups per client: their cost is clearing and adding up the counters, and less so reading the keys
-    const dim3 list_grid(std::min(L.blocks, 16u), n);
+    // a few workgroups per client, whose cost is clearing and adding up the counters, and less so reading the keys; one
+    // for every CU where 16 leave most CUs idle (16 and one for every CU: 1 x 11.2 M 99 -> 72 us, 4 x 11.2 M
+    // 119 -> 112, 8 x 11.2 M 184 -> 181; 12 x 11.2 M 221 with 16, 225 with 32)
+    const dim3 list_grid(std::min(L.blocks, n <= 8u ? std::max(16u, cu_count() / n) : 16u), n);
     if (one_pass) {
       hipLaunchKernelGGL(rank_stream_kernel, dim3(L.blocks, n), dim3(kRankBlock), 0, stream, ptrs, ctls, d, lists, list_cnt,
                          L.wave_cap, status);

@@ -1143,6 +1143,15 @@ def test_fit_alpha_more_clients_than_one_upload_holds():
     check_fit([(rng.standard_t(3, 5000) * 1e-3).astype(np.float32) for _ in range(600)])
 
 
+# The collecting pass has a workgroup for every CU, two where a client's share of them is not a whole number, or those of the
+# other passes where short lists would need more room; the lists' passes 16 a client or, up to eight clients, one for every CU.
+@pytest.mark.parametrize("n,d", [(1, 16_385), (1, 4_200_001), (2, 2_104_225), (8, 150_003), (9, 150_003), (12, 70_001), (100, 40_000), (129, 20_000)])
+def test_fit_alpha_at_the_steps_of_the_workgroups(n, d):
+    rng = np.random.default_rng(n + d)
+    host = [(rng.standard_t(3, d) * 1e-3).astype(np.float32) for _ in range(min(n, 5))]
+    check_fit([host[c % len(host)] for c in range(n)])
+
+
 @pytest.mark.parametrize("d", [2_100_003, 2_097_152])
 def test_fit_alpha_in_one_pass(d):
     """From 7 x 2^24 coordinates on the level-1 bins of the ranks are guessed from a sample: ordinary vectors, tied ones, and
