@@ -12,6 +12,7 @@
 //                  tile_table work items they need
 //   tile_table     one streaming pass over all records: for every list, the
 //                  first record of every output tile (and the order/range checks)
+//   merged_table   the three of them in one launch, for a few streams
 //   decode_tiles   fused decode + accumulate + single write of each tile (a second
 //                  instance splits QSGD's sign bit from the level)
 #include <hip/hip_runtime.h>
