@@ -323,19 +323,26 @@ int cvlc_device_status(const void* d_workspace, void* hip_stream, uint32_t* stat
  * process brackets the stages selected in stage_mask (bit i = stage i) with a
  * pair of HIP events on the call's stream.  cvlc_profile_stop waits for those
  * events and returns, per stage, the summed elapsed milliseconds and the number
- * of brackets; both arrays hold CVLC_PROFILE_STAGES entries.  Not thread safe. */
+ * of brackets; both arrays hold CVLC_PROFILE_STAGES entries.  A stage that a
+ * call does not have gets no bracket: vectors of up to 65 536 coordinates are
+ * encoded without SAMPLE, FILTER, REFILTER and LAYOUT, and as a rule without
+ * SETUP; up to eight streams are decoded without SETUP as a rule.  Not thread
+ * safe. */
 enum {
-  CVLC_STAGE_ENC_SETUP = 0,    /* clear scratch, upload per-client parameters   */
+  CVLC_STAGE_ENC_SETUP = 0,    /* clear scratch, upload per-client parameters; short vectors: */
+                               /* only where one launch's arguments do not hold them */
   CVLC_STAGE_ENC_SAMPLE = 1,   /* sample histogram -> candidate threshold       */
   CVLC_STAGE_ENC_FILTER = 2,   /* the full pass over the update vectors         */
-  CVLC_STAGE_ENC_REFILTER = 3, /* prefix of the kept runs, boundaries' bins; */
+  CVLC_STAGE_ENC_REFILTER = 3, /* prefix of the kept runs, boundaries' bins;    */
                                /* keep-all second pass if the sample misjudged  */
-  CVLC_STAGE_ENC_SELECT = 4,   /* dense candidate list, exact boundary keys, ties */
+  CVLC_STAGE_ENC_SELECT = 4,   /* dense candidate list, exact boundary keys, ties; short */
+                               /* vectors: all that lies before the group counts */
   CVLC_STAGE_ENC_CLASSIFY = 5, /* group counts and statistics                   */
   CVLC_STAGE_ENC_LAYOUT = 6,   /* prefix sums, headers, statistics block        */
   CVLC_STAGE_ENC_EMIT = 7,     /* quantise + pack                               */
   CVLC_STAGE_DEC_SETUP = 8,    /* header parsing, list numbering                */
-  CVLC_STAGE_DEC_TABLE = 9,    /* per-list tile boundaries                      */
+  CVLC_STAGE_DEC_TABLE = 9,    /* per-list tile boundaries; a few streams: all that lies */
+                               /* before the tiles                              */
   CVLC_STAGE_DEC_TILES = 10,   /* fused decode + accumulate                     */
   CVLC_STAGE_FIT_ALPHA = 11,   /* cvlc_fit_alpha, the whole call                */
   CVLC_PROFILE_STAGES = 12

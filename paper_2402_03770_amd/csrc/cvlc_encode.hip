@@ -2701,10 +2701,10 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
   const uint32_t n_src = d / kSamplePiece;
   const uint32_t n_s = n_src < kSampleChunksMax ? n_src : kSampleChunksMax;
 
-  profile_mark(CVLC_STAGE_ENC_SETUP, true, stream);
   // the status word and the control blocks start every call at zero
   uint32_t zero_n16 = (uint32_t)((is_short ? SL.ctl : L.zero_bytes) / 16u);  // n <= 65535 clients: below 2^32 pieces
   auto short_select = [&](auto source, uint32_t clients, bool first) {
+    StageScope scope(CVLC_STAGE_ENC_SELECT, stream);
     hipLaunchKernelGGL(short_select_kernel<decltype(source)>, dim3(clients), dim3(kShortBlock), 0, stream, source, ws.params, ws.ctl, ws,
                        d_stats_out, first ? 1u : 0u);
   };
@@ -2719,6 +2719,7 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
     chunk.pad = 0;
     uint32_t refs[kUploadWords];  // the chunk's references, appended behind its templates when it is sent
     bool one_chunk = true;  // all clients' parameters fit one launch's arguments
+    bool uploading = false;
     auto send = [&](bool last) {
       std::memcpy(&chunk.data[chunk.n_templates * kParamWords], refs, (size_t)chunk.n_clients * kRefWords * 4u);
       one_chunk = one_chunk && last;
@@ -2726,6 +2727,8 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
         short_select(chunk, chunk.n_clients, true);
         return;
       }
+      if (!uploading) profile_mark(CVLC_STAGE_ENC_SETUP, true, stream);
+      uploading = true;
       const uint32_t blocks = zero_n16 ? (zero_n16 + 1023u) / 1024u : 1u;
       hipLaunchKernelGGL(upload_kernel, dim3(blocks < 512u ? blocks : 512u), dim3(256), 0, stream,
                          reinterpret_cast<uint32_t*>(ws.params), chunk, reinterpret_cast<uint4*>(base + L.status),
@@ -2776,9 +2779,9 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
       }
     }
     if (chunk.n_clients) send(true);
+    if (uploading) profile_mark(CVLC_STAGE_ENC_SETUP, false, stream);
     if (is_short && !one_chunk) short_select(ParamsUploaded{ws.params}, n, false);
   }
-  profile_mark(CVLC_STAGE_ENC_SETUP, false, stream);
 
   if (!is_short) {
     {

@@ -121,6 +121,21 @@ def test_cfg1_roundtrip_bit_exact():
     assert np.all(got[~kept] == 0) and kept.sum() == p.k
 
 
+@pytest.mark.parametrize("cfg,clients,kernel", [(1, 1, "short_select_kernel"), (2, 2, "filter_kernel")])
+def test_benchmark_reports_the_kernel_that_ran(cfg, clients, kernel, monkeypatch, capsys):
+    """Short vectors have no filter launch, whose bracket the benchmark's roofline was read off."""
+    import json
+    import sys
+
+    import bench
+
+    monkeypatch.setattr(sys, "argv", ["bench.py", "--cfg", str(cfg), "--clients", str(clients), "--steps", "2", "--warmup", "1",
+                                      "--no-cpu-baseline", "--stages"])
+    assert bench.main() == 0
+    line = json.loads(capsys.readouterr().out.strip().splitlines()[-1])
+    assert line["roofline"]["kernel"] == kernel and line["roofline"]["launch_ms"] > 0.0 and line["value"] > 0.0
+
+
 def test_encode_is_deterministic_and_seed_sensitive():
     U = syn.update_vector(1, 5, d=50_000)
     p = orc.plan_fractions(U.size, [6, 3, 1], [0.05, 0.1, 0.2])
