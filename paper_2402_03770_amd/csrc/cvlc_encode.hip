@@ -1572,7 +1572,6 @@ __global__ __launch_bounds__(kShortBlock) void short_select_kernel(Params source
   static_assert(sizeof(SegPartial) * kSegCopies == kShortBlock * 4u, "a word per thread");
   reinterpret_cast<uint32_t*>(ctl->seg)[tid] = 0;
   for (uint32_t i = tid; i < 32u * kNormLimbs; i += kShortBlock) ws.norm_limbs[(size_t)client * 32u * kNormLimbs + i] = 0;
-  if (stats_out && tid < R) stats_out[(size_t)client * kStatsStride + tid].errsq = 0.0;  // the pack kernel adds to it when asked to
   const uint32_t flags = tid < kTopBins - (0x7F800000u >> kTopShift) ? S.top[(0x7F800000u >> kTopShift) + tid] : 0u;
   locate_short(S);
   const bool dead = check_room && short_of_room(S, update, d, ws.dense_cap, p.sample_rank);  // uniform
@@ -1585,7 +1584,8 @@ __global__ __launch_bounds__(kShortBlock) void short_select_kernel(Params source
     ctl->emit_claim = 0;
     if (dead) p.stream[0] = 0u;  // not a stream header
   }
-  if (dead) return;
+  if (dead) return;  // a refused client's statistics are not touched
+  if (stats_out && tid < R) stats_out[(size_t)client * kStatsStride + tid].errsq = 0.0;  // the pack kernel adds to it when asked to
   select_short(S, update, d);
   if (tid < 32u) {
     const bool none = tid >= R || S.rank[tid] == 0u;

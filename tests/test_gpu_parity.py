@@ -318,10 +318,12 @@ def test_short_vectors_of_many_plans():
     check_encode(host, plans, 23, list(range(n)))
 
 
-def test_short_vectors_are_refused_by_the_same_rule():
+@pytest.mark.parametrize("error_stats", [False, True])
+@pytest.mark.parametrize("d", [50_047, SHORT_MAX + 47])
+def test_short_vectors_are_refused_by_the_same_rule(d, error_stats):
     """A vector has as many candidates as it has keys at or above the lower edge of the 13-bit bin that holds the sample's
     rank-th largest, the sample being all but the last d mod 64 coordinates; a workspace with less room refuses it."""
-    d, k = 50_047, 9_000
+    k = 9_000
     rng = np.random.default_rng(31)
     U = rng.standard_normal(d).astype(np.float32)
     key = U.view(np.uint32) & np.uint32(0x7FFFFFFF)
@@ -335,11 +337,18 @@ def test_short_vectors_are_refused_by_the_same_rule():
     for room, expected in ((c, 0), (c - slack, cv.DEV_WORKSPACE)):
         stream = cv.new_stream_buffer(p, DEV)
         stream.fill_(-1)
+        stats = torch.full((cv.STATS_STRIDE * C.sizeof(cv.SegStats),), 0xA5, dtype=torch.uint8, device=DEV)
         ws = cv.new_workspace(cv.encode_workspace_bytes_for(d, 1, room), DEV)
         ws.fill_(255)
-        cv.encode_batch([p], [torch.from_numpy(U).to(DEV)], 21, [3], [stream], ws)
+        cv.encode_batch([p], [torch.from_numpy(U).to(DEV)], 21, [3], [stream], ws, stats, error_stats=error_stats)
         assert cv.device_status(ws) == expected
         assert (int(stream[0].item()) == 0) == (expected != 0)
+        # a refused client's entries are not written, not even in part; an encoded one's all are
+        entries = stats.view(cv.STATS_STRIDE, -1)
+        assert bool((entries[p.n_coded + 1:] == 0xA5).all())
+        assert bool((entries[: p.n_coded + 1] == 0xA5).all(dim=1).any()) == (expected != 0)
+        if expected:
+            assert bool((stats == 0xA5).all())
 
 
 def encode_stage_us(update, plan, stage, repeats=5):
