@@ -1665,12 +1665,6 @@ __device__ __forceinline__ uint64_t same_group_lanes(uint32_t g) {
   return coded & ~(((uint64_t)differ_hi << 32) | differ_lo);
 }
 
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor(v, o, 64));
-  return v;
-}
-
 // Loads span `span` of the dense list (kPerLane candidates per lane, row j at
 // span*512 + j*64 + lane, i.e. in position order).  No branch around the loads (a lane past
 // the end reads the last candidate again): all eight are in flight before the first is waited for.

@@ -351,6 +351,47 @@ def test_short_vectors_are_refused_by_the_same_rule(d, error_stats):
             assert bool((stats == 0xA5).all())
 
 
+def _equal_keys(kind, d, rng):
+    """Short vectors whose boundaries' bins (14 bits of the key) hold more than is set aside, or large classes of equal keys."""
+    sign = np.where(rng.random(d) < 0.5, -1.0, 1.0)
+    if kind == "one magnitude":
+        return (sign * 1e-3).astype(np.float32)
+    if kind == "two magnitudes":
+        return (sign * np.where(rng.random(d) < 0.4, 3e-3, 1e-3)).astype(np.float32)
+    if kind == "seven magnitudes":
+        return (sign * rng.integers(1, 8, d) * 1e-3).astype(np.float32)
+    if kind == "int8":
+        x = rng.standard_normal(d)
+        return (np.round(x * 127 / np.abs(x).max()) * 1e-5).astype(np.float32)
+    if kind == "two a bin":        # as many keys as bfloat16 has in a bin, most of the vector in three bins
+        return (sign * (1.0 + rng.integers(0, 6, d) / 128.0)).astype(np.float32)
+    if kind == "five in one bin":  # no key of a bin is most of it
+        return (sign * (1.0 + rng.integers(0, 5, d) / 1024.0)).astype(np.float32)
+    if kind == "one bin":          # nothing but different keys
+        return (sign * (1.0 + rng.permutation(d) * 2.0 ** -23)).astype(np.float32)
+    if kind == "sorted":           # a bin's keys side by side: few wavefronts come across them
+        return np.sort(rng.standard_normal(d)).astype(np.float32)
+    assert kind == "at the ends"   # a class whose members are the first and the last coordinates
+    x = (rng.standard_normal(d) * 1e-3).astype(np.float32)
+    x[:70] = x[-150:] = 2e-3
+    return x
+
+
+@pytest.mark.parametrize("R", [1, 6, 31])
+@pytest.mark.parametrize("kind", ["one magnitude", "two magnitudes", "seven magnitudes", "int8", "two a bin", "five in one bin", "one bin",
+                                  "sorted", "at the ends"])
+@pytest.mark.parametrize("d", [9001, 40_003, SHORT_MAX - 1, SHORT_MAX])
+def test_short_vectors_with_full_bins(d, kind, R):
+    """All three ways that the members of the boundaries' bins are counted in, and the ties of each."""
+    U = _equal_keys(kind, d, np.random.default_rng(d + R))
+    counts = [max(1, d * 9 // 10 * (r + 1) // (R * (R + 1) // 2)) for r in range(R)]
+    if kind == "at the ends":      # a boundary inside the class, in each of its halves
+        k = int(np.count_nonzero(np.abs(U) > 2e-3))
+        counts = [k + 60, 50, 100][: min(R, 3)] + [7] * max(R - 3, 0)
+    p = orc.plan_manual(d, [max(1, 14 - r // 2) for r in range(R)], counts)
+    check_encode([U], [p], 29, [5])
+
+
 def encode_stage_us(update, plan, stage, repeats=5):
     """Shortest time of a stage of an encode call, on a workspace full of ones: what the call before left there must not matter."""
     ws = cv.new_workspace(cv.encode_workspace_bytes(plan.d, 1), DEV)
