@@ -2599,6 +2599,24 @@ uint32_t filter_resident_blocks() {
   return cached[dev];
 }
 
+// Short vectors take three launches instead of ten: 1 x 2000 54 -> 26 us, 1 x 65 536 59 -> 41 (31 groups 68 -> 50), 32 x 65 536
+// 76 -> 48, 100 x 65 536 of 31 groups 207 -> 122.  They go up to 65 536 coordinates because a place in one has 16 bits (a part of
+// 256 coordinates and a byte): longer ones have not been tried.
+// Of many long ones the general path reads all and then works on what it keeps, which is less than going through all of it
+// again in the counting and the packing pass, unless next to nothing or a good part is kept.  us in ten launches and in
+// three, 3 % kept: 144 x 65 536 104 and 90, 256 x 58 000 150 and 142, 300 x 65 536 191 and 203, 513 x 65 536 314 and 346, 2000 x 65 536
+// 1244 and 1314, 2000 x 40 000 1247 and 1245; 30 % kept, 300 x 65 536 222 and 215; half a percent, 208 x 65 536 136 and 124.
+constexpr uint64_t kShortAll = 9u << 20;      // coordinates of a batch: 144 of the longest
+constexpr uint32_t kShortAnyNumber = 40960u;  // coordinates of a vector
+bool short_pays(uint32_t n, const cvlc_plan_t* plans) {
+  const uint64_t all = (uint64_t)n * plans[0].d;
+  if (all <= kShortAll || plans[0].d <= kShortAnyNumber) return true;
+  uint64_t kept = 0;
+  for (uint32_t i = 0; i < n; ++i)
+    for (uint32_t r = 0; r < plans[i].n_coded; ++r) kept += plans[i].count[r];
+  return kept * 128u <= all || kept * 10u >= all * 3u;
+}
+
 }  // namespace
 }  // namespace cvlc
 
@@ -2647,10 +2665,7 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
   const uint32_t d = plans[0].d;
   const EncodeLayout L = encode_layout(d, n, candidate_room(d, n, ws_bytes));
   const ShortLayout SL = short_layout(d, n);
-  // Short vectors take three launches instead of ten, whatever their number: 1 x 2000 52 -> 25 us, 1 x 65 536 59 -> 40 (31
-  // groups 64 -> 48), 32 x 65 536 76 -> 46, 100 x 65 536 116 -> 82, 1000 x 65 536 707 -> 563 (3 % kept: 516 either way).  Beyond
-  // 65 536 coordinates a position takes more than 16 bits in the list, and two passes of one workgroup 10 us more for every 65 536.
-  const bool is_short = d <= kShortMax && SL.total <= ws_bytes;
+  const bool is_short = d <= kShortMax && SL.total <= ws_bytes && short_pays(n, plans);
   char* base = static_cast<char*>(d_workspace);
   Workspace ws;
   ws.status = reinterpret_cast<uint32_t*>(base + L.status);

@@ -309,6 +309,21 @@ def test_short_vectors(d, kind, R):
     assert_stream_equal(words[0], orc.encode(U, q, 20, 7).words)
 
 
+@pytest.mark.parametrize("n,d,share,filtered", [(144, SHORT_MAX, 0.03, False), (145, SHORT_MAX, 0.03, True), (145, SHORT_MAX, 0.007, False),
+                                                (145, SHORT_MAX, 0.301, False), (231, 40_961, 0.03, True), (300, 40_960, 0.03, False)])
+def test_many_short_vectors(n, d, share, filtered):
+    """Many long ones of the short vectors, of which some but not much is kept, are encoded like long vectors."""
+    rng = np.random.default_rng(n)
+    U = [rng.standard_normal(d).astype(np.float32) for _ in range(3)]
+    p = orc.plan_manual(d, [9, 5], [d // 1000, int(d * share) - d // 1000])
+    cv.profile_start(["enc_filter"])
+    words, _, status, _ = gpu_encode([U[c % 3] for c in range(n)], [p] * n, 31, list(range(n)), want_stats=False)
+    assert ("enc_filter" in cv.profile_stop()) == filtered
+    assert status == 0
+    for c in (0, 1, 2, n // 2, n - 1):
+        assert_stream_equal(words[c], orc.encode(U[c % 3], p, 31, c).words, f"client {c}")
+
+
 def test_short_vectors_of_many_plans():
     """More different plans than one launch's arguments hold, groups of no coordinates among them."""
     d, n = 3001, 45
