@@ -162,8 +162,8 @@ def test_ragged_sizes(d):
     check_decode(refs, d)
 
 
-def test_degenerate_plans():
-    d = 20_000
+@pytest.mark.parametrize("d", [20_000, 70_001])
+def test_degenerate_plans(d):
     U = syn.update_vector(2, 1, d=d)
     cases = [
         ([], []),                                  # nothing coded: header-only stream
@@ -251,7 +251,8 @@ def test_boundary_ties_inside_smooth_data():
 
 
 @pytest.mark.parametrize("n,d", [(1, 1024), (1, 1025), (2, 3 * 1024 - 1), (6, 1024 * 1024), (6, 1024 * 1024 + 1),
-                                 (7, 2048 * 877 + 2047), (12, 1024 * 1024 + 8191)])
+                                 (7, 2048 * 877 + 2047), (12, 1024 * 1024 + 8191),
+                                 (1, 65 * 1024), (1, 65 * 1024 + 1), (2, 66 * 1024 - 1)])   # lengths that have a filter
 def test_region_lengths(n, d):
     """The filter's regions have 1024 to 8192 coordinates, by the size of the batch: sizes at the steps of that rule
     and with a last region of one coordinate, one missing, or one too many."""
@@ -580,6 +581,16 @@ def test_more_clients_than_the_chip_holds_workgroups_for():
     check_decode(refs, d)
 
 
+def test_more_clients_of_long_vectors_than_the_chip_holds_workgroups_for():
+    """The same for vectors that pass the filter, whose gather and layout have a workgroup or more per client."""
+    d, n = 66_001, 96
+    host = [syn.update_vector(3 if c % 3 else 2, 1100 + c, d=d) for c in range(n)]
+    plans = [orc.plan_manual(d, [max(1, 12 - r) for r in range(R)], [(d // 60 + 13 * (c % 5)) // R + r for r in range(R)])
+             for c, R in ((c, (15, 31, 4)[c % 3]) for c in range(n))]
+    refs, _ = check_encode(host, plans, 5, list(range(n)))
+    check_decode(refs, d)
+
+
 def test_more_streams_than_one_header_launch_takes():
     """130 streams: their pointers travel as kernel arguments, 112 a launch, so the headers are parsed by two
     launches and the lists numbered by a third (up to 112 streams one launch does both)."""
@@ -754,8 +765,112 @@ def test_malformed_streams_set_status_and_stay_in_bounds():
     assert status == 0
 
 
-def test_non_finite_update_sets_status():
-    d = 30_000
+def build_stream(d, groups, quant=cv.QUANT_PQ, client=0):
+    """A stream written by hand: groups of (code length, ascending positions, codes, first and second header value)."""
+    s = max(1, (d - 1).bit_length())
+    words = [np.array([0x434C5643, 1 | quant << 16, d, len(groups), s, np.float32(1.0).view(np.uint32), client, 0], dtype=np.uint64)]
+    payloads = []
+    for y, pos, codes, a, b in groups:
+        words.append(np.array([y, len(pos), np.float32(a).view(np.uint32), np.float32(b).view(np.uint32)], dtype=np.uint64))
+        W, n = s + y, len(pos)
+        rec = np.asarray(pos, np.uint64) | np.asarray(codes, np.uint64) << np.uint64(s)
+        bit = np.arange(n, dtype=np.uint64) * np.uint64(W)
+        bits = np.zeros(((n * W + 31) // 32 + 3) * 32, dtype=np.uint8)
+        for i in range(W):
+            bits[bit + np.uint64(i)] = (rec >> np.uint64(i)) & np.uint64(1)
+        payloads.append(np.packbits(bits, bitorder="little").view(np.uint32)[: (n * W + 31) // 32].astype(np.uint64))
+    out = np.concatenate(words + payloads).astype(np.uint32)
+    out[7] = out.size
+    return out
+
+
+def check_decode_ulp(refs, d, quant=cv.QUANT_PQ):
+    got, status = gpu_decode([torch.from_numpy(s.view(np.int32)).to(DEV) for s in refs], d, quant=quant)
+    assert status == 0
+    ref = orc.decode_aggregate(refs, d).astype(np.float64)
+    # fp64 sums in free order, rounded to fp32 once: half a unit of the last place on either side
+    assert np.all(np.abs(got - ref) <= 2.0 ** -23 * np.abs(ref) + 1e-12 * abs_terms(refs, d))
+
+
+# Positions of more than 25 bits are read by eight bytes and, where a raw code follows, a ninth: 1 .. 8 streams (headers, numbers and
+# table in one launch), 9 and 26 of them (two and three launches).
+@pytest.mark.parametrize("quant", [cv.QUANT_PQ, cv.QUANT_QSGD])
+@pytest.mark.parametrize("n", [1, 3, 8, 9, 26])
+def test_decode_positions_of_26_bits(n, quant):
+    d = (1 << 25) + 12_345
+    rng = np.random.default_rng(n)
+    refs = []
+    for c in range(n):
+        groups = [(32, [d - 1 - c], [np.float32(0.5 + c).view(np.uint32)], 1.0, 0.0)]     # one record, in the last tile
+        for y, count in ((32, 500), (16, 3000), (7, 1), (2, 2000)):
+            pos = np.sort(np.unique(np.concatenate([rng.integers(0, d, count), [c, d - 1]]))) if count > 1 else [d // 2 + c]
+            codes = rng.standard_normal(len(pos)).astype(np.float32).view(np.uint32) if y == 32 else rng.integers(0, 1 << y, len(pos))
+            groups.append((y, pos, codes, *((2.0, 0.0) if quant else (-1.0, 1.5))))
+        groups.append((3, np.arange(8192 * 7 - 1, 8192 * 8 + 1), rng.integers(0, 8, 8194), *((2.0, 0.0) if quant else (-1.0, 1.5))))   # a whole tile
+        refs.append(build_stream(d, groups, quant, c))
+    check_decode_ulp(refs, d, quant)
+
+
+# Tiles of 8192 coordinates with lists dealt out to 1, 2, 4 and 8 groups of wavefronts and to two sweeps.
+@pytest.mark.parametrize("n,R", [(1, 31), (8, 8), (5, 25), (9, 28), (17, 31)])
+def test_decode_large_tiles_of_many_lists(n, R):
+    d = (1 << 23) + 77
+    rng = np.random.default_rng(n * 100 + R)
+    refs = []
+    for c in range(n):
+        groups = []
+        for r in range(R):
+            pos = np.unique(rng.integers(0, d, int(rng.integers(0, 3000))))
+            if (c + r) % 9 == 0:                                   # every coordinate of a tile and of the last one
+                pos = np.unique(np.concatenate([pos, np.arange(8192 * (5 + r) - 1, 8192 * (6 + r) + 1), np.arange(d - 700, d)]))
+            y = max(1, 16 - r // 2)
+            groups.append((y, pos, rng.integers(0, 1 << y, len(pos)), -0.5 - r, 2.0 + r))
+        refs.append(build_stream(d, groups, client=c))
+    check_decode_ulp(refs, d)
+
+
+# One malformed stream among good ones: 1 + 1 (headers, numbers and table in one launch), 1 + 8 (numbered by the launch that parses)
+# and 1 + 27 (by a launch of its own), tiles of 4096 and of 8192 coordinates.
+@pytest.mark.parametrize("n_good", [1, 8, 27])
+@pytest.mark.parametrize("d", [40_000, (1 << 23) + 77])
+def test_a_malformed_stream_among_good_ones(d, n_good):
+    rng = np.random.default_rng(d + n_good)
+    s = (d - 1).bit_length()
+
+    def one(client):
+        groups = []
+        for y in (9, 4):
+            pos = np.unique(np.concatenate([rng.integers(0, d, 3000), np.arange(9000, 9500)]))
+            groups.append((y, pos, rng.integers(0, 1 << y, len(pos)), -1.0, 1.5))
+        return build_stream(d, groups, client=client)
+
+    good = [one(c) for c in range(n_good)]
+    base = one(99)
+    weights = rng.uniform(0.5, 1.5, n_good + 1).tolist()
+    expected = orc.decode_aggregate(good, d, weights=weights[:n_good]).astype(np.float64)
+    tol = 2.0 ** -22 * np.abs(expected) + 1e-12
+    headers, records = [], []
+    for at, value in ((0, 1), (1, 2 << 16), (2, 1), (3, 64), (4, 1), (5, 0x80000000), (7, 1), (8, 16), (9, 1), (10, 0x40000000)):
+        w = base.copy()
+        w[at] ^= np.uint32(value)
+        headers.append(w)
+    w = base.copy(); w[16] |= np.uint32((1 << s) - 1); records.append(w)      # first position >= d
+    w = base.copy(); w[16:40] = base[40:64]; records.append(w)                 # positions out of order
+    for w in headers + records:
+        with pytest.raises(orc.OracleError):
+            orc.decode_aggregate([w], d)
+        streams = [torch.from_numpy(x.view(np.int32)).to(DEV) for x in good + [w]]
+        got, status = gpu_decode(streams, d, weights=weights)
+        assert status & cv.DEV_STREAM
+        assert np.all(np.isfinite(got))
+        if any(w is h for h in headers):                          # contributes nothing; the others add up
+            assert np.all(np.abs(got - expected) <= tol)
+    got, status = gpu_decode([torch.from_numpy(x.view(np.int32)).to(DEV) for x in good + [base]], d, weights=weights)
+    assert status == 0                                            # the untouched stream decodes
+
+
+@pytest.mark.parametrize("d", [30_000, 70_001])
+def test_non_finite_update_sets_status(d):
     p = orc.plan_fractions(d, [8], [0.1])
     for bad in (np.nan, np.inf, -np.inf):
         U = syn.update_vector(1, 0, d=d)
@@ -826,10 +941,11 @@ def test_random_plans_sizes_and_quantisers():
 
 
 # --------------------------------------------------------------------------- the caller's stream
-def test_every_call_runs_on_the_callers_stream():
+@pytest.mark.parametrize("d", [150_001, 40_001])
+def test_every_call_runs_on_the_callers_stream(d):
     """All work is enqueued on the stream handed in: on a side stream, behind a long-running
     kernel that produces the input, results are right without any device-wide synchronisation."""
-    d, n = 150_001, 2
+    n = 2
     host = [syn.update_vector(2, c, d=d) for c in range(n)]
     po = orc.plan_alg1(d, d, 5, -0.6)
     pl = to_lib_plan(po)
@@ -869,11 +985,12 @@ def test_every_call_runs_on_the_callers_stream():
     del filler
 
 
-def test_calls_can_be_captured_in_a_graph_and_replayed():
+@pytest.mark.parametrize("d", [90_001, 30_001])
+def test_calls_can_be_captured_in_a_graph_and_replayed(d):
     """The calls only launch kernels on the caller's stream (clears included), so a step can be
     recorded once and replayed: three replays on fresh inputs, with eager work and
     synchronisation in between, each checked against the oracle."""
-    d, n = 90_001, 3
+    n = 3
     po = orc.plan_manual(d, [10, 5, 2], [900, 4000, 9000])
     pl = to_lib_plan(po)
     updates = [torch.zeros(d, dtype=torch.float32, device=DEV) for _ in range(n)]
@@ -1001,8 +1118,8 @@ def test_qsgd_on_colliding_magnitudes_and_extreme_exponents(kind):
     check_qsgd([wide, -wide[::-1].copy()], plans * 2, 42, [0, 1])
 
 
-def test_qsgd_norm_overflow_and_mismatched_quantiser_are_reported():
-    d = 10_000
+@pytest.mark.parametrize("d", [10_000, 70_001])
+def test_qsgd_norm_overflow_and_mismatched_quantiser_are_reported(d):
     U = np.full(d, 3.0e38, dtype=np.float32)                       # every square is finite in the limbs, the norm is not
     p = orc.plan_manual(d, [8], [100], quant=orc.QSGD)
     _, _, status, _ = gpu_encode([U], [p], 1, [0], want_stats=False)
