@@ -886,8 +886,9 @@ int cvlc_decode_aggregate(uint32_t n, const void* const* d_streams, const size_t
     sa.pad = 0;
     return sa;
   };
-  // The most items that the streams can hold (a record has a code bit at least): a wavefront each, all of them resident, or the
-  // general path, whose table kernel starts without a prologue (8 x 25.6 M: 50.2 us, merged 53.4; 8 x 11.2 M, within the limit:
+  // Up to eight streams, a wavefront of the workgroup each (several to a wavefront have not been tried).  The most items that the
+  // streams can hold (a record has a code bit at least): a wavefront each, all of them resident, or the general path,
+  // whose table kernel starts without a prologue (8 x 25.6 M: 50.2 us, merged 53.4; 8 x 11.2 M, within the limit:
   // 35.6 and 34.4).
   uint64_t items_most = 0;
   for (uint32_t i = 0; i < n && n <= kMergedStreams; ++i)

@@ -9,7 +9,8 @@
 // position.  Launch chain per batch of clients (no kernel waits on another
 // workgroup and none needs a memory fence; every dependency is a kernel
 // boundary):
-// (short vectors, up to 65 536 coordinates: short_select, count and emit only)
+// (short vectors, up to 65 536 coordinates: short_select, count and emit only, unless they
+// are very many; see short_pays)
 //   upload        per-client parameters as kernel arguments; clears the
 //                 call's control blocks
 //   sample_hist   strided sample of |U| -> histogram of the top 13 key bits
@@ -1490,7 +1491,8 @@ __global__ __launch_bounds__(kSelectBlock) void select_kernel(const ClientParams
 // (cvlc_select.h): exact keys of all boundaries, and where a boundary cuts a class of equal keys the position
 // of the last one inside.  There are no candidates: the counting and packing passes go through the vector itself, a
 // coordinate's number is its position.  The kernel also puts the client's parameters and control block in place.
-// All latency (and what one CU gets of the memory's bandwidth).
+// Latency, and the instructions that one CU issues for every coordinate (1 x 65 536, three groups: 21 us, of which the first count
+// takes 6.5 and setting the boundaries' bins aside 8).
 
 // The parameters come as kernel arguments, or have been uploaded before (batches of many different plans).
 struct ParamsUploaded {
@@ -1542,6 +1544,7 @@ __device__ __forceinline__ bool short_of_room(ShortSelect& S, const float* updat
   return all > room;
 }
 
+static_assert(sizeof(UploadChunk) + sizeof(Workspace) + 4u * sizeof(void*) <= 4096, "kernel arguments are limited to 4 KB");
 template <class Params>
 __global__ __launch_bounds__(kShortBlock) void short_select_kernel(Params source, ClientParams* params, ClientCtl* ctls, Workspace ws,
                                                                    cvlc_seg_stats_t* stats_out, uint32_t first_launch) {
