@@ -881,6 +881,23 @@ def test_non_finite_update_sets_status(d):
             orc.encode(U, p, 1, 0)
 
 
+@pytest.mark.parametrize("d", [9001, 40_003, SHORT_MAX - 1, 70_001])
+def test_nan_of_the_largest_patterns(d):
+    """The largest keys there are, at a boundary, in vectors whose last visit has lanes to spare: reported, and the groups
+    have their sizes all the same (the selection goes by bit patterns)."""
+    rng = np.random.default_rng(d)
+    U = rng.standard_normal(d).astype(np.float32)
+    at = rng.choice(d, 230, replace=False)
+    U.view(np.uint32)[at[:30]] = 0x7FFFFFFF
+    U.view(np.uint32)[at[30:]] = 0xFFFE1234
+    p = to_lib_plan(orc.plan_manual(d, [8, 4], [100, 500]))
+    stream = cv.new_stream_buffer(p, DEV)
+    ws = cv.new_workspace(cv.encode_workspace_bytes(d, 1), DEV)
+    ws.fill_(255)
+    cv.encode_batch([p], [torch.from_numpy(U).to(DEV)], 3, [1], [stream], ws)
+    assert cv.device_status(ws) == cv.DEV_NONFINITE
+
+
 # --------------------------------------------------------------------------- seeded random sweep
 def test_random_plans_sizes_and_quantisers():
     """150 seeded combinations of length, group count, code lengths (raw, empty and 1-bit groups
