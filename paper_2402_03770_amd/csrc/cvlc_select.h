@@ -107,15 +107,15 @@ __device__ __forceinline__ void visit_short(const float* update, uint32_t d, Vis
   }
 }
 
-// counts[at] += unit for the lanes that are `on`.  Lanes that share the first one's counter add together: a rank inside a
+// counts[at] += 1 for the lanes that are `on`.  Lanes that share the first one's counter add together: a rank inside a
 // large class of equal keys would have all 64 queue up at one counter.
-__device__ __forceinline__ void add_together(uint32_t* counts, uint32_t at, bool on, uint32_t unit) {
+__device__ __forceinline__ void add_together(uint32_t* counts, uint32_t at, bool on) {
   const uint64_t mask = __ballot(on);
   if (!mask) return;  // uniform
   const uint32_t leader = (uint32_t)__builtin_ctzll(mask), lead = __builtin_amdgcn_readlane(at, leader);
   const uint64_t same = __ballot(on && at == lead);
   const bool first = lane_id() == leader;
-  if (first || (on && at != lead)) atomicAdd(&counts[at], first ? (uint32_t)__popcll(same) * unit : unit);
+  if (first || (on && at != lead)) atomicAdd(&counts[at], first ? (uint32_t)__popcll(same) : 1u);
 }
 
 // counts[at[c]] += unit for the lanes that are on[c], keys of a visit.  The first of them tells whether a class of kLargeClass
@@ -438,7 +438,7 @@ __device__ __forceinline__ void select_short(ShortSelect& S, const float* update
   if (listed) {
     for (uint32_t i = lane; i - lane < n_mine; i += kWave) {
       const bool on = i < n_mine;
-      add_together(&S.mid[0][0], (on ? S.list[wave][i] : 0u) >> 16, on, 1u);  // row * kMidDigits + digit
+      add_together(&S.mid[0][0], (on ? S.list[wave][i] : 0u) >> 16, on);  // row * kMidDigits + digit
     }
   } else {
     visit_short(update, d, [&](uint32_t, const uint32_t (&key)[4]) {
@@ -474,7 +474,7 @@ __device__ __forceinline__ void select_short(ShortSelect& S, const float* update
   if (listed) {
     for (uint32_t i = lane; i - lane < n_mine; i += kWave) {
       const uint32_t entry = i < n_mine ? S.list[wave][i] : 0u, u = i < n_mine ? (&S.mid[0][0])[entry >> 16] : 0u;
-      add_together(&S.low[0][0], (u - 1u) * kLowDigits + ((entry >> kPartShift) & (kLowDigits - 1u)), u != 0u, 1u);
+      add_together(&S.low[0][0], (u - 1u) * kLowDigits + ((entry >> kPartShift) & (kLowDigits - 1u)), u != 0u);
     }
     if (counted && wave == 0 && lane < kShortRanks && S.n_same[lane]) {
       const uint32_t key = S.same[lane], u = S.mid[lane >> same_bits][(key >> kMidShift) & (kMidDigits - 1u)];
@@ -543,7 +543,9 @@ __device__ __forceinline__ void visit_ties(ShortSelect& S, const float* update, 
         for (uint32_t step = kParts / kShortWaves / 2u; step; step >>= 1)
           if (S.start[(visit + step) * kShortWaves + wave] <= i) visit += step;
         const uint32_t part = wave == 0u && S.tail_start <= i ? d / 4u * 4u >> kPartShift : visit * kShortWaves + wave;
-        add_together(counts, part_word(v - 1u, part), v != 0u, 1u << ((part & 1u) * 16u));
+        // One by one, ten rounds at most: lanes with the same word may count different halves of it (the last d mod 4 coordinates'
+        // part can be the neighbour of one of the first wavefront's).
+        if (v) atomicAdd(&counts[part_word(v - 1u, part)], 1u << ((part & 1u) * 16u));
       }
     } else {
       visit_short(update, d, [&](uint32_t first, const uint32_t (&key)[4]) {

@@ -396,7 +396,7 @@ def _equal_keys(kind, d, rng):
 @pytest.mark.parametrize("R", [1, 6, 31])
 @pytest.mark.parametrize("kind", ["one magnitude", "two magnitudes", "seven magnitudes", "int8", "two a bin", "five in one bin", "one bin",
                                   "sorted", "at the ends"])
-@pytest.mark.parametrize("d", [9001, 40_003, SHORT_MAX - 1, SHORT_MAX])
+@pytest.mark.parametrize("d", [479, 9001, 12_591, 40_003, SHORT_MAX - 1, SHORT_MAX])   # 479, 12 591: the last three in a part of their own
 def test_short_vectors_with_full_bins(d, kind, R):
     """All three ways that the members of the boundaries' bins are counted in, and the ties of each."""
     U = _equal_keys(kind, d, np.random.default_rng(d + R))
