@@ -1359,7 +1359,8 @@ __global__ __launch_bounds__(kSelectBlock) void select_kernel(const ClientParams
     if (tid == 0) S.rem[r] = rem;
   } else {
     uint32_t over = my_over;
-    if (first != r) {
+    if (first != r) {  // the gather filled the list of the bin's first boundary
+      entries = (GlobalU64Ptr)ctl->list[first].entries;
       seen = seen_of(first);
       over = ctl->over_cnt[first];
     }
@@ -1416,7 +1417,7 @@ __global__ __launch_bounds__(kSelectBlock) void select_kernel(const ClientParams
     uint32_t rem = S.rem[b];
     unsigned long long prefix = 0;  // members at hand: those whose bits from `known` up are `prefix`
     uint32_t known = 63;            // keys have 31 bits
-    while (!found) {
+    while (!found && known != 0u) {  // no two members are alike: one is left at bit 0 at the latest
       __syncthreads();  // the round before is done with what is written below
       if (tid == 0) {
         S.min = ~0ull;

@@ -291,6 +291,19 @@ def test_selection_bins(d, kind, share):
     check_encode([U], [p], 17, [4])
 
 
+# A bin's members fit LDS up to 2048 of them, and the pool of its first boundary (6735 entries here) up to half of that.
+@pytest.mark.parametrize("members", [2047, 2048, 2049, 2700, 3367, 3368])
+def test_boundaries_that_share_a_bin_on_both_sides_of_its_lists_limits(members):
+    """32 classes of equal keys, each a selection bin of its own, most of them with two boundaries."""
+    d = 600_001
+    rng = np.random.default_rng(members)
+    U = (rng.standard_normal(d) * 1e-3).astype(np.float32)
+    U[rng.permutation(d)[: 32 * members]] = np.repeat(1.0 + np.arange(32) / 1024.0, members).astype(np.float32)
+    U *= np.where(rng.random(d) < 0.5, -1.0, 1.0).astype(np.float32)
+    p = orc.plan_manual(d, [max(1, 12 - r // 3) for r in range(31)], [300 + 17 * (r % 7) if r % 2 else 3300 for r in range(31)])
+    check_encode([U], [p], 33, [6])
+
+
 SHORT_MAX = 65_536  # vectors up to here are selected by one workgroup
 
 
