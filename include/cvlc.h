@@ -325,8 +325,8 @@ int cvlc_device_status(const void* d_workspace, void* hip_stream, uint32_t* stat
  * events and returns, per stage, the summed elapsed milliseconds and the number
  * of brackets; both arrays hold CVLC_PROFILE_STAGES entries.  A stage that a
  * call does not have gets no bracket: vectors of up to 65 536 coordinates are
- * encoded without SAMPLE, FILTER, REFILTER and LAYOUT, and as a rule without
- * SETUP; up to eight streams are decoded without SETUP as a rule.  Not thread
+ * encoded without SAMPLE, FILTER and REFILTER, and as a rule without
+ * SETUP; only batches of many clients that keep much have LAYOUT; up to eight streams are decoded without SETUP as a rule.  Not thread
  * safe. */
 enum {
   CVLC_STAGE_ENC_SETUP = 0,    /* clear scratch, upload per-client parameters; short vectors: */
@@ -338,7 +338,8 @@ enum {
   CVLC_STAGE_ENC_SELECT = 4,   /* dense candidate list, exact boundary keys, ties; short */
                                /* vectors: all that lies before the group counts */
   CVLC_STAGE_ENC_CLASSIFY = 5, /* group counts and statistics                   */
-  CVLC_STAGE_ENC_LAYOUT = 6,   /* prefix sums, headers, statistics block        */
+  CVLC_STAGE_ENC_LAYOUT = 6,   /* prefix sums, headers, statistics block (as a  */
+                               /* rule part of the packing)                     */
   CVLC_STAGE_ENC_EMIT = 7,     /* quantise + pack                               */
   CVLC_STAGE_DEC_SETUP = 8,    /* header parsing, list numbering                */
   CVLC_STAGE_DEC_TABLE = 9,    /* per-list tile boundaries; a few streams: all that lies */

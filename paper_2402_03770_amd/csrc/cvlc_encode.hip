@@ -38,7 +38,8 @@
 //                 QSGD quantiser also every group's exact sum of squares in
 //                 integer limbs
 //   layout        prefix of the per-span counts, headers (QSGD: the group norms
-//                 from the exact sums), statistics
+//                 from the exact sums), statistics; batches of many clients that keep
+//                 much only, in others emit does that for itself
 //   emit          per chunk of 8 spans: record number from prefix and span
 //                 number, stochastic rounding (Philox4x32-10) and bit packing;
 //                 on request the error energy of every group
@@ -1734,6 +1735,19 @@ __device__ __forceinline__ uint16_t* span_places(const Workspace& ws, uint32_t c
   return ws.cand_idx + (size_t)client * ws.d;
 }
 
+// What the counting and the packing pass work on, and where a record's number inside its group comes from.
+enum PassMode {
+  kByLayout,  // dense candidates; the layout kernel turns the spans' counts into prefixes
+  kByChunks,  // dense candidates; the counting pass also leaves every chunk's counts, from which a packing workgroup makes the prefixes it needs
+  kShortVec,  // a short vector's coordinates; a packing workgroup adds up the spans' counts
+};
+
+// kByChunks: members of every group in every chunk of eight spans, 32 words a chunk, in the place of the region slots' values,
+// which nothing reads once the boundaries are found (a chunk has 4096 candidates, a client d entries).
+__device__ __forceinline__ uint32_t* chunk_totals(const Workspace& ws, uint32_t client) { return ws.cand_val + (size_t)client * ws.d; }
+static_assert(kSpan * kChunkSpans >= 32u, "a chunk's counts take no more room than its candidates");
+constexpr uint32_t kChunkSets = 16;  // chunks whose counts a counting workgroup holds in LDS
+
 constexpr uint32_t kLimbBanks = 2;  // copies of a workgroup's limb counters, to thin out colliding LDS atomics
 
 // Every wavefront takes spans of 512 candidates (gw, gw + wavefronts, ...) and
@@ -1746,17 +1760,22 @@ constexpr uint32_t kLimbBanks = 2;  // copies of a workgroup's limb counters, to
 // collide; they are reduced once at the end.  Wavefronts do not wait for each
 // other before that.
 // QSGD: also the exact sum of squares of every group (see above).
-// SHORT: the coordinates of a short vector take the candidates' place (short_select_kernel); most may be dropped, so
-// those are neither numbered nor kept in the columns, their energy stays in a register.  The pass also clears the
-// stream, whose words the packing pass ORs into.
-template <bool QSGD, bool SHORT>
+// kShortVec: the coordinates of a short vector take the candidates' place (short_select_kernel); most may be dropped, so
+// those are neither numbered nor kept in the columns, their energy stays in a register.
+// Without a layout kernel the pass also clears the stream, whose words the packing pass ORs into (45 MB of 32 x 11.2 M: 4 us;
+// by workgroups of their own in the selection's launch, which leaves the memory idle: 8).
+// kByChunks: a workgroup's eight wavefronts are on the eight spans of a chunk; the chunk's counts add up in LDS.
+template <bool QSGD, PassMode MODE>
 __global__ __launch_bounds__(kEmitBlock) void count_kernel(const ClientParams* __restrict__ params,
-                                                           ClientCtl* __restrict__ ctls, Workspace ws) {
+                                                           ClientCtl* __restrict__ ctls, Workspace ws,
+                                                           cvlc_seg_stats_t* __restrict__ stats_out) {
+  constexpr bool SHORT = MODE == kShortVec, CHUNKS = MODE == kByChunks;
   __shared__ Thresholds thr;
   __shared__ unsigned long long s_limb[QSGD ? kLimbBanks : 1][QSGD ? 32 : 1][kNormLimbs];  // bank = lane mod kLimbBanks
   __shared__ uint32_t s_max[33][kWave], s_negmin[33][kWave];
   __shared__ double s_sq[33][kWave];
   __shared__ uint32_t s_cnt[kEmitWaves][32];
+  __shared__ uint32_t s_chunk[CHUNKS ? kChunkSets : 1u][32];
   const uint32_t client = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
   const ClientParams& p = params[client];
   ClientCtl* ctl = ctls + client;
@@ -1765,8 +1784,13 @@ __global__ __launch_bounds__(kEmitBlock) void count_kernel(const ClientParams* _
   const uint32_t n_spans = (n + kSpan - 1) / kSpan;
   const uint32_t* __restrict__ val = SHORT ? (const uint32_t*)(GlobalConstWordPtr)p.update : ws.dense_val + (size_t)client * ws.dense_cap;
   uint32_t* __restrict__ span_cnt = ws.span_cnt + (size_t)client * (ws.max_spans + 1) * 32;
-  if (SHORT)
+  if (SHORT || CHUNKS)
     for (uint32_t i = blockIdx.x * kEmitBlock + tid; i < p.total_words; i += gridDim.x * kEmitBlock) ((GlobalWordPtr)p.stream)[i] = 0;
+  if (CHUNKS) {
+    if (stats_out && blockIdx.x == 0 && tid < R) stats_out[(size_t)client * kStatsStride + tid].errsq = 0.0;  // the pack kernel adds to it when asked to
+    static_assert(kChunkSets * 32u == kEmitBlock, "a counter per thread");
+    (&s_chunk[0][0])[tid] = 0;
+  }
   load_thresholds(thr, ctl, R);
   if (tid < kEmitWaves * 32) (&s_cnt[0][0])[tid] = 0;
   for (uint32_t i = tid; i < 33 * kWave; i += kEmitBlock) {
@@ -1781,9 +1805,25 @@ __global__ __launch_bounds__(kEmitBlock) void count_kernel(const ClientParams* _
   uint32_t* running = s_cnt[wave];  // members of every group (the dropped ones last) in the rows so far
   const uint32_t span_step = gridDim.x * kEmitWaves;
   double tail = 0.0;  // SHORT: energy of the dropped
+  // kByChunks: the counts of the workgroup's chunks `first` .. `last` - 1 (its t-th chunk is blockIdx.x + t * gridDim.x)
+  auto write_chunks = [&](uint32_t first, uint32_t last) {
+    const uint32_t t = first + tid / 32u;
+    if (t < last) chunk_totals(ws, client)[(size_t)(blockIdx.x + t * gridDim.x) * 32u + tid % 32u] = (&s_chunk[0][0])[tid];
+  };
+  uint32_t turn = 0;  // ... and the one at hand; wavefronts past the last span have an empty turn, so that all meet every kChunkSets turns
   uint32_t ahead[kPerLane];  // the next span's value bits, asked for before the current span is worked on
   if (blockIdx.x * kEmitWaves + wave < n_spans) load_span(val, n, blockIdx.x * kEmitWaves + wave, ahead);
-  for (uint32_t span = blockIdx.x * kEmitWaves + wave; span < n_spans; span += span_step) {
+  for (uint32_t span = blockIdx.x * kEmitWaves + wave; CHUNKS ? span - wave < n_spans : span < n_spans; span += span_step) {
+    if (CHUNKS) {
+      if (turn && turn % kChunkSets == 0u) {  // uniform over the workgroup
+        __syncthreads();
+        write_chunks(turn - kChunkSets, turn);
+        (&s_chunk[0][0])[tid] = 0;  // the same thread's counter
+        __syncthreads();
+      }
+      ++turn;
+      if (span >= n_spans) continue;
+    }
     uint32_t v[kPerLane], grp[kPerLane];
 #pragma unroll
     for (uint32_t j = 0; j < kPerLane; ++j) v[j] = ahead[j];
@@ -1827,8 +1867,10 @@ __global__ __launch_bounds__(kEmitBlock) void count_kernel(const ClientParams* _
     }
     wave_lds_fence();
     if (lane < 32) {
-      span_cnt[(size_t)span * 32 + lane] = running[lane];
+      const uint32_t members = running[lane];
+      span_cnt[(size_t)span * 32 + lane] = members;
       running[lane] = 0;
+      if (CHUNKS) atomicAdd(&s_chunk[(turn - 1u) % kChunkSets][lane], members);
     }
     wave_lds_fence();
 #pragma unroll
@@ -1855,6 +1897,7 @@ __global__ __launch_bounds__(kEmitBlock) void count_kernel(const ClientParams* _
     if (lane == 0) atomicAdd(&ctl->seg[blockIdx.x % kSegCopies].sumsq[R], tail);
   }
   __syncthreads();
+  if (CHUNKS && turn) write_chunks((turn - 1u) / kChunkSets * kChunkSets, turn);
   if (QSGD) {  // a workgroup sees fewer than 2^31 candidates, so no counter has wrapped
     unsigned long long* dst = ws.norm_limbs + (size_t)client * 32 * kNormLimbs;
     for (uint32_t i = tid; i < R * kNormLimbs; i += kEmitBlock) {
@@ -2217,7 +2260,9 @@ __device__ __forceinline__ uint32_t quantise(float x, float m, float inv, uint32
 
 constexpr uint32_t kChunkCands = kSpan * kChunkSpans;         // 4096
 constexpr uint32_t kShortSpans = kShortMax / kSpan;
-static_assert(kShortSpans % (kEmitBlock / 32u) == 0, "a short vector's spans are dealt out to the threads evenly");
+constexpr uint32_t kBlocks = kEmitBlock / 32u;                // of spans or chunks whose counts a packing workgroup adds up, a thread per block and group
+constexpr uint32_t kBlockShiftMin = 3;                        // a block has eight chunks at least
+static_assert(kShortSpans % kBlocks == 0, "a short vector's spans are dealt out to the threads evenly");
 constexpr uint32_t kEdgeChunks = 8;                           // chunks whose shared stream words a workgroup holds back
 constexpr uint32_t kStageWords = kChunkCands * 2 + 2 * 32;    // every record is < 64 bits; two edge words per group
 
@@ -2240,12 +2285,14 @@ struct alignas(16) EmitGroup {  // per (chunk, group)
 // the statistics block (Lemma 1's left side for this draw), xtilde being the
 // centroid value the decoder will compute from the header.
 // QSGD: the code is the level of |x| on [0, norm] with the sign bit above it.
-// SHORT: a short vector's coordinates in the candidates' place.  There is no layout launch: every workgroup adds up the
-// spans' counts and the groups' statistics for itself (a few KB), a client's first one also writes its headers.
-template <bool ERR, bool QSGD, bool SHORT>
-__global__ __launch_bounds__(kEmitBlock, SHORT ? 4 : 6) void emit_kernel(const ClientParams* __restrict__ params,
+// kShortVec: a short vector's coordinates in the candidates' place.
+// kByChunks, kShortVec: there is no layout launch, every workgroup makes what it needs of the prefix from the chunks' or the spans'
+// counts (at most 16 KB) and derives the groups' values for itself; a client's first one also writes its headers.
+template <bool ERR, bool QSGD, PassMode MODE>
+__global__ __launch_bounds__(kEmitBlock, MODE == kShortVec ? 4 : 6) void emit_kernel(const ClientParams* __restrict__ params,
                                                           ClientCtl* __restrict__ ctls, Workspace ws, uint64_t seed,
                                                           cvlc_seg_stats_t* __restrict__ stats_out) {
+  constexpr bool SHORT = MODE == kShortVec, CHUNKS = MODE == kByChunks;
   __shared__ double s_err[ERR ? kEmitWaves : 1][32];  // per wavefront, per group
   __shared__ uint32_t s_stage[kStageWords];
   // A chunk's tables, two sets: the next chunk's are filled while the current one is written out.
@@ -2255,6 +2302,8 @@ __global__ __launch_bounds__(kEmitBlock, SHORT ? 4 : 6) void emit_kernel(const C
   __shared__ uint32_t s_nwords[2][32];             // words the chunk touches in each group
   __shared__ uint32_t s_stage_off[2][33];
   __shared__ uint32_t s_payload[32];
+  __shared__ uint32_t s_size[32];                  // records of every group
+  __shared__ EmitGroup s_const[32];                // W, y, m, inv, step of every group
   __shared__ uint32_t s_next;                      // the chunk the workgroup takes after the current one
   // The first and the last word of a (chunk, group) run are OR-ed into the stream by device-wide atomics.
   // Whatever the wavefront loads next waits for their acknowledgement (the counter of outstanding memory
@@ -2262,9 +2311,11 @@ __global__ __launch_bounds__(kEmitBlock, SHORT ? 4 : 6) void emit_kernel(const C
   // issued together.
   __shared__ uint32_t s_edge_word[kEdgeChunks][32][2];  // the bits; 0: nothing to OR
   __shared__ uint32_t s_edge_at[kEdgeChunks][32][2];    // the stream word they belong to
-  __shared__ uint32_t s_prefix[SHORT ? kShortSpans + 1u : 1u][32];  // members of every group in the spans before
-  __shared__ uint32_t s_part[SHORT ? kEmitBlock / 32u : 1u][32];
-  __shared__ uint32_t s_sum[SHORT && QSGD ? 32 : 1][kNormLimbs];
+  // kShortVec: members of every group in the spans before; kByChunks: ... in the chunks before every 2^block_shift-th
+  __shared__ uint32_t s_prefix[SHORT ? kShortSpans + 1u : CHUNKS ? kBlocks : 1u][32];
+  __shared__ uint32_t s_part[SHORT || CHUNKS ? kBlocks : 1u][32];
+  __shared__ uint32_t s_sum[(SHORT || CHUNKS) && QSGD ? 32 : 1][kNormLimbs];
+  __shared__ double s_dropped[CHUNKS ? kEmitWaves : 1u];
   // Workgroups are dispatched in the order of their linear index and a CU serves its oldest first: the
   // clients' workgroups are interleaved in that order, so that every client has workgroups of every age.
   const uint32_t linear = blockIdx.y * gridDim.x + blockIdx.x;
@@ -2284,18 +2335,38 @@ __global__ __launch_bounds__(kEmitBlock, SHORT ? 4 : 6) void emit_kernel(const C
   GlobalWordPtr stream = (GlobalWordPtr)p.stream;
   const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32), client_id = p.client_id;
 
-  uint32_t my_P = 0, my_W = 0, my_y = 0;
-  float my_m = 0.0f, my_inv = 0.0f, my_step = 0.0f;
-  if constexpr (SHORT) {
-    // the spans' counts: a thread takes group tid mod 32 of eight neighbouring spans
-    constexpr uint32_t kSpansEach = kShortSpans / (kEmitBlock / 32u);
+  // what thread r of the first 32 needs of group r for every chunk's tables (in registers it is every thread's, and the passes
+  // that make their own prefix spill)
+  if (tid < 32u) {
+    s_size[tid] = 0;
+    s_const[tid] = EmitGroup{0u, 0u, 0u, 0u, 0.0f, 0.0f, 0u, 0.0f};
+  }
+  const uint32_t* __restrict__ totals = chunk_totals(ws, client);
+  const uint32_t n_chunks = (n_spans + kChunkSpans - 1u) / kChunkSpans;
+  uint32_t block_shift = kBlockShiftMin;
+  if constexpr (SHORT || CHUNKS) {
+    // The counts: a thread takes group tid mod 32 of eight neighbouring spans, or of a block of neighbouring chunks, eight
+    // as a rule, more where there are more than 128 of them.
+    constexpr uint32_t kSpansEach = kShortSpans / kBlocks;
+    static_assert(kSpansEach == 1u << kBlockShiftMin, "eight loads together either way");
     const uint32_t g = tid % 32u, part = tid / 32u;
     uint32_t c[kSpansEach], sum = 0;
+    if constexpr (SHORT) {
 #pragma unroll
-    for (uint32_t i = 0; i < kSpansEach; ++i) {
-      const uint32_t span = part * kSpansEach + i;
-      c[i] = prefix[(size_t)min(span, n_spans - 1u) * 32 + g];
-      c[i] = span < n_spans ? c[i] : 0u;
+      for (uint32_t i = 0; i < kSpansEach; ++i) {
+        const uint32_t span = part * kSpansEach + i;
+        c[i] = prefix[(size_t)min(span, n_spans - 1u) * 32 + g];
+        c[i] = span < n_spans ? c[i] : 0u;
+      }
+    } else {
+      while ((n_chunks - 1u) >> block_shift >= kBlocks) ++block_shift;
+      const uint32_t last = min((part + 1u) << block_shift, n_chunks);
+      for (uint32_t from = part << block_shift; from < last; from += kSpansEach) {
+#pragma unroll
+        for (uint32_t i = 0; i < kSpansEach; ++i) c[i] = totals[(size_t)min(from + i, n_chunks - 1u) * 32 + g];
+#pragma unroll
+        for (uint32_t i = 0; i < kSpansEach; ++i) sum += from + i < last ? c[i] : 0u;
+      }
     }
     const uint32_t my_group = min(tid, CVLC_MAX_CODED - 1u), y = p.y[my_group], P = p.Z[my_group] - (my_group ? p.Z[my_group - 1u] : 0u);
     uint32_t enc_max = 0, enc_negmin = 0, flags = 0;
@@ -2308,45 +2379,61 @@ __global__ __launch_bounds__(kEmitBlock, SHORT ? 4 : 6) void emit_kernel(const C
         sumsq += ctl->seg[i].sumsq[tid];
       }
     }
+    if (CHUNKS && block_x == 0) {  // ... and by the filter, region by region
+      const double* rsq = ws.region_sumsq + (size_t)client * ws.n_regions;
+      double dropped = 0.0;
+      for (uint32_t i = tid; i < ws.n_regions; i += kEmitBlock) dropped += rsq[i];
+      dropped = wave_sum_f64(dropped);
+      if (lane == 0) s_dropped[wave] = dropped;
+    }
+    if constexpr (SHORT) {
 #pragma unroll
-    for (uint32_t i = 0; i < kSpansEach; ++i) sum += c[i];
+      for (uint32_t i = 0; i < kSpansEach; ++i) sum += c[i];
+    }
     s_part[part][g] = sum;
     if (wave == 0) {
       const uint32_t payload = group_payload(p, sbits);
       if (lane < 32u) s_payload[lane] = payload;
     }
     __syncthreads();
-    uint32_t run = 0;
-    for (uint32_t i = 0; i < part; ++i) run += s_part[i][g];
+    uint32_t run = 0, all = 0;
+    if constexpr (SHORT) {
+      for (uint32_t i = 0; i < part; ++i) run += s_part[i][g];
 #pragma unroll
-    for (uint32_t i = 0; i < kSpansEach; ++i) {
-      s_prefix[part * kSpansEach + i][g] = run;
-      run += c[i];
+      for (uint32_t i = 0; i < kSpansEach; ++i) {
+        s_prefix[part * kSpansEach + i][g] = run;
+        run += c[i];
+      }
+      if (part == kBlocks - 1u) s_prefix[kShortSpans][g] = run;
+    } else {
+#pragma unroll
+      for (uint32_t i = 0; i < kBlocks; ++i) {
+        const uint32_t x = s_part[i][g];
+        run += i < part ? x : 0u;
+        all += x;
+      }
+      s_prefix[part][g] = run;
     }
-    if (part == kEmitBlock / 32u - 1u) s_prefix[kShortSpans][g] = run;
     if (tid < R) {
       const GroupValues gv = group_values(P, y, enc_max, enc_negmin, QSGD ? CVLC_QUANT_QSGD : CVLC_QUANT_PQ,
                                           ws.norm_limbs + ((size_t)client * 32 + tid) * kNormLimbs, s_sum[QSGD ? tid : 0u], &flags);
-      my_P = gv.P;
-      my_W = sbits + y;
-      my_y = y;
-      my_m = gv.low;
-      my_inv = gv.inv;
-      my_step = gv.step;
+      s_size[tid] = gv.P;
+      s_const[tid] = EmitGroup{0u, 0u, sbits + y, y, gv.low, gv.inv, 0u, gv.step};
       if (block_x == 0) write_group(p, client, tid, gv, sumsq, QSGD ? CVLC_QUANT_QSGD : CVLC_QUANT_PQ, stats_out);
     }
-    if (block_x == 0 && tid == R) write_global(p, client, ws.d, sbits, sumsq, QSGD ? CVLC_QUANT_QSGD : CVLC_QUANT_PQ, stats_out);
+    if (block_x == 0 && tid == R) {
+      if constexpr (CHUNKS)
+        for (uint32_t w = 0; w < kEmitWaves; ++w) sumsq += s_dropped[w];
+      write_global(p, client, ws.d, sbits, sumsq, QSGD ? CVLC_QUANT_QSGD : CVLC_QUANT_PQ, stats_out);
+    }
     __syncthreads();
-    if (tid < R && s_prefix[kShortSpans][tid] != my_P) flags |= CVLC_DEV_INTERNAL;  // spans past the last are empty
+    if constexpr (SHORT) all = s_prefix[kShortSpans][g];  // spans past the last are empty
+    if (tid < R && all != P) flags |= CVLC_DEV_INTERNAL;  // g = tid
     if (block_x == 0 && flags) atomicOr(ws.status, flags);
   } else if (tid < 32 && tid < R) {
     const GroupInfo* gi = ws.group_info + client;
-    my_P = gi->P[tid];
-    my_W = gi->W[tid];
-    my_y = gi->y[tid];
-    my_m = gi->m[tid];
-    my_inv = gi->inv[tid];
-    my_step = gi->step[tid];
+    s_size[tid] = gi->P[tid];
+    s_const[tid] = EmitGroup{0u, 0u, gi->W[tid], gi->y[tid], gi->m[tid], gi->inv[tid], 0u, gi->step[tid]};
     s_payload[tid] = gi->payload[tid];
   }
   const double inv_B = ERR ? 1.0 / (double)p.B : 0.0;  // the scaling operation of Sec. IV-B
@@ -2355,8 +2442,29 @@ __global__ __launch_bounds__(kEmitBlock, SHORT ? 4 : 6) void emit_kernel(const C
   // What a chunk needs of the layout's prefix: the record numbers the wavefront's span starts at (lanes
   // 0..31: one group each) and, for the first 32 threads, the chunk's record run of a group.
   uint32_t ahead_row = 0, ahead_first = 0, ahead_last = 0;
+  // By chunks: the counts of the chunks between the block's first and this one, of the spans before the wavefront's in the
+  // chunk, and of the chunk itself; the two halves of the wavefront take every second row.
+  constexpr uint32_t kPairs = kChunkSpans / 2u;
+  uint32_t ahead_chunk[CHUNKS ? kPairs : 1u], ahead_span[CHUNKS ? kPairs : 1u];
+  static_assert(kChunkSpans == 1u << kBlockShiftMin, "as many spans in a chunk as chunks in a block at least");
+  auto last_eight = [&](uint32_t c) {  // the first of the last eight chunks or fewer in the block before chunk c
+    const uint32_t block = c >> block_shift << block_shift;
+    return c > block ? block + (c - 1u - block) / kChunkSpans * kChunkSpans : block;
+  };
   auto ask_prefix = [&](uint32_t c) {
     if (!chunk_exists(c)) return;  // uniform
+    if constexpr (CHUNKS) {
+      const uint32_t g = lane & 31u, half = lane >> 5, from = last_eight(c);
+      ahead_row = 0;
+      for (uint32_t x = (c >> block_shift << block_shift) + half; x < from; x += 2u) ahead_row += totals[(size_t)x * 32u + g];
+#pragma unroll
+      for (uint32_t u = 0; u < kPairs; ++u) {
+        ahead_chunk[u] = totals[(size_t)min(from + 2u * u + half, c) * 32u + g];
+        ahead_span[u] = prefix[(size_t)min(c * kChunkSpans + 2u * u + half, n_spans - 1u) * 32u + g];
+      }
+      if (wave == 0) ahead_last = totals[(size_t)c * 32u + g];
+      return;
+    }
     const uint32_t span = c * kChunkSpans + wave;
     auto row = [&](uint32_t sp, uint32_t g) { return SHORT ? s_prefix[sp][g] : prefix[(size_t)sp * 32 + g]; };
     if (lane < 32) ahead_row = span < n_spans ? row(span, lane) : 0u;
@@ -2381,14 +2489,27 @@ __global__ __launch_bounds__(kEmitBlock, SHORT ? 4 : 6) void emit_kernel(const C
     }
   };
   // Fills set `to` of the chunk tables from what ask_prefix brought.
-  auto set_up = [&](uint32_t to) {
+  auto set_up = [&](uint32_t to, uint32_t c) {
+    if constexpr (CHUNKS) {
+      if (!chunk_exists(c)) return;  // uniform
+      const uint32_t half = lane >> 5, from = last_eight(c);
+#pragma unroll
+      for (uint32_t u = 0; u < kPairs; ++u) {
+        ahead_row += from + 2u * u + half < c ? ahead_chunk[u] : 0u;
+        ahead_row += 2u * u + half < wave ? ahead_span[u] : 0u;
+      }
+      ahead_row += (uint32_t)__shfl_xor((int)ahead_row, 32, 64);
+      ahead_row += s_prefix[c >> block_shift][lane & 31u];
+      ahead_first = ahead_row;  // read by the first wavefront, whose span is the chunk's first
+      ahead_last += ahead_row;
+    }
     if (lane < 32) s_wrun[to][wave][lane] = ahead_row;
     if (tid < 32) {
       const uint32_t r = tid;
-      uint32_t nwords = 0, W = 0, first = 0, last = 0, bit_in_word = 0;
+      EmitGroup eg = s_const[r];
+      uint32_t nwords = 0, first = 0, last = 0, bit_in_word = 0;
       if (r < R) {
-        const uint32_t P = my_P;
-        W = my_W;
+        const uint32_t P = s_size[r], W = eg.W;
         // the chunk's record run of group r: [first, last), clamped so that every write stays inside
         // the group's payload even if an internal check has failed
         first = ahead_first;
@@ -2407,15 +2528,9 @@ __global__ __launch_bounds__(kEmitBlock, SHORT ? 4 : 6) void emit_kernel(const C
       const uint32_t incl = wave_incl_scan_u32(nwords);
       s_stage_off[to][r] = incl - nwords;
       if (r == 31) s_stage_off[to][32] = incl;
-      EmitGroup eg;
       eg.first = first;
       eg.lim = last;
-      eg.W = W;
-      eg.y = my_y;
-      eg.m = my_m;
-      eg.inv = my_inv;
       eg.stage_bit = (incl - nwords) * 32u + bit_in_word;  // bit of record `first` in the staged image
-      eg.step = my_step;
       s_grp[to][r] = eg;
     }
   };
@@ -2437,7 +2552,7 @@ __global__ __launch_bounds__(kEmitBlock, SHORT ? 4 : 6) void emit_kernel(const C
   ask_prefix(block_x);
   ask_candidates(block_x);
   for (uint32_t i = tid; i < kStageWords; i += kEmitBlock) s_stage[i] = 0;
-  set_up(0);
+  set_up(0, block_x);
   uint32_t cur = 0;
   for (uint32_t c = block_x; chunk_exists(c); cur ^= 1u) {
     uint32_t claimed = 0;
@@ -2516,7 +2631,7 @@ __global__ __launch_bounds__(kEmitBlock, SHORT ? 4 : 6) void emit_kernel(const C
         }
       }
     }
-    set_up(cur ^ 1u);  // the next chunk's tables (after the last chunk: tables nobody reads)
+    set_up(cur ^ 1u, c_next);  // the next chunk's tables (after the last chunk: tables nobody reads)
     c = c_next;
     if (++held == kEdgeChunks) {  // uniform
       __syncthreads();
@@ -2619,6 +2734,24 @@ bool short_pays(uint32_t n, const cvlc_plan_t* plans) {
   for (uint32_t i = 0; i < n; ++i)
     for (uint32_t r = 0; r < plans[i].n_coded; ++r) kept += plans[i].count[r];
   return kept * 128u <= all || kept * 10u >= all * 3u;
+}
+
+// Whether the packing pass makes its prefixes from the chunks' counts (kByChunks) or a layout kernel does.  The layout is one
+// workgroup per client: a launch of 7 us, and 30 us for every million coordinates that the client with the most keeps.  In its
+// place the counting pass clears the streams, not only the words at the runs' ends, and every packing workgroup goes through its
+// client's chunks: 0.7 us for every million coordinates kept in all.  us with the layout and without it: 1 x 70 000 58.7 and
+// 55.6, 1 x 11.2 M 86.4 and 79.7, the same half kept 259 and 193, 1 x 25.6 M half kept 501 and 352, 8 x 1.2 M 79.9 and 75.3,
+// 14 x 25.6 M 483 and 471, QSGD 8 x 11.2 M 178.3 and 174.2, 32 x 11.2 M 458.7 and 460.2, 100 x 3 M level, 100 x 25.6 M of budgets
+// that differ 3483 and 3493.
+bool chunks_pay(uint32_t n, const cvlc_plan_t* plans) {
+  uint64_t all = 0, most = 0;
+  for (uint32_t i = 0; i < n; ++i) {
+    uint64_t k = 0;
+    for (uint32_t r = 0; r < plans[i].n_coded; ++r) k += plans[i].count[r];
+    all += k;
+    most = std::max(most, k);
+  }
+  return all <= 32u * most + (8u << 20);
 }
 
 }  // namespace
@@ -2820,16 +2953,23 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
         hipLaunchKernelGGL(select_kernel, dim3(max_R, n), dim3(kSelectBlock), 0, stream, ws.params, ws.ctl, ws);
     }
   }
+  const PassMode mode = is_short ? kShortVec : (chunks_pay(n, plans) ? kByChunks : kByLayout);
+  auto by_mode = [&](auto choose) {
+    if (mode == kShortVec) return choose(std::integral_constant<PassMode, kShortVec>());
+    if (mode == kByChunks) return choose(std::integral_constant<PassMode, kByChunks>());
+    return choose(std::integral_constant<PassMode, kByLayout>());
+  };
   // count: wavefronts walk the spans; about what the device holds at once (four workgroups per CU)
   uint32_t g_count = (1024u + n - 1) / n;
   if (g_count > (ws.max_spans + kEmitWaves - 1) / kEmitWaves) g_count = (ws.max_spans + kEmitWaves - 1) / kEmitWaves;
   {
     StageScope scope(CVLC_STAGE_ENC_CLASSIFY, stream);
-    auto kernel = quant == CVLC_QUANT_QSGD ? (is_short ? count_kernel<true, true> : count_kernel<true, false>)
-                                           : (is_short ? count_kernel<false, true> : count_kernel<false, false>);
-    hipLaunchKernelGGL(kernel, dim3(g_count, n), dim3(kEmitBlock), 0, stream, ws.params, ws.ctl, ws);
+    auto choose = [&](auto m) {
+      return quant == CVLC_QUANT_QSGD ? count_kernel<true, decltype(m)::value> : count_kernel<false, decltype(m)::value>;
+    };
+    hipLaunchKernelGGL(by_mode(choose), dim3(g_count, n), dim3(kEmitBlock), 0, stream, ws.params, ws.ctl, ws, d_stats_out);
   }
-  if (!is_short) {
+  if (mode == kByLayout) {
     StageScope scope(CVLC_STAGE_ENC_LAYOUT, stream);
     hipLaunchKernelGGL(layout_kernel, dim3(n), dim3(kWideBlock), 0, stream, ws.params, ws.ctl, ws, d_stats_out, quant);
   }
@@ -2840,13 +2980,12 @@ int cvlc_encode_batch(uint32_t n, const cvlc_plan_t* plans, const float* const* 
     const uint32_t max_chunks = (ws.max_spans + kChunkSpans - 1) / kChunkSpans;
     if (g_emit > max_chunks) g_emit = max_chunks;
     const bool err = flags & CVLC_ENCODE_ERROR_STATS, qsgd = quant == CVLC_QUANT_QSGD;
-    auto choose = [&](auto short_vectors) {
-      constexpr bool kShort = decltype(short_vectors)::value;
-      return err ? (qsgd ? emit_kernel<true, true, kShort> : emit_kernel<true, false, kShort>)
-                 : (qsgd ? emit_kernel<false, true, kShort> : emit_kernel<false, false, kShort>);
+    auto choose = [&](auto m) {
+      constexpr PassMode kMode = decltype(m)::value;
+      return err ? (qsgd ? emit_kernel<true, true, kMode> : emit_kernel<true, false, kMode>)
+                 : (qsgd ? emit_kernel<false, true, kMode> : emit_kernel<false, false, kMode>);
     };
-    auto kernel = is_short ? choose(std::true_type{}) : choose(std::false_type{});
-    hipLaunchKernelGGL(kernel, dim3(g_emit, n), dim3(kEmitBlock), 0, stream, ws.params, ws.ctl, ws, seed, d_stats_out);
+    hipLaunchKernelGGL(by_mode(choose), dim3(g_emit, n), dim3(kEmitBlock), 0, stream, ws.params, ws.ctl, ws, seed, d_stats_out);
   }
   return hip_check(hipGetLastError());
 }

@@ -261,6 +261,45 @@ def test_region_lengths(n, d):
     check_encode(host, plans, 14, list(range(n)))
 
 
+def _keep_all_plan(d, quant=cv.QUANT_PQ):
+    counts = [d // 50, d // 7, d // 3]
+    return orc.plan_manual(d, [11, 6, 4, 2], counts + [d - sum(counts)], quant=quant)
+
+
+def check_some_streams(host, plans, which, seed=21):
+    """A batch whose streams are compared for the clients in `which` only."""
+    words, stats, status, _ = gpu_encode(host, plans, seed, list(range(len(host))), error_stats=True)
+    assert status == 0
+    for c in which:
+        ref = orc.encode(host[c], plans[c], seed, c)
+        assert_stream_equal(words[c], ref.words, f"client {c}")
+        assert_stats_close(stats[c], ref.stats, plans[c].R, error_stats=True)
+
+
+@pytest.mark.parametrize("quant", [cv.QUANT_PQ, cv.QUANT_QSGD])
+@pytest.mark.parametrize("chunks,more", [(16, 1), (128, 0), (128, 1), (256, 1)])
+def test_packing_at_the_steps_of_the_chunk_prefix(chunks, more, quant):
+    """Sixteen blocks of eight chunks of 4096 candidates, of sixteen from the 129th chunk on, of 32 from the 257th on."""
+    d = chunks * 4096 + more
+    check_some_streams([syn.update_vector(2, 60 + chunks, d=d)], [_keep_all_plan(d, quant)], [0])
+
+
+def test_packing_by_workgroups_of_more_chunks_than_their_counters_hold():
+    """1024 clients: one counting workgroup each, with counters for sixteen chunks at a time; two clients have 21."""
+    n, d = 1024, 20 * 4096 + 1
+    vectors = [syn.update_vector(2, 70 + c, d=d) for c in range(4)]
+    plans = [_keep_all_plan(d) if c in (3, 1022) else orc.plan_manual(d, [9, 4], [100, 200 + c % 5]) for c in range(n)]
+    check_some_streams([vectors[c % 4] for c in range(n)], plans, [0, 3, 517, 1022, 1023])
+
+
+@pytest.mark.parametrize("quant", [cv.QUANT_PQ, cv.QUANT_QSGD])
+def test_packing_by_the_layout(quant):
+    """So many clients that keep so much that a layout kernel numbers the chunks."""
+    n, d = 48, 128 * 4096 + 1537
+    vectors = [syn.update_vector(2, 80 + c, d=d) for c in range(3)]
+    check_some_streams([vectors[c % 3] for c in range(n)], [_keep_all_plan(d, quant)] * n, [0, 25, 47])
+
+
 def _selection_vectors(kind, d, rng):
     """Magnitudes that the selection bins (a thousandth of the sampled candidates each, 16 octaves of them) fit badly."""
     sign = np.where(rng.random(d) < 0.5, -1.0, 1.0)
