@@ -326,7 +326,7 @@ int cvlc_device_status(const void* d_workspace, void* hip_stream, uint32_t* stat
  * of brackets; both arrays hold CVLC_PROFILE_STAGES entries.  A stage that a
  * call does not have gets no bracket: vectors of up to 65 536 coordinates are
  * encoded without SAMPLE, FILTER and REFILTER, and as a rule without
- * SETUP; only batches of many clients that keep much have LAYOUT; up to eight streams are decoded without SETUP as a rule.  Not thread
+ * SETUP; only batches of many clients that keep much have LAYOUT; up to 112 streams are decoded without SETUP.  Not thread
  * safe. */
 enum {
   CVLC_STAGE_ENC_SETUP = 0,    /* clear scratch, upload per-client parameters; short vectors: */
@@ -342,7 +342,7 @@ enum {
                                /* rule part of the packing)                     */
   CVLC_STAGE_ENC_EMIT = 7,     /* quantise + pack                               */
   CVLC_STAGE_DEC_SETUP = 8,    /* header parsing, list numbering                */
-  CVLC_STAGE_DEC_TABLE = 9,    /* per-list tile boundaries; a few streams: all that lies */
+  CVLC_STAGE_DEC_TABLE = 9,    /* per-list tile boundaries; up to 112 streams: all that lies */
                                /* before the tiles                              */
   CVLC_STAGE_DEC_TILES = 10,   /* fused decode + accumulate                     */
   CVLC_STAGE_FIT_ALPHA = 11,   /* cvlc_fit_alpha, the whole call                */

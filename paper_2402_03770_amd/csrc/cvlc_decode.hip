@@ -6,13 +6,12 @@
 // list is sorted.  Each workgroup owns a tile of output coordinates, pulls the
 // slice of every list that falls into its tile, accumulates in LDS in fp64 and
 // writes the tile once; nothing is scattered into global memory.
-//   parse_headers  validate headers (which must name the quantiser the caller
-//                  expects), build one descriptor per list
-//   compact_lists  the non-empty lists, numbered consecutively, with the
-//                  tile_table work items they need
-//   tile_table     one streaming pass over all records: for every list, the
-//                  first record of every output tile (and the order/range checks)
-//   merged_table   the three of them in one launch, for a few streams
+//   stream_table   validate headers (which must name the quantiser the caller
+//                  expects), number the lists, and in one streaming pass over all
+//                  records find, for every list, the first record of every output
+//                  tile (and check order and range)
+//   parse_headers, compact_lists, tile_table
+//                  the same in three launches, for more than 112 streams
 //   decode_tiles   fused decode + accumulate + single write of each tile (a second
 //                  instance splits QSGD's sign bit from the level)
 #include <hip/hip_runtime.h>
@@ -31,7 +30,11 @@ namespace {
 constexpr uint32_t kListsPerClient = 32;   // descriptor slots per client (CVLC_MAX_CODED used)
 constexpr uint32_t kTabChunk = 512;        // records per tile_table work item (one wavefront, eight a lane)
 
-struct CompactDesc {  // one non-empty (client, group) record list, 32 bytes
+// LDS accesses of one wavefront complete in order; this keeps the compiler from
+// moving them across the point where lanes read what other lanes wrote.
+__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+struct CompactDesc {  // one (client, group) record list, 32 bytes
   const uint32_t* payload;
   double weight;  // w_i
   uint32_t P;
@@ -40,8 +43,8 @@ struct CompactDesc {  // one non-empty (client, group) record list, 32 bytes
 };
 static_assert(sizeof(CompactDesc) == 32, "CompactDesc is read as two 16-byte pieces");
 
-struct DecodeCtl {  // written by compact_lists
-  uint32_t n_active;  // non-empty lists
+struct DecodeCtl {  // written by stream_table or compact_lists
+  uint32_t n_active;  // lists: the non-empty ones, or (stream_table) all that the headers name
   uint32_t n_items;   // tile_table work items in all
 };
 
@@ -104,12 +107,11 @@ __device__ __forceinline__ uint64_t wave_incl_scan_u64(uint64_t v) {
   return v;
 }
 
-// Whole wavefront: the headers of one stream.
-__device__ __forceinline__ void parse_stream(const StreamArg& sa, uint32_t client, ListDesc* descs, uint32_t d, uint32_t n,
-                                             uint32_t* __restrict__ stream_bad, uint32_t quant) {
+// Whole wavefront: the headers of one stream.  Lane r gets list r (no records: P = 0, also past the last group and in a stream
+// that fails a check); the result, the same for all lanes, is whether all checks held.
+__device__ __forceinline__ bool parse_lists(const StreamArg& sa, uint32_t d, uint32_t n, uint32_t quant, ListDesc* list) {
   const uint32_t t = lane_id();
   GlobalConstWordPtr w = (GlobalConstWordPtr)sa.words;
-  ListDesc* out = descs + (size_t)client * kListsPerClient;
   bool ok = sa.n_words >= kGlobalHeaderWords;  // everything about `ok` is uniform over the wavefront
   uint32_t g[kGlobalHeaderWords] = {0, 0, 0, 0, 0, 0, 0, 0};
   // The group headers are asked for together with the global header, before the number of groups is known
@@ -150,10 +152,9 @@ __device__ __forceinline__ void parse_stream(const StreamArg& sa, uint32_t clien
   const uint64_t total = first_payload + (((uint64_t)__shfl((uint32_t)(incl >> 32), 63, 64) << 32) | __shfl((uint32_t)incl, 63, 64));
   const uint64_t k = ((uint64_t)__shfl((uint32_t)(k_incl >> 32), 63, 64) << 32) | __shfl((uint32_t)k_incl, 63, 64);
   ok = ok && k <= d && total == g[7] && sa.n_words >= total;
-  if (t == 0) stream_bad[client] = ok ? 0u : 1u;  // gathered into the status word by the next kernel
-  if (t < kListsPerClient) {
-    ListDesc ld;
-    ld.payload = nullptr; ld.weight = 0.0; ld.P = 0; ld.W = 0; ld.s = 0; ld.y = 0; ld.m = 0.0f; ld.step = 0.0f;
+  ListDesc ld;
+  ld.payload = nullptr; ld.weight = 0.0; ld.P = 0; ld.W = 0; ld.s = 0; ld.y = 0; ld.m = 0.0f; ld.step = 0.0f;
+  {
     if (ok && t < R) {
       float step = 0.0f, inv = 0.0f;
       if (y != 32) {
@@ -173,8 +174,18 @@ __device__ __forceinline__ void parse_stream(const StreamArg& sa, uint32_t clien
       ld.m = m;
       ld.step = step;
     }
-    out[t] = ld;
   }
+  *list = ld;
+  return ok;
+}
+
+__device__ __forceinline__ void parse_stream(const StreamArg& sa, uint32_t client, ListDesc* descs, uint32_t d, uint32_t n,
+                                             uint32_t* __restrict__ stream_bad, uint32_t quant) {
+  const uint32_t t = lane_id();
+  ListDesc list;
+  const bool ok = parse_lists(sa, d, n, quant, &list);
+  if (t == 0) stream_bad[client] = ok ? 0u : 1u;  // gathered into the status word by the next kernel
+  if (t < kListsPerClient) descs[(size_t)client * kListsPerClient + t] = list;
 }
 
 __global__ __launch_bounds__(64) void parse_headers_kernel(ParseChunk chunk, ListDesc* descs, uint32_t d, uint32_t n,
@@ -229,22 +240,6 @@ __global__ __launch_bounds__(1024) void compact_lists_kernel(const ListDesc* __r
                                                              uint32_t* status) {
   __shared__ uint32_t scan_tmp[16];
   compact_lists(descs, n_lists, cdesc, item_start, ctl, stream_bad, n, status, scan_tmp);
-}
-
-// Both steps in one launch, for calls of a few streams: the sixteen wavefronts
-// share out the streams, then the workgroup numbers the lists it has just described.
-constexpr uint32_t kFusedStreams = 24;
-static_assert(kFusedStreams <= kParseStreams, "one set of arguments");
-__global__ __launch_bounds__(1024) void setup_kernel(ParseChunk chunk, ListDesc* descs, uint32_t d, uint32_t quant,
-                                                     CompactDesc* __restrict__ cdesc, uint32_t* __restrict__ item_start,
-                                                     DecodeCtl* ctl, uint32_t* stream_bad, uint32_t* status) {
-  __shared__ uint32_t scan_tmp[16];
-  const uint32_t n = chunk.count;
-  for (uint32_t i = threadIdx.x / kWave; i < n; i += 1024u / kWave)  // uniform per wavefront
-    parse_stream(chunk.args[i], i, descs, d, n, stream_bad, quant);
-  __threadfence_block();
-  __syncthreads();  // the descriptors and flags written above are read below by other wavefronts of this workgroup
-  compact_lists(descs, n * kListsPerClient, cdesc, item_start, ctl, stream_bad, n, status, scan_tmp);
 }
 
 // ------------------------------------------------------------------ 2. tile table
@@ -430,94 +425,104 @@ __global__ __launch_bounds__(kBlock, 8) void tile_table_kernel(const CompactDesc
   if (bad) atomicOr(status, CVLC_DEV_STREAM);
 }
 
-// ---- a few streams: headers, list numbers and table in one launch
-// A call of a few streams is little but launches and the latencies of its headers (8 streams of 1.2 M coordinates: header
-// kernel 6.2 us, table 4.3; the call 17.4 -> 14.1 us in one launch, 1 x 1.2 M 18.7 -> 13.9, 1 x 11.2 M 26.8 -> 23.8): every workgroup parses the streams for itself, a wavefront each, and numbers the lists, in LDS;
-// workgroup 0 leaves both where decode_tiles looks for them.  The status word starts in this launch, so that what the
-// workgroups find goes to a word of each, which decode_tiles adds to it.
-constexpr uint32_t kMergedBlock = 512, kMergedWaves = kMergedBlock / kWave;
-constexpr uint64_t kMergedBlocksMax = 1024;  // four to a CU, all resident
-constexpr uint32_t kMergedStreams = kMergedWaves, kMergedLists = kMergedStreams * kListsPerClient;
-static_assert(kMergedLists <= kMergedBlock, "a thread per list");
-struct MergedArgs {
-  uint32_t n, pad;
-  StreamArg args[kMergedStreams];
+// ---- up to 112 streams: headers, list numbers and table in one launch
+// A workgroup belongs to one stream: its first wavefront parses that stream's headers (and reads the other streams' numbers of
+// groups, for the place of its lists among all), its wavefronts share out the stream's items.
+// us of the launches before decode_tiles, headers, list numbers and items in launches of their own (up to eight streams: in one, whose
+// workgroups each parsed all of them) and now: 32 x 11.2 M 27.0 and 20.9, 100 x 25.6 M 136 and 127, 8 x 1.2 M 8.3 and 7.4.  About
+// 6 of them are the headers (every wavefront for itself: 9.6 with 32 streams, at whose few lines all of them queue up).
+// What bounds the items is the read of the streams and, of 100 x 25.6 M, 39 MB of table written in between.  Level or slower
+// (us of 100 x 25.6 M): a third of the vector instructions, by turns whose loads share one offset and one shift, 137; loads eight
+// turns ahead 137; 16-byte loads an item ahead through LDS 135 (the loads alone 80, dwords 98); the items of neighbouring
+// wavefronts side by side 129 (neighbouring stores of a list's row then come from two XCDs).
+template <uint32_t STREAMS>
+struct StreamArgs {
+  uint32_t count, blocks;
+  StreamArg args[STREAMS];
+  uint16_t first[STREAMS];  // the stream's first workgroup
+};
+constexpr uint32_t kFewStreams = 8;  // whose arguments take 300 bytes instead of 3.8 KB
+static_assert(sizeof(StreamArgs<kParseStreams>) <= 3840, "kernel arguments are limited to 4 KB");
+struct TableShared {
+  uint64_t payload[kWave];
+  uint32_t P[kWave], wsy[kWave], first[kWave];
+  uint32_t before, bad, first_block, blocks;
 };
 
-template <bool WIDE>
-__global__ __launch_bounds__(kMergedBlock, 8) void merged_table_kernel(MergedArgs in, uint32_t quant, CompactDesc* __restrict__ cdesc,
-                                                                       DecodeCtl* ctl, uint32_t* table, uint32_t d, uint32_t tile_shift,
-                                                                       uint32_t n_tiles, uint32_t* __restrict__ found, uint32_t* status) {
-  __shared__ ListDesc descs[kMergedLists];
-  __shared__ alignas(16) CompactDesc lists[kMergedLists];
-  __shared__ uint32_t item_start[kMergedLists + 1], stream_bad[kMergedStreams], scan_a[kMergedWaves], scan_b[kMergedWaves];
-  const uint32_t tid = threadIdx.x, lane = lane_id();
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  if (wave < in.n) parse_stream(in.args[wave], wave, descs, d, in.n, stream_bad, quant);
-  __syncthreads();
-  // the lists with records, numbered in (stream, group) order, and the items before each
-  const bool live = tid < in.n * kListsPerClient && descs[min(tid, kMergedLists - 1u)].P > 0u;
-  const uint32_t P = live ? descs[tid].P : 0u, items = (P + kTabChunk - 1u) / kTabChunk;
-  const uint32_t incl = wave_incl_scan_u32(items);
-  const uint64_t mask = __ballot(live);
-  if (lane == kWave - 1u) {
-    scan_a[wave] = incl;
-    scan_b[wave] = (uint32_t)__popcll(mask);
-  }
-  __syncthreads();
-  uint32_t first = incl - items, pos = lanes_below(mask), n_items = 0, n_active = 0;
+template <bool WIDE, uint32_t STREAMS>
+__global__ __launch_bounds__(kBlock, 8) void stream_table_kernel(StreamArgs<STREAMS> in, uint32_t quant, CompactDesc* __restrict__ cdesc,
+                                                                 DecodeCtl* ctl, uint32_t* table, uint32_t d, uint32_t tile_shift,
+                                                                 uint32_t n_tiles, uint32_t* __restrict__ found, uint32_t* status) {
+  __shared__ TableShared S;
+  const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  if (wave == 0) {
+    constexpr uint32_t kTurns = (STREAMS + kWave - 1u) / kWave;
+    uint32_t client = 0, first_block = 0;
 #pragma unroll
-  for (uint32_t w = 0; w < kMergedWaves; ++w) {
-    const uint32_t xa = scan_a[w], xb = scan_b[w];
-    if (w < wave) { first += xa; pos += xb; }
-    n_items += xa;
-    n_active += xb;
-  }
-  if (live) {
-    const ListDesc ld = descs[tid];
-    CompactDesc c;
-    c.payload = ld.payload; c.weight = ld.weight; c.P = ld.P; c.wsy = ld.W | (ld.s << 8) | (ld.y << 16);
-    c.m = ld.m; c.step = ld.step;
-    lists[pos] = c;
-    item_start[pos] = first;
-    if (blockIdx.x == 0) cdesc[pos] = c;
-  }
-  if (tid == 0) {
-    item_start[n_active] = n_items;
-    if (blockIdx.x == 0) {
-      uint32_t any_bad = 0;
-      for (uint32_t i = 0; i < in.n; ++i) any_bad |= stream_bad[i];
-      *status = any_bad ? CVLC_DEV_STREAM : 0u;
-      ctl->n_active = n_active;
-      ctl->n_items = n_items;
+    for (uint32_t i = 0; i < kTurns; ++i) {
+      const uint32_t c = i * kWave + lane, f = in.first[min(c, in.count - 1u)];
+      const uint64_t at_or_before = __ballot(c < in.count && f <= blockIdx.x);  // firsts ascend: a prefix
+      if (at_or_before) first_block = __builtin_amdgcn_readlane(f, 63u - (uint32_t)__builtin_clzll(at_or_before));
+      client += (uint32_t)__popcll(at_or_before);
+    }
+    client = __builtin_amdgcn_readfirstlane(client - 1u);
+    // at most 31 lists a stream whatever its header says
+    uint32_t before = 0, groups = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kTurns; ++i) {
+      const uint32_t c = i * kWave + lane;
+      const uint32_t g = c <= client ? min(((GlobalConstWordPtr)in.args[min(c, client)].words)[3], CVLC_MAX_CODED) : 0u;
+      before += c < client ? g : 0u;
+      groups += c == client ? g : 0u;
+    }
+    ListDesc list;
+    const bool ok = parse_lists(in.args[client], d, in.count, quant, &list);
+    before = wave_sum_u32(before);
+    groups = wave_sum_u32(groups);
+    const uint32_t items = (list.P + kTabChunk - 1u) / kTabChunk, wsy = list.W | (list.s << 8) | (list.y << 16);
+    S.payload[lane] = (uint64_t)list.payload;
+    S.P[lane] = list.P;
+    S.wsy[lane] = wsy;
+    S.first[lane] = wave_incl_scan_u32(items) - items;  // lanes past the last list: the number of items
+    if (lane == 0) {
+      S.before = before;
+      S.bad = ok ? 0u : 1u;
+      S.first_block = first_block;
+      S.blocks = (client + 1u < in.count ? in.first[client + 1u] : in.blocks) - first_block;
+    }
+    if (blockIdx.x == first_block) {
+      if (lane < groups) {
+        CompactDesc c;
+        c.payload = list.payload; c.weight = list.weight; c.P = list.P; c.wsy = wsy;
+        c.m = list.m; c.step = list.step;
+        cdesc[before + lane] = c;
+      }
+      if (lane == 0 && client == in.count - 1u) {
+        ctl->n_active = before + groups;
+        *status = 0;  // what the workgroups find goes to a word of each, which decode_tiles adds to it
+      }
     }
   }
   __syncthreads();
+  const uint32_t first = S.first[lane], before = __builtin_amdgcn_readfirstlane(S.before);
+  const uint32_t n_items = __builtin_amdgcn_readlane(first, kWave - 1u);
+  const uint32_t n_waves = __builtin_amdgcn_readfirstlane(S.blocks) * kWavesPerBlock, me = (blockIdx.x - __builtin_amdgcn_readfirstlane(S.first_block)) * kWavesPerBlock + wave;
+  bool bad = S.bad != 0u;
   // neighbouring items to a wavefront; few of them to the workgroups that start first
-  const uint64_t n_waves = (uint64_t)gridDim.x * kMergedWaves, me = (uint64_t)blockIdx.x * kMergedWaves + wave;
-  n_items = __builtin_amdgcn_readfirstlane(n_items);
-  n_active = __builtin_amdgcn_readfirstlane(n_active);
-  uint32_t q_begin = (uint32_t)(me * n_items / n_waves), q_end = (uint32_t)((me + 1u) * n_items / n_waves);
+  uint32_t q = (uint32_t)((uint64_t)me * n_items / n_waves), q_end = (uint32_t)((uint64_t)(me + 1u) * n_items / n_waves);
   if (n_items <= n_waves) {
-    q_begin = min((uint32_t)me, n_items);
-    q_end = min((uint32_t)me + 1u, n_items);
+    q = min(me, n_items);
+    q_end = min(me + 1u, n_items);
   }
-  bool bad = false;
-  if (q_begin < q_end) {  // uniform per wavefront
-    uint32_t before = 0;  // lists that start at or before the first item: their starts ascend
-    for (uint32_t base = 0; base < n_active; base += kWave)
-      before += (uint32_t)__popcll(__ballot(base + lane < n_active && item_start[min(base + lane, n_active)] <= q_begin));
-    uint32_t a = before - 1u;
-    for (uint32_t q = q_begin; q < q_end; ++q) {
-      while (q >= (uint32_t)__builtin_amdgcn_readfirstlane(item_start[a + 1u])) ++a;  // every list has an item: one step at most
-      const uint4* dsrc = reinterpret_cast<const uint4*>(lists + a);
-      bad |= table_item<WIDE>(dsrc[0], dsrc[1], a, __builtin_amdgcn_readfirstlane(item_start[a]), q, table, d, tile_shift, n_tiles);
-    }
+  for (; q < q_end; ++q) {  // uniform per wavefront
+    const uint32_t a = (uint32_t)__popcll(__ballot(first <= q)) - 1u;  // a list without records has no item of its own
+    const uint64_t payload = S.payload[a];
+    bad |= table_item<WIDE>(make_uint4((uint32_t)payload, (uint32_t)(payload >> 32), 0u, 0u), make_uint4(S.P[a], S.wsy[a], 0u, 0u), before + a,
+                            __builtin_amdgcn_readlane(first, a), q, table, d, tile_shift, n_tiles);
   }
   const int any = __syncthreads_or((int)bad);
-  if (tid == 0) found[blockIdx.x] = any ? 1u : 0u;
+  if (threadIdx.x == 0) found[blockIdx.x] = any ? 1u : 0u;
 }
-
 
 // ------------------------------------------------------------------ 3. fused decode + accumulate
 // Persistent workgroups walk the output tiles, neighbouring tiles at the same
@@ -572,10 +577,6 @@ __device__ __forceinline__ uint32_t wave_incl_scan_rows(uint32_t v) {
   v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143 /* row_bcast:31 */, 0xC, 0xF, false);
   return v;
 }
-
-// LDS accesses of one wavefront complete in order; this keeps the compiler from
-// moving them across the point where lanes read what other lanes wrote.
-__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // SIGNED: the streams' codes hold a sign bit above the level (QSGD).
 // WIDE: positions of more than 25 bits, which with a raw 32-bit code may not lie in eight bytes from the one they start in.
@@ -886,51 +887,48 @@ int cvlc_decode_aggregate(uint32_t n, const void* const* d_streams, const size_t
     sa.pad = 0;
     return sa;
   };
-  // Up to eight streams, a wavefront of the workgroup each (several to a wavefront have not been tried).  The most items that the
-  // streams can hold (a record has a code bit at least): a wavefront each, all of them resident, or the general path,
-  // whose table kernel starts without a prologue (8 x 25.6 M: 50.2 us, merged 53.4; 8 x 11.2 M, within the limit:
-  // 35.6 and 34.4).
-  uint64_t items_most = 0;
-  for (uint32_t i = 0; i < n && n <= kMergedStreams; ++i)
-    items_most += (uint64_t)stream_bytes[i] * 8u / ((position_bits(d) + 1u) * kTabChunk) + CVLC_MAX_CODED;
-  const bool merged = n > 0 && n <= kMergedStreams && items_most <= kMergedBlocksMax * kMergedWaves;
-  // a word for every workgroup in the place of the list descriptors, of which there is room for 320 a stream
+  // A word for every workgroup of stream_table in the place of the list descriptors, of which there is room for 320 a stream.
   uint32_t* found = reinterpret_cast<uint32_t*>(descs);
-  const uint32_t merged_blocks = (uint32_t)std::min<uint64_t>((items_most + kMergedWaves - 1u) / kMergedWaves,
-                                                              (uint64_t)n_lists * sizeof(ListDesc) / sizeof(uint32_t));
-  if (merged) {
+  uint32_t n_found = 0;
+  if (n > 0 && n <= kParseStreams) {
     StageScope scope(CVLC_STAGE_DEC_TABLE, stream);
-    MergedArgs in;
-    in.n = n;
-    in.pad = 0;
-    for (uint32_t i = 0; i < kMergedStreams; ++i) in.args[i] = i < n ? stream_arg(i) : StreamArg{};
-    auto kernel = wide ? merged_table_kernel<true> : merged_table_kernel<false>;
-    hipLaunchKernelGGL(kernel, dim3(merged_blocks), dim3(kMergedBlock), 0, stream, in, quant, cdesc, ctl, table, d, shift, n_tiles,
-                       found, status);
+    // workgroups by the streams' lengths, all resident, but no more than a wavefront for every item that a stream can hold (a
+    // record has a code bit at least)
+    constexpr uint64_t kMost = kListsPerClient * sizeof(ListDesc) / sizeof(uint32_t);
+    uint64_t all = 0;
+    for (uint32_t i = 0; i < n; ++i) all += stream_bytes[i];
+    auto launch = [&](auto& in, auto kernel) {
+      in.count = n;
+      for (uint32_t i = 0; i < n; ++i) {
+        const uint64_t items = (uint64_t)stream_bytes[i] * 8u / ((position_bits(d) + 1u) * kTabChunk) + CVLC_MAX_CODED;
+        in.args[i] = stream_arg(i);
+        in.first[i] = (uint16_t)n_found;
+        n_found += (uint32_t)std::min({((uint64_t)kTableBlocks * stream_bytes[i] + all - 1u) / all, (items + kWavesPerBlock - 1u) / kWavesPerBlock, kMost});
+      }
+      in.blocks = n_found;
+      hipLaunchKernelGGL(kernel, dim3(n_found), dim3(kBlock), 0, stream, in, quant, cdesc, ctl, table, d, shift, n_tiles, found, status);
+    };
+    static_assert(kTableBlocks + kParseStreams < (1u << 16), "the workgroups are numbered in 16 bits");
+    if (n <= kFewStreams) {
+      StreamArgs<kFewStreams> in;
+      launch(in, wide ? stream_table_kernel<true, kFewStreams> : stream_table_kernel<false, kFewStreams>);
+    } else {
+      StreamArgs<kParseStreams> in;
+      launch(in, wide ? stream_table_kernel<true, kParseStreams> : stream_table_kernel<false, kParseStreams>);
+    }
   } else {
     profile_mark(CVLC_STAGE_DEC_SETUP, true, stream);
     {
       ParseChunk chunk;
       chunk.pad[0] = chunk.pad[1] = 0;
-      // One launch parses and numbers, 3.5 us for every 16 streams; two launches, the first with a workgroup per stream, take
-      // 4.2 + 3.8 for 17 and 4.8 + 10.8 for 100 (35 us in one).  The second launch costs a small call 2 us on the host:
-      // a call of 17 streams of 20 000 coordinates takes 20.5 us with one and 22.6 with two, of 32 25 either way.
-      const bool fused = n > 0 && n <= kFusedStreams;
       for (uint32_t first = 0; first < n; first += kParseStreams) {
         chunk.first = first;
         chunk.count = (n - first < kParseStreams) ? n - first : kParseStreams;
         for (uint32_t i = 0; i < chunk.count; ++i) chunk.args[i] = stream_arg(first + i);
-        if (fused)
-          hipLaunchKernelGGL(setup_kernel, dim3(1), dim3(1024), 0, stream, chunk, descs, d, quant, cdesc, item_start, ctl,
-                             stream_bad, status);
-        else
-          hipLaunchKernelGGL(parse_headers_kernel, dim3(chunk.count), dim3(64), 0, stream, chunk, descs, d, n, stream_bad,
-                             quant);
+        hipLaunchKernelGGL(parse_headers_kernel, dim3(chunk.count), dim3(64), 0, stream, chunk, descs, d, n, stream_bad, quant);
       }
       // also for n = 0: writes the (empty) list counts and the status word
-      if (!fused)
-        hipLaunchKernelGGL(compact_lists_kernel, dim3(1), dim3(1024), 0, stream, descs, n_lists, cdesc, item_start, ctl,
-                           stream_bad, n, status);
+      hipLaunchKernelGGL(compact_lists_kernel, dim3(1), dim3(1024), 0, stream, descs, n_lists, cdesc, item_start, ctl, stream_bad, n, status);
     }
     profile_mark(CVLC_STAGE_DEC_SETUP, false, stream);
     if (n > 0) {
@@ -950,7 +948,7 @@ int cvlc_decode_aggregate(uint32_t n, const void* const* d_streams, const size_t
                   : large ? (qsgd ? decode_tiles_kernel<true, false, kDecShiftMax> : decode_tiles_kernel<false, false, kDecShiftMax>)
                           : (qsgd ? decode_tiles_kernel<true, false, kDecShiftMin> : decode_tiles_kernel<false, false, kDecShiftMin>);
     hipLaunchKernelGGL(kernel, dim3(g), dim3(kDecBlock), 0, stream, cdesc, ctl, table, d_out, d, n_tiles, position_bits(d),
-                       flags & CVLC_DECODE_ACCUMULATE, found, merged ? merged_blocks : 0u, status);
+                       flags & CVLC_DECODE_ACCUMULATE, found, n_found, status);
   }
   return hip_check(hipGetLastError());
 }

@@ -587,6 +587,21 @@ def test_decode_at_the_steps_of_the_lists_share(n, R, quant):
 
 
 # Tiles of 4096 coordinates below 2^23, of 8192 from there on.
+@pytest.mark.parametrize("n", [8, 9, 64, 65, 112, 113])
+def test_decode_of_streams_of_unequal_lengths(n):
+    """Few and many streams' arguments, the last number that one launch parses and the first that it does not; the workgroups
+    go by the streams' lengths: one stream has nearly all records, some have empty groups, some none at all."""
+    d = 200_003
+    refs = []
+    for c in range(n):
+        U = syn.update_vector(2 + c % 2, 2500 + c, d=d)
+        counts = [40_000, 90_000, 30_000] if c == n // 2 else [[0, 0, 0], [5, 0, 40], [0, 700, 0], [300, 513, 1024]][c % 4]
+        refs.append(orc.encode(U, orc.plan_manual(d, [9, 6, 2], counts), 9, c).words)
+    check_decode(refs, d)
+    order = list(range(n))[::-1]
+    check_decode([refs[c] for c in order], d, weights=np.random.default_rng(n).uniform(-1.0, 1.0, n).astype(np.float32).tolist())
+
+
 @pytest.mark.parametrize("d", [(1 << 23) - 1, 1 << 23, (1 << 23) + 4097])
 def test_decode_on_both_sides_of_the_large_tiles(d):
     rng = np.random.default_rng(d)
