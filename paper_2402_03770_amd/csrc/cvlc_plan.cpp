@@ -157,15 +157,73 @@ class Algorithm1 {
     return a + b;
   }
 
-  // Atomic operation: golden-section search for the minimiser of the strongly
+  // Derivative of pair_cost (PQ) by Pr.  With L = 2^y - 1 and y = u/P - s the weight P/L^2/B^2 grows as
+  // (1 + 2 ln2 (1 + 1/L) u/P) / L^2 / B^2; the power-law term's own derivative is beta times the term over its rank.
+  double pair_slope(double Pr, const Pair& pr) const {
+    const double Pr1 = pr.X - Pr, Z = pr.z_r2 + Pr1;
+    const double term_r1 = law_.term(Z);
+    const double fall = Z < 1.0 ? 0.0 : (law_.log_limit ? 1.0 / Z : law_.beta * term_r1 / Z);  // term_r1 falls by this as Pr grows
+    auto weight = [&](double P, double* grows) {
+      const double bits = u_ / P, y = bits - (double)s_;
+      const double levels = std::exp2(y) - 1.0, unit = err_.inv_b2 / (levels * levels);
+      *grows = unit * (1.0 + 1.3862943611198906 * (1.0 + 1.0 / levels) * bits);
+      return P * unit + err_.inv_bc2;
+    };
+    double grows, grows1;
+    const double w = weight(Pr, &grows), w1 = weight(Pr1, &grows1);
+    return (grows * (pr.term_r - term_r1) + w * fall - grows1 * (term_r1 - pr.term_r2) - w1 * fall) / law_.denom;
+  }
+
+  // Zero of pair_slope in [lo, hi], or the end that the cost falls towards, from x on: secant steps inside what is known to hold the
+  // zero, halving it where they do not help.  NaN if the slope is not a number somewhere.
+  double flat_point(double lo, double hi, double x, const Pair& pr) const {
+    double a = lo, b = hi, x_before = 0.0, g_before = 0.0, width = 2.0 * (hi - lo);
+    bool a_known = false, b_known = false, one = false;  // whether the slope has been seen below 0 at a, above 0 at b, and anywhere
+    x = std::min(std::max(x, lo), hi);
+    const double close = 1e-11 * hi;
+    for (int it = 0; it < 200; ++it) {
+      const double g = pair_slope(x, pr);
+      if (!(std::fabs(g) <= std::numeric_limits<double>::max())) return std::numeric_limits<double>::quiet_NaN();
+      if (g == 0.0) return x;
+      if (g < 0.0) {
+        if (x == hi) return hi;
+        a = x;
+        a_known = true;
+      } else {
+        if (x == lo) return lo;
+        b = x;
+        b_known = true;
+      }
+      double next = one ? x - g * (x - x_before) / (g - g_before) : x - (g < 0.0 ? -1.0 : 1.0) * 1e-3 * (hi - lo);
+      const bool halve = it % 4 == 3 && a_known && b_known && b - a > 0.5 * width;
+      if (it % 4 == 3) width = b - a;
+      x_before = x;
+      g_before = g;
+      one = true;
+      if (!(next > a)) next = a_known ? a + 0.5 * (b - a) : lo;
+      else if (!(next < b)) next = b_known ? a + 0.5 * (b - a) : hi;
+      else if (halve) next = a + 0.5 * (b - a);
+      if (std::fabs(next - x) <= close && (a_known || next != lo) && (b_known || next != hi)) return next;
+      x = next;
+    }
+    return x;
+  }
+
+  // Atomic operation: the minimiser of the strongly
   // convex pair cost (Lemma 3) on (X/2, X), kept inside "one update, the quantiser's
-  // shortest code" (1 bit for PQ; QSGD needs a sign bit and a level bit).
-  double atomic_operation(double X, double z_r2) const {
+  // shortest code" (1 bit for PQ; QSGD needs a sign bit and a level bit).  PQ without scaling: where the derivative is zero, half a dozen
+  // evaluations from the size before on.  QSGD, whose error model has a kink, and scale factors, whose constant part buries the
+  // minimum in rounding so that the search decides the plan's last unit: golden-section search, 82 evaluations.
+  double atomic_operation(double X, double z_r2, double size_before) const {
     const double p_max = u_ / ((double)s_ + y_min_);
     double lo = 0.5 * X, hi = X - 1.0;
     if (hi > p_max) hi = p_max;
     if (lo < X - p_max) lo = X - p_max;
     if (!(hi > lo)) return 0.5 * X > p_max ? p_max : 0.5 * X;
+    if (quant_ == CVLC_QUANT_PQ && err_.inv_bc2 == 0.0) {
+      const double flat = flat_point(lo, hi, size_before, pair(X, z_r2));
+      if (flat >= lo && flat <= hi) return flat;  // a number
+    }
     const double g = 0.6180339887498949;
     double x1 = hi - g * (hi - lo), x2 = lo + g * (hi - lo);
     const Pair pr = pair(X, z_r2);
@@ -193,7 +251,7 @@ class Algorithm1 {
       double moved = 0.0, z_r2 = 0.0;
       for (uint32_t r = 1; r < R_; ++r) {
         const double X = Pc[r - 1] + Pc[r];
-        const double Pr = atomic_operation(X, z_r2);
+        const double Pr = atomic_operation(X, z_r2, Pc[r]);
         const double delta = std::fabs(Pr - Pc[r]);
         if (delta > moved) moved = delta;
         Pc[r] = Pr;
@@ -270,10 +328,10 @@ int plan_algorithm1(uint32_t d, uint64_t budget, uint32_t R, double alpha, float
   if (k_max > (double)d) k_max = (double)d;
   if (k_max < k_min) return CVLC_ERR_BUDGET;
   const Algorithm1 alg(d, R, out->s, u, alpha, (double)B, quant);
-  // Equidistant search over k.  The 128 searches know nothing of each other and take hundreds of microseconds each at
-  // seven groups (milliseconds at 31): they are shared out between up to 16 threads, and the first of the best is taken
-  // as if they had been done in order (7 groups, 1.2 M coordinates: 53 ms with one thread and the pairs' outer
-  // power-law terms computed each time, 1.9 ms now).
+  // Equidistant search over k.  The 128 searches know nothing of each other: they are shared out between up to 16 threads,
+  // and the first of the best is taken as if they had been done in order.  A thread takes about 15 us to start, so that few
+  // groups take ten (3 and 7 groups, us: 4 threads 436, 8 296, 10 281, 12 290, 16 320; with golden-section searches, 20 times the
+  // evaluations, 2 000).
   constexpr int kGrid = 128, kThreads = 16;
   struct Candidate {
     double gamma;
@@ -288,7 +346,7 @@ int plan_algorithm1(uint32_t d, uint64_t budget, uint32_t R, double alpha, float
     }
   };
   {
-    const Helpers room(R > 1 ? kThreads - 1 : 0);  // one group: nothing to balance, microseconds in all
+    const Helpers room(R > 8 ? kThreads - 1 : R > 1 ? 9 : 0);  // one group: nothing to balance, microseconds in all
     std::thread helpers[kThreads - 1];
     try {
       for (int t = 0; t < room.taken(); ++t) helpers[t] = std::thread(search);

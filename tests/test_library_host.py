@@ -87,6 +87,16 @@ def test_planner_matches_oracle_on_random_inputs():
         assert _same(cv.plan(d, code_len=y, fractions=frac, B=B), orc.plan_fractions(d, y, frac, B))
 
 
+@pytest.mark.parametrize("alpha", [-0.05, -0.4, -0.5, -0.75, -1.9])
+@pytest.mark.parametrize("R,B", [(2, 1.0), (7, 1.0), (31, 1.0), (7, 3.0)])
+def test_planner_by_slope_and_by_search(R, alpha, B):
+    """Without scaling a pair's minimum is where its derivative is zero, with scaling it is searched for; the oracle searches."""
+    for d, bits in ((70, 9.0), (150_000, 0.03), (25_600_000, 2.0)):
+        budget = int(d * bits) + 256 + 200 * R
+        po = orc.plan_alg1(d, budget, R, alpha, B=B)
+        assert _same(cv.plan(d, budget, n_coded=R, alpha=alpha, B=B), po), (d, bits)
+
+
 def test_plan_errors():
     with pytest.raises(cv.CvlcError) as e:
         cv.plan(1000, 256 + 3 * 128, code_len=[4, 2, 1])
