@@ -329,9 +329,8 @@ int plan_algorithm1(uint32_t d, uint64_t budget, uint32_t R, double alpha, float
   if (k_max < k_min) return CVLC_ERR_BUDGET;
   const Algorithm1 alg(d, R, out->s, u, alpha, (double)B, quant);
   // Equidistant search over k.  The 128 searches know nothing of each other: they are shared out between up to 16 threads,
-  // and the first of the best is taken as if they had been done in order.  A thread takes about 15 us to start, so that few
-  // groups take ten (3 and 7 groups, us: 4 threads 436, 8 296, 10 281, 12 290, 16 320; with golden-section searches, 20 times the
-  // evaluations, 2 000).
+  // and the first of the best is taken as if they had been done in order (7 groups, 1.2 M coordinates: 424 us, with ten threads
+  // 480; with golden-section searches, twelve times the evaluations, 2 007).
   constexpr int kGrid = 128, kThreads = 16;
   struct Candidate {
     double gamma;
@@ -346,7 +345,7 @@ int plan_algorithm1(uint32_t d, uint64_t budget, uint32_t R, double alpha, float
     }
   };
   {
-    const Helpers room(R > 8 ? kThreads - 1 : R > 1 ? 9 : 0);  // one group: nothing to balance, microseconds in all
+    const Helpers room(R > 1 ? kThreads - 1 : 0);  // one group: nothing to balance, microseconds in all
     std::thread helpers[kThreads - 1];
     try {
       for (int t = 0; t < room.taken(); ++t) helpers[t] = std::thread(search);
