@@ -176,6 +176,34 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* scratc
   return before + incl - v;
 }
 
+// Two of them at once: the prefix of v is returned, w becomes its own.
+template <uint32_t NW>
+__device__ __forceinline__ uint32_t block_excl_scan2(uint32_t v, uint32_t& w, uint32_t* scratch_v, uint32_t* scratch_w,
+                                                     uint32_t* total_v, uint32_t* total_w) {
+  const uint32_t incl_v = wave_incl_scan_u32(v), incl_w = wave_incl_scan_u32(w), wave = threadIdx.x / kWave;
+  __syncthreads();
+  if (lane_id() == kWave - 1) {
+    scratch_v[wave] = incl_v;
+    scratch_w[wave] = incl_w;
+  }
+  __syncthreads();
+  uint32_t before_v = 0, before_w = 0, sum_v = 0, sum_w = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < NW; ++i) {
+    const uint32_t a = scratch_v[i], b = scratch_w[i];
+    if (i < wave) {
+      before_v += a;
+      before_w += b;
+    }
+    sum_v += a;
+    sum_w += b;
+  }
+  *total_v = sum_v;
+  *total_w = sum_w;
+  w = before_w + incl_w - w;
+  return before_v + incl_v - v;
+}
+
 // hist[bin] += 1 for every lane with `active`, using one LDS atomic per distinct
 // bin in the wavefront (lanes that share a bin elect the lowest one).  Must be
 // reached by all lanes of the wavefront.  `bin` must fit in NBITS bits.

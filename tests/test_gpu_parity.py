@@ -252,10 +252,12 @@ def test_boundary_ties_inside_smooth_data():
 
 @pytest.mark.parametrize("n,d", [(1, 1024), (1, 1025), (2, 3 * 1024 - 1), (6, 1024 * 1024), (6, 1024 * 1024 + 1),
                                  (7, 2048 * 877 + 2047), (12, 1024 * 1024 + 8191),
-                                 (1, 65 * 1024), (1, 65 * 1024 + 1), (2, 66 * 1024 - 1)])   # lengths that have a filter
+                                 (1, 65 * 1024), (1, 65 * 1024 + 1), (2, 66 * 1024 - 1),   # lengths that have a filter
+                                 (1, 2048 * 1024), (1, 2048 * 1024 + 1), (1, 4096 * 8192 + 1)])
 def test_region_lengths(n, d):
     """The filter's regions have 1024 to 8192 coordinates, by the size of the batch: sizes at the steps of that rule
-    and with a last region of one coordinate, one missing, or one too many."""
+    and with a last region of one coordinate, one missing, or one too many; and one region more than the threads of the
+    region scan take at one, two and four each."""
     host = [syn.update_vector(2 + c % 2, 300 + c, d=d) for c in range(n)]
     plans = [orc.plan_fractions(d, [9, 6, 3], [0.004, 0.01, 0.03 + 0.01 * (c % 3)]) for c in range(n)]
     check_encode(host, plans, 14, list(range(n)))
