@@ -22,6 +22,8 @@
 //   pass<3>     keys that match a 22-bit prefix: counts of the last 9 bits
 //   walk<3>     the keys themselves; the fit (fp64, one thread per client)
 //
+// Vectors of up to 65 536 coordinates: one workgroup per client does all of it (rank_short).
+//
 // Only a few percent of a vector's keys lie in a level-1 bin that holds one of
 // the ranks.  Given a workspace with room for them (cvlc_fit_workspace_bytes_for)
 // the second pass writes those keys out, every wavefront to a stretch of its
@@ -52,13 +54,14 @@
 #include <type_traits>
 
 #include "cvlc_common.h"
+#include "cvlc_select.h"
 
 namespace cvlc {
 namespace {
 
 constexpr uint32_t kRanksMax = CVLC_FIT_RANKS_MAX;
-constexpr uint32_t kTopBins = 8192;   // level 1: key >> 18
-constexpr uint32_t kTopShift = 18;
+constexpr uint32_t kLevel1Bins = 8192;   // level 1: key >> 18
+constexpr uint32_t kLevel1Shift = 18;
 constexpr uint32_t kSubBits = 9;      // levels 2 and 3
 constexpr uint32_t kSubBins = 1u << kSubBits;
 constexpr uint32_t kRankBlock = 1024;
@@ -78,7 +81,7 @@ struct RankSet {  // the ranks of one call, ascending, as kernel arguments
 
 // Per-client state; cleared by the init kernel.
 struct RankCtl {
-  uint32_t top[kTopBins];               // level-1 counts of all d keys
+  uint32_t top[kLevel1Bins];               // level-1 counts of all d keys
   uint32_t sub[kRanksMax * kSubBins];   // per class: counts of the level's digit (cleared again by walk<2>)
   uint32_t prefix[kRanksMax];           // key prefix of rank j known so far (13, 22, 31 bits)
   uint32_t rem[kRanksMax];              // rank j counted inside its prefix class, 1-based from the largest key
@@ -87,7 +90,7 @@ struct RankCtl {
   uint32_t n_cls;
   uint32_t missed;                      // a rank lies outside the guessed bins: the lists do not hold its class
   uint32_t pad[2];
-  uint8_t guess[kTopBins / 8u];         // level-1 bins whose keys the lists hold, a bit each
+  uint8_t guess[kLevel1Bins / 8u];         // level-1 bins whose keys the lists hold, a bit each
 };
 
 struct RankLayout {
@@ -179,18 +182,18 @@ __device__ __forceinline__ void stream_keys(const float* update, uint32_t d, Vis
 __global__ __launch_bounds__(kRankBlock) void rank_hist1_kernel(const float* const* __restrict__ updates,
                                                                 RankCtl* __restrict__ ctls, uint32_t d,
                                                                 uint32_t* status) {
-  __shared__ uint32_t hist[kTopBins];
+  __shared__ uint32_t hist[kLevel1Bins];
   RankCtl* ctl = ctls + blockIdx.y;
-  for (uint32_t i = threadIdx.x; i < kTopBins; i += kRankBlock) hist[i] = 0;
+  for (uint32_t i = threadIdx.x; i < kLevel1Bins; i += kRankBlock) hist[i] = 0;
   __syncthreads();
   bool nonfinite = false;
   stream_keys(updates[blockIdx.y], d, [&](uint32_t key) {
     nonfinite |= key >= 0x7F800000u;
-    atomicAdd(&hist[key >> kTopShift], 1u);
+    atomicAdd(&hist[key >> kLevel1Shift], 1u);
   });
   const int any_nonfinite = __syncthreads_or((int)nonfinite);
   if (any_nonfinite && threadIdx.x == 0) atomicOr(status, CVLC_DEV_NONFINITE);
-  for (uint32_t i = threadIdx.x; i < kTopBins; i += kRankBlock) {
+  for (uint32_t i = threadIdx.x; i < kLevel1Bins; i += kRankBlock) {
     const uint32_t h = hist[i];
     if (h) atomicAdd(&ctl->top[i], h);
   }
@@ -258,9 +261,9 @@ __device__ __forceinline__ uint32_t write_classes(RankCtl* ctl, const uint32_t* 
 // (into LDS, valid after the next barrier).
 __device__ __forceinline__ void level1_walk(const RankCtl* ctl, const RankSet& ranks, uint32_t* scan_tmp,
                                             uint32_t* s_prefix, uint32_t* s_rem) {
-  // thread t owns `per` bins ending at top = kTopBins - 1 - per * t, largest keys first
-  constexpr uint32_t per = kTopBins / kRankBlock;
-  const uint32_t top = kTopBins - 1 - per * threadIdx.x;
+  // thread t owns `per` bins ending at top = kLevel1Bins - 1 - per * t, largest keys first
+  constexpr uint32_t per = kLevel1Bins / kRankBlock;
+  const uint32_t top = kLevel1Bins - 1 - per * threadIdx.x;
   uint32_t h[per], mine = 0;
 #pragma unroll
   for (uint32_t i = 0; i < per; ++i) {
@@ -295,7 +298,7 @@ __global__ __launch_bounds__(kRankBlock) void rank_pass_kernel(const float* cons
                                                                RankCtl* __restrict__ ctls, uint32_t d, KeyLists kl,
                                                                std::conditional_t<WALK, RankSet, NoRanks> ranks) {
   __shared__ uint32_t hist[kRanksMax * kSubBins];
-  __shared__ alignas(16) uint8_t first_cls[kTopBins];
+  __shared__ alignas(16) uint8_t first_cls[kLevel1Bins];
   __shared__ uint32_t cls_prefix[kRanksMax + 1];
   __shared__ uint32_t scan_tmp[kRankWaves], s_prefix[kRanksMax], s_rem[kRanksMax], s_n_cls, s_missed;  // WALK
   RankCtl* ctl = ctls + blockIdx.y;
@@ -326,7 +329,7 @@ __global__ __launch_bounds__(kRankBlock) void rank_pass_kernel(const float* cons
     if (threadIdx.x <= kRanksMax) cls_prefix[threadIdx.x] = threadIdx.x < n_cls ? ctl->cls_prefix[threadIdx.x] : 0xFFFFFFFFu;
   }
   for (uint32_t i = threadIdx.x; i < n_cls * kSubBins; i += kRankBlock) hist[i] = 0;
-  for (uint32_t i = threadIdx.x; i < kTopBins / 4u; i += kRankBlock)
+  for (uint32_t i = threadIdx.x; i < kLevel1Bins / 4u; i += kRankBlock)
     reinterpret_cast<uint32_t*>(first_cls)[i] = 0xFFFFFFFFu;
   __syncthreads();
   if (threadIdx.x < n_cls) {
@@ -337,7 +340,7 @@ __global__ __launch_bounds__(kRankBlock) void rank_pass_kernel(const float* cons
   }
   __syncthreads();
   auto visit = [&](uint32_t key) {
-    const uint32_t bin = key >> kTopShift;
+    const uint32_t bin = key >> kLevel1Shift;
     uint32_t c = first_cls[bin];
     if (c == kNoClass) return;
     if (LEVEL == 2) {
@@ -466,7 +469,7 @@ __global__ __launch_bounds__(kRankBlock) void rank_collect_kernel(const float* c
                                                                   RankCtl* __restrict__ ctls, RankSet ranks,
                                                                   uint32_t d, uint32_t* __restrict__ lists,
                                                                   uint32_t* __restrict__ list_cnt, uint32_t wave_cap) {
-  __shared__ alignas(16) uint8_t first_cls[kTopBins];
+  __shared__ alignas(16) uint8_t first_cls[kLevel1Bins];
   __shared__ uint32_t stage[kRankWaves][kCollectStage];
   __shared__ uint32_t s_fill[kRankWaves];  // keys a wavefront has staged
   __shared__ uint32_t level2[kRanksMax * kSubBins];
@@ -475,7 +478,7 @@ __global__ __launch_bounds__(kRankBlock) void rank_collect_kernel(const float* c
   __shared__ uint32_t s_n_cls;
   RankCtl* ctl = ctls + blockIdx.y;
   if (GUESSED && !ctl->missed) return;  // uniform
-  for (uint32_t i = threadIdx.x; i < kTopBins / 4u; i += kRankBlock)
+  for (uint32_t i = threadIdx.x; i < kLevel1Bins / 4u; i += kRankBlock)
     reinterpret_cast<uint32_t*>(first_cls)[i] = 0xFFFFFFFFu;
   level1_walk(ctl, ranks, scan_tmp, s_prefix, s_rem);
   __syncthreads();
@@ -504,7 +507,7 @@ __global__ __launch_bounds__(kRankBlock) void rank_collect_kernel(const float* c
   auto take = [&](const uint32_t* k, uint32_t n_keys, bool valid) {
     uint32_t hit = 0, cls[4];
     for (uint32_t c = 0; c < n_keys; ++c) {
-      cls[c] = first_cls[k[c] >> kTopShift];
+      cls[c] = first_cls[k[c] >> kLevel1Shift];
       hit |= (cls[c] != kNoClass ? 1u : 0u) << c;
     }
     if (valid && hit) {
@@ -584,9 +587,9 @@ constexpr uint32_t kSampleWgs = 16;        // workgroups per client
 
 // Workgroup g takes pieces g, g + 16, ...: its counts are those of an evenly spread sample of its own.  The sum of the
 // parts goes to `sub`, which the guess leaves cleared, the parts' counts of key >> 21 to parts, 16 a client and bin.
-constexpr uint32_t kPartShift = 21, kPartBins = 1u << (31u - kPartShift), kPartStep = kTopBins / kPartBins;
+constexpr uint32_t kSampledPartShift = 21, kPartBins = 1u << (31u - kSampledPartShift), kPartStep = kLevel1Bins / kPartBins;
 static_assert(kSamplePiecesMax / kSampleWgs * kPieceQuads * 4u < (1u << 16), "a part's counts and their sums fit 16 bits");
-static_assert(kTopBins <= kRanksMax * kSubBins, "the sample's counts fit where the second level's will stand");
+static_assert(kLevel1Bins <= kRanksMax * kSubBins, "the sample's counts fit where the second level's will stand");
 // The more pieces, the nearer the margins (32 x 11.2 M: lists of 6 % of the keys instead of 8, of 9 % for vectors of rows
 // instead of 17); an eighth of the vector is read at most.
 constexpr uint32_t kSampleDeep = 4, kSampleTurn = kRankBlock * kSampleDeep;  // float4 a workgroup asks for together
@@ -598,8 +601,8 @@ static_assert(kSampleWgs == kPieceQuads && kSamplePiecesMin % kSampleTurn == 0 &
 
 __global__ __launch_bounds__(kRankBlock) void rank_sample_kernel(const float* const* __restrict__ updates, RankCtl* __restrict__ ctls,
                                                                  uint16_t* __restrict__ parts, uint32_t n_pieces, uint32_t sampled) {
-  __shared__ uint32_t hist[kTopBins];
-  for (uint32_t i = threadIdx.x; i < kTopBins; i += kRankBlock) hist[i] = 0;
+  __shared__ uint32_t hist[kLevel1Bins];
+  for (uint32_t i = threadIdx.x; i < kLevel1Bins; i += kRankBlock) hist[i] = 0;
   __syncthreads();
   GlobalFloat4Ptr src = (GlobalFloat4Ptr)updates[blockIdx.y];
   const uint32_t quads = sampled * kPieceQuads / kSampleWgs;
@@ -614,10 +617,10 @@ __global__ __launch_bounds__(kRankBlock) void rank_sample_kernel(const float* co
 #pragma unroll
     for (uint32_t u = 0; u < kSampleDeep; ++u)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) atomicAdd(&hist[(__float_as_uint(v[u][c]) & 0x7FFFFFFFu) >> kTopShift], 1u);
+      for (int c = 0; c < 4; ++c) atomicAdd(&hist[(__float_as_uint(v[u][c]) & 0x7FFFFFFFu) >> kLevel1Shift], 1u);
   }
   __syncthreads();
-  for (uint32_t i = threadIdx.x; i < kTopBins; i += kRankBlock) {
+  for (uint32_t i = threadIdx.x; i < kLevel1Bins; i += kRankBlock) {
     const uint32_t h = hist[i];
     if (h) atomicAdd(&ctls[blockIdx.y].sub[i], h);
   }
@@ -639,14 +642,14 @@ __global__ __launch_bounds__(kRankBlock) void rank_sample_kernel(const float* co
 // Wrong only costs time: the second pass.
 __global__ __launch_bounds__(kRankBlock) void rank_guess_kernel(RankCtl* __restrict__ ctls, const uint16_t* __restrict__ parts,
                                                                 RankSet ranks, uint32_t d, uint32_t sampled) {
-  constexpr uint32_t per = kTopBins / kRankBlock, kPairs = kSampleWgs / 2u;
+  constexpr uint32_t per = kLevel1Bins / kRankBlock, kPairs = kSampleWgs / 2u;
   const float size = (float)(sampled * kPieceQuads * 4u);
   static_assert(per == 8u, "a byte of the bit set per thread");
   __shared__ uint32_t s_pair[kPairs][kRankWaves], scan_tmp[kRankWaves], s_extra[kRankWaves];
   __shared__ float s_factor[kRankWaves], s_bins[kRankWaves], s_place[kRanksMax], s_spread[kRanksMax], s_margin[kRanksMax];
   RankCtl* ctl = ctls + blockIdx.x;
   const uint32_t lane = lane_id(), wave = wave_id();
-  const uint32_t first = kTopBins - per * (threadIdx.x + 1u);  // thread 0 owns the largest keys
+  const uint32_t first = kLevel1Bins - per * (threadIdx.x + 1u);  // thread 0 owns the largest keys
   uint32_t h[per], mine = 0;
 #pragma unroll
   for (uint32_t i = 0; i < per; ++i) h[i] = ctl->sub[first + i];
@@ -761,12 +764,12 @@ __global__ __launch_bounds__(kRankBlock) void rank_stream_kernel(const float* co
                                                                  uint32_t* __restrict__ lists,
                                                                  uint32_t* __restrict__ list_cnt, uint32_t wave_cap,
                                                                  uint32_t* status) {
-  __shared__ uint32_t hist[kTopBins];
-  __shared__ uint32_t guess[kTopBins / 32u];
+  __shared__ uint32_t hist[kLevel1Bins];
+  __shared__ uint32_t guess[kLevel1Bins / 32u];
   __shared__ uint32_t stage[kRankWaves][kCollectStage];
   RankCtl* ctl = ctls + blockIdx.y;
-  for (uint32_t i = threadIdx.x; i < kTopBins; i += kRankBlock) hist[i] = 0;
-  if (threadIdx.x < kTopBins / 32u) guess[threadIdx.x] = reinterpret_cast<const uint32_t*>(ctl->guess)[threadIdx.x];
+  for (uint32_t i = threadIdx.x; i < kLevel1Bins; i += kRankBlock) hist[i] = 0;
+  if (threadIdx.x < kLevel1Bins / 32u) guess[threadIdx.x] = reinterpret_cast<const uint32_t*>(ctl->guess)[threadIdx.x];
   __syncthreads();
   const uint32_t lane = lane_id(), wave = wave_id();
   const size_t list = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kRankWaves + wave;
@@ -796,7 +799,7 @@ __global__ __launch_bounds__(kRankBlock) void rank_stream_kernel(const float* co
     lds_fence();
   };
   auto take = [&](uint32_t key, bool valid) {
-    const uint32_t bin = key >> kTopShift;
+    const uint32_t bin = key >> kLevel1Shift;
     if (valid) atomicAdd(&hist[bin], 1u);
     nonfinite |= valid && key >= 0x7F800000u;
     const bool keep = valid && ((guess[bin >> 5] >> (bin & 31u)) & 1u);
@@ -831,10 +834,48 @@ __global__ __launch_bounds__(kRankBlock) void rank_stream_kernel(const float* co
   if (lane == 0) list_cnt[list] = run;
   const int any_nonfinite = __syncthreads_or((int)nonfinite);
   if (any_nonfinite && threadIdx.x == 0) atomicOr(status, CVLC_DEV_NONFINITE);
-  for (uint32_t i = threadIdx.x; i < kTopBins; i += kRankBlock) {
+  for (uint32_t i = threadIdx.x; i < kLevel1Bins; i += kRankBlock) {
     const uint32_t h = hist[i];
     if (h) atomicAdd(&ctl->top[i], h);
   }
+}
+
+// ------------------------------------------------------------------ short vectors: one launch
+// A workgroup per client finds the keys at all ranks together (cvlc_select.h) and fits.  The pointers come as kernel arguments.
+// The status word is written by the one workgroup of a single client; several add to what a launch before has cleared.
+// us in six launches and in one or two: 1 x 2000 25.9 and 11.7, 1 x 20 000 30.5 and 15.6, 1 x 65 536 33.4 and 25.1, 32 x 65 536 37.7
+// and 27.7, 100 x 65 536 54.9 and 26.7, 600 x 65 536 139 and 87, 2000 x 65 536 359 and 281; of one magnitude 80.8 and 40.5, bfloat16
+// 33.3 and 26.0, nearly all zeros 74.7 and 36.9.  Slower only at the upper end of the range and for what queues up at few
+// counters: 65 536 coordinates of seven magnitudes 55 and 62 (9001: 41.5 and 21.5), sorted ones 45 and 56 (29.1 and 14.0).
+__global__ __launch_bounds__(kShortBlock) void rank_short_kernel(PtrChunk c, RankSet ranks, uint32_t d, uint32_t* __restrict__ keys_out,
+                                                                 double* __restrict__ alpha_out, uint32_t* status, uint32_t single) {
+  __shared__ ShortSelect S;
+  __shared__ uint32_t s_keys[kRanksMax];
+  const uint32_t client = c.first + blockIdx.x, tid = threadIdx.x;
+  const float* update = c.ptr[blockIdx.x];
+  clear_short(S);
+  __syncthreads();
+  if (tid < ranks.n) S.rank[tid] = ranks.rank[tid];
+  if (tid == 0) {
+    S.n_ranks = ranks.n;
+    S.extra = 0;
+  }
+  count_top(S, update, d);
+  constexpr uint32_t kNonfinite = 0x7F800000u >> kTopShift;  // the first bin of Inf and NaN; the first wavefront looks at all of them
+  static_assert(kTopBins - kNonfinite <= kWave && kRanksMax >= 17u && kRanksMax <= kShortRanks, "a bin per lane; all ranks of a short vector");
+  const uint64_t flagged = __ballot(tid < kTopBins - kNonfinite && S.top[kNonfinite + min(tid, kTopBins - kNonfinite - 1u)] != 0u);
+  if (tid == 0) {
+    if (single) *status = flagged ? CVLC_DEV_NONFINITE : 0u;
+    else if (flagged) atomicOr(status, CVLC_DEV_NONFINITE);
+  }
+  locate_short(S);
+  select_short(S, update, d);
+  if (tid < kRanksMax) {
+    s_keys[tid] = tid < ranks.n ? S.prefix[tid] : 0u;
+    if (keys_out) keys_out[(size_t)client * kRanksMax + tid] = s_keys[tid];
+  }
+  __syncthreads();
+  fit_exponent(s_keys, ranks, alpha_out + client);
 }
 
 uint32_t cu_count() {
@@ -917,6 +958,22 @@ int cvlc_fit_alpha(uint32_t n, const float* const* d_updates, uint32_t d, double
   ranks.n = cvlc_fit_ranks(d, ranks.rank);
 
   StageScope scope(CVLC_STAGE_FIT_ALPHA, stream);
+  if (d <= kShortMax) {
+    PtrChunk chunk;
+    if (n > 1u) {
+      chunk.first = chunk.count = 0;
+      for (uint32_t i = 0; i < kPtrChunk; ++i) chunk.ptr[i] = nullptr;
+      hipLaunchKernelGGL(rank_init_kernel, dim3(1), dim3(256), 0, stream, ptrs, chunk, reinterpret_cast<uint4*>(base), (size_t)1);
+    }
+    for (uint32_t first = 0; first < n; first += kPtrChunk) {
+      chunk.first = first;
+      chunk.count = std::min(n - first, kPtrChunk);
+      for (uint32_t i = 0; i < kPtrChunk; ++i) chunk.ptr[i] = i < chunk.count ? d_updates[first + i] : nullptr;
+      hipLaunchKernelGGL(rank_short_kernel, dim3(chunk.count), dim3(kShortBlock), 0, stream, chunk, ranks, d, d_keys_out, d_alpha_out, status,
+                         n == 1u ? 1u : 0u);
+    }
+    return hip_check(hipGetLastError());
+  }
   {
     PtrChunk chunk;
     for (uint32_t first = 0; first < n; first += kPtrChunk) {

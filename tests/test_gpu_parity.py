@@ -1428,6 +1428,18 @@ def test_fit_alpha_more_clients_than_one_upload_holds():
 
 # The collecting pass has a workgroup for every CU, two where a client's share of them is not a whole number, or those of the
 # other passes where short lists would need more room; the lists' passes 16 a client or, up to eight clients, one for every CU.
+@pytest.mark.parametrize("kind", ["plain", "bfloat16", "few values", "zeros", "octaves"])
+@pytest.mark.parametrize("n,d", [(1, 3), (1, 1023), (2, 4099), (1, SHORT_MAX - 1), (1, SHORT_MAX), (2, SHORT_MAX), (1, SHORT_MAX + 1), (449, 130)])
+def test_fit_alpha_of_short_vectors(n, d, kind):
+    """One workgroup per client, up to 448 clients a launch; a single one writes the status word itself."""
+    rng = np.random.default_rng(d)
+    host = [_selection_vectors(kind, d, rng) for _ in range(n)]
+    check_fit(host)
+    if n <= 2:
+        host[-1][d // 2] = np.float32(np.inf)
+        assert gpu_fit_alpha(host)[-1] == 1
+
+
 @pytest.mark.parametrize("n,d", [(1, 16_385), (1, 4_200_001), (2, 2_104_225), (8, 150_003), (9, 150_003), (12, 70_001), (100, 40_000), (129, 20_000)])
 def test_fit_alpha_at_the_steps_of_the_workgroups(n, d):
     rng = np.random.default_rng(n + d)
