@@ -395,51 +395,59 @@ __device__ __forceinline__ void fit_exponent(const uint32_t* s_keys, const RankS
   }
 }
 
-// One wavefront per class: lane l holds the 8 digits ending at 511 - 8 l.
+// A wavefront takes two classes: lane l holds the 8 digits ending at 511 - 8 l, and what is known of rank l.
+// One workgroup per client, all latency: everything is asked for at once, before the number of classes is known, and a class goes
+// through its own ranks only (all ranks' classes looked up in LDS for every class, the counts asked for class by class: level 2
+// 7.8 us and level 3 9.6 for 32 clients, now 5.0 and 7.0).
 template <int LEVEL>
 __global__ __launch_bounds__(kRankBlock) void rank_walk_kernel(RankCtl* __restrict__ ctls, RankSet ranks,
                                                                uint32_t* __restrict__ keys_out,
                                                                double* __restrict__ alpha_out) {
-  __shared__ uint32_t s_old_prefix[kRanksMax], s_old_rem[kRanksMax], s_cls[kRanksMax];
   __shared__ uint32_t s_prefix[kRanksMax], s_rem[kRanksMax];
   RankCtl* ctl = ctls + blockIdx.x;
-  const uint32_t n_cls = ctl->n_cls;
-  if (threadIdx.x < ranks.n) {
-    s_old_prefix[threadIdx.x] = ctl->prefix[threadIdx.x];
-    s_old_rem[threadIdx.x] = ctl->rem[threadIdx.x];
-    s_cls[threadIdx.x] = ctl->cls[threadIdx.x];
+  constexpr uint32_t per = kSubBins / kWave, kTurns = kRanksMax / kRankWaves;
+  typedef uint32_t __attribute__((ext_vector_type(4))) Words4;
+  static_assert(per == 8u && sizeof(RankCtl) % 16u == 0 && offsetof(RankCtl, sub) % 16u == 0, "two 16-byte loads");
+  const uint32_t lane = lane_id(), wave = wave_id(), top = kSubBins - 1 - per * lane, rank = min(lane, kRanksMax - 1u);
+  Words4 counts[kTurns][2];
+#pragma unroll
+  for (uint32_t t = 0; t < kTurns; ++t) {
+    const Words4* bins = reinterpret_cast<const Words4*>(ctl->sub + (wave + t * kRankWaves) * kSubBins + (top + 1u - per));
+    counts[t][0] = bins[0];
+    counts[t][1] = bins[1];
   }
-  __syncthreads();
-  constexpr uint32_t per = kSubBins / kWave;
-  const uint32_t lane = lane_id();
-  for (uint32_t c = wave_id(); c < n_cls; c += kRankWaves) {
-    uint32_t* bins = ctl->sub + c * kSubBins;
-    const uint32_t top = kSubBins - 1 - per * lane;
+  const uint32_t cls = ctl->cls[rank], old_rem = ctl->rem[rank], old_prefix = ctl->prefix[rank];
+#pragma unroll
+  for (uint32_t t = 0; t < kTurns; ++t) {
+    const uint32_t c = wave + t * kRankWaves;
+    uint64_t todo = __ballot(lane < ranks.n && cls == c);
+    if (!todo) continue;  // uniform: no such class
     uint32_t h[per], mine = 0;
 #pragma unroll
     for (uint32_t i = 0; i < per; ++i) {
-      h[i] = bins[top - i];
+      h[i] = counts[t][(per - 1u - i) / 4u][(per - 1u - i) % 4u];
       mine += h[i];
     }
     if (LEVEL == 2) {  // the next level counts into the same bins
-#pragma unroll
-      for (uint32_t i = 0; i < per; ++i) bins[top - i] = 0;
+      Words4* bins = reinterpret_cast<Words4*>(ctl->sub + c * kSubBins + (top + 1u - per));
+      bins[0] = bins[1] = Words4{0u, 0u, 0u, 0u};
     }
     const uint32_t above = wave_incl_scan_u32(mine) - mine;
-    for (uint32_t j = 0; j < ranks.n; ++j) {
-      if (s_cls[j] != c) continue;
-      const uint32_t target = s_old_rem[j];
-      if (above < target && target <= above + mine) {
+    while (todo) {
+      const uint32_t j = (uint32_t)__builtin_ctzll(todo);
+      const uint32_t target = (uint32_t)__builtin_amdgcn_readlane(old_rem, j), prefix = (uint32_t)__builtin_amdgcn_readlane(old_prefix, j);
+      if (above < target && target <= above + mine) {  // one lane
         uint32_t acc = above;
 #pragma unroll
         for (uint32_t i = 0; i < per; ++i) {
           if (acc < target && target <= acc + h[i]) {
-            s_prefix[j] = (s_old_prefix[j] << kSubBits) | (top - i);
+            s_prefix[j] = (prefix << kSubBits) | (top - i);
             s_rem[j] = target - acc;
           }
           acc += h[i];
         }
       }
+      todo &= todo - 1u;
     }
   }
   __syncthreads();
