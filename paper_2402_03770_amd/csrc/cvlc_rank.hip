@@ -258,11 +258,17 @@ __device__ __forceinline__ uint32_t write_classes(RankCtl* ctl, const uint32_t* 
 }
 
 // Level 1, whole workgroup: from the client's counts of key >> 18, the bin of every rank and the rank inside it
-// (into LDS, valid after the next barrier).
+// (into LDS, valid after the next barrier, up to which `sums` is in use).  A wavefront per rank searches the running sums, the block
+// of 128 bins first: most ranks lie in the bins of one or two wavefronts, so that threads that look for the ranks in their own
+// bins leave them to those: pass<2> with its walk 28.0 us -> 23.9 at 32 x 11.2 M, the call 390.6 -> 384.5, 1 x 11.2 M 51.6 -> 44.9,
+// 8 x 1.2 M 50.9 -> 41.9, 1 x 300 000 33.1 -> 26.6.
+constexpr uint32_t kBlockBins = kLevel1Bins / kWave, kWalkSums = kLevel1Bins + 1u + kWave + 1u;
+static_assert(kBlockBins == 2u * kWave && kWalkSums <= kRanksMax * kSubBins, "two bins of a block per lane; room where the level-2 counts will be");
 __device__ __forceinline__ void level1_walk(const RankCtl* ctl, const RankSet& ranks, uint32_t* scan_tmp,
-                                            uint32_t* s_prefix, uint32_t* s_rem) {
+                                            uint32_t* s_prefix, uint32_t* s_rem, uint32_t* sums) {
   // thread t owns `per` bins ending at top = kLevel1Bins - 1 - per * t, largest keys first
   constexpr uint32_t per = kLevel1Bins / kRankBlock;
+  static_assert(kBlockBins % per == 0, "a block begins with a thread's bins");
   const uint32_t top = kLevel1Bins - 1 - per * threadIdx.x;
   uint32_t h[per], mine = 0;
 #pragma unroll
@@ -271,19 +277,26 @@ __device__ __forceinline__ void level1_walk(const RankCtl* ctl, const RankSet& r
     mine += h[i];
   }
   uint32_t total;
-  const uint32_t above = block_excl_scan<kRankWaves>(mine, scan_tmp, &total);
-  for (uint32_t j = 0; j < ranks.n; ++j) {
-    const uint32_t target = ranks.rank[j];
-    if (above < target && target <= above + mine) {
-      uint32_t acc = above;
+  uint32_t above = block_excl_scan<kRankWaves>(mine, scan_tmp, &total);
+  uint32_t* blocks = sums + kLevel1Bins + 1u;  // keys before every block, and all
+  if (threadIdx.x * per % kBlockBins == 0) blocks[threadIdx.x * per / kBlockBins] = above;
 #pragma unroll
-      for (uint32_t i = 0; i < per; ++i) {
-        if (acc < target && target <= acc + h[i]) {
-          s_prefix[j] = top - i;
-          s_rem[j] = target - acc;
-        }
-        acc += h[i];
-      }
+  for (uint32_t i = 0; i < per; ++i) {
+    sums[threadIdx.x * per + i] = above;
+    above += h[i];
+  }
+  if (threadIdx.x == kRankBlock - 1u) sums[kLevel1Bins] = blocks[kWave] = above;
+  __syncthreads();
+  const uint32_t lane = lane_id();
+  for (uint32_t j = wave_id(); j < ranks.n; j += kRankWaves) {
+    const uint32_t target = ranks.rank[j];  // 1 .. d: inside some bin
+    const uint32_t c = min((uint32_t)__popcll(__ballot(blocks[lane + 1u] < target)), kWave - 1u);
+    const uint32_t* s = sums + c * kBlockBins + 2u * lane;
+    const uint32_t k = min(c * kBlockBins + (uint32_t)__popcll(__ballot(s[1] < target)) + (uint32_t)__popcll(__ballot(s[2] < target)),
+                           kLevel1Bins - 1u);
+    if (lane == 0) {
+      s_prefix[j] = kLevel1Bins - 1u - k;
+      s_rem[j] = target - sums[k];
     }
   }
 }
@@ -305,7 +318,7 @@ __global__ __launch_bounds__(kRankBlock) void rank_pass_kernel(const float* cons
   uint32_t n_cls;
   if constexpr (WALK) {
     if (threadIdx.x <= kRanksMax) cls_prefix[threadIdx.x] = 0xFFFFFFFFu;
-    level1_walk(ctl, ranks, scan_tmp, s_prefix, s_rem);
+    level1_walk(ctl, ranks, scan_tmp, s_prefix, s_rem, hist);
     __syncthreads();
     if (threadIdx.x < kWave) {
       const uint32_t bin = threadIdx.x < ranks.n ? s_prefix[threadIdx.x] : 0u;
@@ -368,7 +381,8 @@ __global__ __launch_bounds__(kRankBlock) void rank_walk1_kernel(RankCtl* __restr
   __shared__ uint32_t scan_tmp[kRankWaves];
   __shared__ uint32_t s_prefix[kRanksMax], s_rem[kRanksMax];
   RankCtl* ctl = ctls + blockIdx.x;
-  level1_walk(ctl, ranks, scan_tmp, s_prefix, s_rem);
+  __shared__ uint32_t sums[kWalkSums];
+  level1_walk(ctl, ranks, scan_tmp, s_prefix, s_rem, sums);
   __syncthreads();
   if (threadIdx.x < kWave) write_classes(ctl, s_prefix, s_rem, ranks.n);
 }
@@ -488,7 +502,7 @@ __global__ __launch_bounds__(kRankBlock) void rank_collect_kernel(const float* c
   if (GUESSED && !ctl->missed) return;  // uniform
   for (uint32_t i = threadIdx.x; i < kLevel1Bins / 4u; i += kRankBlock)
     reinterpret_cast<uint32_t*>(first_cls)[i] = 0xFFFFFFFFu;
-  level1_walk(ctl, ranks, scan_tmp, s_prefix, s_rem);
+  level1_walk(ctl, ranks, scan_tmp, s_prefix, s_rem, level2);
   __syncthreads();
   if (threadIdx.x < kWave) {
     uint32_t c;
@@ -661,8 +675,8 @@ __global__ __launch_bounds__(kRankBlock) void rank_guess_kernel(RankCtl* __restr
   // keys in the bins before bin k and in the blocks of 128 bins before block c, largest keys first
   __shared__ alignas(16) uint32_t s_sum[kLevel1Bins + 1];
   __shared__ uint32_t s_block[kWave + 1], s_bits[kLevel1Bins / 32u], s_expected[kLevel1Bins / 32u];
-  constexpr uint32_t kBlockBins = kLevel1Bins / kWave, kMarkWords = kLevel1Bins / 32u;
-  static_assert(kBlockBins == 2u * kWave && kBlockBins % per == 0 && 2u * kMarkWords <= kRankBlock, "two bins of a block per lane");
+  constexpr uint32_t kMarkWords = kLevel1Bins / 32u;
+  static_assert(kBlockBins % per == 0 && 2u * kMarkWords <= kRankBlock, "a block begins with a thread's bins");
   RankCtl* ctl = ctls + blockIdx.x;
   const uint32_t lane = lane_id(), wave = wave_id();
   const uint32_t first = kLevel1Bins - per * (threadIdx.x + 1u);  // thread 0 owns the largest keys
