@@ -1447,6 +1447,16 @@ def test_fit_alpha_at_the_steps_of_the_workgroups(n, d):
     check_fit([host[c % len(host)] for c in range(n)])
 
 
+@pytest.mark.parametrize("bins", [(0, 8159), (127, 128, 129), tuple(range(0, 8160, 128)), tuple(range(127, 8160, 128)), (8159,), (4095, 4096)])
+def test_fit_alpha_at_the_borders_of_the_walks_blocks(bins):
+    """The level-1 walk searches blocks of 128 bins (key >> 18), then a block's bins: keys in the bins next to the borders, in the
+    lowest and in the highest bin of finite numbers."""
+    d = SHORT_MAX + 4097
+    rng = np.random.default_rng(len(bins) + bins[0])
+    keys = (rng.choice(np.array(bins, dtype=np.uint32), d) << 18) | rng.integers(0, 1 << 18, d, dtype=np.uint32)
+    check_fit([keys.view(np.float32), -np.sort(keys).view(np.float32)])
+
+
 @pytest.mark.parametrize("d", [2_100_003, 2_097_152])
 def test_fit_alpha_in_one_pass(d):
     """From 7 x 2^24 coordinates on the level-1 bins of the ranks are guessed from a sample: ordinary vectors, tied ones, and
