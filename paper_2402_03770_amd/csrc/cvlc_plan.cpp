@@ -142,7 +142,9 @@ class Algorithm1 {
  public:
   Algorithm1(uint32_t d, uint32_t R, uint32_t s, double usable_bits, double alpha, double B, uint32_t quant)
       : d_(d), R_(R), s_(s), u_(usable_bits), law_((double)d, alpha), err_(B, quant), alpha_(alpha), B_(B),
-        quant_(quant), y_min_(quant == CVLC_QUANT_QSGD ? 2.0 : 1.0) {}
+        quant_(quant), y_min_(quant == CVLC_QUANT_QSGD ? 2.0 : 1.0),
+        by_slope_(quant == CVLC_QUANT_PQ && err_.inv_bc2 == 0.0 && alpha >= -4.0 && alpha < 0.0 &&
+                  (law_.log_limit || std::fabs(law_.beta) > 1e-3)) {}
 
   // f(X, P_{r-1}, P_r) of Eq. (6) as a function of P_r: the pair's outer ends stay, and so do their power-law terms.
   struct Pair {
@@ -211,16 +213,15 @@ class Algorithm1 {
 
   // Atomic operation: the minimiser of the strongly
   // convex pair cost (Lemma 3) on (X/2, X), kept inside "one update, the quantiser's
-  // shortest code" (1 bit for PQ; QSGD needs a sign bit and a level bit).  PQ without scaling: where the derivative is zero, half a dozen
-  // evaluations from the size before on.  QSGD, whose error model has a kink, and scale factors, whose constant part buries the
-  // minimum in rounding so that the search decides the plan's last unit: golden-section search, 82 evaluations.
-  double atomic_operation(double X, double z_r2, double size_before) const {
+  // shortest code" (1 bit for PQ; QSGD needs a sign bit and a level bit).  By slope: where the derivative is zero, half a dozen
+  // evaluations from the size before on.  Else by golden-section search, 82 evaluations.
+  double atomic_operation(double X, double z_r2, double size_before, bool by_slope) const {
     const double p_max = u_ / ((double)s_ + y_min_);
     double lo = 0.5 * X, hi = X - 1.0;
     if (hi > p_max) hi = p_max;
     if (lo < X - p_max) lo = X - p_max;
     if (!(hi > lo)) return 0.5 * X > p_max ? p_max : 0.5 * X;
-    if (quant_ == CVLC_QUANT_PQ && err_.inv_bc2 == 0.0) {
+    if (by_slope) {
       const double flat = flat_point(lo, hi, size_before, pair(X, z_r2));
       if (flat >= lo && flat <= hi) return flat;  // a number
     }
@@ -242,24 +243,43 @@ class Algorithm1 {
     return 0.5 * (lo + hi);
   }
 
-  // SMO-style sweeps for one k, then integer code lengths (clamped to 1..16,
-  // non-increasing) and refilled group sizes; returns gamma of the integer plan.
-  double solve(double k, uint32_t* y, uint32_t* P) const {
-    double Pc[CVLC_MAX_CODED];
+  // SMO-style sweeps for one k.  By slope: returns whether the search is known to end at the same code lengths.  The search finds
+  // a size only as well as the cost's rounding lets it: 5e-9 of the size off as a rule, 7e-8 at most in 400 000 k of random
+  // requests (4 to 3e7 coordinates, up to 60 bits each).  That matters where u / size is next to a whole number, as it is for
+  // groups of whole sizes in small vectors, and where the sweeps may end one earlier or later, which moves a size by less than 2.
+  bool balance(double k, bool by_slope, double (&Pc)[CVLC_MAX_CODED]) const {
+    constexpr double kLoose = 1e-6;
+    double nearest_stop = 1.0, largest = 0.0;
     for (uint32_t r = 0; r < R_; ++r) Pc[r] = k / (double)R_;
     for (int sweep = 0; sweep < 200; ++sweep) {
       double moved = 0.0, z_r2 = 0.0;
       for (uint32_t r = 1; r < R_; ++r) {
         const double X = Pc[r - 1] + Pc[r];
-        const double Pr = atomic_operation(X, z_r2, Pc[r]);
+        const double Pr = atomic_operation(X, z_r2, Pc[r], by_slope);
         const double delta = std::fabs(Pr - Pc[r]);
         if (delta > moved) moved = delta;
         Pc[r] = Pr;
         Pc[r - 1] = X - Pr;
         z_r2 += Pc[r - 1];
       }
+      nearest_stop = std::min(nearest_stop, std::fabs(moved - 0.5));
       if (moved < 0.5) break;
     }
+    if (!by_slope) return true;
+    for (uint32_t r = 0; r < R_; ++r) largest = std::max(largest, Pc[r]);
+    const double stop = nearest_stop < kLoose * largest ? 2.0 : 0.0;
+    for (uint32_t r = 0; r < R_; ++r) {
+      const double t = u_ / Pc[r], y = t - (double)s_;  // lengths of 1 and 16 are the ends: the steps are at 2 .. 16
+      if (y > 1.5 && y < 16.5 && std::fabs(t - std::round(t)) <= t * (kLoose + stop / Pc[r])) return false;
+    }
+    return true;
+  }
+
+  // The group sizes for one k, then integer code lengths (clamped to 1..16,
+  // non-increasing) and refilled group sizes; returns gamma of the integer plan.
+  double solve(double k, uint32_t* y, uint32_t* P) const {
+    double Pc[CVLC_MAX_CODED];
+    if (!by_slope_ || !balance(k, true, Pc)) balance(k, false, Pc);
     uint64_t room = d_;
     for (uint32_t r = 0; r < R_; ++r) {
       double yr = std::floor(u_ / Pc[r]) - (double)s_;
@@ -284,6 +304,12 @@ class Algorithm1 {
   double alpha_, B_;
   uint32_t quant_;
   double y_min_;
+  // Where the pairs' minima are found by slope: PQ (QSGD's error model has a kink) without scaling (the constant part of a scale factor
+  // buries the minimum in rounding, so that the search decides the plan's last unit), and an exponent for which the pair cost is
+  // convex and of a size that its rounding leaves alone: Lemma 3 assumes alpha < 0; below -10 the tail's energy vanishes beside the
+  // head's and the two end up to a tenth of a size apart; near beta = 0, but for the limit itself, the power-law terms cancel (1e-6 of
+  // a size at beta = 2e-5, 1e-2 at 2e-10).  Equal magnitudes fit an alpha of about 0 of either sign.
+  bool by_slope_;
 };
 
 // CPUs the calling thread may run on.
@@ -330,7 +356,7 @@ int plan_algorithm1(uint32_t d, uint64_t budget, uint32_t R, double alpha, float
   const Algorithm1 alg(d, R, out->s, u, alpha, (double)B, quant);
   // Equidistant search over k.  The 128 searches know nothing of each other: they are shared out between up to 16 threads,
   // and the first of the best is taken as if they had been done in order (7 groups, 1.2 M coordinates: 424 us, with ten threads
-  // 480; with golden-section searches, twelve times the evaluations, 2 007).
+  // 480; with golden-section searches alone, twelve times the evaluations, 2 007).
   constexpr int kGrid = 128, kThreads = 16;
   struct Candidate {
     double gamma;

@@ -97,6 +97,15 @@ def test_planner_by_slope_and_by_search(R, alpha, B):
         assert _same(cv.plan(d, budget, n_coded=R, alpha=alpha, B=B), po), (d, bits)
 
 
+@pytest.mark.parametrize("d,budget,R,alpha", [
+    (64, 1857, 6, 0.0), (32, 1384, 3, -1e-17), (32, 1340, 3, 6e-16), (128, 2876, 5, -1e-12), (80, 2447, 7, 0.399),
+    (96, 3340, 7, 1.7056901265513946), (232, 5544, 5, 4.043337868879016),   # no slope to go by: alpha is not below 0
+    (144, 3173, 7, -0.010392105860938531),                                 # a size next to a step of the code lengths
+    (245, 31 * 608 + 256, 31, -50.5047), (11_200_000, 11_200_000, 15, -0.5 + 1e-9)])
+def test_planner_where_the_slope_does_not_decide(d, budget, R, alpha):
+    assert _same(cv.plan(d, budget, n_coded=R, alpha=alpha), orc.plan_alg1(d, budget, R, alpha))
+
+
 def test_plan_errors():
     with pytest.raises(cv.CvlcError) as e:
         cv.plan(1000, 256 + 3 * 128, code_len=[4, 2, 1])
