@@ -246,9 +246,9 @@ class Algorithm1 {
   // SMO-style sweeps for one k.  By slope: returns whether the search is known to end at the same code lengths.  The search finds
   // a size only as well as the cost's rounding lets it: 5e-9 of the size off as a rule, 7e-8 at most in 400 000 k of random
   // requests (4 to 3e7 coordinates, up to 60 bits each).  That matters where u / size is next to a whole number, as it is for
-  // groups of whole sizes in small vectors, and where the sweeps may end one earlier or later, which moves a size by less than 2.
+  // groups of whole sizes in small vectors, and where the sweeps may end one earlier or later, which moves a size by little more than half a unit in either of its pairs.
   bool balance(double k, bool by_slope, double (&Pc)[CVLC_MAX_CODED]) const {
-    constexpr double kLoose = 1e-6;
+    constexpr double kLoose = 2e-7;
     double nearest_stop = 1.0, largest = 0.0;
     for (uint32_t r = 0; r < R_; ++r) Pc[r] = k / (double)R_;
     for (int sweep = 0; sweep < 200; ++sweep) {
@@ -267,7 +267,7 @@ class Algorithm1 {
     }
     if (!by_slope) return true;
     for (uint32_t r = 0; r < R_; ++r) largest = std::max(largest, Pc[r]);
-    const double stop = nearest_stop < kLoose * largest ? 2.0 : 0.0;
+    const double stop = nearest_stop < kLoose * largest ? 1.25 : 0.0;
     for (uint32_t r = 0; r < R_; ++r) {
       const double t = u_ / Pc[r], y = t - (double)s_;  // lengths of 1 and 16 are the ends: the steps are at 2 .. 16
       if (y > 1.5 && y < 16.5 && std::fabs(t - std::round(t)) <= t * (kLoose + stop / Pc[r])) return false;
