@@ -2759,21 +2759,24 @@ bool short_pays(uint32_t n, const cvlc_plan_t* plans) {
 }
 
 // Whether the packing pass makes its prefixes from the chunks' counts (kByChunks) or a layout kernel does.  The layout is one
-// workgroup per client: a launch of 7 us, and 30 us for every million coordinates that the client with the most keeps.  In its
-// place the counting pass clears the streams, not only the words at the runs' ends, and every packing workgroup goes through its
-// client's chunks: 0.7 us for every million coordinates kept in all.  us with the layout and without it: 1 x 70 000 58.7 and
-// 55.6, 1 x 11.2 M 86.4 and 79.7, the same half kept 259 and 193, 1 x 25.6 M half kept 501 and 352, 8 x 1.2 M 79.9 and 75.3,
-// 14 x 25.6 M 483 and 471, QSGD 8 x 11.2 M 178.3 and 174.2, 32 x 11.2 M 458.7 and 460.2, 100 x 3 M level, 100 x 25.6 M of budgets
-// that differ 3483 and 3493.
+// workgroup per client: a launch of 5 us, and about 14 us for every million coordinates that the client with the most keeps.  In its
+// place the counting pass clears the streams, not only the words at the runs' ends, which goes with all that is kept, and every
+// packing workgroup goes through its client's chunks for every chunk of its own, beyond 128 of them one by one: that goes with all that
+// is kept times what a client keeps.  Both sides were timed for 220 calls, of 1 to 300 clients that keep 1 % to all of 70 000 to
+// 4e8 coordinates in 7, 15 and 31 groups; the line takes the slower side by more than 2 % in three of them, 5 % at most, and in
+// two of these the difference is one of runs.  us with the layout and by chunks: 1 x 1.2 M 64 and 60, 1 x 11.2 M 79 and 72, half kept 257 and
+// 188, 1 x 25.6 M all kept 957 and 717, 1 x 1e8 half kept 2042 and 1778, all kept 3843 and 4096, 1 x 2e8 all kept 7677 and 11 494; 8 x 1.2 M
+// 77 and 73, 8 x 11.2 M 160 and 152, all kept 1157 and 1246; 32 x 11.2 M 453 and 450, a quarter kept 1261 and 1320, half kept 2247 and
+// 2487; 100 x 300 000 125 and 122, 100 x 1.2 M half kept 837 and 870, 100 x 11.2 M 1330 and 1357 (where nothing else is said, 3 %).
 bool chunks_pay(uint32_t n, const cvlc_plan_t* plans) {
-  uint64_t all = 0, most = 0;
+  double all = 0.0, most = 0.0;  // millions of coordinates
   for (uint32_t i = 0; i < n; ++i) {
     uint64_t k = 0;
     for (uint32_t r = 0; r < plans[i].n_coded; ++r) k += plans[i].count[r];
-    all += k;
-    most = std::max(most, k);
+    all += 1e-6 * (double)k;
+    most = std::max(most, 1e-6 * (double)k);
   }
-  return all <= 32u * most + (8u << 20);
+  return all * (3.0 + most) <= 60.0 * most + 80.0;
 }
 
 }  // namespace
