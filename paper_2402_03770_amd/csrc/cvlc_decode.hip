@@ -452,7 +452,7 @@ struct TableShared {
 template <bool WIDE, uint32_t STREAMS>
 __global__ __launch_bounds__(kBlock, 8) void stream_table_kernel(StreamArgs<STREAMS> in, uint32_t quant, CompactDesc* __restrict__ cdesc,
                                                                  DecodeCtl* ctl, uint32_t* table, uint32_t d, uint32_t tile_shift,
-                                                                 uint32_t n_tiles, uint32_t* __restrict__ found, uint32_t* status) {
+                                                                 uint32_t n_tiles, uint8_t* __restrict__ found, uint32_t* status) {
   __shared__ TableShared S;
   const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   if (wave == 0) {
@@ -499,7 +499,7 @@ __global__ __launch_bounds__(kBlock, 8) void stream_table_kernel(StreamArgs<STRE
       }
       if (lane == 0 && client == in.count - 1u) {
         ctl->n_active = before + groups;
-        *status = 0;  // what the workgroups find goes to a word of each, which decode_tiles adds to it
+        *status = 0;  // what the workgroups find goes to a byte of each, which decode_tiles adds to it
       }
     }
   }
@@ -585,7 +585,7 @@ __global__ __launch_bounds__(kDecBlock, SHIFT == kDecShiftMin ? 6 : 4) void deco
                                                               const DecodeCtl* __restrict__ ctl,
                                                               const uint32_t* __restrict__ table, float* out,
                                                               uint32_t d, uint32_t n_tiles, uint32_t s, uint32_t accumulate,
-                                                              const uint32_t* __restrict__ found, uint32_t n_found,
+                                                              const uint8_t* __restrict__ found, uint32_t n_found,
                                                               uint32_t* status) {
   constexpr uint32_t kTile = 1u << SHIFT, kHalf = half_turns(SHIFT), kTurns = 2u * kHalf;
   __shared__ DecodeShared<SHIFT> S;
@@ -887,28 +887,39 @@ int cvlc_decode_aggregate(uint32_t n, const void* const* d_streams, const size_t
     sa.pad = 0;
     return sa;
   };
-  // A word for every workgroup of stream_table in the place of the list descriptors, of which there is room for 320 a stream.
-  uint32_t* found = reinterpret_cast<uint32_t*>(descs);
+  // A byte for every workgroup of stream_table: in the place of the list descriptors, or where the table's rows end (a stream has
+  // 31 at most, of the larger tiles if there are such) if that is more.
+  uint8_t* found = reinterpret_cast<uint8_t*>(descs);
   uint32_t n_found = 0;
   if (n > 0 && n <= kParseStreams) {
     StageScope scope(CVLC_STAGE_DEC_TABLE, stream);
-    // workgroups by the streams' lengths, all resident, but no more than a wavefront for every item that a stream can hold (a
-    // record has a code bit at least)
-    constexpr uint64_t kMost = kListsPerClient * sizeof(ListDesc) / sizeof(uint32_t);
+    const size_t rows_end = L.table + (size_t)n * CVLC_MAX_CODED * (n_tiles + 1u) * sizeof(uint32_t);
+    size_t room = (size_t)n_lists * sizeof(ListDesc);
+    if (L.total - rows_end > room) {
+      found = reinterpret_cast<uint8_t*>(base + rows_end);
+      room = L.total - rows_end;
+    }
+    // Workgroups by the streams' lengths, all resident, but no more than a wavefront for every item that a stream can hold (a
+    // record has a code bit at least).  us a call with up to 320 workgroups a stream and up to 63 in all more than the device
+    // holds, which start when others end, and now: 1 x 11.2 M all kept 57.5 and 42.9, 1 x 25.6 M all kept 111.6 and 78.9, half
+    // kept 73.8 and 57.1 (1024 workgroups 59.0), 2 x 11.2 M half kept 50.5 and 45.2; 9 x 11.2 M half kept 132.8 and 126.7, 25 x 1.2 M half
+    // kept 62.1 and 58.2, 100 x 11.2 M 121.9 and 115.9.
     uint64_t all = 0;
     for (uint32_t i = 0; i < n; ++i) all += stream_bytes[i];
+    const uint64_t most = std::min<uint64_t>(kTableBlocks, room) - n;
+    static_assert(kListsPerClient * sizeof(ListDesc) > kParseStreams, "room for a workgroup a stream at least");
     auto launch = [&](auto& in, auto kernel) {
       in.count = n;
       for (uint32_t i = 0; i < n; ++i) {
         const uint64_t items = (uint64_t)stream_bytes[i] * 8u / ((position_bits(d) + 1u) * kTabChunk) + CVLC_MAX_CODED;
         in.args[i] = stream_arg(i);
         in.first[i] = (uint16_t)n_found;
-        n_found += (uint32_t)std::min({((uint64_t)kTableBlocks * stream_bytes[i] + all - 1u) / all, (items + kWavesPerBlock - 1u) / kWavesPerBlock, kMost});
+        n_found += (uint32_t)std::min(1u + most * stream_bytes[i] / all, (items + kWavesPerBlock - 1u) / kWavesPerBlock);
       }
       in.blocks = n_found;
       hipLaunchKernelGGL(kernel, dim3(n_found), dim3(kBlock), 0, stream, in, quant, cdesc, ctl, table, d, shift, n_tiles, found, status);
     };
-    static_assert(kTableBlocks + kParseStreams < (1u << 16), "the workgroups are numbered in 16 bits");
+    static_assert(kTableBlocks < (1u << 16), "the workgroups are numbered in 16 bits");
     if (n <= kFewStreams) {
       StreamArgs<kFewStreams> in;
       launch(in, wide ? stream_table_kernel<true, kFewStreams> : stream_table_kernel<false, kFewStreams>);

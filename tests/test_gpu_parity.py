@@ -979,6 +979,30 @@ def test_a_malformed_stream_among_good_ones(d, n_good):
     assert status == 0                                            # the untouched stream decodes
 
 
+@pytest.mark.parametrize("d,n", [(1_200_007, 1), (5_000_000, 1), (5_000_000, 3), (9_000_001, 1), (9_000_001, 5)])
+def test_a_position_twice_anywhere_in_a_long_stream(d, n):
+    """Two equal positions in a row are seen by the table's pass only, in one of up to 2048 workgroups; what those find lies in the
+    place of the list descriptors or where the table ends.  Records of 32 bits, a word each."""
+    s = (d - 1).bit_length()
+    plan = cv.plan_manual(d, [32 - s], [d // 2])
+    streams = [cv.new_stream_buffer(plan, DEV) for _ in range(n)]
+    ws = cv.new_workspace(cv.encode_workspace_bytes(d, n), DEV)
+    cv.encode_batch([plan] * n, [torch.randn(d, device=DEV, generator=torch.Generator(DEV).manual_seed(c)) for c in range(n)], 3,
+                    list(range(n)), streams, ws)
+    clean, status = gpu_decode(streams, d)
+    assert status == 0
+    words = streams[-1]
+    for e in (1, 511, 512, 513, d // 6, d // 4 + 1, d // 2 - 513, d // 2 - 1):
+        kept = words[12 + e].item()
+        words[12 + e] = words[11 + e]
+        got, status = gpu_decode(streams, d)
+        assert status == cv.DEV_STREAM, e
+        # fp64 sums in free order, each rounded to fp32 once: a unit of the last place, but for the coordinate hit twice and the one left
+        # out (several streams' values may cancel: the terms are below 4, fp64 keeps 2^-50 of them)
+        assert np.count_nonzero(np.abs(got - clean) > 2.0 ** -23 * np.abs(clean) + 2.0 ** -48) <= 2
+        words[12 + e] = kept
+
+
 @pytest.mark.parametrize("d", [30_000, 70_001])
 def test_non_finite_update_sets_status(d):
     p = orc.plan_fractions(d, [8], [0.1])
