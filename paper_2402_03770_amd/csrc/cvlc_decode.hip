@@ -44,8 +44,9 @@ struct CompactDesc {  // one (client, group) record list, 32 bytes
 static_assert(sizeof(CompactDesc) == 32, "CompactDesc is read as two 16-byte pieces");
 
 struct DecodeCtl {  // written by stream_table or compact_lists
-  uint32_t n_active;  // lists: the non-empty ones, or (stream_table) all that the headers name
-  uint32_t n_items;   // tile_table work items in all
+  uint32_t n_active;  // lists with records
+  uint32_t n_items;   // compact_lists: tile_table work items in all
+  uint32_t sparse;    // stream_table: some lists are empty; a list's row of the table is then not its number but row_of[number]
 };
 
 struct DecodeLayout {
@@ -230,6 +231,7 @@ __device__ __forceinline__ void compact_lists(const ListDesc* descs, uint32_t n_
     item_start[lists_before] = items_before;
     ctl->n_active = lists_before;
     ctl->n_items = items_before;
+    ctl->sparse = 0;
   }
 }
 
@@ -427,7 +429,10 @@ __global__ __launch_bounds__(kBlock, 8) void tile_table_kernel(const CompactDesc
 
 // ---- up to 112 streams: headers, list numbers and table in one launch
 // A workgroup belongs to one stream: its first wavefront parses that stream's headers (and reads the other streams' numbers of
-// groups, for the place of its lists among all), its wavefronts share out the stream's items.
+// groups, for the rows of its lists among all), its wavefronts share out the stream's items.  One of the stream's workgroups
+// numbers its lists with records: its other wavefronts, which wait for the first one, count those of the streams before.
+// (With the empty lists among the numbered ones, which decode_tiles then deals out and sweeps over, 100 x 11.2 M of one group with
+// records and 30 without took 74.7 us for 50.4, 30 x 11.2 M of four and 27 53.5 for 46.2.)
 // us of the launches before decode_tiles, headers, list numbers and items in launches of their own (up to eight streams: in one, whose
 // workgroups each parsed all of them) and now: 32 x 11.2 M 27.0 and 20.9, 100 x 25.6 M 136 and 127, 8 x 1.2 M 8.3 and 7.4.  About
 // 6 of them are the headers (every wavefront for itself: 9.6 with 32 streams, at whose few lines all of them queue up).
@@ -446,28 +451,43 @@ static_assert(sizeof(StreamArgs<kParseStreams>) <= 3840, "kernel arguments are l
 struct TableShared {
   uint64_t payload[kWave];
   uint32_t P[kWave], wsy[kWave], first[kWave];
-  uint32_t before, bad, first_block, blocks;
+  uint32_t before, bad;
+  uint32_t live_before[kWavesPerBlock];
 };
+
+// Whether the stream's header says that its group g has records, be the header right or wrong.
+__device__ __forceinline__ bool names_records(const StreamArg& sa, uint32_t g) {
+  GlobalConstWordPtr w = (GlobalConstWordPtr)sa.words;
+  const uint32_t groups = w[3], P = w[min((uint64_t)(kGlobalHeaderWords + kSegHeaderWords * g + 1u), sa.n_words - 1u)];
+  return g < min(groups, CVLC_MAX_CODED) && P != 0u;
+}
 
 template <bool WIDE, uint32_t STREAMS>
 __global__ __launch_bounds__(kBlock, 8) void stream_table_kernel(StreamArgs<STREAMS> in, uint32_t quant, CompactDesc* __restrict__ cdesc,
-                                                                 DecodeCtl* ctl, uint32_t* table, uint32_t d, uint32_t tile_shift,
-                                                                 uint32_t n_tiles, uint8_t* __restrict__ found, uint32_t* status) {
+                                                                 DecodeCtl* ctl, uint32_t* __restrict__ row_of, uint32_t* table, uint32_t d,
+                                                                 uint32_t tile_shift, uint32_t n_tiles, uint8_t* __restrict__ found,
+                                                                 uint32_t* status) {
   __shared__ TableShared S;
   const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  if (wave == 0) {
-    constexpr uint32_t kTurns = (STREAMS + kWave - 1u) / kWave;
-    uint32_t client = 0, first_block = 0;
+  constexpr uint32_t kTurns = (STREAMS + kWave - 1u) / kWave;
+  uint32_t client = 0, first_block = 0;
 #pragma unroll
-    for (uint32_t i = 0; i < kTurns; ++i) {
-      const uint32_t c = i * kWave + lane, f = in.first[min(c, in.count - 1u)];
-      const uint64_t at_or_before = __ballot(c < in.count && f <= blockIdx.x);  // firsts ascend: a prefix
-      if (at_or_before) first_block = __builtin_amdgcn_readlane(f, 63u - (uint32_t)__builtin_clzll(at_or_before));
-      client += (uint32_t)__popcll(at_or_before);
-    }
-    client = __builtin_amdgcn_readfirstlane(client - 1u);
+  for (uint32_t i = 0; i < kTurns; ++i) {
+    const uint32_t c = i * kWave + lane, f = in.first[min(c, in.count - 1u)];
+    const uint64_t at_or_before = __ballot(c < in.count && f <= blockIdx.x);  // firsts ascend: a prefix
+    if (at_or_before) first_block = __builtin_amdgcn_readlane(f, 63u - (uint32_t)__builtin_clzll(at_or_before));
+    client += (uint32_t)__popcll(at_or_before);
+  }
+  client = __builtin_amdgcn_readfirstlane(client - 1u);
+  const uint32_t blocks = __builtin_amdgcn_readfirstlane((client + 1u < in.count ? in.first[client + 1u] : in.blocks) - first_block);
+  // The stream's workgroup that numbers its lists: of as many streams as a power of two the first ones would all be on a few CUs of
+  // one XCD (32 x 11.2 M: the launch 28 us instead of 22).
+  const bool leads = blockIdx.x == first_block + client % blocks;  // uniform
+  ListDesc list;
+  uint32_t groups = 0;
+  if (wave == 0) {
     // at most 31 lists a stream whatever its header says
-    uint32_t before = 0, groups = 0;
+    uint32_t before = 0;
 #pragma unroll
     for (uint32_t i = 0; i < kTurns; ++i) {
       const uint32_t c = i * kWave + lane;
@@ -475,38 +495,57 @@ __global__ __launch_bounds__(kBlock, 8) void stream_table_kernel(StreamArgs<STRE
       before += c < client ? g : 0u;
       groups += c == client ? g : 0u;
     }
-    ListDesc list;
     const bool ok = parse_lists(in.args[client], d, in.count, quant, &list);
     before = wave_sum_u32(before);
     groups = wave_sum_u32(groups);
-    const uint32_t items = (list.P + kTabChunk - 1u) / kTabChunk, wsy = list.W | (list.s << 8) | (list.y << 16);
+    const uint32_t items = (list.P + kTabChunk - 1u) / kTabChunk;
     S.payload[lane] = (uint64_t)list.payload;
     S.P[lane] = list.P;
-    S.wsy[lane] = wsy;
+    S.wsy[lane] = list.W | (list.s << 8) | (list.y << 16);
     S.first[lane] = wave_incl_scan_u32(items) - items;  // lanes past the last list: the number of items
     if (lane == 0) {
       S.before = before;
       S.bad = ok ? 0u : 1u;
-      S.first_block = first_block;
-      S.blocks = (client + 1u < in.count ? in.first[client + 1u] : in.blocks) - first_block;
     }
-    if (blockIdx.x == first_block) {
-      if (lane < groups) {
-        CompactDesc c;
-        c.payload = list.payload; c.weight = list.weight; c.P = list.P; c.wsy = wsy;
-        c.m = list.m; c.step = list.step;
-        cdesc[before + lane] = c;
+  } else if (leads) {
+    constexpr uint32_t kStep = 2u * (kWavesPerBlock - 1u), kDeep = 4u;  // streams looked at together, half a wavefront each, and times over
+    uint32_t live = 0;
+    for (uint32_t base = 0; base < client; base += kDeep * kStep) {
+      bool names[kDeep];
+#pragma unroll
+      for (uint32_t u = 0; u < kDeep; ++u) {
+        const uint32_t c = base + u * kStep + (wave - 1u) * 2u + (lane >> 5);
+        names[u] = names_records(in.args[min(c, client)], lane & 31u) && c < client;  // no branch around the loads
       }
-      if (lane == 0 && client == in.count - 1u) {
-        ctl->n_active = before + groups;
-        *status = 0;  // what the workgroups find goes to a byte of each, which decode_tiles adds to it
-      }
+#pragma unroll
+      for (uint32_t u = 0; u < kDeep; ++u) live += (uint32_t)__popcll(__ballot(names[u]));
     }
+    if (lane == 0) S.live_before[wave] = live;
   }
   __syncthreads();
+  if (leads && wave == 0) {
+    uint32_t live = 0;
+    for (uint32_t w = 1; w < kWavesPerBlock; ++w) live += S.live_before[w];
+    const bool mine = names_records(in.args[client], min(lane, CVLC_MAX_CODED));
+    const uint64_t mask = __ballot(mine);
+    if (mine) {  // a refused stream's lists have no records
+      const uint32_t number = live + lanes_below(mask);
+      CompactDesc c;
+      c.payload = list.payload; c.weight = list.weight; c.P = list.P; c.wsy = S.wsy[lane];
+      c.m = list.m; c.step = list.step;
+      cdesc[number] = c;
+      row_of[number] = S.before + lane;
+    }
+    if (lane == 0 && client == in.count - 1u) {
+      live += (uint32_t)__popcll(mask);
+      ctl->n_active = live;
+      ctl->sparse = live != S.before + groups;
+      *status = 0;  // what the workgroups find goes to a byte of each, which decode_tiles adds to it
+    }
+  }
   const uint32_t first = S.first[lane], before = __builtin_amdgcn_readfirstlane(S.before);
   const uint32_t n_items = __builtin_amdgcn_readlane(first, kWave - 1u);
-  const uint32_t n_waves = __builtin_amdgcn_readfirstlane(S.blocks) * kWavesPerBlock, me = (blockIdx.x - __builtin_amdgcn_readfirstlane(S.first_block)) * kWavesPerBlock + wave;
+  const uint32_t n_waves = blocks * kWavesPerBlock, me = (blockIdx.x - first_block) * kWavesPerBlock + wave;
   bool bad = S.bad != 0u;
   // neighbouring items to a wavefront; few of them to the workgroups that start first
   uint32_t q = (uint32_t)((uint64_t)me * n_items / n_waves), q_end = (uint32_t)((uint64_t)(me + 1u) * n_items / n_waves);
@@ -582,7 +621,7 @@ __device__ __forceinline__ uint32_t wave_incl_scan_rows(uint32_t v) {
 // WIDE: positions of more than 25 bits, which with a raw 32-bit code may not lie in eight bytes from the one they start in.
 template <bool SIGNED, bool WIDE, uint32_t SHIFT>
 __global__ __launch_bounds__(kDecBlock, SHIFT == kDecShiftMin ? 6 : 4) void decode_tiles_kernel(const CompactDesc* __restrict__ cdesc,
-                                                              const DecodeCtl* __restrict__ ctl,
+                                                              const DecodeCtl* __restrict__ ctl, const uint32_t* __restrict__ row_of,
                                                               const uint32_t* __restrict__ table, float* out,
                                                               uint32_t d, uint32_t n_tiles, uint32_t s, uint32_t accumulate,
                                                               const uint8_t* __restrict__ found, uint32_t n_found,
@@ -591,7 +630,7 @@ __global__ __launch_bounds__(kDecBlock, SHIFT == kDecShiftMin ? 6 : 4) void deco
   __shared__ DecodeShared<SHIFT> S;
   const uint32_t tid = threadIdx.x, lane = lane_id();
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const uint32_t n_active = __builtin_amdgcn_readfirstlane(ctl->n_active);
+  const uint32_t n_active = __builtin_amdgcn_readfirstlane(ctl->n_active), sparse = __builtin_amdgcn_readfirstlane(ctl->sparse);
   // Sweeps over the lists, of equal length.  In a sweep the lists are dealt out to 1, 2, 4 or 8 groups of wavefronts so that no
   // lane gets two, and wavefronts of the same group share out the records.  One by one where one sweep takes them all (clients
   // differ in what they keep of a layer: four neighbouring lists at a time make a 4 us longer call of 32 streams of 11.2 M
@@ -614,10 +653,11 @@ __global__ __launch_bounds__(kDecBlock, SHIFT == kDecShiftMin ? 6 : 4) void deco
     dd[0] = src[0];
     dd[1] = src[1];
   };
-  auto request_rows = [&](uint32_t tile, uint32_t l0) {
+  auto row_of_mine = [&](uint32_t l0) { return sparse ? row_of[min(l0 + mine, n_active - 1u)] : l0 + mine; };  // uniform
+  auto request_rows = [&](uint32_t tile, uint32_t l0, uint32_t row) {
     uint2 r = make_uint2(0u, 0u);
     if (tile < n_tiles && mine < per_sweep && l0 + mine < n_active) {
-      const uint64_t two = load8((GlobalBytePtr)(table + (size_t)(l0 + mine) * (n_tiles + 1) + tile));
+      const uint64_t two = load8((GlobalBytePtr)(table + (size_t)row * (n_tiles + 1) + tile));
       r.x = (uint32_t)two;
       r.y = (uint32_t)(two >> 32);
     }
@@ -637,9 +677,12 @@ __global__ __launch_bounds__(kDecBlock, SHIFT == kDecShiftMin ? 6 : 4) void deco
   uint32_t round = 0, l0 = 0;
   uint2 next_rows = make_uint2(0u, 0u);
   uint4 next_desc[2] = {make_uint4(0u, 0u, 0u, 0u), make_uint4(0u, 0u, 0u, 0u)};
+  uint32_t next_row = 0;  // of the list whose table entries are asked for next
   if (n_active) {
-    next_rows = request_rows(tile_of(0), 0);
+    next_row = row_of_mine(0);
+    next_rows = request_rows(tile_of(0), 0, next_row);
     request_desc(0, next_desc);
+    if (n_sweeps > 1u) next_row = row_of_mine(per_sweep);
   }
   for (uint32_t i = tid; i < kTile; i += kDecBlock) S.acc[i] = 0.0;
   SliceInfo* slices = S.slice[wave];
@@ -654,7 +697,8 @@ __global__ __launch_bounds__(kDecBlock, SHIFT == kDecShiftMin ? 6 : 4) void deco
       const uint2 rows = next_rows;
       const uint4 d0 = next_desc[0], d1 = next_desc[1];
       if (n_sweeps > 1u) request_desc(next_l0, next_desc);
-      next_rows = request_rows(next_tile, next_l0);
+      next_rows = request_rows(next_tile, next_l0, next_row);
+      if (n_sweeps > 1u) next_row = row_of_mine(next_l0 + per_sweep >= n_active ? 0u : next_l0 + per_sweep);
       // this lane's list: its slice [begin, end) from two neighbouring table entries (none: both are 0)
       const uint32_t P = d1.x, W = d1.y & 0xFFu;
       const uint32_t begin = min(rows.x, P), end = min(rows.y, P);  // table entries of a malformed list may hold anything
@@ -917,7 +961,7 @@ int cvlc_decode_aggregate(uint32_t n, const void* const* d_streams, const size_t
         n_found += (uint32_t)std::min(1u + most * stream_bytes[i] / all, (items + kWavesPerBlock - 1u) / kWavesPerBlock);
       }
       in.blocks = n_found;
-      hipLaunchKernelGGL(kernel, dim3(n_found), dim3(kBlock), 0, stream, in, quant, cdesc, ctl, table, d, shift, n_tiles, found, status);
+      hipLaunchKernelGGL(kernel, dim3(n_found), dim3(kBlock), 0, stream, in, quant, cdesc, ctl, item_start, table, d, shift, n_tiles, found, status);
     };
     static_assert(kTableBlocks < (1u << 16), "the workgroups are numbered in 16 bits");
     if (n <= kFewStreams) {
@@ -958,7 +1002,7 @@ int cvlc_decode_aggregate(uint32_t n, const void* const* d_streams, const size_t
     auto kernel = wide    ? (qsgd ? decode_tiles_kernel<true, true, kDecShiftMax> : decode_tiles_kernel<false, true, kDecShiftMax>)
                   : large ? (qsgd ? decode_tiles_kernel<true, false, kDecShiftMax> : decode_tiles_kernel<false, false, kDecShiftMax>)
                           : (qsgd ? decode_tiles_kernel<true, false, kDecShiftMin> : decode_tiles_kernel<false, false, kDecShiftMin>);
-    hipLaunchKernelGGL(kernel, dim3(g), dim3(kDecBlock), 0, stream, cdesc, ctl, table, d_out, d, n_tiles, position_bits(d),
+    hipLaunchKernelGGL(kernel, dim3(g), dim3(kDecBlock), 0, stream, cdesc, ctl, item_start, table, d_out, d, n_tiles, position_bits(d),
                        flags & CVLC_DECODE_ACCUMULATE, found, n_found, status);
   }
   return hip_check(hipGetLastError());

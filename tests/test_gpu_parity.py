@@ -645,6 +645,33 @@ def test_decode_of_streams_of_unequal_lengths(n):
     check_decode([refs[c] for c in order], d, weights=np.random.default_rng(n).uniform(-1.0, 1.0, n).astype(np.float32).tolist())
 
 
+@pytest.mark.parametrize("n,R,filled", [(1, 31, 1), (3, 31, 0), (8, 31, 2), (9, 31, 30), (70, 7, 6), (100, 31, 8), (112, 31, 1), (112, 31, 20)])
+def test_decode_of_streams_of_many_empty_groups(n, R, filled):
+    """Lists with records are numbered, and swept over, without the empty ones (one to six sweeps here); a stream whose header is
+    wrong, first, last or in the middle, is left out and reported."""
+    rng = np.random.default_rng(n * 40 + filled)
+    d = 9001
+    refs = []
+    for c in range(n):
+        counts = np.zeros(R, dtype=int)
+        counts[rng.permutation(R)[:filled]] = rng.integers(1, d // (4 * R), filled)
+        ys = sorted((int(v) for v in rng.integers(2, 17, R)), reverse=True)
+        refs.append(orc.encode(rng.standard_t(3, d).astype(np.float32), orc.plan_manual(d, ys, counts.tolist()), 5, c).words)
+    weights = rng.uniform(0.5, 1.5, n).astype(np.float32).tolist()
+    check_decode(refs, d, weights=weights)
+    for wrong in sorted({0, n // 2, n - 1}):
+        bad = refs[wrong].copy()
+        bad[2] += 1
+        dev = [torch.from_numpy((bad if c == wrong else w).view(np.int32)).to(DEV) for c, w in enumerate(refs)]
+        got, status = gpu_decode(dev, d, weights=weights)
+        assert status == cv.DEV_STREAM
+        rest = [c for c in range(n) if c != wrong]
+        left = [refs[c] for c in rest], d, [weights[c] for c in rest]
+        expected = orc.decode_aggregate(left[0], d, weights=left[2]).astype(np.float64) if rest else np.zeros(d)
+        tol = 1e-5 * abs_terms(*left) if rest else 0.0
+        assert np.all(np.abs(got - expected) <= tol)
+
+
 @pytest.mark.parametrize("d", [(1 << 23) - 1, 1 << 23, (1 << 23) + 4097])
 def test_decode_on_both_sides_of_the_large_tiles(d):
     rng = np.random.default_rng(d)
