@@ -180,26 +180,24 @@ __device__ __forceinline__ bool parse_lists(const StreamArg& sa, uint32_t d, uin
   return ok;
 }
 
-__device__ __forceinline__ void parse_stream(const StreamArg& sa, uint32_t client, ListDesc* descs, uint32_t d, uint32_t n,
-                                             uint32_t* __restrict__ stream_bad, uint32_t quant) {
-  const uint32_t t = lane_id();
-  ListDesc list;
-  const bool ok = parse_lists(sa, d, n, quant, &list);
-  if (t == 0) stream_bad[client] = ok ? 0u : 1u;  // gathered into the status word by the next kernel
-  if (t < kListsPerClient) descs[(size_t)client * kListsPerClient + t] = list;
-}
-
 __global__ __launch_bounds__(64) void parse_headers_kernel(ParseChunk chunk, ListDesc* descs, uint32_t d, uint32_t n,
                                                            uint32_t* __restrict__ stream_bad, uint32_t quant) {
-  parse_stream(chunk.args[blockIdx.x], chunk.first + blockIdx.x, descs, d, n, stream_bad, quant);
+  const uint32_t t = lane_id(), client = chunk.first + blockIdx.x;
+  ListDesc list;
+  const bool ok = parse_lists(chunk.args[blockIdx.x], d, n, quant, &list);
+  if (t == 0) stream_bad[client] = ok ? 0u : 1u;  // gathered into the status word by the next kernel
+  if (t < kListsPerClient) descs[(size_t)client * kListsPerClient + t] = list;
 }
 
 // ------------------------------------------------------------------ 1b. the non-empty lists
 // One workgroup of 1024 threads.  Lists with records are numbered in (client,
 // group) order; item_start is the exclusive prefix of their tile_table work items.
-__device__ __forceinline__ void compact_lists(const ListDesc* descs, uint32_t n_lists, CompactDesc* __restrict__ cdesc,
-                                              uint32_t* __restrict__ item_start, DecodeCtl* ctl,
-                                              const uint32_t* stream_bad, uint32_t n, uint32_t* status, uint32_t* scan_tmp) {
+__global__ __launch_bounds__(1024) void compact_lists_kernel(const ListDesc* __restrict__ descs, uint32_t n_lists,
+                                                             CompactDesc* __restrict__ cdesc,
+                                                             uint32_t* __restrict__ item_start, DecodeCtl* ctl,
+                                                             const uint32_t* __restrict__ stream_bad, uint32_t n,
+                                                             uint32_t* status) {
+  __shared__ uint32_t scan_tmp[16];
   const uint32_t tid = threadIdx.x;
   // the call's status word starts here: set if any stream failed its header checks
   uint32_t any_bad = 0;
@@ -235,15 +233,6 @@ __device__ __forceinline__ void compact_lists(const ListDesc* descs, uint32_t n_
   }
 }
 
-__global__ __launch_bounds__(1024) void compact_lists_kernel(const ListDesc* __restrict__ descs, uint32_t n_lists,
-                                                             CompactDesc* __restrict__ cdesc,
-                                                             uint32_t* __restrict__ item_start, DecodeCtl* ctl,
-                                                             const uint32_t* __restrict__ stream_bad, uint32_t n,
-                                                             uint32_t* status) {
-  __shared__ uint32_t scan_tmp[16];
-  compact_lists(descs, n_lists, cdesc, item_start, ctl, stream_bad, n, status, scan_tmp);
-}
-
 // ------------------------------------------------------------------ 2. tile table
 // table[list][t] = index of the first record of `list` whose position lies in
 // output tile t or later; entry n_tiles holds the list length.  (List-major: a
@@ -269,28 +258,20 @@ __device__ __forceinline__ uint64_t load8(GlobalBytePtr p) { return ((const Byte
 struct ItemOwner {
   uint32_t list, first_item, next_list;
 };
-// Whole wavefront, 64 probes a round: one round for up to 64 lists, two for up to 4096.  lead: in a call of up to
-// kLeadLists lists lane l holds item_start[l], asked for before the number of non-empty lists is known (beyond that the
-// load is in the way of 8192 wavefronts).  The last round's lanes hold the two starts: a load that waits for
-// the one before is half a microsecond at the head of a small call's kernel.  (A binary search by every lane costs log2 rounds, in
-// LDS a copy of item_start per workgroup first: beyond 2048 lists, where the copy did not fit, it was twelve dependent
-// loads per item and two thirds of the kernel.)
-constexpr uint32_t kLeadLists = 512;
-__device__ __forceinline__ ItemOwner owner_of(const uint32_t* __restrict__ item_start, uint32_t lead, uint32_t n_lists,
-                                              uint32_t n_active, uint32_t n_items, uint32_t q) {
+// Whole wavefront, 64 probes a round: one round for up to 64 lists, two for up to 4096.  The last round's lanes hold the two starts.
+// (A binary search by every lane costs log2 rounds: beyond 2048 lists it was twelve dependent loads per item and two thirds
+// of the kernel.)
+__device__ __forceinline__ ItemOwner owner_of(const uint32_t* __restrict__ item_start, uint32_t n_active, uint32_t q) {
   const uint32_t lane = lane_id();
   uint32_t a = 0, len = n_active;  // the owner is one of a .. a + len - 1
-  uint32_t start = lane < n_active ? lead : n_items;
-  if (n_lists > kLeadLists || len > kWave) {  // uniform
-    while (len > kWave) {
-      const uint32_t step = (len + kWave - 1u) / kWave;
-      const bool hit = lane * step < len && item_start[min(a + lane * step, n_active)] <= q;
-      const uint32_t last = (uint32_t)__popcll(__ballot(hit)) - 1u;  // item_start ascends and its first entry is 0: the hits are a prefix
-      a += last * step;
-      len = min(step, len - last * step);
-    }
-    start = item_start[min(a + lane, n_active)];
+  while (len > kWave) {  // uniform
+    const uint32_t step = (len + kWave - 1u) / kWave;
+    const bool hit = lane * step < len && item_start[min(a + lane * step, n_active)] <= q;
+    const uint32_t last = (uint32_t)__popcll(__ballot(hit)) - 1u;  // item_start ascends and its first entry is 0: the hits are a prefix
+    a += last * step;
+    len = min(step, len - last * step);
   }
+  const uint32_t start = item_start[min(a + lane, n_active)];
   const uint32_t last = (uint32_t)__popcll(__ballot(lane < len && start <= q)) - 1u;
   ItemOwner o;
   o.list = __builtin_amdgcn_readfirstlane(a + last);
@@ -397,22 +378,20 @@ template <bool WIDE>
 __global__ __launch_bounds__(kBlock, 8) void tile_table_kernel(const CompactDesc* __restrict__ cdesc,
                                                          const uint32_t* __restrict__ item_start,
                                                          const DecodeCtl* __restrict__ ctl, uint32_t* table,
-                                                         uint32_t d, uint32_t tile_shift, uint32_t n_tiles, uint32_t n_lists, uint32_t* status) {
-  const uint32_t tid = threadIdx.x, lane = lane_id();
-  const uint32_t lead = n_lists <= kLeadLists ? item_start[min(lane, n_lists)] : 0u;  // the array has room for n_lists + 1
+                                                         uint32_t d, uint32_t tile_shift, uint32_t n_tiles, uint32_t* status) {
+  const uint32_t tid = threadIdx.x;
   const uint32_t n_active = ctl->n_active, n_items = ctl->n_items;
   // A wavefront takes neighbouring items, so that it looks for the owner of the first one only and then walks on.
   constexpr uint64_t n_waves = kTableBlocks * kWavesPerBlock;
   const uint64_t me = blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(tid / kWave);
-  // Few items go to the first workgroups, which start a microsecond before the last ones (one stream of 2000 coordinates:
-  // 2.1 us; 3.9 with its three items in the middle and at the end of the launch and two loads more in a chain).
+  // Few items go to the first workgroups, which start a microsecond before the last ones.
   uint32_t q_begin = (uint32_t)(me * n_items / n_waves), q_end = (uint32_t)((me + 1u) * n_items / n_waves);
   if (n_items <= n_waves) {
     q_begin = min((uint32_t)me, n_items);
     q_end = min((uint32_t)me + 1u, n_items);
   }
   if (q_begin >= q_end) return;  // uniform
-  const ItemOwner owner = owner_of(item_start, lead, n_lists, n_active, n_items, q_begin);
+  const ItemOwner owner = owner_of(item_start, n_active, q_begin);
   uint32_t a = owner.list, first_item = owner.first_item, next_list = owner.next_list;  // uniform
   bool bad = false;
   for (uint32_t q = q_begin; q < q_end; ++q) {  // uniform per wavefront
@@ -991,7 +970,7 @@ int cvlc_decode_aggregate(uint32_t n, const void* const* d_streams, const size_t
       // the number of work items is only known on the device
       auto kernel = wide ? tile_table_kernel<true> : tile_table_kernel<false>;
       hipLaunchKernelGGL(kernel, dim3(kTableBlocks), dim3(kBlock), 0, stream, cdesc, item_start, ctl, table, d, shift, n_tiles,
-                         n_lists, status);
+                         status);
     }
   }
   {

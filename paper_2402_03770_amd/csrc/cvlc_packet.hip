@@ -16,6 +16,8 @@
 // of mtu bytes.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "cvlc_common.h"
 
 namespace cvlc {
@@ -23,10 +25,26 @@ namespace {
 
 constexpr uint32_t kPktMagic = 0x504C5643u;  // "CVLP"
 constexpr uint32_t kPktHeaderWords = CVLC_PACKET_HEADER_WORDS;
-// One workgroup per packet.  A wavefront each was too little: 973 packets are one wavefront for every SIMD, which went through a
-// packet's words in six round trips.
-constexpr uint32_t kPktBlock = 256;
-constexpr uint32_t kPktDeep = 2;             // words of a thread that are asked for together: 1500-byte packets take one turn
+// The kernels that move records have a workgroup per packet, of THREADS threads that ask for DEEP words each together.  How many:
+//   up to 128 words a packet    a wavefront, two words a lane: 25.6 M coordinates all kept, 241 757 packets of 512 bytes, packetize 65 us
+//                               (four wavefronts 196), 5.1 M of 64 bytes 1203 us (4133); depacketize 1527 (1540) and 19 911 (21 515)
+//   up to 384 words, where four wavefronts a packet are more than the device holds
+//                               a wavefront, six words a lane: 8486 packets of 1500 bytes 7.3 us (10.5), 77 951 39 (72)
+//   else                        four wavefronts, two words a lane: 973 packets of 1500 bytes are one wavefront for every SIMD, and one that
+//                               goes through them by itself takes 7.1 us for 4.0; 3040 packets of 9000 bytes 13 us (six words a lane of one
+//                               wavefront 13, two 17), 206 of 65 532 19 (38, 56)
+// A grid has less than 2^32 threads (one of more is cut off without an error): more than 2^23 packets take several launches.
+template <typename Launch>
+void by_packet_shape(uint32_t n, uint32_t words, Launch launch) {
+  using One = std::integral_constant<uint32_t, 64>;
+  constexpr uint32_t kMost = 1u << 23;
+  for (uint32_t first = 0, count; first < n; first += count) {
+    count = n - first < kMost ? n - first : kMost;
+    if (words <= 128u) launch(first, count, One(), std::integral_constant<uint32_t, 2>());
+    else if (words <= 384u && n > 2048u) launch(first, count, One(), std::integral_constant<uint32_t, 6>());
+    else launch(first, count, std::integral_constant<uint32_t, 256>(), std::integral_constant<uint32_t, 2>());
+  }
+}
 
 typedef const uint32_t __attribute__((address_space(1))) * GlobalConstWordPtr;
 typedef uint32_t __attribute__((address_space(1))) * GlobalWordPtr;
@@ -53,16 +71,17 @@ struct PacketPlan {  // what the sender's kernel needs from the plan
 // down to bit 0 of the packet's payload; the rest of the packet's slot is zeroed.
 // All latency: a lane per group finds the packet's (every lane in a loop over the groups, with two divisions each), and all loads
 // are out before the first is waited for (the header's six one after the other, the words 64 at a time): 973 packets 7.1 -> 4.0 us.
-__global__ __launch_bounds__(kPktBlock) void packetize_kernel(PacketPlan plan, const uint32_t* __restrict__ stream,
-                                                              uint32_t* __restrict__ packets) {
-  const uint32_t mtu = plan.mtu_words * 4u;
+template <uint32_t THREADS, uint32_t DEEP>
+__global__ __launch_bounds__(THREADS) void packetize_kernel(PacketPlan plan, uint32_t first_packet, const uint32_t* __restrict__ stream,
+                                                            uint32_t* __restrict__ packets) {
+  const uint32_t mtu = plan.mtu_words * 4u, packet = first_packet + blockIdx.x;
   const uint32_t lane = lane_id(), tid = threadIdx.x;
   if (plan.R == 0) return;  // the grid has exactly one workgroup per packet; never taken
-  const uint64_t from = __ballot(lane < plan.R && plan.first[min(lane, CVLC_MAX_CODED - 1u)] <= blockIdx.x);  // a group has a packet at least: a prefix
+  const uint64_t from = __ballot(lane < plan.R && plan.first[min(lane, CVLC_MAX_CODED - 1u)] <= packet);  // a group has a packet at least: a prefix
   const uint32_t r = (uint32_t)__popcll(from) - 1u;
-  const uint32_t P = plan.P[r], y = plan.y[r], W = plan.s + y, cap = packet_cap(mtu, W), e0 = (blockIdx.x - plan.first[r]) * cap;
+  const uint32_t P = plan.P[r], y = plan.y[r], W = plan.s + y, cap = packet_cap(mtu, W), e0 = (packet - plan.first[r]) * cap;
   const uint32_t c = P - e0 < cap ? P - e0 : cap;
-  GlobalWordPtr out = (GlobalWordPtr)(packets + (size_t)blockIdx.x * plan.mtu_words);
+  GlobalWordPtr out = (GlobalWordPtr)(packets + (size_t)packet * plan.mtu_words);
   // word `tid` of the header, where the stream has it
   const uint32_t at = tid == 1u || tid == 2u ? tid : tid == 3u ? 6u : tid == 4u ? 5u : kGlobalHeaderWords + kSegHeaderWords * r + (tid == 8u ? 2u : 3u);
   uint32_t field = ((GlobalConstWordPtr)stream)[at];
@@ -72,19 +91,19 @@ __global__ __launch_bounds__(kPktBlock) void packetize_kernel(PacketPlan plan, c
   const uint32_t w0 = (uint32_t)(bit0 >> 5), sh = (uint32_t)(bit0 & 31u);
   const uint32_t nbits = c * W, n_out = (nbits + 31u) >> 5, n_words = plan.mtu_words - kPktHeaderWords;
   GlobalConstWordPtr src = (GlobalConstWordPtr)(stream + plan.payload[r]);
-  for (uint32_t base = 0; base < n_words; base += kPktDeep * kPktBlock) {
-    uint32_t a[kPktDeep], b[kPktDeep];
+  for (uint32_t base = 0; base < n_words; base += DEEP * THREADS) {
+    uint32_t a[DEEP], b[DEEP];
     if (n_out) {  // uniform; an empty group has no words
 #pragma unroll
-      for (uint32_t u = 0; u < kPktDeep; ++u) {
-        const uint32_t w = w0 + base + u * kPktBlock + tid;
+      for (uint32_t u = 0; u < DEEP; ++u) {
+        const uint32_t w = w0 + base + u * THREADS + tid;
         a[u] = src[min(w, group_words - 1u)];
         b[u] = src[min(w + 1u, group_words - 1u)];
       }
     }
 #pragma unroll
-    for (uint32_t u = 0; u < kPktDeep; ++u) {
-      const uint32_t i = base + u * kPktBlock + tid;
+    for (uint32_t u = 0; u < DEEP; ++u) {
+      const uint32_t i = base + u * THREADS + tid;
       uint32_t v = 0;
       if (i < n_out) {
         v = sh ? (a[u] >> sh) | ((w0 + i + 1u < group_words ? b[u] : 0u) << (32u - sh)) : a[u];
@@ -105,8 +124,7 @@ __global__ __launch_bounds__(kPktBlock) void packetize_kernel(PacketPlan plan, c
 // ------------------------------------------------------------------ receiver
 struct ReassemblyState {  // at the start of the workspace, after the status word's 256 bytes
   uint32_t valid;         // 1: the second kernel may copy
-  uint32_t R, s, pad;
-  uint32_t y[32], P[32], payload[32], first_packet[32];
+  uint32_t payload[32];   // every group's first stream word
 };
 
 constexpr uint32_t kGatherBlock = 1024;
@@ -244,15 +262,9 @@ __global__ __launch_bounds__(kGatherBlock) void reassemble_headers_kernel(const 
     }
   }
   __syncthreads();
-  if (tid < 32) {
-    st->y[tid] = tid < R ? g_y[tid] : 0;
-    st->P[tid] = tid < R ? g_P[tid] : 0;
-    st->payload[tid] = tid < R ? g_payload[tid] : 0;
-    st->first_packet[tid] = tid < R ? g_first[tid] : 0;
-  }
+  if (tid < 32) st->payload[tid] = tid < R ? g_payload[tid] : 0;
   if (tid == 0) {
     st->valid = s_bad ? 0u : 1u;
-    st->R = R; st->s = s; st->pad = 0;
     *status = s_bad ? CVLC_DEV_STREAM : 0u;
     if (s_bad) stream[0] = 0;  // what is there is not a stream
   }
@@ -263,17 +275,18 @@ __global__ __launch_bounds__(kGatherBlock) void reassemble_headers_kernel(const 
 // and the last are OR-ed into the words the header kernel cleared.
 // The packet's own header says all but where the group's payload begins (the header kernel has found them alike), so that
 // the packet's words are asked for with it: 973 packets 5.3 -> 4.9 us.
-__global__ __launch_bounds__(kPktBlock) void reassemble_payload_kernel(const uint32_t* __restrict__ packets,
+template <uint32_t THREADS, uint32_t DEEP>
+__global__ __launch_bounds__(THREADS) void reassemble_payload_kernel(const uint32_t* __restrict__ packets, uint32_t first_packet,
                                                                        uint32_t mtu_words,
                                                                        const ReassemblyState* __restrict__ st,
                                                                        uint32_t* __restrict__ stream) {
-  GlobalConstWordPtr pk = (GlobalConstWordPtr)(packets + (size_t)blockIdx.x * mtu_words), src = pk + kPktHeaderWords;
+  GlobalConstWordPtr pk = (GlobalConstWordPtr)(packets + (size_t)(first_packet + blockIdx.x) * mtu_words), src = pk + kPktHeaderWords;
   const uint32_t n_src = mtu_words - kPktHeaderWords, tid = threadIdx.x;
-  uint32_t hi[kPktDeep], lo[kPktDeep];
+  uint32_t hi[DEEP], lo[DEEP];
   auto ask = [&](uint32_t base) {
 #pragma unroll
-    for (uint32_t u = 0; u < kPktDeep; ++u) {
-      const uint32_t i = base + u * kPktBlock + tid;
+    for (uint32_t u = 0; u < DEEP; ++u) {
+      const uint32_t i = base + u * THREADS + tid;
       hi[u] = src[min(i, n_src - 1u)];
       lo[u] = src[min(max(i, 1u) - 1u, n_src - 1u)];
     }
@@ -291,11 +304,11 @@ __global__ __launch_bounds__(kPktBlock) void reassemble_payload_kernel(const uin
   GlobalWordPtr dst = (GlobalWordPtr)(stream + payload + w0);
   // word k of the packet's records, the bits beyond the last one cleared
   auto word = [&](uint32_t k, uint32_t v) { return k < full ? v : (k == full ? v & part : 0u); };
-  for (uint32_t base = 0; base <= last; base += kPktDeep * kPktBlock) {
+  for (uint32_t base = 0; base <= last; base += DEEP * THREADS) {
     if (base) ask(base);
 #pragma unroll
-    for (uint32_t u = 0; u < kPktDeep; ++u) {
-      const uint32_t i = base + u * kPktBlock + tid;
+    for (uint32_t u = 0; u < DEEP; ++u) {
+      const uint32_t i = base + u * THREADS + tid;
       if (i > last) continue;
       const uint32_t below = i ? word(i - 1u, lo[u]) : 0u;
       const uint32_t v = sh ? (word(i, hi[u]) << sh) | (below >> (32u - sh)) : word(i, hi[u]);
@@ -376,8 +389,10 @@ int cvlc_packetize(const cvlc_plan_t* plan, const void* d_stream, uint32_t mtu_b
       payload += (uint32_t)payload_words(pp.P[r], pp.s + pp.y[r]);
     }
   }
-  hipLaunchKernelGGL(packetize_kernel, dim3((uint32_t)n), dim3(kPktBlock), 0, static_cast<hipStream_t>(hip_stream), pp,
-                     static_cast<const uint32_t*>(d_stream), static_cast<uint32_t*>(d_packets_out));
+  by_packet_shape((uint32_t)n, pp.mtu_words - kPktHeaderWords, [&](uint32_t from, uint32_t count, auto threads, auto deep) {
+    hipLaunchKernelGGL((packetize_kernel<threads.value, deep.value>), dim3(count), dim3(threads.value), 0,
+                       static_cast<hipStream_t>(hip_stream), pp, from, static_cast<const uint32_t*>(d_stream), static_cast<uint32_t*>(d_packets_out));
+  });
   return hip_check(hipGetLastError());
 }
 
@@ -403,8 +418,10 @@ int cvlc_depacketize(const void* d_packets, uint32_t n_packets, uint32_t mtu_byt
   hipLaunchKernelGGL(reassemble_headers_kernel, dim3(1), dim3(kGatherBlock), 0, stream,
                      static_cast<const uint32_t*>(d_packets), n_packets, mtu_bytes / 4u, d,
                      static_cast<uint32_t*>(d_stream_out), (uint64_t)(capacity / 4u), status, st, seen);
-  hipLaunchKernelGGL(reassemble_payload_kernel, dim3(n_packets), dim3(kPktBlock), 0, stream,
-                     static_cast<const uint32_t*>(d_packets), mtu_bytes / 4u, st, static_cast<uint32_t*>(d_stream_out));
+  by_packet_shape(n_packets, mtu_bytes / 4u - kPktHeaderWords, [&](uint32_t from, uint32_t count, auto threads, auto deep) {
+    hipLaunchKernelGGL((reassemble_payload_kernel<threads.value, deep.value>), dim3(count), dim3(threads.value), 0, stream,
+                       static_cast<const uint32_t*>(d_packets), from, mtu_bytes / 4u, st, static_cast<uint32_t*>(d_stream_out));
+  });
   return hip_check(hipGetLastError());
 }
 

@@ -594,15 +594,18 @@ def test_a_class_of_equal_keys_is_cut_in_few_passes():
     assert t[1] < 40 * t[0], t
 
 
-@pytest.mark.parametrize("n,R", [(1, 1), (9, 7), (16, 4), (13, 5), (16, 31), (17, 3), (17, 4), (25, 31), (133, 31)])
-def test_decode_at_the_steps_of_the_list_search(n, R):
-    """The search for an item's list takes 64 lists a round, the first round's starts asked for ahead in calls of up to 16
-    streams: 1, 63, 64, 65, 496, 51, 68, 775 and 4123 lists; one launch for the headers up to 24 streams, two beyond."""
+@pytest.mark.parametrize("n,lists", [(113, 0), (113, 1), (113, 63), (113, 64), (113, 65), (113, 68), (113, 496), (113, 3503), (133, 4096), (133, 4097),
+                                     (133, 4123)])
+def test_decode_at_the_steps_of_the_list_search(n, lists):
+    """The search for an item's list, in calls of more streams than one launch parses and numbers, takes 64 lists a round: up to
+    64, up to 4096 and more of the streams' 31 groups each have records, a few of them several items."""
     d = 6000
-    rng = np.random.default_rng(n)
-    host = [(rng.standard_normal(d) * 1e-3).astype(np.float32) for _ in range(min(n, 8))]
-    p = orc.plan_manual(d, [8] * R, [600 if r == R // 2 and R < 8 else 20 for r in range(R)])
-    refs = [orc.encode(host[c % 8], p, 3, c).words for c in range(n)]
+    rng = np.random.default_rng(lists)
+    host = [(rng.standard_normal(d) * 1e-3).astype(np.float32) for _ in range(8)]
+    filled = np.zeros(n * 31, dtype=int)
+    filled[rng.permutation(n * 31)[:lists]] = 20
+    filled[np.flatnonzero(filled)[::29]] = 1100
+    refs = [orc.encode(host[c % 8], orc.plan_manual(d, [8] * 31, filled[c * 31: c * 31 + 31].tolist()), 3, c).words for c in range(n)]
     check_decode(refs, d, weights=rng.uniform(0.5, 1.5, n).tolist())
 
 
@@ -629,7 +632,6 @@ def test_decode_at_the_steps_of_the_lists_share(n, R, quant):
     assert np.all(np.abs(got - ref) <= 2.0 ** -23 * np.abs(ref) + 1e-12 * abs_terms(refs, d))
 
 
-# Tiles of 4096 coordinates below 2^23, of 8192 from there on.
 @pytest.mark.parametrize("n", [8, 9, 64, 65, 112, 113])
 def test_decode_of_streams_of_unequal_lengths(n):
     """Few and many streams' arguments, the last number that one launch parses and the first that it does not; the workgroups
@@ -672,6 +674,7 @@ def test_decode_of_streams_of_many_empty_groups(n, R, filled):
         assert np.all(np.abs(got - expected) <= tol)
 
 
+# Tiles of 4096 coordinates below 2^23, of 8192 from there on.
 @pytest.mark.parametrize("d", [(1 << 23) - 1, 1 << 23, (1 << 23) + 4097])
 def test_decode_on_both_sides_of_the_large_tiles(d):
     rng = np.random.default_rng(d)
@@ -1419,6 +1422,44 @@ def test_packets_at_the_benchmark_size():
     assert np.array_equal(buf.cpu().numpy().view(np.uint32).reshape(n, 375), ref_pk)
     out, status = gpu_depacketize(buf.view(n, 375).flip(0).contiguous(), n, d, 1500, words[0].size)
     assert status == 0 and np.array_equal(out.cpu().numpy().view(np.uint32), words[0])
+
+
+@pytest.mark.parametrize("mtu,packets", [(552, 300), (556, 300), (1576, 2047), (1576, 2049), (1580, 2049)])
+def test_packets_at_the_steps_of_their_kernels(mtu, packets):
+    """A packet is moved by one wavefront up to 128 words behind its header, up to 384 where there are more than 2048 of them, and
+    by four else."""
+    s = 21
+    d = (1 << s) - 3
+    cap = (8 * mtu - 320) // (s + 9)
+    po = orc.plan_manual(d, [9, 9, 9], [cap * (packets - 7) - 1, 2 * cap, 4 * cap + 1])
+    words, _, status, streams = gpu_encode([syn.update_vector(2, 3, d=d)], [po], 4, [2], want_stats=False)
+    assert status == 0
+    pl = to_lib_plan(po)
+    buf, n = gpu_packetize(pl, streams[0], mtu)
+    ref, _ = orc.packetize(words[0], d, mtu)
+    assert n == packets and np.array_equal(buf.cpu().numpy().view(np.uint32)[: ref.size], ref.ravel())
+    out, status = gpu_depacketize(buf.view(-1, mtu // 4)[:n].flip(0).contiguous(), n, d, mtu, words[0].size)
+    assert status == 0
+    assert np.array_equal(out.cpu().numpy().view(np.uint32)[: words[0].size], words[0])
+
+
+@pytest.mark.parametrize("bits", [23, 24, 26])
+def test_more_packets_than_a_grid_holds_threads_for(bits):
+    """A grid has less than 2^32 threads, and the launch of one of more starts the rest of that division without an error: four
+    wavefronts to 2^24 packets left all but five of them out, one to 2^26 too.  The stream's records are any bits: neither
+    side looks at them."""
+    d, mtu, n = (1 << 30) + 1, 64, (1 << bits) + 5
+    plan = cv.plan_manual(d, [13], [4 * n - 1])                # 44 bits a record, four to a packet
+    assert cv.packet_count(plan, mtu) == n
+    stream = torch.randint(-2 ** 31, 2 ** 31 - 1, (plan.stream_bytes // 4,), dtype=torch.int32, device=DEV)
+    header = [0x434C5643, 1, d, 1, 31, np.float32(1.0).view(np.uint32), 7, plan.stream_bytes // 4, 13, 4 * n - 1, 0, 0]
+    stream[:12] = torch.from_numpy(np.array(header, dtype=np.uint32).view(np.int32)).to(DEV)
+    stream[-1] &= (1 << ((4 * n - 1) * 44 % 32)) - 1           # the bits behind the last record are zero
+    packets, count = gpu_packetize(plan, stream, mtu)
+    assert count == n
+    out, status = gpu_depacketize(packets, n, d, mtu, stream.numel())
+    assert status == 0
+    assert torch.equal(out[: stream.numel()], stream)
 
 
 @pytest.mark.parametrize("k,mtu", [(6 * 1024, 64), (6 * 1024 + 1, 64), (40_000, 64), (1_700_000, 64)])
