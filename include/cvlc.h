@@ -326,7 +326,8 @@ int cvlc_device_status(const void* d_workspace, void* hip_stream, uint32_t* stat
  * of brackets; both arrays hold CVLC_PROFILE_STAGES entries.  A stage that a
  * call does not have gets no bracket: vectors of up to 65 536 coordinates are
  * encoded without SAMPLE, FILTER and REFILTER, and as a rule without
- * SETUP; only batches of many clients that keep much have LAYOUT; up to 112 streams are decoded without SETUP.  Not thread
+ * SETUP; only batches that keep much have LAYOUT; up to 112 streams are
+ * decoded without SETUP.  Not thread
  * safe. */
 enum {
   CVLC_STAGE_ENC_SETUP = 0,    /* clear scratch, upload per-client parameters; short vectors: */

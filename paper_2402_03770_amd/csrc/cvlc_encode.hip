@@ -1536,7 +1536,7 @@ __device__ __forceinline__ uint32_t short_param(const ParamsUploaded& u, uint32_
 // workgroup, after locate_short; leaves S.top and S.upto as they were.
 static_assert(kSampleShift == kTopShift + 1u && kShortMax <= kSampleChunksMax * kSamplePiece, "two bins to a sample bin, all pieces sampled");
 __device__ __forceinline__ uint32_t short_missing(uint32_t d) { return d % kSamplePiece; }
-__device__ __forceinline__ bool short_of_room(ShortSelect& S, const float* update, uint32_t d, uint32_t room, uint32_t rank) {
+__device__ __forceinline__ bool short_of_room(EncodeSelect& S, const float* update, uint32_t d, uint32_t room, uint32_t rank) {
   if (rank == 0u) return true;  // no threshold: all d are candidates
   const uint32_t missing = short_missing(d);
   const uint32_t upto = S.extra - S.extra_rem + S.top[S.extra_bin] + ((S.extra_bin & 1u) ? S.top[S.extra_bin - 1u] : 0u);
@@ -1572,7 +1572,7 @@ static_assert(sizeof(UploadChunk) + sizeof(Workspace) + 4u * sizeof(void*) <= 40
 template <class Params>
 __global__ __launch_bounds__(kShortBlock) void short_select_kernel(Params source, ClientParams* params, ClientCtl* ctls, Workspace ws,
                                                                    cvlc_seg_stats_t* stats_out, uint32_t first_launch) {
-  __shared__ ShortSelect S;
+  __shared__ EncodeSelect S;
   __shared__ uint32_t s_params[kParamWords];
   const uint32_t client = short_client(source), tid = threadIdx.x;
   const uint32_t d = ws.d;

@@ -895,13 +895,12 @@ __global__ __launch_bounds__(kRankBlock) void rank_stream_kernel(const float* co
 // ------------------------------------------------------------------ short vectors: one launch
 // A workgroup per client finds the keys at all ranks together (cvlc_select.h) and fits.  The pointers come as kernel arguments.
 // The status word is written by the one workgroup of a single client; several add to what a launch before has cleared.
-// us in six launches and in one or two: 1 x 2000 25.9 and 11.7, 1 x 20 000 30.5 and 15.6, 1 x 65 536 33.4 and 25.1, 32 x 65 536 37.7
-// and 27.7, 100 x 65 536 54.9 and 26.7, 600 x 65 536 139 and 87, 2000 x 65 536 359 and 281; of one magnitude 80.8 and 40.5, bfloat16
-// 33.3 and 26.0, nearly all zeros 74.7 and 36.9.  Slower only at the upper end of the range and for what queues up at few
-// counters: 65 536 coordinates of seven magnitudes 55 and 62 (9001: 41.5 and 21.5), sorted ones 45 and 56 (29.1 and 14.0).
+// us in six launches and in one or two: 1 x 2000 25.9 and 11.7, 1 x 20 000 30.5 and 15.6, 1 x 65 536 33.4 and 25.5, 32 x 65 536 37.7
+// and 27.7, 100 x 65 536 54.9 and 26.7, 600 x 65 536 139 and 87, 2000 x 65 536 359 and 281; 65 536 of one magnitude 80.8 and 40.4, of five
+// 61.6 and 49.3, bfloat16 33.6 and 26.1, nearly all zeros 75 and 36, sorted ones 46 and 36 (with both signs 44 and 41).
 __global__ __launch_bounds__(kShortBlock) void rank_short_kernel(PtrChunk c, RankSet ranks, uint32_t d, uint32_t* __restrict__ keys_out,
                                                                  double* __restrict__ alpha_out, uint32_t* status, uint32_t single) {
-  __shared__ ShortSelect S;
+  __shared__ FitSelect S;
   __shared__ uint32_t s_keys[kRanksMax];
   const uint32_t client = c.first + blockIdx.x, tid = threadIdx.x;
   const float* update = c.ptr[blockIdx.x];
@@ -915,7 +914,7 @@ __global__ __launch_bounds__(kShortBlock) void rank_short_kernel(PtrChunk c, Ran
   count_top(S, update, d);
   constexpr uint32_t kNonfinite = 0x7F800000u >> kTopShift;  // the first bin of Inf and NaN; the first wavefront looks at all of them
   static_assert(kTopBins - kNonfinite <= kWave && kRanksMax >= 17u && kRanksMax <= kShortRanks, "a bin per lane; all ranks of a short vector");
-  const uint64_t flagged = __ballot(tid < kTopBins - kNonfinite && S.top[kNonfinite + min(tid, kTopBins - kNonfinite - 1u)] != 0u);
+  const uint64_t flagged = __ballot(tid < kTopBins - kNonfinite && S.top[top_at<FitSelect>(kNonfinite + min(tid, kTopBins - kNonfinite - 1u))] != 0u);
   if (tid == 0) {
     if (single) *status = flagged ? CVLC_DEV_NONFINITE : 0u;
     else if (flagged) atomicOr(status, CVLC_DEV_NONFINITE);

@@ -2,7 +2,9 @@
 // ranks are found together, by counts of 14, 9 and 8 bits.  The first count goes through the vector; the keys in the bins
 // that hold a rank are then set aside in LDS and counted there.  Where they are too many, a sample names a key of every such
 // bin, and the keys equal to it are counted instead of set aside (many equal keys, the usual reason); where that does not
-// help, the further counts go through the vector again.  Part of the encoder, for vectors of up to kShortMax coordinates.
+// help, the further counts go through the vector again.  For vectors of up to kShortMax coordinates; the encoder's short_select
+// (EncodeSelect) and the exponent fit's rank_short (FitSelect) use it.  Both read the counters of the bins of Inf and NaN between
+// count_top and select_short, so that the first count's stay as they are up to there.
 //
 // All latency, and instructions where keys are many: one per key of 65 536 is 0.4 us.  (With the keys in registers, 64 a
 // thread, and everything unrolled over them there were 73 KB of code, more than the instruction cache holds, and nothing
@@ -45,6 +47,7 @@ struct ShortSelect {
   uint32_t n_list[kShortWaves];
   uint32_t upto[kShortBlock];  // keys in the bins of threads 0 .. t (16 bins a thread, largest keys first)
   uint32_t scan_tmp[kShortWaves], members;
+  uint32_t pooled;             // kPooled: entries in the common part of the lists
   uint32_t listed;             // 1: nobody's list ran over
   uint32_t counted;            // 1: the keys equal to same[] are not in the lists, their numbers by parts are in `tag` ...
   uint32_t same_bits;          // ... 1 << same_bits places a row
@@ -60,6 +63,26 @@ struct ShortSelect {
   uint32_t row[kShortRanks];     // row of `low`
   uint32_t equal[kShortRanks];   // keys equal to the rank's
 };
+
+// What the two users differ in.
+// kSpread: the bins of the first count lie so that powers of two, and whatever else differs in the exponent alone, are not all in
+// one bank of LDS: a fit of 65 536 coordinates of 7, 16 and 32 magnitudes, 2^-k each, 61, 58 and 58 us and now 44, 37 and 36 (in the launches
+// of long vectors 56, 50 and 46).  An instruction a key, 0.2 us of 25; the encoder has never had its bins otherwise.
+// kPooled: the members are counted only, in whatever order: of the lists' room a fifth is common to all wavefronts, so that a
+// sorted vector's members, which a few of them come across, find room as a rule (65 536 sorted normal ones 50 us and now 36, 45
+// in the launches of long vectors).
+struct EncodeSelect : ShortSelect {
+  static constexpr bool kSpread = false, kPooled = false;
+};
+struct FitSelect : ShortSelect {
+  static constexpr bool kSpread = true, kPooled = true;
+};
+
+// Where a bin of the first count is.  Aligned sixteens of bins stay together.
+template <class Select>
+__device__ __forceinline__ uint32_t top_at(uint32_t bin) {
+  return Select::kSpread ? bin ^ (bin >> 6) : bin;
+}
 
 typedef float __attribute__((ext_vector_type(4))) ShortFloat4;
 typedef const ShortFloat4 __attribute__((address_space(1))) * ShortFloat4Ptr;
@@ -122,12 +145,15 @@ __device__ __forceinline__ void add_together(uint32_t* counts, uint32_t at, bool
 // lanes or more is about: then its members add together, and a second one's.  What is left is added one by one, which costs what the
 // largest class of a wavefront has lanes, several times over.  (Looked for among all keys, classes cost a vector of 65 536
 // different magnitudes 8 us; in a loop, of which there is no need, 1 us.)
+// SCALE: bytes that `at` counts in.
 constexpr uint32_t kLargeClass = 16;
+template <uint32_t SCALE = 4u>
 __device__ __forceinline__ void add_visit(uint32_t* counts, const uint32_t (&at)[4], bool (&on)[4], uint32_t unit) {
+  auto counter = [&](uint32_t i) { return SCALE == 4u ? counts + i : reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(counts) + i * SCALE); };
   auto one_by_one = [&]() {
 #pragma unroll
     for (uint32_t c = 0; c < 4u; ++c)
-      if (on[c]) atomicAdd(&counts[at[c]], unit);
+      if (on[c]) atomicAdd(counter(at[c]), unit);
   };
   uint32_t lead, n;
   auto large_class = [&]() {
@@ -139,7 +165,7 @@ __device__ __forceinline__ void add_visit(uint32_t* counts, const uint32_t (&at)
   auto together = [&]() {
 #pragma unroll
     for (uint32_t c = 1; c < 4u; ++c) n += (uint32_t)__popcll(__ballot(on[c] && at[c] == lead));
-    if (lane_id() == 0u) atomicAdd(&counts[lead], n * unit);
+    if (lane_id() == 0u) atomicAdd(counter(lead), n * unit);
 #pragma unroll
     for (uint32_t c = 0; c < 4u; ++c) on[c] = on[c] && at[c] != lead;
   };
@@ -154,20 +180,23 @@ __device__ __forceinline__ void add_visit(uint32_t* counts, const uint32_t (&at)
 
 // The first count and its running sums.  Zeros, of which a vector may hold any number, are not counted one by one.
 // Whole workgroup; S.top is all zeros (and a barrier lies behind that).  Ends with a barrier.
-__device__ __forceinline__ void count_top(ShortSelect& S, const float* update, uint32_t d) {
+template <class Select>
+__device__ __forceinline__ void count_top(Select& S, const float* update, uint32_t d) {
   visit_short(update, d, [&](uint32_t, const uint32_t (&key)[4]) {
     uint32_t at[4];
     bool on[4];
 #pragma unroll
     for (uint32_t c = 0; c < 4u; ++c) {
-      at[c] = key[c] >> kTopShift;
+      // top_at, in bytes: (a ^ b) & c in one instruction (three-operand bitwise op with its truth table)
+      if (Select::kSpread) at[c] = __builtin_amdgcn_bitop3_b32(key[c] >> (kTopShift - 2u), key[c] >> (kTopShift + 4u), (kTopBins - 1u) * 4u, 0x28);
+      else at[c] = key[c] >> kTopShift;
       on[c] = (int32_t)key[c] > 0;
     }
-    add_visit(S.top, at, on, 1u);
+    add_visit<Select::kSpread ? 1u : 4u>(S.top, at, on, 1u);
   });
   __syncthreads();
   constexpr uint32_t kBins = kTopBins / kShortBlock;
-  const uint4* mine = reinterpret_cast<const uint4*>(&S.top[kTopBins - kBins * (threadIdx.x + 1u)]);
+  const uint4* mine = reinterpret_cast<const uint4*>(&S.top[top_at<Select>(kTopBins - kBins * (threadIdx.x + 1u)) & ~(kBins - 1u)]);
   uint32_t sum = 0, total;
 #pragma unroll
   for (uint32_t i = 0; i < kBins / 4u; ++i) {
@@ -182,7 +211,8 @@ __device__ __forceinline__ void count_top(ShortSelect& S, const float* update, u
 }
 
 // Bin of the first count that holds the rank-th largest key (1 <= rank <= d) and the rank inside it.
-__device__ __forceinline__ void find_top(const ShortSelect& S, uint32_t rank, uint32_t* bin, uint32_t* rem) {
+template <class Select>
+__device__ __forceinline__ void find_top(const Select& S, uint32_t rank, uint32_t* bin, uint32_t* rem) {
   constexpr uint32_t kBins = kTopBins / kShortBlock;
   uint32_t t = 0;
 #pragma unroll
@@ -192,7 +222,7 @@ __device__ __forceinline__ void find_top(const ShortSelect& S, uint32_t rank, ui
   const uint32_t largest = kTopBins - 1u - kBins * t;
 #pragma unroll
   for (uint32_t i = 0; i < kBins; ++i) {  // the bin: as many of the thread's as the rank lies behind
-    const uint32_t h = S.top[largest - i];
+    const uint32_t h = S.top[top_at<Select>(largest - i)];
     if (found == i && left > h && i + 1u < kBins) {
       left -= h;
       ++found;
@@ -279,13 +309,14 @@ __device__ __forceinline__ void clear_short(ShortSelect& S) {
   if (tid < kParts) S.start[tid] = 0xFFFFu;
   if (tid == 0) {
     S.tail_start = 0xFFFFu;
-    S.others = 0;
+    S.others = S.pooled = 0;
   }
 }
 
 // After count_top: the bins of the first count that hold the ranks, S.members keys in all, and the extra rank's.  Whole
 // workgroup; ends with a barrier.
-__device__ __forceinline__ void locate_short(ShortSelect& S) {
+template <class Select>
+__device__ __forceinline__ void locate_short(Select& S) {
   if (wave_id() == 0) {
     const uint32_t lane = lane_id(), n = S.n_ranks;
     const uint32_t rank = lane < n ? S.rank[lane] : (lane == kShortRanks ? S.extra : 0u);
@@ -294,7 +325,7 @@ __device__ __forceinline__ void locate_short(ShortSelect& S) {
     bool opens;
     const uint32_t row = short_row(rank != 0u && lane < n, bin, &opens);
     if (opens) S.tag[bin] = (uint8_t)(row + 1u);
-    const uint32_t members = wave_sum_u32(opens ? S.top[bin] : 0u);
+    const uint32_t members = wave_sum_u32(opens ? S.top[top_at<Select>(bin)] : 0u);
     if (rank && lane < n) {
       S.prefix[lane] = bin;
       S.rem[lane] = rem;
@@ -310,7 +341,8 @@ __device__ __forceinline__ void locate_short(ShortSelect& S) {
 }
 
 // After locate_short: S.prefix, S.rem and S.equal of every rank of S.rank.  Whole workgroup; ends with a barrier.
-__device__ __forceinline__ void select_short(ShortSelect& S, const float* update, uint32_t d) {
+template <class Select>
+__device__ __forceinline__ void select_short(Select& S, const float* update, uint32_t d) {
   const uint32_t tid = threadIdx.x, wave = wave_id(), lane = lane_id();
   // ranks ascend, so the last one's row is the last
   const uint32_t n = S.n_ranks, last = n ? n - 1u : 0u, members = S.members;
@@ -323,7 +355,8 @@ __device__ __forceinline__ void select_short(ShortSelect& S, const float* update
   // A wavefront's keys go to a list of its own, at places it counts by itself (places from a counter of the workgroup's: the
   // atomics queue up at it, 6 us for 65 536 coordinates).  Wavefronts take turns over the vector, so that four fifths of the room
   // is theirs alike as a rule; where one's list runs over, nobody's is used.
-  constexpr uint32_t kRoom = kShortWaves * kShortList;
+  constexpr uint32_t kRoom = kShortWaves * kShortList, kOwn = Select::kPooled ? kShortList / 5u * 4u : kShortList, kPool = kRoom - kShortWaves * kOwn;
+  uint32_t* const mine = &S.list[0][0] + wave * kOwn;
   // Past the vector's end the tag is the last bin's.  Only NaN may give it one: such vectors have no lists, which saves the lists'
   // pass a look at every key (1 us of 41).
   const bool lists = S.tag[kTopBins - 1u] == 0u;  // uniform
@@ -356,6 +389,7 @@ __device__ __forceinline__ void select_short(ShortSelect& S, const float* update
     list = lists && (uint64_t)S.others * n_parts <= (uint64_t)kRoom / 10u * 9u * kShortWaves;
   }
   uint32_t n_mine = 0;  // uniform per wavefront
+  bool over = false;    // kPooled: ... and whether a visit's found no room
   auto set_aside = [&](auto some_counted) {
     constexpr bool kCounted = decltype(some_counted)::value;
     visit_short(update, d, [&](uint32_t first, const uint32_t (&key)[4]) {
@@ -386,22 +420,36 @@ __device__ __forceinline__ void select_short(ShortSelect& S, const float* update
 #pragma unroll
       for (uint32_t c = 0; c < 4u; ++c) m[c] = __ballot(kept[c]);
       const uint32_t count = (uint32_t)(__popcll(m[0]) + __popcll(m[1]) + __popcll(m[2]) + __popcll(m[3]));
-      if (lane == 0) {
+      if (lane == 0 && !Select::kPooled) {
         if (tail) S.tail_start = (uint16_t)min(n_mine, 0xFFFEu);
         else S.start[part] = (uint16_t)min(n_mine, 0xFFFEu);
       }
-      if (count && n_mine + count <= kShortList) {  // uniform
-        uint32_t place = n_mine;
+      uint32_t from_place = n_mine;
+      bool fits = n_mine + count <= kOwn;  // uniform
+      if constexpr (Select::kPooled) {
+        if (!fits) {
+          uint32_t from = 0;
+          if (lane == 0) from = atomicAdd(&S.pooled, count);
+          from = __builtin_amdgcn_readfirstlane(from);
+          from_place = (kShortWaves - wave) * kOwn + from;  // counted from the wavefront's own list
+          fits = from + count <= kPool;
+          over = over || !fits;
+        } else {
+          n_mine += count;
+        }
+      }
+      if (count && fits) {  // uniform
+        uint32_t place = from_place;
 #pragma unroll
         for (uint32_t c = 0; c < 4u; ++c) place = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[c] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[c], place));
         const uint32_t within = first & ((1u << kPartShift) - 1u);
 #pragma unroll
         for (uint32_t c = 0; c < 4u; ++c) {
-          if (kept[c]) S.list[wave][place] = ((tag[c] - 1u) << 25) + ((key[c] << kPartShift) & ((1u << 25) - 1u)) + (within + c);
+          if (kept[c]) mine[place] = ((tag[c] - 1u) << 25) + ((key[c] << kPartShift) & ((1u << 25) - 1u)) + (within + c);
           place += kept[c] ? 1u : 0u;
         }
       }
-      n_mine += count;
+      if constexpr (!Select::kPooled) n_mine += count;
     });
   };
   static_assert(25u == kTopShift + kPartShift && kShortRanks <= 128u, "row, bits below the bin's, place: a word");
@@ -410,7 +458,8 @@ __device__ __forceinline__ void select_short(ShortSelect& S, const float* update
     else set_aside(std::false_type{});
     if (lane == 0) S.n_list[wave] = n_mine;
   }
-  const bool listed = !__syncthreads_or(!list || n_mine > kShortList ? 1 : 0);
+  if constexpr (!Select::kPooled) over = n_mine > kShortList;
+  const bool listed = !__syncthreads_or(!list || over ? 1 : 0);
   if (tid == 0) {
     S.listed = listed ? 1u : 0u;
     S.counted = listed && counted ? 1u : 0u;
@@ -435,11 +484,15 @@ __device__ __forceinline__ void select_short(ShortSelect& S, const float* update
       }
     }
   }
+  // every entry of the lists, whole wavefronts together: visit(entry, whether there is one)
+  auto for_listed = [&](auto visit) {
+    for (uint32_t i = lane; i - lane < n_mine; i += kWave) visit(i < n_mine ? mine[i] : 0u, i < n_mine);
+    if (!Select::kPooled) return;
+    const uint32_t pooled = S.pooled;
+    for (uint32_t i = tid; i - lane < pooled; i += kShortBlock) visit(i < pooled ? (&S.list[0][0])[kShortWaves * kOwn + i] : 0u, i < pooled);
+  };
   if (listed) {
-    for (uint32_t i = lane; i - lane < n_mine; i += kWave) {
-      const bool on = i < n_mine;
-      add_together(&S.mid[0][0], (on ? S.list[wave][i] : 0u) >> 16, on);  // row * kMidDigits + digit
-    }
+    for_listed([&](uint32_t entry, bool on) { add_together(&S.mid[0][0], entry >> 16, on); });  // row * kMidDigits + digit
   } else {
     visit_short(update, d, [&](uint32_t, const uint32_t (&key)[4]) {
       uint32_t at[4];
@@ -472,10 +525,10 @@ __device__ __forceinline__ void select_short(ShortSelect& S, const float* update
   __syncthreads();
   const uint32_t n_low = S.row[last] + 1u;
   if (listed) {
-    for (uint32_t i = lane; i - lane < n_mine; i += kWave) {
-      const uint32_t entry = i < n_mine ? S.list[wave][i] : 0u, u = i < n_mine ? (&S.mid[0][0])[entry >> 16] : 0u;
+    for_listed([&](uint32_t entry, bool on) {
+      const uint32_t u = on ? (&S.mid[0][0])[entry >> 16] : 0u;
       add_together(&S.low[0][0], (u - 1u) * kLowDigits + ((entry >> kPartShift) & (kLowDigits - 1u)), u != 0u);
-    }
+    });
     if (counted && wave == 0 && lane < kShortRanks && S.n_same[lane]) {
       const uint32_t key = S.same[lane], u = S.mid[lane >> same_bits][(key >> kMidShift) & (kMidDigits - 1u)];
       if (u) atomicAdd(&S.low[u - 1u][key & (kLowDigits - 1u)], S.n_same[lane]);
@@ -506,7 +559,7 @@ __device__ __forceinline__ void select_short(ShortSelect& S, const float* update
 // aside have been counted by parts; the others are now, every wavefront those of its list, or without lists in one more
 // pass.  done(rank's index, position) is called by one thread.  Whole workgroup.
 template <class Done>
-__device__ __forceinline__ void visit_ties(ShortSelect& S, const float* update, uint32_t d, Done done) {
+__device__ __forceinline__ void visit_ties(EncodeSelect& S, const float* update, uint32_t d, Done done) {
   const uint32_t tid = threadIdx.x, wave = wave_id(), lane = lane_id();
   const uint32_t n_ranks = S.n_ranks, mine = min(lane, kShortRanks - 1u);
   const uint32_t my_equal = S.equal[mine], my_rem = S.rem[mine];  // every wavefront for itself: lane r = rank r

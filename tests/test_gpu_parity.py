@@ -354,7 +354,11 @@ def _selection_vectors(kind, d, rng):
         return (torch.from_numpy((rng.standard_normal(d) * 1e-2).astype(np.float32)).to(torch.bfloat16).float().numpy().copy())
     if kind == "zeros":            # nothing above zero below the first tenth
         return np.where(rng.random(d) < 0.1, sign * rng.random(d), 0.0).astype(np.float32)
+    if kind == "ramp":             # neighbours in one bin, a few of the bins in each part of the vector
+        return np.linspace(1e-6, 1.0, d).astype(np.float32)
     U = (rng.standard_normal(d) * 1e-3).astype(np.float32)
+    if kind == "sorted":
+        return np.sort(U)
     if kind == "one outlier":
         U[rng.integers(d)] = 1e30
     return U
@@ -1502,7 +1506,9 @@ def gpu_fit_alpha(host_updates, two_passes=True):
 def check_fit(host_updates):
     """Magnitudes at the fitted ranks bit for bit; the slope to 1e-11 (fp64 on both
     sides, but two implementations of log)."""
-    refs = [(orc.fit_points(u), orc.fit_alpha(u)) for u in host_updates]
+    of = {id(u): u for u in host_updates}       # some clients may share a vector
+    of = {i: (orc.fit_points(u), orc.fit_alpha(u)) for i, u in of.items()}
+    refs = [of[id(u)] for u in host_updates]
     for two_passes in (True, False):
         alpha, keys, status = gpu_fit_alpha(host_updates, two_passes)
         assert status == 0
@@ -1527,6 +1533,7 @@ def test_fit_alpha_on_the_workload_distributions():
 def test_fit_alpha_on_colliding_magnitudes(kind):
     """Ranks that fall into one class at every radix level, zeros and denormals at the low ranks."""
     check_fit([syn.tie_heavy_vector(kind, 70_001, seed=1)])
+    check_fit([syn.tie_heavy_vector(kind, 81_920, seed=3), syn.tie_heavy_vector(kind, 81_920, seed=4)])
     check_fit([syn.tie_heavy_vector(kind, 16_384, seed=3), syn.tie_heavy_vector(kind, 16_384, seed=4)])
 
 
@@ -1553,27 +1560,44 @@ def test_fit_alpha_recovers_a_power_law_and_feeds_the_planner():
         assert pg.counts() == po.counts() and pg.code_lens() == po.code_len() and pg.total_bits == po.total_bits
 
 
-def test_fit_alpha_more_clients_than_one_upload_holds():
-    """600 short vectors: the pointer table travels in two launches, one workgroup per client."""
+@pytest.mark.parametrize("n,d", [(600, 5000), (449, SHORT_MAX + 3)])
+def test_fit_alpha_more_clients_than_one_upload_holds(n, d):
+    """Short vectors' pointers are the arguments of two launches, one workgroup per client; long ones' pointer table travels in two."""
     rng = np.random.default_rng(13)
-    check_fit([(rng.standard_t(3, 5000) * 1e-3).astype(np.float32) for _ in range(600)])
+    host = [(rng.standard_t(3, d) * 1e-3).astype(np.float32) for _ in range(n if d <= SHORT_MAX else 5)]
+    check_fit([host[c * c % len(host)] if d > SHORT_MAX else host[c] for c in range(n)])
 
 
-# The collecting pass has a workgroup for every CU, two where a client's share of them is not a whole number, or those of the
-# other passes where short lists would need more room; the lists' passes 16 a client or, up to eight clients, one for every CU.
-@pytest.mark.parametrize("kind", ["plain", "bfloat16", "few values", "zeros", "octaves"])
+@pytest.mark.parametrize("kind", ["plain", "bfloat16", "few values", "zeros", "octaves", "sorted", "ramp"])
 @pytest.mark.parametrize("n,d", [(1, 3), (1, 1023), (2, 4099), (1, SHORT_MAX - 1), (1, SHORT_MAX), (2, SHORT_MAX), (1, SHORT_MAX + 1), (449, 130)])
 def test_fit_alpha_of_short_vectors(n, d, kind):
     """One workgroup per client, up to 448 clients a launch; a single one writes the status word itself."""
     rng = np.random.default_rng(d)
     host = [_selection_vectors(kind, d, rng) for _ in range(n)]
     check_fit(host)
-    if n <= 2:
-        host[-1][d // 2] = np.float32(np.inf)
-        assert gpu_fit_alpha(host)[-1] == 1
+    for value in (np.inf, np.nan, np.uint32(0xFFFFFFFF).view(np.float32)):
+        if n <= 2:
+            host[-1][d // 2] = value
+            assert gpu_fit_alpha(host)[-1] == 1
 
 
-@pytest.mark.parametrize("n,d", [(1, 16_385), (1, 4_200_001), (2, 2_104_225), (8, 150_003), (9, 150_003), (12, 70_001), (100, 40_000), (129, 20_000)])
+@pytest.mark.parametrize("bins,waves", [(160, 16), (160, 4), (80, 2), (80, 1)])
+@pytest.mark.parametrize("d", [SHORT_MAX, SHORT_MAX - 253])
+def test_fit_alpha_of_short_vectors_whose_members_a_few_wavefronts_come_across(d, bins, waves):
+    """The keys that share a bin with a rank lie in every sixteenth 256 coordinates: lists of their own for all wavefronts, the
+    common part of the lists in use, and overrun."""
+    rng = np.random.default_rng(bins + waves)
+    keys = np.sort((np.uint32(0x3C000000 >> 17) + rng.integers(0, bins, d, dtype=np.uint32) << 17) | rng.integers(0, 1 << 17, d, dtype=np.uint32))[::-1]
+    member = np.isin(keys >> 17, np.unique(keys[np.array(cv.fit_ranks(d)) - 1] >> 17))
+    order = np.argsort(np.arange(d) // 256 % 16 >= waves, kind="stable")         # the few wavefronts' places first
+    placed = np.empty(d, dtype=np.uint32)
+    placed[order] = np.concatenate([rng.permutation(keys[member]), rng.permutation(keys[~member])])
+    check_fit([np.where(rng.random(d) < 0.5, -1, 1).astype(np.float32) * placed.view(np.float32)])
+
+
+# The collecting pass has a workgroup for every CU, two where a client's share of them is not a whole number, or those of the
+# other passes where short lists would need more room; the lists' passes 16 a client or, up to eight clients, one for every CU.
+@pytest.mark.parametrize("n,d", [(1, SHORT_MAX + 1), (1, 4_200_001), (2, 2_104_225), (8, 150_003), (9, 150_003), (12, 70_001), (100, 70_001), (129, 66_003)])
 def test_fit_alpha_at_the_steps_of_the_workgroups(n, d):
     rng = np.random.default_rng(n + d)
     host = [(rng.standard_t(3, d) * 1e-3).astype(np.float32) for _ in range(min(n, 5))]
