@@ -243,13 +243,18 @@ class Algorithm1 {
     return 0.5 * (lo + hi);
   }
 
-  // SMO-style sweeps for one k.  By slope: returns whether the search is known to end at the same code lengths.  The search finds
-  // a size only as well as the cost's rounding lets it: 5e-9 of the size off as a rule, 7e-8 at most in 400 000 k of random
-  // requests (4 to 3e7 coordinates, up to 60 bits each).  That matters where u / size is next to a whole number, as it is for
-  // groups of whole sizes in small vectors, and where the sweeps may end one earlier or later, which moves a size by little more than half a unit in either of its pairs.
-  bool balance(double k, bool by_slope, double (&Pc)[CVLC_MAX_CODED]) const {
+  // The plan for one k: SMO-style sweeps over the group sizes, then integer code lengths and refilled group sizes; returns gamma of
+  // the integer plan.
+  // `exact` = false: by slope where that can be.  The search would find a size only as well as the cost's rounding lets it: 5e-9 of
+  // the size off as a rule, 7e-8 at most in a million k of random requests (4 to 3e7 coordinates, up to 60 bits each).  That
+  // matters where u / size is next to a whole number, as it is for groups of whole sizes in small vectors, and where the sweeps
+  // may end one earlier or later, which moves a size by little more than half a unit in either of its pairs.  *sure = false says so:
+  // the result is then the least gamma that the search can end at.
+  double solve(double k, bool exact, uint32_t* y, uint32_t* P, bool* sure) const {
     constexpr double kLoose = 2e-7;
-    double nearest_stop = 1.0, largest = 0.0;
+    constexpr uint32_t kMostDoubts = 4;
+    const bool by_slope = by_slope_ && !exact;
+    double Pc[CVLC_MAX_CODED], nearest_stop = 1.0, largest = 0.0;
     for (uint32_t r = 0; r < R_; ++r) Pc[r] = k / (double)R_;
     for (int sweep = 0; sweep < 200; ++sweep) {
       double moved = 0.0, z_r2 = 0.0;
@@ -265,24 +270,39 @@ class Algorithm1 {
       nearest_stop = std::min(nearest_stop, std::fabs(moved - 0.5));
       if (moved < 0.5) break;
     }
-    if (!by_slope) return true;
-    for (uint32_t r = 0; r < R_; ++r) largest = std::max(largest, Pc[r]);
-    const double stop = nearest_stop < kLoose * largest ? 1.25 : 0.0;
+    double bits[CVLC_MAX_CODED];  // a record's, rounded down
+    uint32_t doubts[kMostDoubts], n_doubts = 0;
     for (uint32_t r = 0; r < R_; ++r) {
-      const double t = u_ / Pc[r], y = t - (double)s_;  // lengths of 1 and 16 are the ends: the steps are at 2 .. 16
-      if (y > 1.5 && y < 16.5 && std::fabs(t - std::round(t)) <= t * (kLoose + stop / Pc[r])) return false;
+      bits[r] = std::floor(u_ / Pc[r]);
+      largest = std::max(largest, Pc[r]);
     }
-    return true;
+    const double stop = nearest_stop < kLoose * largest ? 1.25 : 0.0;
+    for (uint32_t r = 0; r < R_ && by_slope; ++r) {
+      const double t = u_ / Pc[r], length = t - (double)s_;  // lengths of 1 and 16 are the ends: the steps are at 2 .. 16
+      if (!(length > 1.5 && length < 16.5 && std::fabs(t - std::round(t)) <= t * (kLoose + stop / Pc[r]))) continue;
+      bits[r] = std::round(t);  // or one less
+      if (n_doubts < kMostDoubts) doubts[n_doubts] = r;
+      ++n_doubts;
+    }
+    *sure = n_doubts == 0;
+    if (n_doubts > kMostDoubts) return -std::numeric_limits<double>::infinity();
+    double least = integer_plan(bits, y, P);
+    for (uint32_t choice = 1; choice < 1u << n_doubts; ++choice) {
+      double other[CVLC_MAX_CODED];
+      std::copy(bits, bits + R_, other);
+      for (uint32_t i = 0; i < n_doubts; ++i)
+        if (choice >> i & 1u) other[doubts[i]] -= 1.0;
+      least = std::min(least, integer_plan(other, y, P));
+    }
+    return least;
   }
 
-  // The group sizes for one k, then integer code lengths (clamped to 1..16,
-  // non-increasing) and refilled group sizes; returns gamma of the integer plan.
-  double solve(double k, uint32_t* y, uint32_t* P) const {
-    double Pc[CVLC_MAX_CODED];
-    if (!by_slope_ || !balance(k, true, Pc)) balance(k, false, Pc);
+ private:
+  // From the bits of a record: lengths clamped to the quantiser's range and non-increasing, groups refilled.
+  double integer_plan(const double* bits, uint32_t* y, uint32_t* P) const {
     uint64_t room = d_;
     for (uint32_t r = 0; r < R_; ++r) {
-      double yr = std::floor(u_ / Pc[r]) - (double)s_;
+      double yr = bits[r] - (double)s_;
       if (yr < y_min_) yr = y_min_;
       if (yr > 16.0) yr = 16.0;
       uint32_t yi = (uint32_t)yr;
@@ -296,7 +316,6 @@ class Algorithm1 {
     return gamma_integer(d_, R_, P, y, alpha_, B_, quant_);
   }
 
- private:
   uint32_t d_, R_, s_;
   double u_;
   PowerLaw law_;
@@ -356,22 +375,27 @@ int plan_algorithm1(uint32_t d, uint64_t budget, uint32_t R, double alpha, float
   const Algorithm1 alg(d, R, out->s, u, alpha, (double)B, quant);
   // Equidistant search over k.  The 128 searches know nothing of each other: they are shared out between up to 16 threads,
   // and the first of the best is taken as if they had been done in order (7 groups, 1.2 M coordinates: 424 us, with ten threads
-  // 480; with golden-section searches alone, twelve times the evaluations, 2 007).
+  // 480; with golden-section searches alone, twelve times the evaluations, 2 007).  Then once more, exactly, those that by slope are
+  // not sure and may be better than the best of the others: next to none (all that are not sure: one plan in ten took 100 us more).
   constexpr int kGrid = 128, kThreads = 16;
   struct Candidate {
     double gamma;
+    bool sure;
     uint32_t y[CVLC_MAX_CODED], P[CVLC_MAX_CODED];
   };
   Candidate found[kGrid];
-  std::atomic<int> next{0};
-  auto search = [&] {
-    for (int g = next.fetch_add(1); g < kGrid; g = next.fetch_add(1)) {
-      const double k = k_min + (k_max - k_min) * (double)g / (double)(kGrid - 1);
-      found[g].gamma = alg.solve(k, found[g].y, found[g].P);
-    }
-  };
-  {
-    const Helpers room(R > 1 ? kThreads - 1 : 0);  // one group: nothing to balance, microseconds in all
+  int todo[kGrid], n_todo = kGrid;
+  for (int g = 0; g < kGrid; ++g) todo[g] = g;
+  auto search_all = [&](bool exact) {
+    std::atomic<int> next{0};
+    auto search = [&] {
+      for (int i = next.fetch_add(1); i < n_todo; i = next.fetch_add(1)) {
+        const int g = todo[i];
+        const double k = k_min + (k_max - k_min) * (double)g / (double)(kGrid - 1);
+        found[g].gamma = alg.solve(k, exact, found[g].y, found[g].P, &found[g].sure);
+      }
+    };
+    const Helpers room(R > 1 ? std::min(kThreads, n_todo) - 1 : 0);  // one group: nothing to balance, microseconds in all
     std::thread helpers[kThreads - 1];
     try {
       for (int t = 0; t < room.taken(); ++t) helpers[t] = std::thread(search);
@@ -381,7 +405,15 @@ int plan_algorithm1(uint32_t d, uint64_t budget, uint32_t R, double alpha, float
     search();
     for (std::thread& t : helpers)
       if (t.joinable()) t.join();
-  }
+  };
+  search_all(false);
+  double best_sure = std::numeric_limits<double>::infinity();
+  for (const Candidate& c : found)
+    if (c.sure && c.gamma < best_sure) best_sure = c.gamma;
+  n_todo = 0;
+  for (int g = 0; g < kGrid; ++g)
+    if (!found[g].sure && !(found[g].gamma > best_sure)) todo[n_todo++] = g;
+  if (n_todo) search_all(true);
   double best = std::numeric_limits<double>::infinity();
   for (const Candidate& c : found) {
     if (c.gamma < best) {
