@@ -327,8 +327,7 @@ int cvlc_device_status(const void* d_workspace, void* hip_stream, uint32_t* stat
  * call does not have gets no bracket: vectors of up to 65 536 coordinates are
  * encoded without SAMPLE, FILTER and REFILTER, and as a rule without
  * SETUP; only batches that keep much have LAYOUT; up to 112 streams are
- * decoded without SETUP.  Not thread
- * safe. */
+ * decoded without SETUP.  Not thread safe. */
 enum {
   CVLC_STAGE_ENC_SETUP = 0,    /* clear scratch, upload per-client parameters; short vectors: */
                                /* only where one launch's arguments do not hold them */

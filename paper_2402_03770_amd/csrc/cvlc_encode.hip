@@ -38,8 +38,8 @@
 //                 QSGD quantiser also every group's exact sum of squares in
 //                 integer limbs
 //   layout        prefix of the per-span counts, headers (QSGD: the group norms
-//                 from the exact sums), statistics; batches of many clients that keep
-//                 much only, in others emit does that for itself
+//                 from the exact sums), statistics; batches that keep much only, in
+//                 others emit does that for itself
 //   emit          per chunk of 8 spans: record number from prefix and span
 //                 number, stochastic rounding (Philox4x32-10) and bit packing;
 //                 on request the error energy of every group
@@ -668,7 +668,7 @@ __global__ __launch_bounds__(kBlock) void filter_kernel(const ClientParams* __re
 // known by then, so a list has room for all of them: a piece for every gather workgroup that has spans to go through,
 // and behind the pieces room for what found its piece full, all members if need be.  Bins grow with the candidates
 // (one to two 1024ths of them from 262 144 kept coordinates on): a list of up to half the boundary's pool lies there,
-// a larger one in the client's own stream buffer, which nothing is written to before the layout and which has
+// a larger one in the client's own stream buffer, which nothing else is written to before the counting pass and which has
 // three bytes and more for every kept coordinate.  For a client whose sample misjudged it lies in the filter's
 // output, which is not looked at then.  Boundaries that share a bin share the list of the first of them.  A bin that
 // holds a large part of all candidates (equal magnitudes) has no list, the select kernel walks the candidates for it.
@@ -2357,8 +2357,8 @@ __global__ __launch_bounds__(kEmitBlock, MODE == kShortVec ? 4 : 6) void emit_ke
   GlobalWordPtr stream = (GlobalWordPtr)p.stream;
   const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32), client_id = p.client_id;
 
-  // what thread r of the first 32 needs of group r for every chunk's tables (in registers it is every thread's, and the passes
-  // that make their own prefix spill)
+  // what thread r of the first 32 needs of group r for every chunk's tables (not in registers, where it would be every
+  // thread's: as it is, three to eight of them spill where the prefix comes from the chunks' counts, none to three where it is the layout's)
   if (tid < 32u) {
     s_size[tid] = 0;
     s_const[tid] = EmitGroup{0u, 0u, 0u, 0u, 0.0f, 0.0f, 0u, 0.0f};
