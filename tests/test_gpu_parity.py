@@ -298,6 +298,14 @@ def test_packing_by_workgroups_of_more_chunks_than_their_counters_hold():
 
 @pytest.mark.parametrize("quant", [cv.QUANT_PQ, cv.QUANT_QSGD])
 def test_packing_by_the_layout(quant):
+    """Many clients that keep all of vectors just too short for a layout kernel to number their chunks."""
+    n, d = 48, 128 * 4096 + 1537
+    vectors = [syn.update_vector(2, 80 + c, d=d) for c in range(3)]
+    check_some_streams([vectors[c % 3] for c in range(n)], [_keep_all_plan(d, quant)] * n, [0, 25, 47])
+
+
+@pytest.mark.parametrize("quant", [cv.QUANT_PQ, cv.QUANT_QSGD])
+def test_packing_by_the_layout_of_plans_that_differ(quant):
     """So many clients that keep so much that a layout kernel numbers the chunks: plans of 4 and of 31 groups, some of them
     empty, and a client of equal magnitudes, for all of which the workspace has no room."""
     n, d, seed, flat = 128, 128 * 4096 + 1537, 21, 77
@@ -598,9 +606,21 @@ def test_a_class_of_equal_keys_is_cut_in_few_passes():
     assert t[1] < 40 * t[0], t
 
 
+@pytest.mark.parametrize("n,R", [(1, 1), (9, 7), (16, 4), (13, 5), (16, 31), (17, 3), (17, 4), (25, 31), (133, 31)])
+def test_decode_at_the_steps_of_the_list_search(n, R):
+    """1, 63, 64, 65, 496, 51, 68, 775 and 4123 lists with records, nearly all of one item: numbered and gone through in one launch
+    up to 112 streams, in three beyond."""
+    d = 6000
+    rng = np.random.default_rng(n)
+    host = [(rng.standard_normal(d) * 1e-3).astype(np.float32) for _ in range(min(n, 8))]
+    p = orc.plan_manual(d, [8] * R, [600 if r == R // 2 and R < 8 else 20 for r in range(R)])
+    refs = [orc.encode(host[c % 8], p, 3, c).words for c in range(n)]
+    check_decode(refs, d, weights=rng.uniform(0.5, 1.5, n).tolist())
+
+
 @pytest.mark.parametrize("n,lists", [(113, 0), (113, 1), (113, 63), (113, 64), (113, 65), (113, 68), (113, 496), (113, 3503), (133, 4096), (133, 4097),
                                      (133, 4123)])
-def test_decode_at_the_steps_of_the_list_search(n, lists):
+def test_decode_at_the_steps_of_the_list_search_of_many_streams(n, lists):
     """The search for an item's list, in calls of more streams than one launch parses and numbers, takes 64 lists a round: up to
     64, up to 4096 and more of the streams' 31 groups each have records, a few of them several items."""
     d = 6000
@@ -1560,12 +1580,17 @@ def test_fit_alpha_recovers_a_power_law_and_feeds_the_planner():
         assert pg.counts() == po.counts() and pg.code_lens() == po.code_len() and pg.total_bits == po.total_bits
 
 
-@pytest.mark.parametrize("n,d", [(600, 5000), (449, SHORT_MAX + 3)])
-def test_fit_alpha_more_clients_than_one_upload_holds(n, d):
-    """Short vectors' pointers are the arguments of two launches, one workgroup per client; long ones' pointer table travels in two."""
+def test_fit_alpha_more_clients_than_one_upload_holds():
+    """600 short vectors: the pointers are the arguments of two launches, one workgroup per client."""
     rng = np.random.default_rng(13)
-    host = [(rng.standard_t(3, d) * 1e-3).astype(np.float32) for _ in range(n if d <= SHORT_MAX else 5)]
-    check_fit([host[c * c % len(host)] if d > SHORT_MAX else host[c] for c in range(n)])
+    check_fit([(rng.standard_t(3, 5000) * 1e-3).astype(np.float32) for _ in range(600)])
+
+
+def test_fit_alpha_more_long_vectors_than_one_upload_holds():
+    """449 vectors of more than 65 536 coordinates, five different ones: the pointer table travels in two launches."""
+    rng = np.random.default_rng(13)
+    host = [(rng.standard_t(3, SHORT_MAX + 3) * 1e-3).astype(np.float32) for _ in range(5)]
+    check_fit([host[c * c % 5] for c in range(449)])
 
 
 @pytest.mark.parametrize("kind", ["plain", "bfloat16", "few values", "zeros", "octaves", "sorted", "ramp"])
@@ -1597,7 +1622,8 @@ def test_fit_alpha_of_short_vectors_whose_members_a_few_wavefronts_come_across(d
 
 # The collecting pass has a workgroup for every CU, two where a client's share of them is not a whole number, or those of the
 # other passes where short lists would need more room; the lists' passes 16 a client or, up to eight clients, one for every CU.
-@pytest.mark.parametrize("n,d", [(1, SHORT_MAX + 1), (1, 4_200_001), (2, 2_104_225), (8, 150_003), (9, 150_003), (12, 70_001), (100, 70_001), (129, 66_003)])
+@pytest.mark.parametrize("n,d", [(1, 16_385), (1, 4_200_001), (2, 2_104_225), (8, 150_003), (9, 150_003), (12, 70_001), (100, 40_000), (129, 20_000),
+                                 (1, SHORT_MAX + 1), (100, 70_001), (129, 66_003)])
 def test_fit_alpha_at_the_steps_of_the_workgroups(n, d):
     rng = np.random.default_rng(n + d)
     host = [(rng.standard_t(3, d) * 1e-3).astype(np.float32) for _ in range(min(n, 5))]
